@@ -2,8 +2,9 @@
  * pg_head.h -- C ABI of the MI355X policy-gradient head.
  *
  * The library computes, for one packed microbatch of a multi-turn RL step, the
- * per-token policy-gradient quantities over the vocabulary without ever writing
- * the [tokens x vocab] logits to device memory:
+ * per-token policy-gradient quantities over the vocabulary without ever holding
+ * the [tokens x vocab] logits: the forward-only calls write none of them, the loss calls
+ * park a bounded number of 256 x 256 logits tiles in the workspace for their backward:
  *
  *   trloo_advantage   turn returns and leave-one-out advantages   (Sec. 4.2, Eq. 2 and 5)
  *   pg_logprob_fwd    LM-head log-prob / entropy / logsumexp of the sampled tokens
@@ -138,6 +139,10 @@ int32_t pg_init(void);
  * Bytes of device workspace the given call needs for these sizes (S is ignored for
  * PG_CALL_LOGPROB_FWD).  Returns 0 if the arguments are invalid or unsupported.
  * The workspace need not be initialised and holds nothing the caller may rely on.
+ * For the loss calls its last part (at most 8 GiB) keeps fp32 logits between the forward and the backward
+ * contractions.  A loss call also takes a workspace that is shorter by any part of it: it then
+ * recomputes the logits that it cannot keep, with the same results, and refuses
+ * (PG_ERR_WORKSPACE_TOO_SMALL) only what is shorter than the rest.
  */
 size_t pg_workspace_bytes(int64_t T, int64_t d, int64_t V, int32_t S, const pg_params* h_params,
                           int32_t which_call);

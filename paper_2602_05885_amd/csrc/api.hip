@@ -2,6 +2,7 @@
 // Nothing here synchronises with the device or allocates device memory.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -43,6 +44,10 @@ uint64_t ds_budget() {
 
 inline size_t align_up(size_t x) { return (x + ALIGN - 1) / ALIGN * ALIGN; }
 
+// Bytes of fp32 logits that a loss call keeps for its backward (Kept in kernels.h): four times the dS scratch
+// of one orientation, so one knob bounds all scratch.
+uint64_t kept_budget() { return 4 * ds_budget(); }
+
 // Leading dimension of the caller-owned W^T cache [d, ld]: the vocabulary rounded up to whole tiles.
 inline int64_t wt_cache_ld(int64_t V) { return pg::pad_ld((V + 255) / 256 * 256); }
 
@@ -62,6 +67,9 @@ struct Plan {
   size_t ctl, counters, queue, flag, c_tok, a_tok, rows, pos, yc, zy, lse2, coefc, lossterm;
   size_t part_m, part_s, part_u, Hc, HcT, Wc, dS, dST, WT, dHacc, rstd_c = 0, norm_partial = 0;
   size_t HcT_lo = 0, dS_lo = 0, dST_lo = 0, WT_lo = 0;   // fp32 heads only
+  size_t kept = 0;     // fp32 logits kept for the backward: the last region
+  int kept_cap = 0;    // ... in 256 x 256 tiles
+  size_t required = 0; // everything but the kept logits
   size_t total = 0;
 };
 
@@ -169,7 +177,14 @@ int32_t make_plan(int64_t T, int64_t d, int64_t V, int32_t S, const pg_params* p
     pl.queue_words = pg::QUEUE_SET_WORDS * pg::queue_sets((int)nchunks);
   }
   pl.queue = take((size_t)pl.queue_words * sizeof(unsigned));
-  pl.total = off > 0 ? off : ALIGN;
+  pl.required = off > 0 ? off : ALIGN;
+  pl.kept = pl.required;
+  if (which != PG_CALL_LOGPROB_FWD) {
+    const uint64_t tile = (uint64_t)pg::KEPT_TILE_FLOATS * sizeof(float);
+    const int64_t all = tiles_v * pl.tiles_t, fit = (int64_t)(kept_budget() / tile);
+    pl.kept_cap = (int)(all < fit ? all : fit);
+  }
+  pl.total = pl.kept + (size_t)pl.kept_cap * pg::KEPT_TILE_FLOATS * sizeof(float);
   return PG_OK;
 }
 
@@ -273,7 +288,7 @@ T* at(void* ws, size_t off) { return reinterpret_cast<T*>(static_cast<char*>(ws)
 // comb.partials_in set, the contraction is skipped and the rows' states come from there.
 void run_forward(const Plan& pl, const pg_params& p, void* ws, const void* H, const void* W, const int32_t* y,
                  int64_t y_offset, const pg::PrepArgs& prep, pg::CombineArgs comb, bool need_HT, hipStream_t st,
-                 const pg::NormFuse* norm = nullptr) {
+                 const pg::NormFuse* norm = nullptr, const pg::Kept& kept = pg::Kept{}) {
   pg::launch_prepass(prep, st);
   const void* Wop = W;
   if (pl.is_f32) {
@@ -300,6 +315,7 @@ void run_forward(const Plan& pl, const pg_params& p, void* ws, const void* H, co
   f.part_m = at<float>(ws, pl.part_m); f.part_s = at<float>(ws, pl.part_s); f.part_u = at<float>(ws, pl.part_u);
   f.ctl = at<pg::Ctl>(ws, pl.ctl);
   f.queue = at<unsigned>(ws, pl.queue);
+  f.kept = kept;
   if (!comb.partials_in) { ProfScope ps(PG_KERNEL_FWD, st); pg::launch_lmhead_fwd(f, st); }
 
   comb.tiles_v = comb.partials_in ? 0 : pl.tiles_v; comb.t_cap = pl.t_cap;
@@ -704,9 +720,15 @@ int32_t loss_fwd_bwd(int sft, const void* H, const void* W, const int32_t* y, co
       return fail(PG_ERR_INVALID_ARG, "mismatch correction needs old_logp and rollout_logp");
   }
   if (misaligned(H) || misaligned(dH) || misaligned(workspace)) return fail(PG_ERR_INVALID_ARG, "H, dH and workspace must be 16-byte aligned");
-  if (workspace_bytes < pl.total) return fail(PG_ERR_WORKSPACE_TOO_SMALL, "workspace has %zu bytes, %zu needed", workspace_bytes, pl.total);
+  if (workspace_bytes < pl.required) return fail(PG_ERR_WORKSPACE_TOO_SMALL, "workspace has %zu bytes, %zu needed", workspace_bytes, pl.required);
   if ((rc = ensure_init())) return rc;
   void* ws = workspace;
+  // A workspace of less than pg_workspace_bytes() keeps fewer logits (none: the backward recomputes them all, as it
+  // does when the rows' states come from elsewhere and no forward contraction runs).
+  pg::Kept kept{};
+  kept.cap = (int)std::min<size_t>(pl.kept_cap, (workspace_bytes - pl.required) / (pg::KEPT_TILE_FLOATS * sizeof(float)));
+  if (shard.partials) kept.cap = 0;
+  if (kept.cap > 0) kept.tiles = at<float>(ws, pl.kept);
   const LaunchGuard guard;
 
   pg::PrepArgs prep = base_prep(pl, ws);
@@ -730,7 +752,7 @@ int32_t loss_fwd_bwd(int sft, const void* H, const void* W, const int32_t* y, co
     nf.X = H; nf.gamma = norm->gamma; nf.eps = norm->eps; nf.dgamma = norm->dgamma;
     nf.rstd_c = at<float>(ws, pl.rstd_c); nf.partial = at<float>(ws, pl.norm_partial);
   }
-  run_forward(pl, p, ws, H, W, y, shard.v_offset, prep, comb, true, st, norm ? &nf : nullptr);
+  run_forward(pl, p, ws, H, W, y, shard.v_offset, prep, comb, true, st, norm ? &nf : nullptr, kept);
 
   pg::FinishArgs fin{at<float>(ws, pl.lossterm), at<unsigned long long>(ws, pl.counters), loss_out,
                      reinterpret_cast<long long*>(counters_out), at<pg::Ctl>(ws, pl.ctl)};
@@ -770,7 +792,7 @@ int32_t loss_fwd_bwd(int sft, const void* H, const void* W, const int32_t* y, co
     pg::Rechunk rc{};
     rc.enabled = pl.nchunks > 1; rc.chunk = c; rc.tiles_v_all = pl.tiles_v; rc.ld_s_all = (int)pg::pad_ld((int64_t)pl.tiles_v * 256);
     rc.cap_s = (long long)pl.t_cap * pl.ld_v; rc.cap_t = (long long)pl.vc * pl.ld_t;
-    g.rc = rc;
+    g.rc = rc; g.kept = kept; g.tiles_v_all = pl.tiles_v;
     unsigned* const queues = at<unsigned>(ws, pl.queue) + pg::QUEUE_SET_WORDS * (1 + 4 * c);
     g.queue = queues; g.queue_lo = queues + 3 * pg::QUEUE_SET_WORDS;
     { ProfScope ps(PG_KERNEL_DLOGITS, st); pg::launch_lmhead_dlogits(g, st); }

@@ -40,6 +40,24 @@ __device__ inline bool rechunk_all(const Rechunk& r, int n_pad, int& ld_t_all) {
          (long long)r.tiles_v_all * 256 * ld_t_all <= r.cap_t;
 }
 
+// Logits kept for the backward.  The dS of the backward needs the logits a second time, after the rows'
+// logsumexp is known.  Recomputing them is a fourth contraction as long as the other three; keeping the
+// fp32 accumulators of a 256 x 256 tile costs 256 KiB of HBM written once and read once.  The workspace holds
+// a bounded number of such tiles (cap): the forward parks the tiles of the first kept_vocab_tiles() vocab
+// tiles (all live token tiles each), as they lie in the registers, and the backward finishes those from
+// memory (dlogits_kept_kernel) and recomputes only the rest.  The kept accumulators are the very values a
+// recompute gives, so dS does not depend on how many are kept.
+struct Kept {
+  float* tiles;         // [cap][KEPT_TILE_FLOATS], null: nothing is kept
+  int cap;
+};
+constexpr int KEPT_TILE_FLOATS = 256 * 256;
+__host__ __device__ inline int kept_vocab_tiles(const Kept& k, int tiles_v, int live_tiles_t) {
+  if (!k.tiles || live_tiles_t <= 0) return 0;
+  const int n = k.cap / live_tiles_t;
+  return n < tiles_v ? n : tiles_v;
+}
+
 // ---- MFMA kernels ---------------------------------------------------------------------
 struct FwdArgs {
   const void* W;        // [V, ldw] bf16
@@ -56,6 +74,7 @@ struct FwdArgs {
   float* part_m;        // [tiles_v, t_cap] each
   float* part_s;
   float* part_u;
+  Kept kept;
   const Ctl* ctl;
   unsigned* queue;      // [8] tile counters of this launch's queue, zero at launch
 };
@@ -84,6 +103,8 @@ struct DlogitsArgs {
   unsigned* queue;      // [8] tile counters of this launch's queue, zero at launch
   unsigned* queue_lo;   // [8] the same for the launch that stores the remainders
   Rechunk rc;
+  Kept kept;            // as the forward had it
+  int tiles_v_all;      // 256-row vocab tiles of the whole head
 };
 
 struct StoreArgs {

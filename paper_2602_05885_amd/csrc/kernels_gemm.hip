@@ -8,6 +8,7 @@
 // vocabulary on the rows (a token's statistics then reduce inside a lane first); the store
 // kernel puts the output's contiguous dimension there (4 consecutive elements per lane).
 #include <cstdlib>
+#include <type_traits>
 
 #include "kernels.h"
 #include "gemm_core.h"
@@ -62,6 +63,7 @@ __device__ __forceinline__ void lmhead_fwd_body(const FwdArgs& a, bool steal, un
   const int wm = wave / WN, wn = wave % WN;
   TileQueue Q;
   Q.init(a.queue, a.tiles_v * tiles_t, 0);
+  const int kept_v = kept_vocab_tiles(a.kept, a.tiles_v, tiles_t);
   float* red = reinterpret_cast<float*>(g_smem + FWD_RED_OFF);
   int* stash = reinterpret_cast<int*>(g_smem + FWD_STASH_OFF);
   volatile int* claim = reinterpret_cast<volatile int*>(g_smem + FWD_CLAIM_OFF);
@@ -116,6 +118,15 @@ __device__ __forceinline__ void lmhead_fwd_body(const FwdArgs& a, bool steal, un
 
     const int v_base = tm * BM + wm * WROWS;            // first vocab row of this wavefront's block
     const bool ragged = (tm * BM + BM > a.V);
+    // park the accumulators for the backward, 1 KiB per instruction, before the statistics, so that the stores drain
+    // under them (d = 5120, V = 151936: 609 -> 640 us at 768 rows, all tiles kept; nothing at 32768 rows, 43 % kept)
+    if (tm < kept_v) {
+      f32x4* kp = reinterpret_cast<f32x4*>(a.kept.tiles + ((size_t)tm * tiles_t + tn) * KEPT_TILE_FLOATS) + wave * (GM * GN * 64) + lane;
+#pragma unroll
+      for (int j = 0; j < GN; ++j)
+#pragma unroll
+        for (int i = 0; i < GM; ++i) __builtin_nontemporal_store(acc[i][j], kp + (j * GM + i) * 64);
+    }
 #pragma unroll
     for (int j = 0; j < GN; ++j) {
       const int tok_l = wn * WCOLS + j * 16 + (lane & 15);
@@ -227,6 +238,121 @@ __device__ __forceinline__ void drain_queue(const TileQueue& Q, bool steal, vola
   }
 }
 
+// Workgroup barrier that orders LDS accesses only: vector memory operations in flight are not waited for.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// What dS needs of one token column.
+struct DsColumn {
+  float c, k2;
+  uint32_t sgn;
+  int y;
+  __device__ __forceinline__ DsColumn(const DlogitsArgs& a, int tok) {
+    c = a.coefc[tok];
+    k2 = __builtin_amdgcn_logf(fabsf(c)) - a.lse2[tok];
+    sgn = c > 0.f ? 0x80008000u : 0u;
+    y = a.yc[tok];
+  }
+};
+
+// dS of one MFMA tile column (GM tiles of 4 rows per lane) from its logits.
+// dS = c (onehot - p) is formed as  -sign(c) 2^(t2 - lse2 + log2|c|)  for every element (one fma
+// and one exp2 each; c = 0 gives 2^-inf = 0), the one-hot term c is added to the single element
+// that holds the sampled token (rare, wave-uniform branch), and the sign goes on with the bf16
+// packing.  LO (fp32 heads): the remainders dS - bf16(dS) instead.
+template <bool LO>
+__device__ __forceinline__ void ds_pack(const DlogitsArgs& a, const DsColumn& col, int v_base, const f32x4 (&z)[GM],
+                                        uint32_t (&pk)[GM][2]) {
+  const int lane = threadIdx.x & 63;
+  const bool ragged = v_base + WROWS > a.V;
+  const int yrel = col.y - v_base;
+  const bool mine = (yrel >= 0) && (yrel < WROWS) && (((yrel >> 2) & 3) == (lane >> 4));
+  const bool any_mine = __any(mine);
+#pragma unroll
+  for (int i = 0; i < GM; ++i) {
+    float g[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) g[r] = __builtin_amdgcn_exp2f(fmaf(z[i][r], a.scale, col.k2));
+    if (any_mine) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (yrel == i * 16 + acc_row(r, lane)) g[r] -= fabsf(col.c);     // sign is applied below
+    }
+    if (ragged) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (v_base + i * 16 + acc_row(r, lane) >= a.V) g[r] = 0.f;
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+      bf16x2 two;
+      two[0] = (__bf16)g[2 * h];
+      two[1] = (__bf16)g[2 * h + 1];
+      if constexpr (LO) {
+        two[0] = (__bf16)(g[2 * h] - (float)two[0]);
+        two[1] = (__bf16)(g[2 * h + 1] - (float)two[1]);
+      }
+      pk[i][h] = __builtin_bit_cast(uint32_t, two) ^ col.sgn;
+    }
+  }
+}
+
+// ---- orientation 1: dS[tok][v], staged as rows of 256 v (wn: 128-token half of the staging area) ----
+template <int HALVES>
+__device__ __forceinline__ void ds_stage_rows(const uint32_t (&pk)[GM][GN][2], char* st, int wm, int wn, int lane) {
+#pragma unroll
+  for (int j = 0; j < GN; ++j) {
+    const int tok_l = (HALVES > 1 ? wn * WCOLS : 0) + j * 16 + (lane & 15);
+#pragma unroll
+    for (int i = 0; i < GM; ++i) {
+      const int v_l = wm * WROWS + i * 16 + ((lane >> 4) << 2);
+      *reinterpret_cast<uint2*>(st + tok_l * EPI_STRIDE + v_l * 2) = make_uint2(pk[i][j][0], pk[i][j][1]);
+    }
+  }
+}
+
+// ---- orientation 2: dS^T[v][tok], staged as rows of tokens ----
+// A quad of lanes holds a 4 (vocab rows) x 4 (tokens) block, one token per lane.  Two
+// butterfly exchanges inside the quad turn it so that lane q holds row q of all four tokens,
+// which then goes to LDS as one 8-byte store (instead of sixteen 2-byte ones per block).
+__device__ __forceinline__ void ds_stage_cols(const uint32_t (&pk)[GM][GN][2], char* st, int stride, int wm, int wn, int lane) {
+  const int q = lane & 3;
+  const uint32_t sel = (q & 1) ? 0x03020706u : 0x05040100u;   // v_perm byte selectors, see below
+  const bool upper = q >= 2;
+  const int row_l = wm * WROWS + ((lane >> 4) << 2) + q;
+  const int tok0_l = wn * WCOLS + (((lane & 15) >> 2) << 2);
+#pragma unroll
+  for (int j = 0; j < GN; ++j) {
+#pragma unroll
+    for (int i = 0; i < GM; ++i) {
+      const uint32_t w0 = pk[i][j][0], w1 = pk[i][j][1];        // rows (0,1), (2,3) of my token
+      // neighbour in the lane pair: even lanes keep the even row of both tokens, odd lanes the odd row
+      const uint32_t p0 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w0, 0xB1, 0xf, 0xf, false);
+      const uint32_t p1 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w1, 0xB1, 0xf, 0xf, false);
+      const uint32_t x0 = __builtin_amdgcn_perm(p0, w0, sel);   // row (q&1),   tokens of my pair
+      const uint32_t x1 = __builtin_amdgcn_perm(p1, w1, sel);   // row 2+(q&1), tokens of my pair
+      // other pair of the quad: lanes 0,1 collect rows 0,1 and lanes 2,3 rows 2,3 of all four tokens
+      const uint32_t send = upper ? x0 : x1;
+      const uint32_t recv = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)send, 0x4E, 0xf, 0xf, false);
+      const uint2 two = upper ? make_uint2(recv, x1) : make_uint2(x0, recv);
+      *reinterpret_cast<uint2*>(st + (row_l + i * 16) * stride + (tok0_l + j * 16) * 2) = two;
+    }
+  }
+}
+
+// ROWS staged rows of ROW_BYTES (LDS pitch STRIDE) -> dst (row pitch ld elements), 16 bytes per lane.
+template <int ROWS, int ROW_BYTES, int STRIDE, int THREADS>
+__device__ __forceinline__ void ds_store(const char* st, __bf16* dst, int ld, int tid) {
+  constexpr int LANES = ROW_BYTES / 16, STEP = THREADS / LANES;
+  const int chunk = tid % LANES, r0 = tid / LANES;
+#pragma unroll 4
+  for (int ps = 0; ps < ROWS / STEP; ++ps) {
+    const int row = r0 + ps * STEP;
+    const i32x4 v = *reinterpret_cast<const i32x4*>(st + row * STRIDE + chunk * 16);
+    __builtin_nontemporal_store(v, reinterpret_cast<i32x4*>(dst + (size_t)row * ld + chunk * 8));
+  }
+}
+
 template <bool LO, class AfterLoop, class BeforeStores>
 __device__ __forceinline__ void dlogits_tile(const DlogitsArgs& a, int tm, int tn, AfterLoop&& after_loop,
                                              BeforeStores&& before_stores) {
@@ -241,118 +367,35 @@ __device__ __forceinline__ void dlogits_tile(const DlogitsArgs& a, int tm, int t
   mainloop(LA, LB, a.K / BK, g_smem, acc);
   after_loop();
 
-  const int v_base = a.v0 + tm * BM + wm * WROWS;     // global vocab index
-  const bool ragged = (a.v0 + tm * BM + BM > a.V);
-
-  // dS = c (onehot - p) is formed as  -sign(c) 2^(t2 - lse2 + log2|c|)  for every element (one fma
-  // and one exp2 each; c = 0 gives 2^-inf = 0), the one-hot term c is added to the single element
-  // that holds the sampled token (rare, wave-uniform branch), and the sign goes on with the bf16
-  // packing.  pk[i][j][h] holds rows 2h, 2h+1 of this lane's 4-row group as a bf16 pair.
-  // For an fp32 head a second launch (LO) recomputes the tile and stores the remainders dS - bf16(dS).
+  // pk[i][j][h] holds rows 2h, 2h+1 of this lane's 4-row group as a bf16 pair.
   uint32_t pk[GM][GN][2];
 #pragma unroll
   for (int j = 0; j < GN; ++j) {
-    const int tok = tn * BN + wn * WCOLS + j * 16 + (lane & 15);
-    const float c = a.coefc[tok];
-    const float k2 = __builtin_amdgcn_logf(fabsf(c)) - a.lse2[tok];
-    const uint32_t sgn = c > 0.f ? 0x80008000u : 0u;
-    const int yrel = a.yc[tok] - v_base;
-    const bool mine = (yrel >= 0) && (yrel < WROWS) && (((yrel >> 2) & 3) == (lane >> 4));
-    const bool any_mine = __any(mine);
+    f32x4 z[GM];
 #pragma unroll
-    for (int i = 0; i < GM; ++i) {
-      float g[4];
+    for (int i = 0; i < GM; ++i) z[i] = acc[i][j];
+    const DsColumn col(a, tn * BN + wn * WCOLS + j * 16 + (lane & 15));
+    uint32_t p[GM][2];
+    ds_pack<LO>(a, col, a.v0 + tm * BM + wm * WROWS, z, p);
 #pragma unroll
-      for (int r = 0; r < 4; ++r) g[r] = __builtin_amdgcn_exp2f(fmaf(acc[i][j][r], a.scale, k2));
-      if (any_mine) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-          if (yrel == i * 16 + acc_row(r, lane)) g[r] -= fabsf(c);     // sign is applied below
-      }
-      if (ragged) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-          if (v_base + i * 16 + acc_row(r, lane) >= a.V) g[r] = 0.f;
-      }
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
-        bf16x2 two;
-        two[0] = (__bf16)g[2 * h];
-        two[1] = (__bf16)g[2 * h + 1];
-        if constexpr (LO) {
-          two[0] = (__bf16)(g[2 * h] - (float)two[0]);
-          two[1] = (__bf16)(g[2 * h + 1] - (float)two[1]);
-        }
-        pk[i][j][h] = __builtin_bit_cast(uint32_t, two) ^ sgn;
-      }
-    }
+    for (int i = 0; i < GM; ++i) { pk[i][j][0] = p[i][0]; pk[i][j][1] = p[i][1]; }
   }
 
-  // ---- orientation 1: dS[tok][v], staged as rows of 256 v ----
-  char* st = g_smem;
-#pragma unroll
-  for (int j = 0; j < GN; ++j) {
-    const int tok_l = wn * WCOLS + j * 16 + (lane & 15);
-#pragma unroll
-    for (int i = 0; i < GM; ++i) {
-      const int v_l = wm * WROWS + i * 16 + ((lane >> 4) << 2);
-      uint2 two = make_uint2(pk[i][j][0], pk[i][j][1]);
-      *reinterpret_cast<uint2*>(st + tok_l * EPI_STRIDE + v_l * 2) = two;
-    }
-  }
+  __bf16* const dS = (LO ? a.dS_lo : a.dS) + ((size_t)tn * BN) * a.ld_s + (size_t)tm * BM;
+  __bf16* const dST = (LO ? a.dST_lo : a.dST) + ((size_t)tm * BM) * a.ld_t + (size_t)tn * BN;
+  ds_stage_rows<WN>(pk, g_smem, wm, wn, lane);
   before_stores();
-  __syncthreads();
-  {
-    const int chunk = tid & 31, r0 = tid >> 5;
-    __bf16* dst = (LO ? a.dS_lo : a.dS) + ((size_t)tn * BN) * a.ld_s + (size_t)tm * BM + chunk * 8;
-#pragma unroll 4
-    for (int ps = 0; ps < 256 / (NTHREADS / 32); ++ps) {
-      const int row = r0 + ps * (NTHREADS / 32);
-      const i32x4 v = *reinterpret_cast<const i32x4*>(st + row * EPI_STRIDE + chunk * 16);
-      __builtin_nontemporal_store(v, reinterpret_cast<i32x4*>(dst + (size_t)row * a.ld_s));
-    }
-  }
-  __syncthreads();
-  // ---- orientation 2: dS^T[v][tok], staged as rows of 256 tokens ----
-  // A quad of lanes holds a 4 (vocab rows) x 4 (tokens) block, one token per lane.  Two
-  // butterfly exchanges inside the quad turn it so that lane q holds row q of all four tokens,
-  // which then goes to LDS as one 8-byte store (instead of sixteen 2-byte ones per block).
-  {
-    const int q = lane & 3;
-    const uint32_t sel = (q & 1) ? 0x03020706u : 0x05040100u;   // v_perm byte selectors, see below
-    const bool upper = q >= 2;
-    const int row_l = wm * WROWS + ((lane >> 4) << 2) + q;
-    const int tok0_l = wn * WCOLS + (((lane & 15) >> 2) << 2);
-#pragma unroll
-    for (int j = 0; j < GN; ++j) {
-#pragma unroll
-      for (int i = 0; i < GM; ++i) {
-        const uint32_t w0 = pk[i][j][0], w1 = pk[i][j][1];        // rows (0,1), (2,3) of my token
-        // neighbour in the lane pair: even lanes keep the even row of both tokens, odd lanes the odd row
-        const uint32_t p0 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w0, 0xB1, 0xf, 0xf, false);
-        const uint32_t p1 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w1, 0xB1, 0xf, 0xf, false);
-        const uint32_t x0 = __builtin_amdgcn_perm(p0, w0, sel);   // row (q&1),   tokens of my pair
-        const uint32_t x1 = __builtin_amdgcn_perm(p1, w1, sel);   // row 2+(q&1), tokens of my pair
-        // other pair of the quad: lanes 0,1 collect rows 0,1 and lanes 2,3 rows 2,3 of all four tokens
-        const uint32_t send = upper ? x0 : x1;
-        const uint32_t recv = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)send, 0x4E, 0xf, 0xf, false);
-        const uint2 two = upper ? make_uint2(recv, x1) : make_uint2(x0, recv);
-        *reinterpret_cast<uint2*>(st + (row_l + i * 16) * EPI_STRIDE_T + (tok0_l + j * 16) * 2) = two;
-      }
-    }
-  }
-  __syncthreads();
-  {
-    const int chunk = tid & 31, r0 = tid >> 5;
-    __bf16* dst = (LO ? a.dST_lo : a.dST) + ((size_t)tm * BM) * a.ld_t + (size_t)tn * BN + chunk * 8;
-#pragma unroll 4
-    for (int ps = 0; ps < 256 / (NTHREADS / 32); ++ps) {
-      const int row = r0 + ps * (NTHREADS / 32);
-      const i32x4 v = *reinterpret_cast<const i32x4*>(st + row * EPI_STRIDE_T + chunk * 16);
-      __builtin_nontemporal_store(v, reinterpret_cast<i32x4*>(dst + (size_t)row * a.ld_t));
-    }
-  }
+  lds_barrier();
+  ds_store<256, 512, EPI_STRIDE, NTHREADS>(g_smem, dS, a.ld_s, tid);
+  lds_barrier();
+  ds_stage_cols(pk, g_smem, EPI_STRIDE_T, wm, wn, lane);
+  lds_barrier();
+  ds_store<256, 512, EPI_STRIDE_T, NTHREADS>(g_smem, dST, a.ld_t, tid);
+}
+
+// Leading vocab tiles of this chunk whose logits the forward kept.
+__device__ __forceinline__ int kept_in_chunk(const DlogitsArgs& a, int tiles_t) {
+  return imin(imax(kept_vocab_tiles(a.kept, a.tiles_v_all, tiles_t) - a.v0 / BM, 0), a.tiles_v);
 }
 
 template <bool LO>
@@ -364,6 +407,11 @@ __global__ __launch_bounds__(NTHREADS) void lmhead_dlogits_kernel(DlogitsArgs a)
     a.v0 = 0; a.tiles_v = a.rc.tiles_v_all; a.ld_s = a.rc.ld_s_all; a.ld_t = ld_t_all;
   }
   const int tiles_t = min(a.tiles_t, ctl.n_pad / BN);   // live token tiles: known only on the device
+  const int skip = kept_in_chunk(a, tiles_t);           // these are finished by dlogits_kept_kernel
+  a.v0 += skip * BM; a.tiles_v -= skip;
+  a.dS += skip * BM; a.dST += (size_t)skip * BM * a.ld_t;
+  if (LO) { a.dS_lo += skip * BM; a.dST_lo += (size_t)skip * BM * a.ld_t; }
+  if (a.tiles_v == 0 || tiles_t == 0) return;
   TileQueue Q;
   Q.init(a.queue, a.tiles_v * tiles_t, 0);
   volatile int* claim = reinterpret_cast<volatile int*>(g_smem + CLAIM_OFF);
@@ -373,6 +421,78 @@ __global__ __launch_bounds__(NTHREADS) void lmhead_dlogits_kernel(DlogitsArgs a)
     map_tile(b, a.tiles_v, tiles_t, tm, tn);
     dlogits_tile<LO>(a, tm, tn, after_loop, before_stores);
   });
+}
+
+// dS of the vocab tiles whose logits the forward kept: the epilogue of the recompute with the accumulators
+// read back instead of computed.  Bound by HBM (256 KiB read and 256 KiB written per 256 x 256 tile); a
+// workgroup takes 256 vocab rows x 128 tokens, i.e. four wavefronts of a kept tile, so that two fit a
+// compute unit (72 KiB of LDS each) and one's loads run under the other's stores.  Measured at d = 5120,
+// V = 151936: 768 rows 119 us (recompute 639 us; 7.8 TB/s, part of the kept tiles still sits in the
+// memory-side cache), 32768 rows 4.8 TB/s, the rate of a plain copy (recompute of the same tiles 4.2 times as
+// long).  Requesting a quarter or half of the next half tile before the stores: 126 us at 768 rows.
+constexpr int KEPT_STRIDE_T = 288;                          // 128 tokens + pad: 72 dwords, see EPI_STRIDE_T
+constexpr int KEPT_THREADS = 256;
+constexpr int KEPT_LDS_BYTES = 256 * KEPT_STRIDE_T;
+static_assert(KEPT_LDS_BYTES >= 128 * EPI_STRIDE && 2 * KEPT_LDS_BYTES <= 160 * 1024, "LDS budget");
+
+template <bool SPLIT>
+__global__ __launch_bounds__(KEPT_THREADS, 2) void dlogits_kept_kernel(DlogitsArgs a) {
+  const Ctl ctl = *a.ctl;
+  int ld_t_all;
+  if (rechunk_all(a.rc, ctl.n_pad, ld_t_all)) {
+    if (a.rc.chunk > 0) return;
+    a.v0 = 0; a.tiles_v = a.rc.tiles_v_all; a.ld_s = a.rc.ld_s_all; a.ld_t = ld_t_all;
+  }
+  const int tiles_t = min(a.tiles_t, ctl.n_pad / BN);
+  const int total = 2 * kept_in_chunk(a, tiles_t) * tiles_t;
+  const int tid = threadIdx.x, lane = tid & 63, wm = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int tm0 = a.v0 / BM;
+  f32x4 acc[GM][GN];
+  auto fetch = [&](int h) {
+    const f32x4* kp = reinterpret_cast<const f32x4*>(a.kept.tiles + ((size_t)tm0 * tiles_t + (h >> 1)) * KEPT_TILE_FLOATS) +
+                      (wm * WN + (h & 1)) * (GM * GN * 64) + lane;
+#pragma unroll
+    for (int j = 0; j < GN; ++j)
+#pragma unroll
+      for (int i = 0; i < GM; ++i) acc[i][j] = __builtin_nontemporal_load(kp + (j * GM + i) * 64);
+  };
+  for (int h = blockIdx.x; h < total; h += gridDim.x) {
+    fetch(h);
+    const int tm = (h >> 1) / tiles_t, tn = (h >> 1) - tm * tiles_t, half = h & 1;
+    const size_t o_s = ((size_t)tn * BN + half * WCOLS) * a.ld_s + (size_t)tm * BM;
+    const size_t o_t = ((size_t)tm * BM) * a.ld_t + (size_t)tn * BN + half * WCOLS;
+    uint32_t pk[GM][GN][2];
+    auto pack = [&](auto lo) {
+#pragma unroll
+      for (int j = 0; j < GN; ++j) {
+        f32x4 z[GM];
+#pragma unroll
+        for (int i = 0; i < GM; ++i) z[i] = acc[i][j];
+        const DsColumn col(a, tn * BN + half * WCOLS + j * 16 + (lane & 15));
+        uint32_t p[GM][2];
+        ds_pack<decltype(lo)::value>(a, col, a.v0 + tm * BM + wm * WROWS, z, p);
+#pragma unroll
+        for (int i = 0; i < GM; ++i) { pk[i][j][0] = p[i][0]; pk[i][j][1] = p[i][1]; }
+      }
+    };
+    auto flush = [&](__bf16* dS, __bf16* dST) {
+      ds_stage_rows<1>(pk, g_smem, wm, 0, lane);
+      lds_barrier();
+      ds_store<128, 512, EPI_STRIDE, KEPT_THREADS>(g_smem, dS, a.ld_s, tid);
+      lds_barrier();
+      ds_stage_cols(pk, g_smem, KEPT_STRIDE_T, wm, 0, lane);
+      lds_barrier();
+      ds_store<256, 256, KEPT_STRIDE_T, KEPT_THREADS>(g_smem, dST, a.ld_t, tid);
+      lds_barrier();
+    };
+    pack(std::false_type{});
+    flush(a.dS + o_s, a.dST + o_t);
+    if constexpr (SPLIT) {
+      fetch(h);                 // read again: held across the stores they would spill
+      pack(std::true_type{});
+      flush(a.dS_lo + o_s, a.dST_lo + o_t);
+    }
+  }
 }
 
 // ------------------------------------------------------------------------------------
@@ -506,6 +626,8 @@ hipError_t init_gemm_kernels() {
                                hipFuncAttributeMaxDynamicSharedMemorySize, PERSISTENT_LDS_BYTES)) != hipSuccess) return e;
   if ((e = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_store_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
                                PERSISTENT_LDS_BYTES)) != hipSuccess) return e;
+  for (const void* k : {reinterpret_cast<const void*>(dlogits_kept_kernel<false>), reinterpret_cast<const void*>(dlogits_kept_kernel<true>)})
+    if ((e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, KEPT_LDS_BYTES)) != hipSuccess) return e;
   int dev = 0, cus = 0;
   if ((e = hipGetDevice(&dev)) != hipSuccess) return e;
   if ((e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess) return e;
@@ -521,6 +643,13 @@ void launch_lmhead_fwd(const FwdArgs& a, hipStream_t s) {
   hipLaunchKernelGGL(lmhead_fwd_kernel, dim3(persistent_grid(a.tiles_v, a.tiles_t)), dim3(NTHREADS), FWD_LDS_BYTES, s, a);
 }
 void launch_lmhead_dlogits(const DlogitsArgs& a, hipStream_t s) {
+  if (a.kept.cap > 0) {    // at most: every half tile of the launch's widest form
+    const long long halves = 2ll * (a.rc.enabled ? a.rc.tiles_v_all : a.tiles_v) * a.tiles_t;
+    const dim3 grid((unsigned)(halves < 2 * g_persistent_grid ? halves : 2 * g_persistent_grid));
+    if (a.dS_lo) hipLaunchKernelGGL(dlogits_kept_kernel<true>, grid, dim3(KEPT_THREADS), KEPT_LDS_BYTES, s, a);
+    else hipLaunchKernelGGL(dlogits_kept_kernel<false>, grid, dim3(KEPT_THREADS), KEPT_LDS_BYTES, s, a);
+    if ((long long)a.kept.cap >= (long long)a.tiles_v_all * a.tiles_t) return;      // whatever is live, all of it is kept
+  }
   hipLaunchKernelGGL(lmhead_dlogits_kernel<false>, dim3(persistent_grid(a.tiles_v, a.tiles_t)), dim3(NTHREADS), PERSISTENT_LDS_BYTES, s, a);
   if (a.dS_lo) {   // fp32 head: the remainders, from a second pass over the same tiles with a queue of its own
     DlogitsArgs lo = a;
