@@ -30,6 +30,7 @@ int32_t fail(int32_t code, const char* fmt, ...) {
 constexpr size_t ALIGN = 256;
 constexpr uint64_t FOUR_GIB = 1ull << 32;
 constexpr uint64_t DS_BUDGET = 2ull << 30;   // bytes per orientation of the dS chunk scratch
+constexpr int64_t ACC_ROWS_SPLIT = 32768;
 constexpr double LOG2E = 1.4426950408889634;
 
 // Tuning knob: PG_HEAD_DS_BUDGET_BYTES overrides the size of the dS chunk scratch (and with
@@ -63,6 +64,7 @@ struct Plan {
   int vc = 0;          // chunk_tiles * 256
   int ld_v = 0;        // leading dimension of the [*, vc] scratch matrices
   int ld_t = 0;        // leading dimension of the [*, t_cap] scratch matrices
+  int acc_rows = 0;    // rows of the dH accumulator
   int queue_words = 0; // tile-queue counters (8 per persistent launch)
   size_t ctl, counters, queue, flag, c_tok, a_tok, rows, pos, yc, zy, lse2, coefc, lossterm;
   size_t part_m, part_s, part_u, Hc, HcT, Wc, dS, dST, WT, dHacc, rstd_c = 0, norm_partial = 0;
@@ -173,7 +175,11 @@ int32_t make_plan(int64_t T, int64_t d, int64_t V, int32_t S, const pg_params* p
       pl.dST_lo = take((size_t)vc * ld_t * 2);
       pl.WT_lo = take((size_t)d * ld_v * 2);
     }
-    pl.dHacc = take((size_t)t_cap * d * 4);
+    // fp32 dH accumulator: one slab of the active rows per part of the split contraction (dh_split); with few rows
+    // there is room for the largest split, up to ACC_ROWS_SPLIT rows in all
+    const int64_t split_rows = pg::SPLIT_MAX * t_cap < ACC_ROWS_SPLIT ? pg::SPLIT_MAX * t_cap : ACC_ROWS_SPLIT;
+    pl.acc_rows = (int)(t_cap > split_rows ? t_cap : split_rows);
+    pl.dHacc = take((size_t)pl.acc_rows * d * 4);
     pl.queue_words = pg::QUEUE_SET_WORDS * pg::queue_sets((int)nchunks);
   }
   pl.queue = take((size_t)pl.queue_words * sizeof(unsigned));
@@ -762,6 +768,7 @@ int32_t loss_fwd_bwd(int sft, const void* H, const void* W, const int32_t* y, co
   const void* Wop = pl.is_f32 ? static_cast<const void*>(at<__bf16>(ws, pl.Wc)) : W;
   const pg::Ctl* ctl = at<pg::Ctl>(ws, pl.ctl);
   const int d_i = (int)pl.d;
+  const int kc0 = (int)(((pl.V < pl.vc ? pl.V : pl.vc) + 255) / 256 * 256);      // contraction length of the first chunk
   for (int c = 0; c < pl.nchunks; ++c) {
     const int v0 = c * pl.vc;
     if (v0 >= pl.V) break;
@@ -817,14 +824,14 @@ int32_t loss_fwd_bwd(int sft, const void* H, const void* W, const int32_t* y, co
     h.tiles_m = pl.tiles_t; h.tiles_n = (d_i + 255) / 256;
     h.C = at<float>(ws, pl.dHacc); h.ldc = d_i;
     h.accumulate = c > 0; h.out_bf16 = 0; h.k_from_ctl = 0; h.m_from_ctl = 1; h.split_k = 1; h.ctl = ctl;
+    h.acc_rows = pl.acc_rows; h.split_stages = kc0 / 64;
     h.queue = queues + 2 * pg::QUEUE_SET_WORDS;
     h.rc = rc; h.rc_role = 2; h.v0 = v0;
     { ProfScope ps(PG_KERNEL_DH, st); pg::launch_gemm_store(h, st); }
   }
 
-  const int kc0 = (int)(((pl.V < pl.vc ? pl.V : pl.vc) + 255) / 256 * 256);      // contraction length of the first chunk
   pg::ScatterArgs sc{at<float>(ws, pl.dHacc), at<int>(ws, pl.pos), dH, (int)pl.T, d_i, pl.is_f32 || shard.dH_f32,
-                     1, pl.t_cap, (d_i + 255) / 256, kc0 / 64, ctl};
+                     1, pl.acc_rows, (d_i + 255) / 256, kc0 / 64, ctl};
   if (norm) pg::launch_scatter_dx_norm(sc, nf, st);
   else pg::launch_scatter_dh(sc, st);
   return guard.check(shard.what ? shard.what : sft ? "pg_sft_fwd_bwd" : norm ? "pg_loss_fwd_bwd_normed" : "pg_loss_fwd_bwd");

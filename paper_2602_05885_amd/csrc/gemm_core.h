@@ -137,21 +137,32 @@ __host__ __device__ inline bool map_tile_interleaved(int bid, int tiles_m, int t
   return true;
 }
 
-// Split-K factor of the dH contraction.  Its row extent is the padded number of active tokens,
-// known only on the device; when those rows give fewer tiles than the chip has compute units
-// (a microbatch most of whose samples were rejected), the contraction length is cut into ks
-// parts that run side by side.  Part p accumulates into its own slab of n_pad rows of the
-// [t_cap, d] accumulator (so ks n_pad <= t_cap), and the final scatter adds the slabs in order.
-// Every kernel derives ks from the same device-side values, so the decomposition, and with it
-// the summation order, is fixed for given inputs.
-__host__ __device__ inline int dh_split(int n_pad, int t_cap, int tiles_n, int k_stages) {
+// Split-K factor of the dH contraction.  Its row extent is the padded number of active tokens, known only on
+// the device, and its contraction (a vocab chunk) is long: with few rows one tile per compute unit leaves most
+// of the chip idle, with a few more the second round of tiles is nearly empty.  The contraction length is
+// therefore cut into ks parts that run side by side.  Part p accumulates into its own slab of n_pad rows of
+// the [acc_rows, d] accumulator (so ks n_pad <= acc_rows), and the final scatter adds the slabs in order.
+// ks minimises the modelled time of the launch, in stages: rounds of 256 tiles, each as long as a part plus
+// SPLIT_TILE_STAGES for what a tile costs beside its main loop (cold start, accumulator read and write, the
+// slab's extra pass in the scatter).  Measured at V = 151936 (one chunk, 2376 stages), dH launch alone:
+//   768 rows, d = 5120 (60 tiles)     one part 1466 us, 4 parts 579 us
+//   3072 rows, d = 4096 (192 tiles)   one part 3167 us, 4 parts 2479 us
+// (Longest split: 8 parts, beyond which the parts of a round no longer get shorter than their own overhead.)
+// Every kernel derives ks from the same device-side values (k_stages: those of the first chunk, for all
+// chunks), so the decomposition, and with it the summation order, is fixed for given inputs.
+constexpr int SPLIT_MAX = 8, SPLIT_MIN_STAGES = 8, SPLIT_TILE_STAGES = 24;
+__host__ __device__ inline int dh_split(int n_pad, int acc_rows, int tiles_n, int k_stages) {
   if (n_pad <= 0) return 1;
   const int tiles = (n_pad / 256) * tiles_n;
-  int ks = 256 / (tiles > 0 ? tiles : 1);
-  if (ks > t_cap / n_pad) ks = t_cap / n_pad;
-  if (ks > k_stages / 8) ks = k_stages / 8;        // every part keeps at least 8 stages
-  if (ks > 8) ks = 8;
-  return ks < 1 ? 1 : ks;
+  int best = 1;
+  long long best_cost = 0;
+  for (int ks = 1; ks <= SPLIT_MAX; ++ks) {
+    if (ks > 1 && ((long long)ks * n_pad > acc_rows || ks * SPLIT_MIN_STAGES > k_stages)) break;
+    const long long rounds = ((long long)tiles * ks + 255) / 256;
+    const long long cost = rounds * ((k_stages + ks - 1) / ks + SPLIT_TILE_STAGES);
+    if (ks == 1 || cost < best_cost) { best = ks; best_cost = cost; }
+  }
+  return best;
 }
 
 // ---- operand slabs in LDS ----------------------------------------------------------

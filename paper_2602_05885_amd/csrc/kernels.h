@@ -123,7 +123,9 @@ struct StoreArgs {
   int out_bf16;
   int k_from_ctl;       // contraction length = padded active-token count
   int m_from_ctl;       // row extent        = padded active-token count
-  int split_k;          // with m_from_ctl: cut K into dh_split() parts, part p writes rows p n_pad + m
+  int split_k;          // with m_from_ctl: cut K into dh_split(n_pad, acc_rows, tiles_n, split_stages) parts, part p writes rows p n_pad + m
+  int acc_rows;         // rows of C
+  int split_stages;     // stages of the first chunk's contraction
   const Ctl* ctl;
   unsigned* queue;      // [8] tile counters of this launch's queue, zero at launch
   Rechunk rc;           // see there; rc_role 0: not a chunked launch, 1: dW of a chunk, 2: dH of a chunk
@@ -245,7 +247,7 @@ struct ScatterArgs {
   int out_f32;
   // split-K slabs of the accumulator (see dh_split): 0 = one slab; else the arguments of dh_split
   // as the first chunk's contraction saw them
-  int split_k, t_cap, tiles_n, k_stages;
+  int split_k, acc_rows, tiles_n, k_stages;
   const Ctl* ctl;
 };
 void launch_scatter_dh(const ScatterArgs& a, hipStream_t s);

@@ -545,7 +545,7 @@ struct StoreShape {
     m_lim = a.m_from_ctl ? min(a.M, ctl.n_pad) : a.M;
     tiles_m = min(a.tiles_m, (m_lim + BM - 1) / BM);
     K = a.k_from_ctl ? ctl.n_pad : a.K;
-    ks = (a.split_k && a.m_from_ctl) ? dh_split(ctl.n_pad, a.M, a.tiles_n, K / BK) : 1;
+    ks = (a.split_k && a.m_from_ctl) ? dh_split(ctl.n_pad, a.acc_rows, a.tiles_n, a.split_stages) : 1;
     total = tiles_m * ks * a.tiles_n;
   }
 };
@@ -658,8 +658,8 @@ void launch_lmhead_dlogits(const DlogitsArgs& a, hipStream_t s) {
   }
 }
 void launch_gemm_store(const StoreArgs& a, hipStream_t s) {
-  // (a split contraction's parts share the row extent: parts x live rows never exceed tiles_m tiles)
-  hipLaunchKernelGGL(gemm_store_kernel, dim3(persistent_grid(a.tiles_m, a.tiles_n)), dim3(NTHREADS), PERSISTENT_LDS_BYTES, s, a);
+  // (a split contraction has at most acc_rows / 256 row tiles over all parts)
+  hipLaunchKernelGGL(gemm_store_kernel, dim3(persistent_grid(a.split_k ? max(a.tiles_m, a.acc_rows / BM) : a.tiles_m, a.tiles_n)), dim3(NTHREADS), PERSISTENT_LDS_BYTES, s, a);
 }
 
 }  // namespace pg

@@ -480,7 +480,7 @@ __global__ __launch_bounds__(256) void scatter_dh_kernel(ScatterArgs a) {
   const int p = a.pos[t];
   const float* src = a.acc + (size_t)(p < 0 ? 0 : p) * a.d;
   const int n_pad = a.ctl->n_pad;
-  const int ks = a.split_k ? dh_split(n_pad, a.t_cap, a.tiles_n, a.k_stages) : 1;
+  const int ks = a.split_k ? dh_split(n_pad, a.acc_rows, a.tiles_n, a.k_stages) : 1;
   const size_t slab = (size_t)n_pad * a.d;
   for (int j = threadIdx.x * 4; j < a.d; j += 256 * 4) {
     float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -1096,7 +1096,7 @@ __global__ __launch_bounds__(256) void scatter_dx_norm_kernel(ScatterArgs a, Nor
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const long long T = a.T;
   const int n_pad = a.ctl->n_pad;
-  const int ks = a.split_k ? dh_split(n_pad, a.t_cap, a.tiles_n, a.k_stages) : 1;
+  const int ks = a.split_k ? dh_split(n_pad, a.acc_rows, a.tiles_n, a.k_stages) : 1;
   const size_t slab = (size_t)n_pad * a.d;
   float dg[NC][8];
   Raw8<F32> gam_raw[NC] = {};
