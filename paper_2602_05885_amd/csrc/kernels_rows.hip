@@ -374,36 +374,46 @@ void launch_transpose_w(const void* W, int is_f32, int64_t V, int d, int ldw, in
 // Merges the per-vocab-tile softmax partials of every compacted row with the online merge rule
 // (m, s, u) + (m2, s2, u2), emits log-prob / entropy / logsumexp, and for the loss call evaluates
 // the clipped surrogate and the coefficient that scales (onehot - softmax) in the backward.
-__global__ __launch_bounds__(256) void combine_kernel(CombineArgs a) {
-  // 64 tokens per workgroup; the four wavefronts each merge every fourth vocab tile's partial
-  // state (online, fixed order), then wavefront 0 merges the four results and finishes the row.
-  __shared__ float sh[3][3][64];
+// The vocab tiles of a row are dealt to COMBINE_WAVES wavefronts, each of which merges every 16th tile's state
+// (online, fixed order) with the loads of four tiles in flight; wavefront 0 then merges the 16 results in order and
+// finishes the row.  With few rows the serial chain of loads and merges is all there is (594 tiles: 76 us with
+// 4 wavefronts and one tile in flight at 768 rows, 15 us so); with many it is HBM-bound (32768 rows: 88 us, 46 us so).
+constexpr int COMBINE_WAVES = 16;
+
+__device__ __forceinline__ void combine_merge(float& M, float& s, float& u, float m2, float s2, float u2) {
+  const float mm = fmaxf(M, m2);
+  const float a1 = __builtin_amdgcn_exp2f(M - mm), a2 = __builtin_amdgcn_exp2f(m2 - mm);
+  u = a1 * (u + (M - mm) * s) + a2 * (u2 + (m2 - mm) * s2);
+  s = a1 * s + a2 * s2;
+  M = mm;
+}
+
+__global__ __launch_bounds__(64 * COMBINE_WAVES) void combine_kernel(CombineArgs a) {
+  __shared__ float sh[COMBINE_WAVES - 1][3][64];
   const Ctl ctl = *a.ctl;
   const int lane = threadIdx.x & 63, part = threadIdx.x >> 6;
   const int i = blockIdx.x * 64 + lane;
   if (blockIdx.x * 64 >= ctl.n_pad) return;      // whole workgroup beyond the padded rows
   float M = -1.0e30f, s = 0.f, u = 0.f;
-  for (int k = part; k < a.tiles_v; k += 4) {
+  int k = part;
+  for (; k + 3 * COMBINE_WAVES < a.tiles_v; k += 4 * COMBINE_WAVES) {
+    float m2[4], s2[4], u2[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const size_t o = (size_t)(k + q * COMBINE_WAVES) * a.t_cap + i;
+      m2[q] = a.part_m[o]; s2[q] = a.part_s[o]; u2[q] = a.part_u[o];
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) combine_merge(M, s, u, m2[q], s2[q], u2[q]);
+  }
+  for (; k < a.tiles_v; k += COMBINE_WAVES) {
     const size_t o = (size_t)k * a.t_cap + i;
-    const float m2 = a.part_m[o], s2 = a.part_s[o], u2 = a.part_u[o];
-    const float mm = fmaxf(M, m2);
-    const float a1 = __builtin_amdgcn_exp2f(M - mm), a2 = __builtin_amdgcn_exp2f(m2 - mm);
-    u = a1 * (u + (M - mm) * s) + a2 * (u2 + (m2 - mm) * s2);
-    s = a1 * s + a2 * s2;
-    M = mm;
+    combine_merge(M, s, u, a.part_m[o], a.part_s[o], a.part_u[o]);
   }
   if (part > 0) { sh[part - 1][0][lane] = M; sh[part - 1][1][lane] = s; sh[part - 1][2][lane] = u; }
   __syncthreads();
   if (part > 0) return;
-#pragma unroll
-  for (int w = 0; w < 3; ++w) {
-    const float m2 = sh[w][0][lane], s2 = sh[w][1][lane], u2 = sh[w][2][lane];
-    const float mm = fmaxf(M, m2);
-    const float a1 = __builtin_amdgcn_exp2f(M - mm), a2 = __builtin_amdgcn_exp2f(m2 - mm);
-    u = a1 * (u + (M - mm) * s) + a2 * (u2 + (m2 - mm) * s2);
-    s = a1 * s + a2 * s2;
-    M = mm;
-  }
+  for (int w = 0; w < COMBINE_WAVES - 1; ++w) combine_merge(M, s, u, sh[w][0][lane], sh[w][1][lane], sh[w][2][lane]);
   const float LN2 = 0.693147180559945309f, LOG2E = 1.44269504088896341f;
   if (a.partials_out) {      // this shard's state of the row, natural-log units
     if (i < ctl.n_active)
@@ -450,7 +460,7 @@ __global__ __launch_bounds__(256) void combine_kernel(CombineArgs a) {
   a.lossterm[i] = c * l;
 }
 void launch_combine(const CombineArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(combine_kernel, dim3(a.t_cap / 64), dim3(256), 0, s, a);
+  hipLaunchKernelGGL(combine_kernel, dim3(a.t_cap / 64), dim3(64 * COMBINE_WAVES), 0, s, a);
 }
 
 // Single workgroup, fixed order, fp64: loss = (sum_t c_t l_t) / norm; publishes the counters.
