@@ -64,10 +64,11 @@ struct Plan {
   int vc = 0;          // chunk_tiles * 256
   int ld_v = 0;        // leading dimension of the [*, vc] scratch matrices
   int ld_t = 0;        // leading dimension of the [*, t_cap] scratch matrices
+  bool direct_fits = false;  // the dH contraction can read W as it lies
   int acc_rows = 0;    // rows of the dH accumulator
   int queue_words = 0; // tile-queue counters (8 per persistent launch)
   size_t ctl, counters, queue, flag, c_tok, a_tok, rows, pos, yc, zy, lse2, coefc, lossterm;
-  size_t part_m, part_s, part_u, Hc, HcT, Wc, dS, dST, WT, dHacc, rstd_c = 0, norm_partial = 0;
+  size_t part_m, part_s, part_u, Hc, HcT, Wc, dS, dST, WT = 0, dHacc, rstd_c = 0, norm_partial = 0;
   size_t HcT_lo = 0, dS_lo = 0, dST_lo = 0, WT_lo = 0;   // fp32 heads only
   size_t kept = 0;     // fp32 logits kept for the backward: the last region
   int kept_cap = 0;    // ... in 256 x 256 tiles
@@ -168,7 +169,8 @@ int32_t make_plan(int64_t T, int64_t d, int64_t V, int32_t S, const pg_params* p
     pl.HcT = take((size_t)d * ld_t * 2);
     pl.dS = take((size_t)t_cap * ld_v * 2);
     pl.dST = take((size_t)vc * ld_t * 2);
-    pl.WT = take((size_t)d * ld_v * 2);
+    pl.direct_fits = (uint64_t)vc * kd * 2 < FOUR_GIB;      // RowsLoader's range
+    if (!pl.direct_fits || t_cap > pg::DIRECT_MAX_ROWS) pl.WT = take((size_t)d * ld_v * 2);
     if (pl.is_f32) {   // bf16 remainders of the four backward operands
       pl.HcT_lo = take((size_t)d * ld_t * 2);
       pl.dS_lo = take((size_t)t_cap * ld_v * 2);
@@ -783,9 +785,14 @@ int32_t loss_fwd_bwd(int sft, const void* H, const void* W, const int32_t* y, co
       wt = static_cast<__bf16*>(p.w_transposed) + v0;
       ld_wt = (int)wt_cache_ld(pl.V);
     }
-    if (!p.w_transposed || !p.w_transposed_valid) pg::launch_transpose_w(W, pl.is_f32, pl.V, d_i, d_i, v0, kc, ld_wt, wt, st);
-    if (pl.is_f32)   // the remainders W - bf16(W) are columns [d, 2d) of the split operand
-      pg::launch_transpose_w(at<__bf16>(ws, pl.Wc) + d_i, 0, pl.V, d_i, pl.kd, v0, kc, pl.ld_v, at<__bf16>(ws, pl.WT_lo), st);
+    // ... unless the dH launch reads W as it lies: for certain (every row count fits), or decided on the device
+    const bool direct = pl.direct_fits && !p.w_transposed, transposed = !direct || pl.t_cap > pg::DIRECT_MAX_ROWS;
+    const pg::DirectRule rule{direct && transposed ? ctl : nullptr};
+    if (transposed) {
+      if (!p.w_transposed || !p.w_transposed_valid) pg::launch_transpose_w(W, pl.is_f32, pl.V, d_i, d_i, v0, kc, ld_wt, wt, rule, st);
+      if (pl.is_f32)   // the remainders W - bf16(W) are columns [d, 2d) of the split operand
+        pg::launch_transpose_w(at<__bf16>(ws, pl.Wc) + d_i, 0, pl.V, d_i, pl.kd, v0, kc, pl.ld_v, at<__bf16>(ws, pl.WT_lo), rule, st);
+    }
 
     pg::DlogitsArgs g{};
     g.W = Wop; g.Hc = at<__bf16>(ws, pl.Hc);
@@ -827,7 +834,17 @@ int32_t loss_fwd_bwd(int sft, const void* H, const void* W, const int32_t* y, co
     h.acc_rows = pl.acc_rows; h.split_stages = kc0 / 64;
     h.queue = queues + 2 * pg::QUEUE_SET_WORDS;
     h.rc = rc; h.rc_role = 2; h.v0 = v0;
-    { ProfScope ps(PG_KERNEL_DH, st); pg::launch_gemm_store(h, st); }
+    h.rule = rule;
+    {
+      ProfScope ps(PG_KERNEL_DH, st);
+      if (transposed) pg::launch_gemm_store(h, st);
+      if (direct) {
+        h.b_k_rows = 1; h.b_rows = rows_valid; h.ldb = pl.kd;
+        h.B = static_cast<const __bf16*>(Wop) + (size_t)v0 * pl.kd;
+        if (pl.is_f32) { h.B_lo = static_cast<const __bf16*>(h.B) + d_i; h.ldb_lo = pl.kd; }
+        pg::launch_gemm_store(h, st);
+      }
+    }
   }
 
   pg::ScatterArgs sc{at<float>(ws, pl.dHacc), at<int>(ws, pl.pos), dH, (int)pl.T, d_i, pl.is_f32 || shard.dH_f32,

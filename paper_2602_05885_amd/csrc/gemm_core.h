@@ -174,6 +174,8 @@ __host__ __device__ inline int dh_split(int n_pad, int acc_rows, int tiles_n, in
 // Loads beyond the buffer resource's size return 0, which pads ragged tiles.
 static_assert(BM == BN, "one loader serves both operands");
 struct TileLoader {
+  static constexpr uint32_t k_step = BK * 2;   // bytes from one stage to the next
+  __device__ __forceinline__ bool on(int kt, int nk) const { return kt < nk; }
   const void* base;
   uint32_t bytes;
   uint32_t voff[CHUNKS];
@@ -216,6 +218,80 @@ struct TileLoader {
   }
 };
 
+// An A operand whose k runs over the ROWS of its matrix (X[k][n], n contiguous): a slab is 64 rows x 256
+// columns, 512 B per row, and the fragments are read transposed (ds_read_b64_tr_b16: a 16-lane group reads 4 rows
+// x 16 columns, lane i receives the 4 rows of column i).  The 32-byte column group p of row r is stored at position
+// p ^ s(r), s(r) = (r & 3) | (((r >> 3) & 1) << 2): the eight rows that a half-wavefront reads then lie in eight
+// different groups of 8 banks.  One wavefront load instruction fills two rows.
+typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
+struct RowsLoader {
+  const void* base;
+  uint32_t bytes;
+  uint32_t voff[CHUNKS];
+  uint32_t k_step;      // bytes from one stage to the next
+  int rows;             // rows that exist
+  // (a stage without a single row is switched off: its offset would lie beyond the resource's range)
+  __device__ __forceinline__ bool on(int kt, int nk) const { return kt < nk && kt * BK < rows; }
+
+  __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(bool on) const {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, on ? bytes : 0u, 0x00020000);
+  }
+  // rows [k_row0, k_rows) of a matrix of row length ld, from column col0 on.  Rows at and beyond k_rows read as
+  // zero; columns beyond the matrix read whatever follows in memory within it (they only reach output columns
+  // that are not stored).  (k_rows - k_row0) ld 2 must stay below 4 GiB.
+  __device__ __forceinline__ void init(const void* base_, int k_rows, int k_row0, int ld, int col0, int tid) {
+    const uint64_t b = reinterpret_cast<uint64_t>(base_) + ((uint64_t)k_row0 * (uint64_t)ld + (uint64_t)col0) * 2u;
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)b);
+    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(b >> 32));
+    base = reinterpret_cast<const void*>(((uint64_t)hi << 32) | lo);
+    rows = __builtin_amdgcn_readfirstlane(max(k_rows - k_row0, 0));
+    bytes = __builtin_amdgcn_readfirstlane(rows > 0 ? (uint32_t)rows * (uint32_t)ld * 2u - (uint32_t)col0 * 2u : 0u);
+    k_step = (uint32_t)BK * (uint32_t)ld * 2u;
+    const int lane = tid & 63, wave = tid >> 6;
+#pragma unroll
+    for (int i = 0; i < CHUNKS; ++i) {
+      const int row = (i * NW + wave) * 2 + (lane >> 5), c = lane & 31;
+      const int s = (row & 3) | (((row >> 3) & 1) << 2);
+      voff[i] = (uint32_t)row * (uint32_t)ld * 2u + (uint32_t)((((c >> 1) ^ s) << 1) | (c & 1)) * 16u;
+    }
+  }
+  __device__ __forceinline__ void issue1(__amdgpu_buffer_rsrc_t r, int i, uint32_t k_byte_off, char* slab, int wave) const {
+    char* dst = slab + (i * NW + wave) * 1024;
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void*)dst, 16, voff[i], k_byte_off, 0, 0);
+  }
+};
+
+// One transposed read.  (The pointer is a restrict parameter so that the read carries alias information of its own: without
+// it the compiler waits for every outstanding global -> LDS load in front of it.  The schedule's barriers order the two.)
+__device__ __forceinline__ bf16x4 ds_read_tr(lds_bf16x4* __restrict__ p) { return __builtin_amdgcn_ds_read_tr16_b64_v4bf16(p); }
+
+// Fragments of the A slab: MFMA tile i of this wavefront, k-half ks of the stage.
+template <class Loader> struct FragA;
+template <> struct FragA<TileLoader> {
+  uint32_t off, koff[2];
+  __device__ __forceinline__ FragA(int lane, int wm) {
+    off = (uint32_t)(wm * WROWS + (lane & 15)) * 128u;
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) koff[ks] = (uint32_t)(((ks * 4 + (lane >> 4)) ^ ((lane >> 1) & 7)) << 4);
+  }
+  __device__ __forceinline__ bf16x8 read(const char* st, int ks, int i) const {
+    return *reinterpret_cast<const bf16x8*>(st + off + i * (16 * 128) + koff[ks]);
+  }
+};
+template <> struct FragA<RowsLoader> {
+  uint32_t off[GM];
+  __device__ __forceinline__ FragA(int lane, int wm) {
+    const int r = (lane & 15) >> 2, g = lane >> 4, s = r | ((g & 1) << 2);
+#pragma unroll
+    for (int i = 0; i < GM; ++i) off[i] = (uint32_t)(g * 8 + r) * 512u + (uint32_t)((wm * GM + i) ^ s) * 32u + (uint32_t)(lane & 3) * 8u;
+  }
+  __device__ __forceinline__ bf16x8 read(const char* st, int ks, int i) const {
+    const char* p = st + off[i] + ks * (32 * 512);
+    const bf16x4 lo = ds_read_tr((lds_bf16x4*)p), hi = ds_read_tr((lds_bf16x4*)(p + 4 * 512));
+    return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+  }
+};
+
 // Accumulates C(256x256) += A(256 x K) B(256 x K)^T for this workgroup's tile, K = 64 nk.
 // acc[i][j] is the 16x16 MFMA tile at rows wm*64+i*16, cols wn*128+j*16 of the workgroup tile;
 // within it, register r of lane l is row 4*(l>>4)+r, column l&15.
@@ -232,7 +308,8 @@ struct TileLoader {
 // On return every load has landed and every wavefront has passed a barrier, so the caller may
 // reuse the LDS.  The barriers carry their own waits; the "memory" clobber keeps LDS accesses on
 // their side of them.
-__device__ __forceinline__ void mainloop(const TileLoader& LA, const TileLoader& LB, int nk, char* smem,
+template <class LoaderA>
+__device__ __forceinline__ void mainloop(const LoaderA& LA, const TileLoader& LB, int nk, char* smem,
                                          f32x4 (&acc)[GM][GN]) {
   constexpr int NS = 2 * GN;          // steps per stage
   constexpr int TAIL = 2;             // steps behind barrier Y
@@ -244,7 +321,7 @@ __device__ __forceinline__ void mainloop(const TileLoader& LA, const TileLoader&
   const int wm = wave / WN, wn = wave % WN;
   const int lrow = lane & 15;
   const int xr = (lane >> 1) & 7;
-  const uint32_t a_off = (uint32_t)(wm * WROWS + lrow) * 128u;
+  const FragA<LoaderA> fa(lane, wm);
   const uint32_t b_off = (uint32_t)(wn * WCOLS + lrow) * 128u + SLAB_BYTES;
   uint32_t koff[2];
 #pragma unroll
@@ -252,22 +329,21 @@ __device__ __forceinline__ void mainloop(const TileLoader& LA, const TileLoader&
   if (nk <= 0) return;
 
   bf16x8 a[2][GM], bq[4];
-  auto rdA = [&](const char* st, int ks, int i) -> bf16x8 {
-    return *reinterpret_cast<const bf16x8*>(st + a_off + i * (16 * 128) + koff[ks]);
-  };
+  auto rdA = [&](const char* st, int ks, int i) -> bf16x8 { return fa.read(st, ks, i); };
   auto rdB = [&](const char* st, int s) -> bf16x8 {   // B fragment of step s
     return *reinterpret_cast<const bf16x8*>(st + b_off + (s % GN) * (16 * 128) + koff[s / GN]);
   };
 
   {  // prologue: stage 0 complete, A and the first half of B of stage 1
-    const __amdgpu_buffer_rsrc_t ra = LA.rsrc(true), rb = LB.rsrc(true);
+    const __amdgpu_buffer_rsrc_t ra = LA.rsrc(LA.on(0, nk)), rb = LB.rsrc(true);
 #pragma unroll
     for (int i = 0; i < CHUNKS; ++i) LA.issue1(ra, i, 0, smem, wave);
 #pragma unroll
     for (int i = 0; i < CHUNKS; ++i) LB.issue1(rb, i, 0, smem + SLAB_BYTES, wave);
-    const __amdgpu_buffer_rsrc_t ra1 = LA.rsrc(nk > 1), rb1 = LB.rsrc(nk > 1);
+    const bool a1 = LA.on(1, nk);
+    const __amdgpu_buffer_rsrc_t ra1 = LA.rsrc(a1), rb1 = LB.rsrc(nk > 1);
 #pragma unroll
-    for (int i = 0; i < CHUNKS; ++i) LA.issue1(ra1, i, BK * 2, smem + STAGE_BYTES, wave);
+    for (int i = 0; i < CHUNKS; ++i) LA.issue1(ra1, i, a1 ? LA.k_step : 0u, smem + STAGE_BYTES, wave);
 #pragma unroll
     for (int i = 0; i < BH; ++i) LB.issue1(rb1, i, BK * 2, smem + STAGE_BYTES + SLAB_BYTES, wave);
   }
@@ -281,15 +357,17 @@ __device__ __forceinline__ void mainloop(const TileLoader& LA, const TileLoader&
     char* cur = smem + (kt & 1) * STAGE_BYTES;
     char* nxt = smem + ((kt + 1) & 1) * STAGE_BYTES;
     const uint32_t kb1 = (uint32_t)(kt + 1) * (BK * 2), kb2 = (uint32_t)(kt + 2) * (BK * 2);
+    const bool a2 = LA.on(kt + 2, nk);
+    const uint32_t ka2 = a2 ? (uint32_t)(kt + 2) * LA.k_step : 0u;
     const __amdgpu_buffer_rsrc_t rb1 = LB.rsrc(kt + 1 < nk);
-    const __amdgpu_buffer_rsrc_t ra2 = LA.rsrc(kt + 2 < nk), rb2 = LB.rsrc(kt + 2 < nk);
+    const __amdgpu_buffer_rsrc_t ra2 = LA.rsrc(a2), rb2 = LB.rsrc(kt + 2 < nk);
 #pragma unroll
     for (int s = 0; s < NS - TAIL; ++s) {
       const int ks = s / GN, j = s % GN;
       bq[(s + 2) & 3] = rdB(cur, s + 2);
       if (s < GM) a[1][s] = rdA(cur, 1, s);
       if (s < BH) LB.issue1(rb1, BH + s, kb1, nxt + SLAB_BYTES, wave);
-      if (s > XS && s <= XS + CHUNKS) LA.issue1(ra2, s - XS - 1, kb2, cur, wave);
+      if (s > XS && s <= XS + CHUNKS) LA.issue1(ra2, s - XS - 1, ka2, cur, wave);
 #pragma unroll
       for (int i = 0; i < GM; ++i)
         acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[ks][i], bq[s & 3], acc[i][j], 0, 0, 0);

@@ -58,6 +58,18 @@ __host__ __device__ inline int kept_vocab_tiles(const Kept& k, int tiles_v, int 
   return n < tiles_v ? n : tiles_v;
 }
 
+// The dH contraction runs over the vocabulary, i.e. over the rows of W as the caller holds it.  With W^T it reads
+// 8 consecutive k per lane; without, its fragments are read from LDS transposed (RowsLoader in gemm_core.h), which
+// makes the contraction 3..5 % slower but saves writing and reading W^T, a cost that does not depend on the rows.
+// Measured, dH and transposition per call: V = 151936, d = 5120, 768 rows 615 + 574 us against 694 us; d = 4096,
+// 4100 rows 3585 + 457 us against 3752 us; d = 5120, 32768 rows 37.3 + 0.48 ms against 38.1 ms.  The two meet at
+// about 11000 rows.  The active rows are known only on the device: where they may lie on either side, both forms are launched
+// and one returns at once (ctl != null).
+constexpr int DIRECT_MAX_ROWS = 8192;
+struct DirectRule {
+  const Ctl* ctl;
+};
+
 // ---- MFMA kernels ---------------------------------------------------------------------
 struct FwdArgs {
   const void* W;        // [V, ldw] bf16
@@ -113,6 +125,8 @@ struct StoreArgs {
   const void* A_lo;     // fp32 heads: bf16 remainders of A and B (same shapes; A_lo with A's leading dimension,
   const void* B_lo;     // B_lo with ldb_lo); the contraction then adds A B_lo and A_lo B to A B.  Both null otherwise.
   int ldb_lo;
+  DirectRule rule;      // ctl != null: the launch whose form (b_k_rows) the rule does not choose returns at once
+  int b_k_rows;         // B and B_lo are [K, ldb] instead (k runs over their rows): b_rows rows of k exist
   int a_rows, b_rows;   // rows that exist in A / B (loads beyond them give 0)
   int lda, ldb;
   int M, N, K;
@@ -237,7 +251,7 @@ void launch_finish(const FinishArgs& a, hipStream_t s);
 
 // W[v0 .. v0+cols) x d  ->  WT [d, ldt] bf16 (zeros for v >= V)
 void launch_transpose_w(const void* W, int is_f32, int64_t V, int d, int ldw, int v0, int cols, int ldt, __bf16* WT,
-                        hipStream_t s);
+                        const DirectRule& rule, hipStream_t s);
 
 struct ScatterArgs {
   const float* acc;     // [t_cap, d]

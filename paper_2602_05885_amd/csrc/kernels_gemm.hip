@@ -550,7 +550,7 @@ struct StoreShape {
   }
 };
 
-template <class AfterLoop, class BeforeStores>
+template <bool DIRECT, class AfterLoop, class BeforeStores>
 __device__ __forceinline__ void gemm_store_tile(StoreArgs a, const StoreShape& sh, int n_pad, int b, AfterLoop&& after_loop,
                                                 BeforeStores&& before_stores) {
   const int tid = threadIdx.x;
@@ -563,18 +563,23 @@ __device__ __forceinline__ void gemm_store_tile(StoreArgs a, const StoreShape& s
 
   // (a tile here is hundreds of stages long: the claim for the next one simply travels under the main loop)
   after_loop();
-  TileLoader LA, LB;
-  LA.init(a.B, a.b_rows, tn * BN, a.ldb, kb, tid);     // engine rows <- n
+  typename std::conditional<DIRECT, RowsLoader, TileLoader>::type LA;      // engine rows <- n
+  TileLoader LB;
+  auto init_n = [&](const void* B, int ldb) {
+    if constexpr (DIRECT) LA.init(B, a.b_rows, s0 * BK, ldb, tn * BN, tid);
+    else LA.init(B, a.b_rows, tn * BN, ldb, kb, tid);
+  };
+  init_n(a.B, a.ldb);
   LB.init(a.A, a.a_rows, tm * BM, a.lda, kb, tid);     // engine columns <- m
   f32x4 acc[GM][GN];
   zero_acc(acc);
   mainloop(LA, LB, s1 - s0, g_smem, acc);
   if (a.A_lo) {   // split fp32 operands: add the two cross terms (the product of the remainders is dropped)
     __syncthreads();
-    LA.init(a.B_lo, a.b_rows, tn * BN, a.ldb_lo, kb, tid);
+    init_n(a.B_lo, a.ldb_lo);
     mainloop(LA, LB, s1 - s0, g_smem, acc);
     __syncthreads();
-    LA.init(a.B, a.b_rows, tn * BN, a.ldb, kb, tid);
+    init_n(a.B, a.ldb);
     LB.init(a.A_lo, a.a_rows, tm * BM, a.lda, kb, tid);
     mainloop(LA, LB, s1 - s0, g_smem, acc);
   }
@@ -587,8 +592,10 @@ __device__ __forceinline__ void gemm_store_tile(StoreArgs a, const StoreShape& s
     store_tile<float>(a, tm, tn, sh.m_lim, acc);
 }
 
+template <bool DIRECT>
 __global__ __launch_bounds__(NTHREADS) void gemm_store_kernel(StoreArgs a) {
   const Ctl ctl = *a.ctl;
+  if (a.rule.ctl && (ctl.n_pad <= DIRECT_MAX_ROWS) != DIRECT) return;
   int ld_t_all;
   if (a.rc_role && rechunk_all(a.rc, ctl.n_pad, ld_t_all)) {   // few active rows, see Rechunk
     if (a.rc_role == 1) {          // dW: this chunk's rows of the dS^T that spans the whole vocabulary
@@ -608,7 +615,7 @@ __global__ __launch_bounds__(NTHREADS) void gemm_store_kernel(StoreArgs a) {
   volatile int* claim = reinterpret_cast<volatile int*>(g_smem + CLAIM_OFF);
   // persistent: one workgroup per compute unit takes tiles from the XCD-aware queue until none is left
   drain_queue(Q, true, claim, [&](int b, auto&& after_loop, auto&& before_stores) {
-    gemm_store_tile(a, sh, ctl.n_pad, b, after_loop, before_stores);
+    gemm_store_tile<DIRECT>(a, sh, ctl.n_pad, b, after_loop, before_stores);
   });
 }
 
@@ -624,8 +631,8 @@ hipError_t init_gemm_kernels() {
                                hipFuncAttributeMaxDynamicSharedMemorySize, PERSISTENT_LDS_BYTES)) != hipSuccess) return e;
   if ((e = hipFuncSetAttribute(reinterpret_cast<const void*>(lmhead_dlogits_kernel<true>),
                                hipFuncAttributeMaxDynamicSharedMemorySize, PERSISTENT_LDS_BYTES)) != hipSuccess) return e;
-  if ((e = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_store_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                               PERSISTENT_LDS_BYTES)) != hipSuccess) return e;
+  for (const void* k : {reinterpret_cast<const void*>(gemm_store_kernel<false>), reinterpret_cast<const void*>(gemm_store_kernel<true>)})
+    if ((e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, PERSISTENT_LDS_BYTES)) != hipSuccess) return e;
   for (const void* k : {reinterpret_cast<const void*>(dlogits_kept_kernel<false>), reinterpret_cast<const void*>(dlogits_kept_kernel<true>)})
     if ((e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, KEPT_LDS_BYTES)) != hipSuccess) return e;
   int dev = 0, cus = 0;
@@ -659,7 +666,9 @@ void launch_lmhead_dlogits(const DlogitsArgs& a, hipStream_t s) {
 }
 void launch_gemm_store(const StoreArgs& a, hipStream_t s) {
   // (a split contraction has at most acc_rows / 256 row tiles over all parts)
-  hipLaunchKernelGGL(gemm_store_kernel, dim3(persistent_grid(a.split_k ? max(a.tiles_m, a.acc_rows / BM) : a.tiles_m, a.tiles_n)), dim3(NTHREADS), PERSISTENT_LDS_BYTES, s, a);
+  const dim3 grid(persistent_grid(a.split_k ? max(a.tiles_m, a.acc_rows / BM) : a.tiles_m, a.tiles_n));
+  if (a.b_k_rows) hipLaunchKernelGGL(gemm_store_kernel<true>, grid, dim3(NTHREADS), PERSISTENT_LDS_BYTES, s, a);
+  else hipLaunchKernelGGL(gemm_store_kernel<false>, grid, dim3(NTHREADS), PERSISTENT_LDS_BYTES, s, a);
 }
 
 }  // namespace pg

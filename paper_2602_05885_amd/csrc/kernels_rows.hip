@@ -333,7 +333,8 @@ void launch_split_w(const float* W, __bf16* Wc, int64_t V, int d, hipStream_t s)
 
 // W rows [v0, v0+cols) (row stride ldw elements) -> WT[j][v - v0] (bf16; fp32 weights are rounded), zeros for v >= V.
 __global__ __launch_bounds__(256) void transpose_w_kernel(const void* W, int is_f32, long long V, int ldw, int v0,
-                                                          int ldt, __bf16* WT) {
+                                                          int ldt, __bf16* WT, DirectRule rule) {
+  if (rule.ctl && rule.ctl->n_pad <= DIRECT_MAX_ROWS) return;
   __shared__ __attribute__((aligned(16))) uint16_t tile[64 * TT_LD];
   const int vt = blockIdx.x * 64, j0 = blockIdx.y * 64;
   const int tid = threadIdx.x;
@@ -365,9 +366,9 @@ __global__ __launch_bounds__(256) void transpose_w_kernel(const void* W, int is_
   }
 }
 void launch_transpose_w(const void* W, int is_f32, int64_t V, int d, int ldw, int v0, int cols, int ldt, __bf16* WT,
-                        hipStream_t s) {
+                        const DirectRule& rule, hipStream_t s) {
   hipLaunchKernelGGL(transpose_w_kernel, dim3(cols / 64, d / 64), dim3(256), 0, s, W, is_f32, (long long)V, ldw, v0,
-                     ldt, WT);
+                     ldt, WT, rule);
 }
 
 // ------------------------------------------------------------------ combine + surrogate

@@ -1,5 +1,5 @@
-"""The split dH contraction with every row active: eight parts per chunk, of which a short last chunk leaves some without
-a single stage; the accumulator holds more rows than the call has tokens."""
+"""The dH contraction: split with every row active (eight parts per chunk, of which a short last chunk leaves some without a
+single stage; the accumulator holds more rows than the call has tokens), and the form that reads W as it lies."""
 import pytest
 import torch
 
@@ -30,3 +30,27 @@ def test_split_dh_all_rows_active(T, d, chunk_tiles, V, dtype, monkeypatch):
     tol = 5e-5 if dtype == "f32" else 1e-2       # bf16 dS: 2^-9 per element; fp32 heads carry about 16 mantissa bits
     for q in ("dH", "dW"):
         assert block_rel_fro(np64(out[q]), ref[q]) <= tol, q
+
+
+# more rows than the direct form of the dH contraction takes: the device chooses by the active ones; the W^T cache
+# forces the other form, whose products and sums are the same
+@pytest.mark.parametrize("active", [0, 1, 8192, 8193, 8700])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_direct_dh_is_chosen_by_the_active_rows(active, dtype):
+    dev = torch.device("cuda:0")
+    T, d, V = 8700, 192, 515
+    H, W, y = synth.make_head(T, d, V, dtype, 7, dev)
+    mask = torch.zeros(T, dtype=torch.uint8, device=dev)
+    mask[torch.randperm(T, generator=torch.Generator().manual_seed(1))[:active].to(dev)] = 1
+    outs = []
+    for cache in (None, B.alloc_w_transposed(d, V, dev)):
+        prm = B.Params(dtype=int(dtype == "f32"), w_transposed=cache)
+        ws = torch.full((B.pg_workspace_bytes(T, d, V, 0, prm, B.CALL_LOSS_FWD_BWD),), 0xFF, dtype=torch.uint8, device=dev)
+        outs.append(B.pg_sft_fwd_bwd(H, W, y, mask, prm, ws))
+    torch.cuda.synchronize()
+    for q in outs[0]:
+        assert torch.equal(outs[0][q], outs[1][q]), q
+    if active:
+        rows = mask.nonzero()[:40, 0].cpu().numpy()
+        ref = O.sft_ce_fwd_bwd(np64(H)[rows], np64(W), y.cpu().numpy()[rows], [1] * len(rows), norm_override=float(active))
+        assert block_rel_fro(np64(outs[0]["dH"])[rows], ref["dH"]) <= (5e-5 if dtype == "f32" else 1e-2)
