@@ -65,10 +65,12 @@ struct Plan {
   int ld_v = 0;        // leading dimension of the [*, vc] scratch matrices
   int ld_t = 0;        // leading dimension of the [*, t_cap] scratch matrices
   bool direct_fits = false;  // the dH contraction can read W as it lies
+  int dw_cap = 0;      // parts of a split dW contraction (0: not split)
   int acc_rows = 0;    // rows of the dH accumulator
   int queue_words = 0; // tile-queue counters (8 per persistent launch)
   size_t ctl, counters, queue, flag, c_tok, a_tok, rows, pos, yc, zy, lse2, coefc, lossterm;
   size_t part_m, part_s, part_u, Hc, HcT, Wc, dS, dST, WT = 0, dHacc, rstd_c = 0, norm_partial = 0;
+  size_t dWslabs = 0;
   size_t HcT_lo = 0, dS_lo = 0, dST_lo = 0, WT_lo = 0;   // fp32 heads only
   size_t kept = 0;     // fp32 logits kept for the backward: the last region
   int kept_cap = 0;    // ... in 256 x 256 tiles
@@ -176,6 +178,12 @@ int32_t make_plan(int64_t T, int64_t d, int64_t V, int32_t S, const pg_params* p
       pl.dS_lo = take((size_t)t_cap * ld_v * 2);
       pl.dST_lo = take((size_t)vc * ld_t * 2);
       pl.WT_lo = take((size_t)d * ld_v * 2);
+    }
+    // A head of so few dW tiles that half of the compute units would idle: parts of the contraction side by side
+    const int64_t dw_tiles = chunk_tiles * ((d + 255) / 256), products = pl.is_f32 ? 3 : 1;
+    if (dw_tiles * products * 2 <= 256) {
+      pl.dw_cap = (int)std::min<int64_t>(pg::DW_SPLIT_MAX, 256 / (dw_tiles * products));
+      pl.dWslabs = take((size_t)pl.dw_cap * products * vc * d * 4);
     }
     // fp32 dH accumulator: one slab of the active rows per part of the split contraction (dh_split); with few rows
     // there is room for the largest split, up to ACC_ROWS_SPLIT rows in all
@@ -821,7 +829,18 @@ int32_t loss_fwd_bwd(int sft, const void* H, const void* W, const int32_t* y, co
     w.accumulate = p.accumulate_dW; w.out_bf16 = p.dW_dtype; w.k_from_ctl = 1; w.m_from_ctl = 0; w.ctl = ctl;
     w.queue = queues + pg::QUEUE_SET_WORDS;
     w.rc = rc; w.rc_role = 1; w.v0 = v0;
-    { ProfScope ps(PG_KERNEL_DW, st); pg::launch_gemm_store(w, st); }
+    if (pl.dw_cap) {
+      pg::DwFoldArgs f{};
+      f.slabs = at<float>(ws, pl.dWslabs); f.dW = w.C; f.n = (long long)rows_valid * d_i; f.slab = (long long)pl.vc * d_i;
+      f.dw_cap = pl.dw_cap; f.products = pl.is_f32 ? 3 : 1; f.accumulate = w.accumulate; f.out_bf16 = w.out_bf16; f.ctl = ctl;
+      w.C = at<float>(ws, pl.dWslabs); w.accumulate = 0; w.out_bf16 = 0; w.dw_cap = pl.dw_cap; w.slab_rows = pl.vc;
+      ProfScope ps(PG_KERNEL_DW, st);
+      pg::launch_gemm_store(w, st);
+      pg::launch_dw_fold(f, st);
+    } else {
+      ProfScope ps(PG_KERNEL_DW, st);
+      pg::launch_gemm_store(w, st);
+    }
 
     pg::StoreArgs h{};   // dHacc[t, :] (+)= sum_v dS[t, v] W^T[:, v]
     h.A = at<__bf16>(ws, pl.dS); h.B = wt;
@@ -848,7 +867,7 @@ int32_t loss_fwd_bwd(int sft, const void* H, const void* W, const int32_t* y, co
   }
 
   pg::ScatterArgs sc{at<float>(ws, pl.dHacc), at<int>(ws, pl.pos), dH, (int)pl.T, d_i, pl.is_f32 || shard.dH_f32,
-                     1, pl.acc_rows, (d_i + 255) / 256, kc0 / 64, ctl};
+                     1, pl.acc_rows, (d_i + 255) / 256, kc0 / 64, pl.is_f32, ctl};
   if (norm) pg::launch_scatter_dx_norm(sc, nf, st);
   else pg::launch_scatter_dh(sc, st);
   return guard.check(shard.what ? shard.what : sft ? "pg_sft_fwd_bwd" : norm ? "pg_loss_fwd_bwd_normed" : "pg_loss_fwd_bwd");

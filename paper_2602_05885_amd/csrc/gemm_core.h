@@ -165,6 +165,22 @@ __host__ __device__ inline int dh_split(int n_pad, int acc_rows, int tiles_n, in
   return best;
 }
 
+// fp32 heads add three products per contraction (A B, A B_lo, A_lo B).  Where the parts of a launch leave room for it,
+// each product is a part of its own, with its own slab, instead of three passes one after the other.
+__host__ __device__ inline int split_products(int split_f32, int tiles, int ks, long long slab_rows, long long acc_rows) {
+  return split_f32 && 3 * ks * tiles <= 256 && 3 * ks * slab_rows <= acc_rows ? 3 : 1;
+}
+// Slabs of the dH accumulator.
+__host__ __device__ inline int dh_slabs(int n_pad, int acc_rows, int tiles_n, int k_stages, int split_f32, int& ks) {
+  ks = dh_split(n_pad, acc_rows, tiles_n, k_stages);
+  return ks * split_products(split_f32, (n_pad / 256) * tiles_n, ks, n_pad, acc_rows);
+}
+
+// Split-K factor of the dW contraction (over the padded active rows) of a head so small that its tiles leave most
+// compute units idle: parts of at least DW_MIN_STAGES stages, at most `cap` of them (what the slabs hold).
+constexpr int DW_MIN_STAGES = 4, DW_SPLIT_MAX = 16;
+__host__ __device__ inline int dw_split(int stages, int cap) { return imax(1, imin(stages / DW_MIN_STAGES, cap)); }
+
 // ---- operand slabs in LDS ----------------------------------------------------------
 // Row r (one of 256) holds its 64 k-values as eight 16-byte chunks; chunk c is stored at
 // position c ^ ((r >> 1) & 7): a 16-lane group of an operand read (16 consecutive rows, same

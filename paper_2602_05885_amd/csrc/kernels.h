@@ -137,8 +137,11 @@ struct StoreArgs {
   int out_bf16;
   int k_from_ctl;       // contraction length = padded active-token count
   int m_from_ctl;       // row extent        = padded active-token count
-  int split_k;          // with m_from_ctl: cut K into dh_split(n_pad, acc_rows, tiles_n, split_stages) parts, part p writes rows p n_pad + m
+  int split_k;          // with m_from_ctl: cut K into dh_slabs(n_pad, acc_rows, tiles_n, split_stages, ..) parts, part p writes rows p n_pad + m
   int acc_rows;         // rows of C
+  int dw_cap;           // > 0, with k_from_ctl: cut K into dw_split(K stages, dw_cap) parts (times three products for fp32
+                        // heads); part p writes rows p slab_rows + m of C, which is fp32 scratch that dw_fold adds up
+  int slab_rows;
   int split_stages;     // stages of the first chunk's contraction
   const Ctl* ctl;
   unsigned* queue;      // [8] tile counters of this launch's queue, zero at launch
@@ -151,6 +154,18 @@ hipError_t init_gemm_kernels();
 void launch_lmhead_fwd(const FwdArgs& a, hipStream_t s);
 void launch_lmhead_dlogits(const DlogitsArgs& a, hipStream_t s);
 void launch_gemm_store(const StoreArgs& a, hipStream_t s);
+
+// dW (+)= the slabs of a split dW contraction, in order
+struct DwFoldArgs {
+  const float* slabs;   // [parts][slab_rows, d]
+  void* dW;             // [rows, d] of this chunk, fp32 or bf16
+  long long n;          // rows d, a multiple of 4
+  long long slab;       // elements from one slab to the next
+  int dw_cap, products; // see StoreArgs
+  int accumulate, out_bf16;
+  const Ctl* ctl;
+};
+void launch_dw_fold(const DwFoldArgs& a, hipStream_t s);
 
 // ---- row / vector kernels ----------------------------------------------------------------
 struct TrlooArgs {
@@ -261,7 +276,7 @@ struct ScatterArgs {
   int out_f32;
   // split-K slabs of the accumulator (see dh_split): 0 = one slab; else the arguments of dh_split
   // as the first chunk's contraction saw them
-  int split_k, acc_rows, tiles_n, k_stages;
+  int split_k, acc_rows, tiles_n, k_stages, split_f32;
   const Ctl* ctl;
 };
 void launch_scatter_dh(const ScatterArgs& a, hipStream_t s);

@@ -68,11 +68,12 @@ __device__ __forceinline__ void lmhead_fwd_body(const FwdArgs& a, bool steal, un
   int* stash = reinterpret_cast<int*>(g_smem + FWD_STASH_OFF);
   volatile int* claim = reinterpret_cast<volatile int*>(g_smem + FWD_CLAIM_OFF);
 
-  // the first two tiles
+  // the first two tiles (of at most one tile per workgroup a second claim would take another workgroup's only one)
   if (tid == 0) {
-    const unsigned k0 = Q.ticket(), k1 = Q.ticket();
+    const bool two = Q.total > (int)gridDim.x;
+    const unsigned k0 = Q.ticket(), k1 = two ? Q.ticket() : 0u;
     claim[0] = Q.resolve(k0, steal);
-    claim[1] = Q.resolve(k1, steal);
+    claim[1] = two ? Q.resolve(k1, steal) : -1;
   }
   __syncthreads();
   const int b_cur = __builtin_amdgcn_readfirstlane(claim[0]), b_nxt = __builtin_amdgcn_readfirstlane(claim[1]);
@@ -540,24 +541,34 @@ __device__ __forceinline__ void store_tile(const StoreArgs& a, int tm, int tn, i
 
 // The run-time extents of a store contraction (the padded active-token count is known only on the device).
 struct StoreShape {
-  int m_lim, tiles_m, K, ks, total;
+  int m_lim, tiles_m, K, ks, products, slab_rows, total;
   __device__ __forceinline__ void init(const StoreArgs& a, const Ctl& ctl) {
     m_lim = a.m_from_ctl ? min(a.M, ctl.n_pad) : a.M;
     tiles_m = min(a.tiles_m, (m_lim + BM - 1) / BM);
     K = a.k_from_ctl ? ctl.n_pad : a.K;
-    ks = (a.split_k && a.m_from_ctl) ? dh_split(ctl.n_pad, a.acc_rows, a.tiles_n, a.split_stages) : 1;
-    total = tiles_m * ks * a.tiles_n;
+    ks = 1; products = 1; slab_rows = ctl.n_pad;
+    if (a.split_k && a.m_from_ctl) {
+      products = dh_slabs(ctl.n_pad, a.acc_rows, a.tiles_n, a.split_stages, a.A_lo != nullptr, ks) / ks;
+    } else if (a.dw_cap > 0) {
+      ks = dw_split(K / BK, a.dw_cap);
+      products = a.A_lo ? 3 : 1;
+      slab_rows = a.slab_rows;
+    }
+    total = tiles_m * ks * products * a.tiles_n;
   }
 };
 
 template <bool DIRECT, class AfterLoop, class BeforeStores>
-__device__ __forceinline__ void gemm_store_tile(StoreArgs a, const StoreShape& sh, int n_pad, int b, AfterLoop&& after_loop,
+__device__ __forceinline__ void gemm_store_tile(StoreArgs a, const StoreShape& sh, int b, AfterLoop&& after_loop,
                                                 BeforeStores&& before_stores) {
   const int tid = threadIdx.x;
   int tm, tn;
-  map_tile_interleaved(b, sh.tiles_m * sh.ks, a.tiles_n, tm, tn);
-  const int part = tm / sh.tiles_m;                    // 0 unless the contraction is split
-  tm -= part * sh.tiles_m;
+  map_tile_interleaved(b, sh.tiles_m * sh.ks * sh.products, a.tiles_n, tm, tn);
+  const int slab = tm / sh.tiles_m;                    // 0 unless the contraction is split
+  tm -= slab * sh.tiles_m;
+  const int part = slab / sh.products, product = slab - part * sh.products;
+  if (product == 1) { a.B = a.B_lo; a.ldb = a.ldb_lo; }
+  if (product == 2) a.A = a.A_lo;
   const int s0 = (int)((long long)part * (sh.K / BK) / sh.ks), s1 = (int)((long long)(part + 1) * (sh.K / BK) / sh.ks);
   const uint32_t kb = (uint32_t)s0 * BK * 2u;          // byte offset of this part's first k
 
@@ -574,7 +585,7 @@ __device__ __forceinline__ void gemm_store_tile(StoreArgs a, const StoreShape& s
   f32x4 acc[GM][GN];
   zero_acc(acc);
   mainloop(LA, LB, s1 - s0, g_smem, acc);
-  if (a.A_lo) {   // split fp32 operands: add the two cross terms (the product of the remainders is dropped)
+  if (a.A_lo && sh.products == 1) {   // split fp32 operands: add the two cross terms (the product of the remainders is dropped)
     __syncthreads();
     init_n(a.B_lo, a.ldb_lo);
     mainloop(LA, LB, s1 - s0, g_smem, acc);
@@ -585,7 +596,7 @@ __device__ __forceinline__ void gemm_store_tile(StoreArgs a, const StoreShape& s
   }
   before_stores();
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // the claim is visible behind this barrier
-  a.C = static_cast<char*>(a.C) + (size_t)part * n_pad * a.ldc * (a.out_bf16 ? 2 : 4);
+  a.C = static_cast<char*>(a.C) + (size_t)slab * sh.slab_rows * a.ldc * (a.out_bf16 ? 2 : 4);
   if (a.out_bf16)
     store_tile<__bf16>(a, tm, tn, sh.m_lim, acc);
   else
@@ -615,7 +626,7 @@ __global__ __launch_bounds__(NTHREADS) void gemm_store_kernel(StoreArgs a) {
   volatile int* claim = reinterpret_cast<volatile int*>(g_smem + CLAIM_OFF);
   // persistent: one workgroup per compute unit takes tiles from the XCD-aware queue until none is left
   drain_queue(Q, true, claim, [&](int b, auto&& after_loop, auto&& before_stores) {
-    gemm_store_tile<DIRECT>(a, sh, ctl.n_pad, b, after_loop, before_stores);
+    gemm_store_tile<DIRECT>(a, sh, b, after_loop, before_stores);
   });
 }
 
@@ -665,8 +676,8 @@ void launch_lmhead_dlogits(const DlogitsArgs& a, hipStream_t s) {
   }
 }
 void launch_gemm_store(const StoreArgs& a, hipStream_t s) {
-  // (a split contraction has at most acc_rows / 256 row tiles over all parts)
-  const dim3 grid(persistent_grid(a.split_k ? max(a.tiles_m, a.acc_rows / BM) : a.tiles_m, a.tiles_n));
+  // (a split dH has at most acc_rows / 256 row tiles over all parts, a split dW dw_cap parts of every product)
+  const dim3 grid(persistent_grid(a.split_k ? max(a.tiles_m, a.acc_rows / BM) : a.tiles_m * max(1, a.dw_cap) * (a.dw_cap && a.A_lo ? 3 : 1), a.tiles_n));
   if (a.b_k_rows) hipLaunchKernelGGL(gemm_store_kernel<true>, grid, dim3(NTHREADS), PERSISTENT_LDS_BYTES, s, a);
   else hipLaunchKernelGGL(gemm_store_kernel<false>, grid, dim3(NTHREADS), PERSISTENT_LDS_BYTES, s, a);
 }

@@ -491,7 +491,8 @@ __global__ __launch_bounds__(256) void scatter_dh_kernel(ScatterArgs a) {
   const int p = a.pos[t];
   const float* src = a.acc + (size_t)(p < 0 ? 0 : p) * a.d;
   const int n_pad = a.ctl->n_pad;
-  const int ks = a.split_k ? dh_split(n_pad, a.acc_rows, a.tiles_n, a.k_stages) : 1;
+  int ks = 1;                                       // slabs
+  if (a.split_k) ks = dh_slabs(n_pad, a.acc_rows, a.tiles_n, a.k_stages, a.split_f32, ks);
   const size_t slab = (size_t)n_pad * a.d;
   for (int j = threadIdx.x * 4; j < a.d; j += 256 * 4) {
     float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -558,6 +559,35 @@ __global__ void finish_partials_kernel(const float* parts, long long T, float* l
 void launch_finish_partials(const float* parts, long long T, float* logp, float* ent, float* lse, hipStream_t s) {
   if (T <= 0) return;
   hipLaunchKernelGGL(finish_partials_kernel, dim3((unsigned)((T + 255) / 256)), dim3(256), 0, s, parts, T, logp, ent, lse);
+}
+
+// Adds the slabs of a split dW contraction (dw_split) in order, and the gradient that was there if it accumulates.
+__global__ __launch_bounds__(256) void dw_fold_kernel(DwFoldArgs a) {
+  const int slabs = dw_split(a.ctl->n_pad / BK, a.dw_cap) * a.products;
+  for (long long e = ((long long)blockIdx.x * 256 + threadIdx.x) * 4; e < a.n; e += (long long)gridDim.x * 256 * 4) {
+    f32x4 v = *reinterpret_cast<const f32x4*>(a.slabs + e);
+    for (int q = 1; q < slabs; ++q) v += *reinterpret_cast<const f32x4*>(a.slabs + q * a.slab + e);
+    if (a.out_bf16) {
+      bf16x4* p = reinterpret_cast<bf16x4*>(reinterpret_cast<__bf16*>(a.dW) + e);
+      if (a.accumulate) {
+        const bf16x4 old = *p;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[r] += (float)old[r];
+      }
+      bf16x4 o;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) o[r] = (__bf16)v[r];
+      *p = o;
+    } else {
+      f32x4* p = reinterpret_cast<f32x4*>(reinterpret_cast<float*>(a.dW) + e);
+      if (a.accumulate) v += *p;
+      *p = v;
+    }
+  }
+}
+void launch_dw_fold(const DwFoldArgs& a, hipStream_t s) {
+  const long long blocks = (a.n / 4 + 255) / 256;
+  hipLaunchKernelGGL(dw_fold_kernel, dim3((unsigned)(blocks < 2048 ? blocks : 2048)), dim3(256), 0, s, a);
 }
 
 void launch_scatter_dh(const ScatterArgs& a, hipStream_t s) {
@@ -1107,7 +1137,8 @@ __global__ __launch_bounds__(256) void scatter_dx_norm_kernel(ScatterArgs a, Nor
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const long long T = a.T;
   const int n_pad = a.ctl->n_pad;
-  const int ks = a.split_k ? dh_split(n_pad, a.acc_rows, a.tiles_n, a.k_stages) : 1;
+  int ks = 1;                                       // slabs
+  if (a.split_k) ks = dh_slabs(n_pad, a.acc_rows, a.tiles_n, a.k_stages, a.split_f32, ks);
   const size_t slab = (size_t)n_pad * a.d;
   float dg[NC][8];
   Raw8<F32> gam_raw[NC] = {};

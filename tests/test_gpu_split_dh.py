@@ -12,9 +12,9 @@ pytestmark = pytest.mark.gpu
 
 
 # (T, d, vocab tiles of the first chunk, V): one row tile and two, one column tile and a ragged second one, a last chunk
-# of 4 stages (fewer than parts) and of one ragged vocab tile, a single chunk
+# of 4 stages (fewer than parts) and of one ragged vocab tile, a single chunk, a head of too many dW tiles to split dW
 @pytest.mark.parametrize("T,d,chunk_tiles,V", [(1, 64, 16, 256 * 17), (300, 320, 16, 256 * 16 + 3), (256, 128, 32, 256 * 33 + 100),
-                                               (513, 64, None, 256 * 20)])
+                                               (513, 64, None, 256 * 20), (300, 64, None, 33100)])
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_split_dh_all_rows_active(T, d, chunk_tiles, V, dtype, monkeypatch):
     dev = torch.device("cuda:0")
