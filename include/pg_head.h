@@ -139,7 +139,7 @@ int32_t pg_init(void);
  * Bytes of device workspace the given call needs for these sizes (S is ignored for
  * PG_CALL_LOGPROB_FWD).  Returns 0 if the arguments are invalid or unsupported.
  * The workspace need not be initialised and holds nothing the caller may rely on.
- * For the loss calls its last part (at most 8 GiB) keeps fp32 logits between the forward and the backward
+ * For the loss calls its last part (at most 9.75 GiB) keeps fp32 logits between the forward and the backward
  * contractions.  A loss call also takes a workspace that is shorter by any part of it: it then
  * recomputes the logits that it cannot keep, with the same results, and refuses
  * (PG_ERR_WORKSPACE_TOO_SMALL) only what is shorter than the rest.

@@ -45,9 +45,10 @@ uint64_t ds_budget() {
 
 inline size_t align_up(size_t x) { return (x + ALIGN - 1) / ALIGN * ALIGN; }
 
-// Bytes of fp32 logits that a loss call keeps for its backward (Kept in kernels.h): four times the dS scratch
-// of one orientation, so one knob bounds all scratch.
-uint64_t kept_budget() { return 4 * ds_budget(); }
+// Bytes of fp32 logits that a loss call keeps for its backward (Kept in kernels.h): 39/8 of the dS scratch of one
+// orientation (9.75 GiB), so one knob bounds all scratch.  A 14B head with 44k rows then needs 15.7 GiB in all,
+// 5 % of the card, and keeps half of its 32768 active rows' logits; every further GiB is worth 1.2 ms of 128 there.
+uint64_t kept_budget() { return ds_budget() / 8 * 39; }
 
 // Leading dimension of the caller-owned W^T cache [d, ld]: the vocabulary rounded up to whole tiles.
 inline int64_t wt_cache_ld(int64_t V) { return pg::pad_ld((V + 255) / 256 * 256); }
