@@ -64,7 +64,12 @@ struct Plan {
   int nchunks = 0;
   int vc = 0;          // chunk_tiles * 256
   int ld_v = 0;        // leading dimension of the [*, vc] scratch matrices
-  int ld_t = 0;        // leading dimension of the [*, t_cap] scratch matrices
+  int ld_h = 0;        // leading dimension of H^T (t_cap columns)
+  int ld_t = 0;        // leading dimension of dS^T (rows_b columns)
+  int rows_b = 0;      // rows of dS: t_cap, or those of a token block
+  int cap_t = 0;       // token tiles of a block (TokenBlocks), 0: one block
+  int nblocks = 1;     // blocks that t_cap rows may need
+  int ld_wt = 0;       // leading dimension of the workspace's W^T: of a chunk, or (token blocks) of all of it
   bool direct_fits = false;  // the dH contraction can read W as it lies
   int dw_cap = 0;      // parts of a split dW contraction (0: not split)
   int acc_rows = 0;    // rows of the dH accumulator
@@ -98,7 +103,9 @@ int32_t check_params(const pg_params* p) {
   return PG_OK;
 }
 
-int32_t make_plan(int64_t T, int64_t d, int64_t V, int32_t S, const pg_params* p, int which, Plan& pl) {
+// blocks: plan a loss call in token blocks if it is one that pays (see TokenBlocks); pl.cap_t says whether it did.
+int32_t make_plan(int64_t T, int64_t d, int64_t V, int32_t S, const pg_params* p, int which, Plan& pl, bool blocks = false) {
+  pl = Plan{};
   int32_t rc = check_params(p);
   if (rc) return rc;
   if (which != PG_CALL_LOGPROB_FWD && which != PG_CALL_LOSS_FWD_BWD && which != PG_CALL_LOSS_FWD_BWD_NORMED)
@@ -144,8 +151,23 @@ int32_t make_plan(int64_t T, int64_t d, int64_t V, int32_t S, const pg_params* p
     pl.rstd_c = take((size_t)t_cap * 4);
     pl.norm_partial = take((size_t)pg::NORM_STRIPS * d * 4);
   }
+  const uint64_t kept_tile = (uint64_t)pg::KEPT_TILE_FLOATS * sizeof(float);
+  const bool keep = which != PG_CALL_LOGPROB_FWD && (kd * (pl.is_f32 ? 2 : 1) >= pg::KEEP_MIN_K || tiles_v * pl.tiles_t <= pg::KEEP_ANY_TILES);
+  const int64_t kept_all = keep ? tiles_v * pl.tiles_t : 0, kept_fit = std::min<int64_t>((int64_t)(kept_budget() / kept_tile), INT32_MAX);
   if (which != PG_CALL_LOGPROB_FWD) {
-    int64_t max_tiles = t_cap > 0 ? (int64_t)(ds_budget() / ((uint64_t)t_cap * 2 * 256)) : tiles_v;
+    // Token blocks: more logits than fit, blocks that are not too small, and a dW that can be added to without a
+    // rounding in between (fp32; an fp32 head's split operands keep to one block).
+    const int64_t td = (d + 255) / 256;
+    if (blocks && !pl.is_f32 && p->dW_dtype == 0 && kd >= pg::BLOCK_MIN_K && kept_all > kept_fit && kept_fit / tiles_v >= pg::BLOCK_MIN_TILES) {
+      pl.cap_t = (int)(kept_fit / tiles_v);
+      if (pl.cap_t * td >= 256) pl.cap_t = (int)(pl.cap_t * td / 256 * 256 / td);      // whole rounds of the dH launch
+      pl.nblocks = (pl.tiles_t + pl.cap_t - 1) / pl.cap_t;
+    }
+    const int64_t rows_b = pl.cap_t ? (int64_t)pl.cap_t * 256 : t_cap;
+    pl.rows_b = (int)rows_b;
+    // (a block has fewer rows and gets half the scratch for them; W^T is then held in full, for all blocks)
+    const uint64_t budget = pl.cap_t ? ds_budget() / 2 : ds_budget();
+    int64_t max_tiles = t_cap > 0 ? (int64_t)(budget / ((uint64_t)rows_b * 2 * 256)) : tiles_v;
     if (max_tiles < 1) max_tiles = 1;
     if (max_tiles > tiles_v) max_tiles = tiles_v;
     // Chunk size: within the scratch budget, the size whose dW launches (chunk_tiles x ceil(d/256)
@@ -153,7 +175,6 @@ int32_t make_plan(int64_t T, int64_t d, int64_t V, int32_t S, const pg_params* p
     // is charged half a round for its launches and its pass over the dH accumulator.
     int64_t chunk_tiles = max_tiles;
     if (tiles_v > max_tiles) {
-      const int64_t td = (d + 255) / 256;
       double best = 1e30;
       for (int64_t ct = max_tiles; ct >= 1 && ct * 3 >= max_tiles * 2; --ct) {
         const int64_t nch = (tiles_v + ct - 1) / ct;
@@ -164,25 +185,26 @@ int32_t make_plan(int64_t T, int64_t d, int64_t V, int32_t S, const pg_params* p
     }
     const int64_t nchunks = (tiles_v + chunk_tiles - 1) / chunk_tiles;
     const int64_t vc = chunk_tiles * 256;
-    const int64_t ld_v = pg::pad_ld(vc), ld_t = pg::pad_ld(t_cap);
-    if ((uint64_t)ld_v * 2 * 256 >= FOUR_GIB || (uint64_t)ld_t * 2 * 256 >= FOUR_GIB)
+    const int64_t ld_v = pg::pad_ld(vc), ld_t = pg::pad_ld(rows_b), ld_h = pg::pad_ld(t_cap);
+    if ((uint64_t)ld_v * 2 * 256 >= FOUR_GIB || (uint64_t)ld_t * 2 * 256 >= FOUR_GIB || (uint64_t)ld_h * 2 * 256 >= FOUR_GIB)
       return fail(PG_ERR_UNSUPPORTED_SHAPE, "256 rows of a backward scratch matrix reach 4 GiB");
     pl.nchunks = (int)nchunks; pl.chunk_tiles = (int)chunk_tiles; pl.vc = (int)vc;
-    pl.ld_v = (int)ld_v; pl.ld_t = (int)ld_t;
-    pl.HcT = take((size_t)d * ld_t * 2);
-    pl.dS = take((size_t)t_cap * ld_v * 2);
+    pl.ld_v = (int)ld_v; pl.ld_t = (int)ld_t; pl.ld_h = (int)ld_h;
+    pl.HcT = take((size_t)d * ld_h * 2);
+    pl.dS = take((size_t)rows_b * ld_v * 2);
     pl.dST = take((size_t)vc * ld_t * 2);
     pl.direct_fits = (uint64_t)vc * kd * 2 < FOUR_GIB;      // RowsLoader's range
-    if (!pl.direct_fits || t_cap > pg::DIRECT_MAX_ROWS) pl.WT = take((size_t)d * ld_v * 2);
+    pl.ld_wt = (int)(pl.cap_t ? wt_cache_ld(V) : ld_v);
+    if (!pl.direct_fits || t_cap > pg::DIRECT_MAX_ROWS) pl.WT = take((size_t)d * pl.ld_wt * 2);
     if (pl.is_f32) {   // bf16 remainders of the four backward operands
-      pl.HcT_lo = take((size_t)d * ld_t * 2);
-      pl.dS_lo = take((size_t)t_cap * ld_v * 2);
+      pl.HcT_lo = take((size_t)d * ld_h * 2);
+      pl.dS_lo = take((size_t)rows_b * ld_v * 2);
       pl.dST_lo = take((size_t)vc * ld_t * 2);
       pl.WT_lo = take((size_t)d * ld_v * 2);
     }
     // A head of so few dW tiles that half of the compute units would idle: parts of the contraction side by side
     const int64_t dw_tiles = chunk_tiles * ((d + 255) / 256), products = pl.is_f32 ? 3 : 1;
-    if (dw_tiles * products * 2 <= 256) {
+    if (dw_tiles * products * 2 <= 256 && !pl.cap_t) {
       pl.dw_cap = (int)std::min<int64_t>(pg::DW_SPLIT_MAX, 256 / (dw_tiles * products));
       pl.dWslabs = take((size_t)pl.dw_cap * products * vc * d * 4);
     }
@@ -191,15 +213,13 @@ int32_t make_plan(int64_t T, int64_t d, int64_t V, int32_t S, const pg_params* p
     const int64_t split_rows = pg::SPLIT_MAX * t_cap < ACC_ROWS_SPLIT ? pg::SPLIT_MAX * t_cap : ACC_ROWS_SPLIT;
     pl.acc_rows = (int)(t_cap > split_rows ? t_cap : split_rows);
     pl.dHacc = take((size_t)pl.acc_rows * d * 4);
-    pl.queue_words = pg::QUEUE_SET_WORDS * pg::queue_sets((int)nchunks);
+    pl.queue_words = pg::QUEUE_SET_WORDS * pg::queue_sets((int)nchunks) * pl.nblocks;
   }
   pl.queue = take((size_t)pl.queue_words * sizeof(unsigned));
   pl.required = off > 0 ? off : ALIGN;
   pl.kept = pl.required;
   if (which != PG_CALL_LOGPROB_FWD) {
-    const uint64_t tile = (uint64_t)pg::KEPT_TILE_FLOATS * sizeof(float);
-    const int64_t all = tiles_v * pl.tiles_t, fit = (int64_t)(kept_budget() / tile);
-    pl.kept_cap = (int)(all < fit ? all : fit);
+    pl.kept_cap = pl.cap_t ? pl.cap_t * pl.tiles_v : (int)std::min(kept_all, kept_fit);
   }
   pl.total = pl.kept + (size_t)pl.kept_cap * pg::KEPT_TILE_FLOATS * sizeof(float);
   return PG_OK;
@@ -300,44 +320,44 @@ struct ProfScope {
 template <typename T>
 T* at(void* ws, size_t off) { return reinterpret_cast<T*>(static_cast<char*>(ws) + off); }
 
-// Steps shared by both calls: pre-pass, operand staging, forward contraction, combine.
+// Steps shared by both calls: pre-pass and operand staging ...
 // y_offset: first vocab row of W within the whole vocabulary (0 unless W is a vocab shard).  With
 // comb.partials_in set, the contraction is skipped and the rows' states come from there.
-void run_forward(const Plan& pl, const pg_params& p, void* ws, const void* H, const void* W, const int32_t* y,
-                 int64_t y_offset, const pg::PrepArgs& prep, pg::CombineArgs comb, bool need_HT, hipStream_t st,
-                 const pg::NormFuse* norm = nullptr, const pg::Kept& kept = pg::Kept{}) {
+void run_staging(const Plan& pl, void* ws, const void* H, const void* W, const int32_t* y, int64_t y_offset,
+                 const pg::PrepArgs& prep, bool need_HT, hipStream_t st, const pg::NormFuse* norm = nullptr) {
   pg::launch_prepass(prep, st);
-  const void* Wop = W;
-  if (pl.is_f32) {
-    pg::launch_split_w(static_cast<const float*>(W), at<__bf16>(ws, pl.Wc), pl.V, (int)pl.d, st);
-    Wop = at<__bf16>(ws, pl.Wc);
-  }
+  if (pl.is_f32) pg::launch_split_w(static_cast<const float*>(W), at<__bf16>(ws, pl.Wc), pl.V, (int)pl.d, st);
   pg::GatherArgs g{};
   g.H = H; g.y = y; g.d = (int)pl.d; g.t_cap = pl.t_cap; g.is_f32 = pl.is_f32;
   g.rows = at<int>(ws, pl.rows); g.Hc = at<__bf16>(ws, pl.Hc);
   g.HcT = need_HT ? at<__bf16>(ws, pl.HcT) : nullptr;
   g.HcT_lo = need_HT && pl.is_f32 ? at<__bf16>(ws, pl.HcT_lo) : nullptr;
-  g.yc = at<int>(ws, pl.yc); g.ctl = at<pg::Ctl>(ws, pl.ctl); g.ld_t = pl.ld_t;
+  g.yc = at<int>(ws, pl.yc); g.ctl = at<pg::Ctl>(ws, pl.ctl); g.ld_t = pl.ld_h;
   g.y_offset = (int)y_offset; g.V = (int)pl.V;
   if (norm) pg::launch_norm_gather(g, *norm, st);
   else pg::launch_gather(g, st);
+}
 
+// ... forward contraction and combine of the rows of one token block (queue: of that block).
+void run_forward(const Plan& pl, const pg_params& p, void* ws, const void* W, pg::CombineArgs comb, const pg::Kept& kept,
+                 const pg::TokenBlocks& blk, unsigned* queue, hipStream_t st) {
   pg::FwdArgs f{};
-  f.W = Wop; f.Hc = at<__bf16>(ws, pl.Hc);
+  f.W = pl.is_f32 ? static_cast<const void*>(at<__bf16>(ws, pl.Wc)) : W; f.Hc = at<__bf16>(ws, pl.Hc);
   f.w_rows = (int)pl.V; f.h_rows = pl.t_cap;
   f.ldw = pl.kd; f.ldh = pl.kd; f.K = pl.kd; f.V = (int)pl.V;
-  f.tiles_v = pl.tiles_v; f.tiles_t = pl.tiles_t; f.t_cap = pl.t_cap;
+  f.tiles_v = pl.tiles_v; f.tiles_t = blk.cap_t ? blk.cap_t : pl.tiles_t; f.t_cap = pl.t_cap;
   f.scale = (float)(LOG2E / (double)p.temperature);
   f.yc = at<int>(ws, pl.yc); f.zy = at<float>(ws, pl.zy);
   f.part_m = at<float>(ws, pl.part_m); f.part_s = at<float>(ws, pl.part_s); f.part_u = at<float>(ws, pl.part_u);
   f.ctl = at<pg::Ctl>(ws, pl.ctl);
-  f.queue = at<unsigned>(ws, pl.queue);
-  f.kept = kept;
+  f.queue = queue;
+  f.kept = kept; f.blk = blk;
   if (!comb.partials_in) { ProfScope ps(PG_KERNEL_FWD, st); pg::launch_lmhead_fwd(f, st); }
 
   comb.tiles_v = comb.partials_in ? 0 : pl.tiles_v; comb.t_cap = pl.t_cap;
   comb.part_m = f.part_m; comb.part_s = f.part_s; comb.part_u = f.part_u;
   comb.zy = f.zy; comb.rows = at<int>(ws, pl.rows); comb.lse2 = at<float>(ws, pl.lse2);
+  comb.blk = blk;
   comb.ctl = f.ctl;
   pg::launch_combine(comb, st);
 }
@@ -435,8 +455,12 @@ int32_t pg_profile_read(double* h_ms, int64_t* h_launches) {
 
 size_t pg_workspace_bytes(int64_t T, int64_t d, int64_t V, int32_t S, const pg_params* h_params, int32_t which_call) {
   Plan pl;
-  if (make_plan(T, d, V, S, h_params, which_call, pl) != PG_OK) return 0;
-  return pl.total;
+  if (make_plan(T, d, V, S, h_params, which_call, pl, true) != PG_OK) return 0;
+  const size_t total = pl.total;
+  if (!pl.cap_t) return total;
+  // (a call that cannot work in blocks, as pg_loss_shard_bwd, uses the one-block plan on the same workspace)
+  if (make_plan(T, d, V, S, h_params, which_call, pl, false) != PG_OK) return 0;
+  return std::max(total, pl.required);
 }
 
 size_t pg_w_transposed_bytes(int64_t d, int64_t V) {
@@ -448,7 +472,7 @@ size_t pg_w_transposed_bytes(int64_t d, int64_t V) {
 
 int64_t pg_backward_chunk_rows(int64_t T, int64_t d, int64_t V, int32_t S, const pg_params* h_params) {
   Plan pl;
-  if (make_plan(T, d, V, S, h_params, PG_CALL_LOSS_FWD_BWD, pl) != PG_OK) return 0;
+  if (make_plan(T, d, V, S, h_params, PG_CALL_LOSS_FWD_BWD, pl, true) != PG_OK) return 0;
   return pl.vc;
 }
 
@@ -483,7 +507,8 @@ int32_t pg_logprob_fwd(const void* H, const void* W, const int32_t* y, const uin
   pg::CombineArgs comb{};
   comb.logp_out = logp_out; comb.ent_out = entropy_out; comb.lse_out = lse_out;
   comb.with_loss = 0;
-  run_forward(pl, *h_params, workspace, H, W, y, 0, prep, comb, false, st);
+  run_staging(pl, workspace, H, W, y, 0, prep, false, st);
+  run_forward(pl, *h_params, workspace, W, comb, pg::Kept{}, pg::TokenBlocks{}, at<unsigned>(workspace, pl.queue), st);
   return guard.check("pg_logprob_fwd");
 }
 
@@ -535,7 +560,8 @@ int32_t pg_head_shard_fwd(const void* H, const void* W_shard, const int32_t* y, 
   pg::CombineArgs comb{};
   comb.with_loss = 0;
   comb.partials_out = partials_out;
-  run_forward(pl, *h_params, workspace, H, W_shard, y, v_offset, prep, comb, false, st);
+  run_staging(pl, workspace, H, W_shard, y, v_offset, prep, false, st);
+  run_forward(pl, *h_params, workspace, W_shard, comb, pg::Kept{}, pg::TokenBlocks{}, at<unsigned>(workspace, pl.queue), st);
   return guard.check("pg_head_shard_fwd");
 }
 
@@ -708,8 +734,11 @@ int32_t loss_fwd_bwd(int sft, const void* H, const void* W, const int32_t* y, co
                      float* entropy_out, int64_t* counters_out, void* workspace, size_t workspace_bytes, void* stream,
                      const Shard& shard, const NormIn* norm) {
   Plan pl;
-  int32_t rc = make_plan(T, d, V, S, h_params, norm ? PG_CALL_LOSS_FWD_BWD_NORMED : PG_CALL_LOSS_FWD_BWD, pl);
+  const int which = norm ? PG_CALL_LOSS_FWD_BWD_NORMED : PG_CALL_LOSS_FWD_BWD;
+  int32_t rc = make_plan(T, d, V, S, h_params, which, pl, !shard.partials);
   if (rc) return rc;
+  // (token blocks keep all their logits: a workspace that has no room for that gets the one-block plan)
+  if (pl.cap_t && workspace_bytes < pl.total && (rc = make_plan(T, d, V, S, h_params, which, pl))) return rc;
   const pg_params& p = *h_params;
   if (!W || !loss_out || !dW) return fail(PG_ERR_INVALID_ARG, "W, loss_out and dW must not be NULL");
   if (misaligned(W) || misaligned(dW)) return fail(PG_ERR_INVALID_ARG, "W and dW must be 16-byte aligned");
@@ -769,106 +798,110 @@ int32_t loss_fwd_bwd(int sft, const void* H, const void* W, const int32_t* y, co
     nf.X = H; nf.gamma = norm->gamma; nf.eps = norm->eps; nf.dgamma = norm->dgamma;
     nf.rstd_c = at<float>(ws, pl.rstd_c); nf.partial = at<float>(ws, pl.norm_partial);
   }
-  run_forward(pl, p, ws, H, W, y, shard.v_offset, prep, comb, true, st, norm ? &nf : nullptr, kept);
+  run_staging(pl, ws, H, W, y, shard.v_offset, prep, true, st, norm ? &nf : nullptr);
 
-  pg::FinishArgs fin{at<float>(ws, pl.lossterm), at<unsigned long long>(ws, pl.counters), loss_out,
-                     reinterpret_cast<long long*>(counters_out), at<pg::Ctl>(ws, pl.ctl)};
-  pg::launch_finish(fin, st);
-
-  // ---- backward, one vocab chunk at a time ----
   const void* Wop = pl.is_f32 ? static_cast<const void*>(at<__bf16>(ws, pl.Wc)) : W;
   const pg::Ctl* ctl = at<pg::Ctl>(ws, pl.ctl);
   const int d_i = (int)pl.d;
   const int kc0 = (int)(((pl.V < pl.vc ? pl.V : pl.vc) + 255) / 256 * 256);      // contraction length of the first chunk
-  for (int c = 0; c < pl.nchunks; ++c) {
-    const int v0 = c * pl.vc;
-    if (v0 >= pl.V) break;
-    const int rows_valid = (int)((pl.V - v0) < pl.vc ? (pl.V - v0) : pl.vc);
-    const int tiles_c = (rows_valid + 255) / 256;
-    const int kc = tiles_c * 256;
+  const int tiles_b = pl.cap_t ? pl.cap_t : pl.tiles_t;
+  for (int b = 0; b < pl.nblocks; ++b) {      // token blocks; the backward of a block one vocab chunk at a time
+    const pg::TokenBlocks blk{pl.cap_t, b};
+    unsigned* const block_queue = at<unsigned>(ws, pl.queue) + (size_t)pg::QUEUE_SET_WORDS * pg::queue_sets(pl.nchunks) * b;
+    run_forward(pl, p, ws, W, comb, kept, blk, block_queue, st);
+    for (int c = 0; c < pl.nchunks; ++c) {
+      const int v0 = c * pl.vc;
+      if (v0 >= pl.V) break;
+      const int rows_valid = (int)((pl.V - v0) < pl.vc ? (pl.V - v0) : pl.vc);
+      const int tiles_c = (rows_valid + 255) / 256;
+      const int kc = tiles_c * 256;
 
-    // W^T of this chunk: in the workspace, or a column range of the caller's cache (filled here unless valid)
-    __bf16* wt = at<__bf16>(ws, pl.WT);
-    int ld_wt = pl.ld_v;
-    if (p.w_transposed) {
-      wt = static_cast<__bf16*>(p.w_transposed) + v0;
-      ld_wt = (int)wt_cache_ld(pl.V);
-    }
-    // ... unless the dH launch reads W as it lies: for certain (every row count fits), or decided on the device
-    const bool direct = pl.direct_fits && !p.w_transposed, transposed = !direct || pl.t_cap > pg::DIRECT_MAX_ROWS;
-    const pg::DirectRule rule{direct && transposed ? ctl : nullptr};
-    if (transposed) {
-      if (!p.w_transposed || !p.w_transposed_valid) pg::launch_transpose_w(W, pl.is_f32, pl.V, d_i, d_i, v0, kc, ld_wt, wt, rule, st);
-      if (pl.is_f32)   // the remainders W - bf16(W) are columns [d, 2d) of the split operand
-        pg::launch_transpose_w(at<__bf16>(ws, pl.Wc) + d_i, 0, pl.V, d_i, pl.kd, v0, kc, pl.ld_v, at<__bf16>(ws, pl.WT_lo), rule, st);
-    }
+      // W^T of this chunk: in the workspace, or a column range of the caller's cache (filled here unless valid)
+      __bf16* wt = at<__bf16>(ws, pl.WT) + (pl.cap_t ? v0 : 0);
+      int ld_wt = pl.ld_wt;
+      if (p.w_transposed) {
+        wt = static_cast<__bf16*>(p.w_transposed) + v0;
+        ld_wt = (int)wt_cache_ld(pl.V);
+      }
+      // ... unless the dH launch reads W as it lies: for certain (every row count fits), or decided on the device
+      const bool direct = pl.direct_fits && !p.w_transposed, transposed = !direct || pl.t_cap > pg::DIRECT_MAX_ROWS;
+      const pg::DirectRule rule{direct && transposed ? ctl : nullptr};
+      if (transposed && b == 0) {
+        if (!p.w_transposed || !p.w_transposed_valid) pg::launch_transpose_w(W, pl.is_f32, pl.V, d_i, d_i, v0, kc, ld_wt, wt, rule, st);
+        if (pl.is_f32)   // the remainders W - bf16(W) are columns [d, 2d) of the split operand
+          pg::launch_transpose_w(at<__bf16>(ws, pl.Wc) + d_i, 0, pl.V, d_i, pl.kd, v0, kc, pl.ld_v, at<__bf16>(ws, pl.WT_lo), rule, st);
+      }
 
-    pg::DlogitsArgs g{};
-    g.W = Wop; g.Hc = at<__bf16>(ws, pl.Hc);
-    g.w_rows = (int)pl.V; g.h_rows = pl.t_cap;
-    g.ldw = pl.kd; g.ldh = pl.kd; g.K = pl.kd; g.V = (int)pl.V; g.v0 = v0; g.ld_s = pl.ld_v; g.ld_t = pl.ld_t;
-    g.tiles_v = tiles_c; g.tiles_t = pl.tiles_t; g.t_cap = pl.t_cap;
-    g.scale = (float)(LOG2E / (double)p.temperature);
-    g.yc = at<int>(ws, pl.yc); g.lse2 = at<float>(ws, pl.lse2); g.coefc = at<float>(ws, pl.coefc);
-    g.dS = at<__bf16>(ws, pl.dS); g.dST = at<__bf16>(ws, pl.dST); g.ctl = ctl;
-    if (pl.is_f32) { g.dS_lo = at<__bf16>(ws, pl.dS_lo); g.dST_lo = at<__bf16>(ws, pl.dST_lo); }
-    pg::Rechunk rc{};
-    rc.enabled = pl.nchunks > 1; rc.chunk = c; rc.tiles_v_all = pl.tiles_v; rc.ld_s_all = (int)pg::pad_ld((int64_t)pl.tiles_v * 256);
-    rc.cap_s = (long long)pl.t_cap * pl.ld_v; rc.cap_t = (long long)pl.vc * pl.ld_t;
-    g.rc = rc; g.kept = kept; g.tiles_v_all = pl.tiles_v;
-    unsigned* const queues = at<unsigned>(ws, pl.queue) + pg::QUEUE_SET_WORDS * (1 + 4 * c);
-    g.queue = queues; g.queue_lo = queues + 3 * pg::QUEUE_SET_WORDS;
-    { ProfScope ps(PG_KERNEL_DLOGITS, st); pg::launch_lmhead_dlogits(g, st); }
+      pg::DlogitsArgs g{};
+      g.W = Wop; g.Hc = at<__bf16>(ws, pl.Hc);
+      g.w_rows = (int)pl.V; g.h_rows = pl.t_cap;
+      g.ldw = pl.kd; g.ldh = pl.kd; g.K = pl.kd; g.V = (int)pl.V; g.v0 = v0; g.ld_s = pl.ld_v; g.ld_t = pl.ld_t;
+      g.tiles_v = tiles_c; g.tiles_t = tiles_b; g.t_cap = pl.t_cap;
+      g.scale = (float)(LOG2E / (double)p.temperature);
+      g.yc = at<int>(ws, pl.yc); g.lse2 = at<float>(ws, pl.lse2); g.coefc = at<float>(ws, pl.coefc);
+      g.dS = at<__bf16>(ws, pl.dS); g.dST = at<__bf16>(ws, pl.dST); g.ctl = ctl;
+      if (pl.is_f32) { g.dS_lo = at<__bf16>(ws, pl.dS_lo); g.dST_lo = at<__bf16>(ws, pl.dST_lo); }
+      pg::Rechunk rc{};
+      rc.enabled = pl.nchunks > 1; rc.chunk = c; rc.tiles_v_all = pl.tiles_v; rc.ld_s_all = (int)pg::pad_ld((int64_t)pl.tiles_v * 256);
+      rc.cap_s = (long long)pl.rows_b * pl.ld_v; rc.cap_t = (long long)pl.vc * pl.ld_t;
+      g.rc = rc; g.kept = kept; g.blk = blk; g.tiles_v_all = pl.tiles_v;
+      unsigned* const queues = block_queue + pg::QUEUE_SET_WORDS * (1 + 4 * c);
+      g.queue = queues; g.queue_lo = queues + 3 * pg::QUEUE_SET_WORDS;
+      { ProfScope ps(PG_KERNEL_DLOGITS, st); pg::launch_lmhead_dlogits(g, st); }
 
-    pg::StoreArgs w{};   // dW[v0 + m, :] = sum_t dS^T[m, t] H^T[:, t]
-    w.A = at<__bf16>(ws, pl.dST); w.B = at<__bf16>(ws, pl.HcT);
-    if (pl.is_f32) { w.A_lo = at<__bf16>(ws, pl.dST_lo); w.B_lo = at<__bf16>(ws, pl.HcT_lo); w.ldb_lo = pl.ld_t; }
-    w.a_rows = pl.vc; w.b_rows = d_i;
-    w.lda = pl.ld_t; w.ldb = pl.ld_t; w.M = rows_valid; w.N = d_i; w.K = pl.t_cap;
-    w.tiles_m = tiles_c; w.tiles_n = (d_i + 255) / 256;
-    w.C = static_cast<char*>(dW) + (size_t)v0 * pl.d * dw_elem; w.ldc = d_i;
-    w.accumulate = p.accumulate_dW; w.out_bf16 = p.dW_dtype; w.k_from_ctl = 1; w.m_from_ctl = 0; w.ctl = ctl;
-    w.queue = queues + pg::QUEUE_SET_WORDS;
-    w.rc = rc; w.rc_role = 1; w.v0 = v0;
-    if (pl.dw_cap) {
-      pg::DwFoldArgs f{};
-      f.slabs = at<float>(ws, pl.dWslabs); f.dW = w.C; f.n = (long long)rows_valid * d_i; f.slab = (long long)pl.vc * d_i;
-      f.dw_cap = pl.dw_cap; f.products = pl.is_f32 ? 3 : 1; f.accumulate = w.accumulate; f.out_bf16 = w.out_bf16; f.ctl = ctl;
-      w.C = at<float>(ws, pl.dWslabs); w.accumulate = 0; w.out_bf16 = 0; w.dw_cap = pl.dw_cap; w.slab_rows = pl.vc;
-      ProfScope ps(PG_KERNEL_DW, st);
-      pg::launch_gemm_store(w, st);
-      pg::launch_dw_fold(f, st);
-    } else {
-      ProfScope ps(PG_KERNEL_DW, st);
-      pg::launch_gemm_store(w, st);
-    }
+      pg::StoreArgs w{};   // dW[v0 + m, :] = sum_t dS^T[m, t] H^T[:, t]
+      w.A = at<__bf16>(ws, pl.dST); w.B = at<__bf16>(ws, pl.HcT);
+      if (pl.is_f32) { w.A_lo = at<__bf16>(ws, pl.dST_lo); w.B_lo = at<__bf16>(ws, pl.HcT_lo); w.ldb_lo = pl.ld_h; }
+      w.a_rows = pl.vc; w.b_rows = d_i;
+      w.lda = pl.ld_t; w.ldb = pl.ld_h; w.M = rows_valid; w.N = d_i; w.K = pl.rows_b;
+      w.tiles_m = tiles_c; w.tiles_n = (d_i + 255) / 256;
+      w.C = static_cast<char*>(dW) + (size_t)v0 * pl.d * dw_elem; w.ldc = d_i;
+      w.accumulate = p.accumulate_dW; w.out_bf16 = p.dW_dtype; w.k_from_ctl = 1; w.m_from_ctl = 0; w.ctl = ctl;
+      w.queue = queues + pg::QUEUE_SET_WORDS;
+      w.rc = rc; w.rc_role = 1; w.v0 = v0; w.blk = blk;
+      if (pl.dw_cap) {
+        pg::DwFoldArgs f{};
+        f.slabs = at<float>(ws, pl.dWslabs); f.dW = w.C; f.n = (long long)rows_valid * d_i; f.slab = (long long)pl.vc * d_i;
+        f.dw_cap = pl.dw_cap; f.products = pl.is_f32 ? 3 : 1; f.accumulate = w.accumulate; f.out_bf16 = w.out_bf16; f.ctl = ctl;
+        w.C = at<float>(ws, pl.dWslabs); w.accumulate = 0; w.out_bf16 = 0; w.dw_cap = pl.dw_cap; w.slab_rows = pl.vc;
+        ProfScope ps(PG_KERNEL_DW, st);
+        pg::launch_gemm_store(w, st);
+        pg::launch_dw_fold(f, st);
+      } else {
+        ProfScope ps(PG_KERNEL_DW, st);
+        pg::launch_gemm_store(w, st);
+      }
 
-    pg::StoreArgs h{};   // dHacc[t, :] (+)= sum_v dS[t, v] W^T[:, v]
-    h.A = at<__bf16>(ws, pl.dS); h.B = wt;
-    if (pl.is_f32) { h.A_lo = at<__bf16>(ws, pl.dS_lo); h.B_lo = at<__bf16>(ws, pl.WT_lo); h.ldb_lo = pl.ld_v; }
-    h.a_rows = pl.t_cap; h.b_rows = d_i;
-    h.lda = pl.ld_v; h.ldb = ld_wt; h.M = pl.t_cap; h.N = d_i; h.K = kc;
-    h.tiles_m = pl.tiles_t; h.tiles_n = (d_i + 255) / 256;
-    h.C = at<float>(ws, pl.dHacc); h.ldc = d_i;
-    h.accumulate = c > 0; h.out_bf16 = 0; h.k_from_ctl = 0; h.m_from_ctl = 1; h.split_k = 1; h.ctl = ctl;
-    h.acc_rows = pl.acc_rows; h.split_stages = kc0 / 64;
-    h.queue = queues + 2 * pg::QUEUE_SET_WORDS;
-    h.rc = rc; h.rc_role = 2; h.v0 = v0;
-    h.rule = rule;
-    {
-      ProfScope ps(PG_KERNEL_DH, st);
-      if (transposed) pg::launch_gemm_store(h, st);
-      if (direct) {
-        h.b_k_rows = 1; h.b_rows = rows_valid; h.ldb = pl.kd;
-        h.B = static_cast<const __bf16*>(Wop) + (size_t)v0 * pl.kd;
-        if (pl.is_f32) { h.B_lo = static_cast<const __bf16*>(h.B) + d_i; h.ldb_lo = pl.kd; }
-        pg::launch_gemm_store(h, st);
+      pg::StoreArgs h{};   // dHacc[t, :] (+)= sum_v dS[t, v] W^T[:, v]
+      h.A = at<__bf16>(ws, pl.dS); h.B = wt;
+      if (pl.is_f32) { h.A_lo = at<__bf16>(ws, pl.dS_lo); h.B_lo = at<__bf16>(ws, pl.WT_lo); h.ldb_lo = pl.ld_v; }
+      h.a_rows = pl.rows_b; h.b_rows = d_i;
+      h.lda = pl.ld_v; h.ldb = ld_wt; h.M = pl.rows_b; h.N = d_i; h.K = kc;
+      h.tiles_m = tiles_b; h.tiles_n = (d_i + 255) / 256;
+      h.C = at<float>(ws, pl.dHacc); h.ldc = d_i;
+      h.accumulate = c > 0; h.out_bf16 = 0; h.k_from_ctl = 0; h.m_from_ctl = 1; h.split_k = 1; h.ctl = ctl;
+      h.acc_rows = pl.acc_rows; h.split_stages = kc0 / 64;
+      h.queue = queues + 2 * pg::QUEUE_SET_WORDS;
+      h.rc = rc; h.rc_role = 2; h.v0 = v0;
+      h.rule = rule; h.blk = blk;
+      {
+        ProfScope ps(PG_KERNEL_DH, st);
+        if (transposed) pg::launch_gemm_store(h, st);
+        if (direct && b * tiles_b * 256 < pg::DIRECT_MAX_ROWS) {     // (a later block holds rows only of more than that)
+          h.b_k_rows = 1; h.b_rows = rows_valid; h.ldb = pl.kd;
+          h.B = static_cast<const __bf16*>(Wop) + (size_t)v0 * pl.kd;
+          if (pl.is_f32) { h.B_lo = static_cast<const __bf16*>(h.B) + d_i; h.ldb_lo = pl.kd; }
+          pg::launch_gemm_store(h, st);
+        }
       }
     }
   }
 
+  pg::FinishArgs fin{at<float>(ws, pl.lossterm), at<unsigned long long>(ws, pl.counters), loss_out,
+                     reinterpret_cast<long long*>(counters_out), at<pg::Ctl>(ws, pl.ctl)};
+  pg::launch_finish(fin, st);
   pg::ScatterArgs sc{at<float>(ws, pl.dHacc), at<int>(ws, pl.pos), dH, (int)pl.T, d_i, pl.is_f32 || shard.dH_f32,
-                     1, pl.acc_rows, (d_i + 255) / 256, kc0 / 64, pl.is_f32, ctl};
+                     1, pl.acc_rows, (d_i + 255) / 256, kc0 / 64, pl.is_f32, pl.cap_t, ctl};
   if (norm) pg::launch_scatter_dx_norm(sc, nf, st);
   else pg::launch_scatter_dh(sc, st);
   return guard.check(shard.what ? shard.what : sft ? "pg_sft_fwd_bwd" : norm ? "pg_loss_fwd_bwd_normed" : "pg_loss_fwd_bwd");

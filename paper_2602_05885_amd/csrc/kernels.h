@@ -11,7 +11,7 @@ struct Ctl;
 // call (the forward, then recompute / dW / dH / remainder recompute of every vocab chunk), all cleared
 // by the pre-pass.
 constexpr int QUEUE_SET_WORDS = 8;
-inline int queue_sets(int nchunks) { return 1 + 4 * nchunks; }
+inline int queue_sets(int nchunks) { return 1 + 4 * nchunks; }     // per token block
 
 // Scratch leading dimensions (multiples of 64 elements = 128 bytes) are made an odd number of
 // 128-byte lines, so that the rows of a tile spread over the memory channels instead of
@@ -70,6 +70,34 @@ struct DirectRule {
   const Ctl* ctl;
 };
 
+// Token blocks.  Where the kept logits of all rows do not fit their share of the workspace, but those of a good
+// number of rows over the whole vocabulary do, the rows are worked off in blocks of at most cap_t token tiles: forward,
+// row epilogue, dS, dW (added to the block before) and dH of a block, then the next one, so that nothing is ever
+// recomputed.  The active rows are known only on the device: the host launches as many blocks as its rows may need
+// and the launches of a block without any return at once.  cap_t is a whole number of rounds of the dH launch
+// (cap_t ceil(d / 256) tiles over 256 compute units), so that cutting the rows adds no half-empty round: dealt evenly, 133 tiles
+// at d = 2048 took 2 x 3 rounds instead of 5, and the call 41.6 ms against 41.0 ms in one block.
+// At d = 5120, V = 151936, 32768 rows, two blocks of 64 tiles took the call from 128.1 to 116.0 ms: the recompute of half of the
+// logits (16 ms) went, the second pass over dW cost 0.4 ms.
+struct TokenBlocks {
+  int cap_t;            // token tiles per block at most; 0: one block holds every row
+  int b;                // this launch's block
+};
+// Where keeping pays, by the contraction length K that a recompute would repeat (once more for the remainders of an fp32
+// head): K = 512 1990 us kept against 1811 us recomputed, 768 2440 / 2390, 1024 2866 / 2990, 2048 4620 / 5370 (4000 rows,
+// V = 103936); and always where no workgroup has more than one tile to recompute (latency).  Token blocks pass over
+// dW and W once more per block: 33912 rows, K = 1024 27.3 ms in blocks against 24.9 ms in one, 1536 31.3 / 33.1,
+// 3072 55.8 / 58.5.
+constexpr int KEEP_MIN_K = 1024, KEEP_ANY_TILES = 256;
+constexpr int BLOCK_MIN_K = 1536;
+constexpr int BLOCK_MIN_TILES = 16;     // smaller blocks would make the passes over dW and W dearer than a recompute
+// Token tiles [t0, t0 + nt) of block k.b when `live` tiles are live.
+__host__ __device__ inline void token_block(const TokenBlocks& k, int live, int& t0, int& nt) {
+  if (k.cap_t <= 0) { t0 = 0; nt = k.b == 0 ? live : 0; return; }
+  t0 = k.b * k.cap_t < live ? k.b * k.cap_t : live;
+  nt = live - t0 < k.cap_t ? live - t0 : k.cap_t;
+}
+
 // ---- MFMA kernels ---------------------------------------------------------------------
 struct FwdArgs {
   const void* W;        // [V, ldw] bf16
@@ -87,6 +115,7 @@ struct FwdArgs {
   float* part_s;
   float* part_u;
   Kept kept;
+  TokenBlocks blk;
   const Ctl* ctl;
   unsigned* queue;      // [8] tile counters of this launch's queue, zero at launch
 };
@@ -116,6 +145,7 @@ struct DlogitsArgs {
   unsigned* queue_lo;   // [8] the same for the launch that stores the remainders
   Rechunk rc;
   Kept kept;            // as the forward had it
+  TokenBlocks blk;      // dS and dS^T hold this block's rows only
   int tiles_v_all;      // 256-row vocab tiles of the whole head
 };
 
@@ -137,6 +167,7 @@ struct StoreArgs {
   int out_bf16;
   int k_from_ctl;       // contraction length = padded active-token count
   int m_from_ctl;       // row extent        = padded active-token count
+  TokenBlocks blk;      // of the token extent
   int split_k;          // with m_from_ctl: cut K into dh_slabs(n_pad, acc_rows, tiles_n, split_stages, ..) parts, part p writes rows p n_pad + m
   int acc_rows;         // rows of C
   int dw_cap;           // > 0, with k_from_ctl: cut K into dw_split(K stages, dw_cap) parts (times three products for fp32
@@ -219,7 +250,7 @@ struct GatherArgs {
   __bf16* Hc;           // [t_cap, ldh]   bf16: ldh = d;  fp32: ldh = 3d = [hi | hi | lo]
   __bf16* HcT;          // [d, ld_t] (nullable): transpose of the bf16 operand / of the hi parts
   __bf16* HcT_lo;       // [d, ld_t] (nullable, fp32 only): transpose of the lo parts
-  int ld_t;
+  int ld_t;             // leading dimension of HcT and HcT_lo
   int* yc;              // y - y_offset where that lies in [0, V), else -1
   int y_offset, V;      // first vocab row and number of vocab rows of the weight operand
   const Ctl* ctl;
@@ -251,6 +282,7 @@ struct CombineArgs {
   // row's state from there (the state merged over all shards) instead of from part_*.
   float* partials_out;
   const float* partials_in;
+  TokenBlocks blk;
   const Ctl* ctl;
 };
 void launch_combine(const CombineArgs& a, hipStream_t s);
@@ -277,6 +309,7 @@ struct ScatterArgs {
   // split-K slabs of the accumulator (see dh_split): 0 = one slab; else the arguments of dh_split
   // as the first chunk's contraction saw them
   int split_k, acc_rows, tiles_n, k_stages, split_f32;
+  int cap_t;            // see TokenBlocks: several blocks are never split
   const Ctl* ctl;
 };
 void launch_scatter_dh(const ScatterArgs& a, hipStream_t s);

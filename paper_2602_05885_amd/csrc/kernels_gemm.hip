@@ -56,9 +56,15 @@ constexpr int FWD_LDS_BYTES = FWD_CLAIM_OFF + 16;
 constexpr int PROBE_FIRST = 150, PROBE_TILES = 16;
 
 template <bool PROBE>
-__device__ __forceinline__ void lmhead_fwd_body(const FwdArgs& a, bool steal, unsigned long long* tl) {
+__device__ __forceinline__ void lmhead_fwd_body(FwdArgs a, bool steal, unsigned long long* tl) {
   const Ctl ctl = *a.ctl;
-  const int tiles_t = min(a.tiles_t, ctl.n_pad / BN);          // live token tiles: known only on the device
+  int t0, nt;
+  token_block(a.blk, ctl.n_pad / BN, t0, nt);
+  const int tiles_t = min(a.tiles_t, nt);                      // live token tiles: known only on the device
+  if (tiles_t <= 0) return;
+  a.Hc = static_cast<const char*>(a.Hc) + (size_t)t0 * BN * a.ldh * 2; a.h_rows -= t0 * BN;
+  a.yc += t0 * BN; a.zy += t0 * BN;
+  a.part_m += t0 * BN; a.part_s += t0 * BN; a.part_u += t0 * BN;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave / WN, wn = wave % WN;
   TileQueue Q;
@@ -444,7 +450,11 @@ __global__ __launch_bounds__(KEPT_THREADS, 2) void dlogits_kept_kernel(DlogitsAr
     if (a.rc.chunk > 0) return;
     a.v0 = 0; a.tiles_v = a.rc.tiles_v_all; a.ld_s = a.rc.ld_s_all; a.ld_t = ld_t_all;
   }
-  const int tiles_t = min(a.tiles_t, ctl.n_pad / BN);
+  int t0, nt;
+  token_block(a.blk, ctl.n_pad / BN, t0, nt);
+  const int tiles_t = min(a.tiles_t, nt);
+  if (tiles_t <= 0) return;
+  a.yc += t0 * BN; a.lse2 += t0 * BN; a.coefc += t0 * BN;
   const int total = 2 * kept_in_chunk(a, tiles_t) * tiles_t;
   const int tid = threadIdx.x, lane = tid & 63, wm = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int tm0 = a.v0 / BM;
@@ -542,12 +552,16 @@ __device__ __forceinline__ void store_tile(const StoreArgs& a, int tm, int tn, i
 // The run-time extents of a store contraction (the padded active-token count is known only on the device).
 struct StoreShape {
   int m_lim, tiles_m, K, ks, products, slab_rows, total;
+  int t0, nt;             // token tiles of this launch's block
+  uint32_t b_off;         // dW: byte offset of the block's first column in a row of H^T
   __device__ __forceinline__ void init(const StoreArgs& a, const Ctl& ctl) {
-    m_lim = a.m_from_ctl ? min(a.M, ctl.n_pad) : a.M;
+    token_block(a.blk, ctl.n_pad / BM, t0, nt);
+    m_lim = a.m_from_ctl ? min(a.M, nt * BM) : a.M;
     tiles_m = min(a.tiles_m, (m_lim + BM - 1) / BM);
-    K = a.k_from_ctl ? ctl.n_pad : a.K;
+    K = a.k_from_ctl ? nt * BM : a.K;
+    b_off = a.k_from_ctl ? (uint32_t)t0 * BM * 2u : 0u;
     ks = 1; products = 1; slab_rows = ctl.n_pad;
-    if (a.split_k && a.m_from_ctl) {
+    if (a.split_k && a.m_from_ctl && nt * BM == ctl.n_pad) {
       products = dh_slabs(ctl.n_pad, a.acc_rows, a.tiles_n, a.split_stages, a.A_lo != nullptr, ks) / ks;
     } else if (a.dw_cap > 0) {
       ks = dw_split(K / BK, a.dw_cap);
@@ -578,7 +592,7 @@ __device__ __forceinline__ void gemm_store_tile(StoreArgs a, const StoreShape& s
   TileLoader LB;
   auto init_n = [&](const void* B, int ldb) {
     if constexpr (DIRECT) LA.init(B, a.b_rows, s0 * BK, ldb, tn * BN, tid);
-    else LA.init(B, a.b_rows, tn * BN, ldb, kb, tid);
+    else LA.init(B, a.b_rows, tn * BN, ldb, kb + sh.b_off, tid);
   };
   init_n(a.B, a.ldb);
   LB.init(a.A, a.a_rows, tm * BM, a.lda, kb, tid);     // engine columns <- m
@@ -621,6 +635,11 @@ __global__ __launch_bounds__(NTHREADS) void gemm_store_kernel(StoreArgs a) {
   }
   StoreShape sh;
   sh.init(a, ctl);
+  if (a.blk.b > 0) {
+    if (sh.nt <= 0) return;
+    if (a.k_from_ctl) a.accumulate = 1;                              // dW: on top of the blocks before
+  }
+  if (a.m_from_ctl) a.C = static_cast<float*>(a.C) + (size_t)sh.t0 * BM * a.ldc;      // dH: this block's rows of the accumulator
   TileQueue Q;
   Q.init(a.queue, sh.total, 1);
   volatile int* claim = reinterpret_cast<volatile int*>(g_smem + CLAIM_OFF);

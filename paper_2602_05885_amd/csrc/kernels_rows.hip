@@ -393,8 +393,10 @@ __global__ __launch_bounds__(64 * COMBINE_WAVES) void combine_kernel(CombineArgs
   __shared__ float sh[COMBINE_WAVES - 1][3][64];
   const Ctl ctl = *a.ctl;
   const int lane = threadIdx.x & 63, part = threadIdx.x >> 6;
-  const int i = blockIdx.x * 64 + lane;
-  if (blockIdx.x * 64 >= ctl.n_pad) return;      // whole workgroup beyond the padded rows
+  int t0, nt;
+  token_block(a.blk, ctl.n_pad / BN, t0, nt);
+  if ((int)blockIdx.x * 64 >= nt * BN) return;   // whole workgroup beyond the padded rows
+  const int i = t0 * BN + blockIdx.x * 64 + lane;
   float M = -1.0e30f, s = 0.f, u = 0.f;
   int k = part;
   for (; k + 3 * COMBINE_WAVES < a.tiles_v; k += 4 * COMBINE_WAVES) {
@@ -461,7 +463,7 @@ __global__ __launch_bounds__(64 * COMBINE_WAVES) void combine_kernel(CombineArgs
   a.lossterm[i] = c * l;
 }
 void launch_combine(const CombineArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(combine_kernel, dim3(a.t_cap / 64), dim3(64 * COMBINE_WAVES), 0, s, a);
+  hipLaunchKernelGGL(combine_kernel, dim3((a.blk.cap_t > 0 ? a.blk.cap_t * BN : a.t_cap) / 64), dim3(64 * COMBINE_WAVES), 0, s, a);
 }
 
 // Single workgroup, fixed order, fp64: loss = (sum_t c_t l_t) / norm; publishes the counters.
@@ -492,7 +494,7 @@ __global__ __launch_bounds__(256) void scatter_dh_kernel(ScatterArgs a) {
   const float* src = a.acc + (size_t)(p < 0 ? 0 : p) * a.d;
   const int n_pad = a.ctl->n_pad;
   int ks = 1;                                       // slabs
-  if (a.split_k) ks = dh_slabs(n_pad, a.acc_rows, a.tiles_n, a.k_stages, a.split_f32, ks);
+  if (a.split_k && (a.cap_t <= 0 || n_pad <= a.cap_t * BM)) ks = dh_slabs(n_pad, a.acc_rows, a.tiles_n, a.k_stages, a.split_f32, ks);
   const size_t slab = (size_t)n_pad * a.d;
   for (int j = threadIdx.x * 4; j < a.d; j += 256 * 4) {
     float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -1138,7 +1140,7 @@ __global__ __launch_bounds__(256) void scatter_dx_norm_kernel(ScatterArgs a, Nor
   const long long T = a.T;
   const int n_pad = a.ctl->n_pad;
   int ks = 1;                                       // slabs
-  if (a.split_k) ks = dh_slabs(n_pad, a.acc_rows, a.tiles_n, a.k_stages, a.split_f32, ks);
+  if (a.split_k && (a.cap_t <= 0 || n_pad <= a.cap_t * BM)) ks = dh_slabs(n_pad, a.acc_rows, a.tiles_n, a.k_stages, a.split_f32, ks);
   const size_t slab = (size_t)n_pad * a.d;
   float dg[NC][8];
   Raw8<F32> gam_raw[NC] = {};
