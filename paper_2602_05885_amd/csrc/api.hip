@@ -899,11 +899,10 @@ int32_t loss_fwd_bwd(int sft, const void* H, const void* W, const int32_t* y, co
 
   pg::FinishArgs fin{at<float>(ws, pl.lossterm), at<unsigned long long>(ws, pl.counters), loss_out,
                      reinterpret_cast<long long*>(counters_out), at<pg::Ctl>(ws, pl.ctl)};
-  pg::launch_finish(fin, st);
   pg::ScatterArgs sc{at<float>(ws, pl.dHacc), at<int>(ws, pl.pos), dH, (int)pl.T, d_i, pl.is_f32 || shard.dH_f32,
                      1, pl.acc_rows, (d_i + 255) / 256, kc0 / 64, pl.is_f32, pl.cap_t, ctl};
-  if (norm) pg::launch_scatter_dx_norm(sc, nf, st);
-  else pg::launch_scatter_dh(sc, st);
+  if (norm) pg::launch_scatter_dx_norm(sc, nf, fin, st);
+  else pg::launch_scatter_dh(sc, fin, st);
   return guard.check(shard.what ? shard.what : sft ? "pg_sft_fwd_bwd" : norm ? "pg_loss_fwd_bwd_normed" : "pg_loss_fwd_bwd");
 }
 

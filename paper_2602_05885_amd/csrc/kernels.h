@@ -294,7 +294,6 @@ struct FinishArgs {
   long long* counters_out;
   const Ctl* ctl;
 };
-void launch_finish(const FinishArgs& a, hipStream_t s);
 
 // W[v0 .. v0+cols) x d  ->  WT [d, ldt] bf16 (zeros for v >= V)
 void launch_transpose_w(const void* W, int is_f32, int64_t V, int d, int ldw, int v0, int cols, int ldt, __bf16* WT,
@@ -312,7 +311,8 @@ struct ScatterArgs {
   int cap_t;            // see TokenBlocks: several blocks are never split
   const Ctl* ctl;
 };
-void launch_scatter_dh(const ScatterArgs& a, hipStream_t s);
+// (the loss and the counters come from the same launch)
+void launch_scatter_dh(const ScatterArgs& a, const FinishArgs& fin, hipStream_t s);
 
 // RMS normalisation fused around the head (h = x rstd gamma in front of it, its backward behind dH):
 // the forward is applied while the active rows are compacted, the backward while dH is scattered.
@@ -327,7 +327,7 @@ struct NormFuse {
 // Hc[i, :] = normalised row rows[i] of X (zeros on padding), yc[i] as launch_gather; then Hc -> HcT.
 void launch_norm_gather(const GatherArgs& g, const NormFuse& n, hipStream_t s);
 // dX[t, :] = RMSNorm backward of the accumulated dH row of t (zeros for rows that are not active); dgamma.
-void launch_scatter_dx_norm(const ScatterArgs& a, const NormFuse& n, hipStream_t s);
+void launch_scatter_dx_norm(const ScatterArgs& a, const NormFuse& n, const FinishArgs& fin, hipStream_t s);
 
 // out[t] = merge(a[t], b[t]) of two per-row softmax states (m, s, u, z_y), [T][4] each.
 void launch_merge_partials(const float* a, const float* b, float* out, long long T, hipStream_t s);

@@ -178,29 +178,59 @@ __global__ __launch_bounds__(256) void prep_segment_kernel(PrepArgs a) {
   if (ntr) atomicAdd(&a.counters[5], ntr);
 }
 
-// Single workgroup: exclusive scan of the active flags -> compacted row list, inverse map,
-// counts and the loss normaliser.
+// Single workgroup: exclusive scan of the active flags -> compacted row list, inverse map, counts and the loss
+// normaliser.  A wavefront takes a contiguous run of rows, 256 at a time (four flags per lane in one load), counts
+// them, and after the wavefronts' totals are known ranks them with a lane prefix.  Latency is all there is: one row at a time per
+// thread, as it was, took 64 us at 43697 rows and 19 us at 16082; so 24 and 9 us.
 __global__ __launch_bounds__(1024) void prep_compact_kernel(PrepArgs a) {
-  __shared__ int sh[1024];
-  const int tid = threadIdx.x;
-  const int chunk = (a.T + 1023) / 1024;
-  const int lo = min(a.T, tid * chunk), hi = min(a.T, lo + chunk);
+  __shared__ int total_of[16];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int run = (a.T + 16 * 256 - 1) / (16 * 256) * 256;      // rows per wavefront (wave 15's may reach beyond T)
+  const int lo = wave * run, hi = lo < a.T ? (a.T - lo < run ? a.T : lo + run) : lo;
+  // four flags from row t on (the flag array is padded to whole groups; rows beyond T count as inactive)
+  auto flags = [&](int t) -> unsigned {
+    unsigned f = 0;
+    if (t < hi) f = *reinterpret_cast<const unsigned*>(a.flag + t) & 0x01010101u;
+    if (t + 4 > hi && t < hi) f &= (1u << ((hi - t) * 8)) - 1u;
+    return f;
+  };
   int cnt = 0;
-  for (int t = lo; t < hi; ++t) cnt += a.flag[t] ? 1 : 0;
-  sh[tid] = cnt;
+#pragma unroll 4
+  for (int t = lo + lane * 4; t < hi; t += 256) cnt += __popc(flags(t));
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) cnt += __shfl_xor(cnt, off);
+  if (lane == 0) total_of[wave] = cnt;
   __syncthreads();
-  for (int off = 1; off < 1024; off <<= 1) {
-    const int v = (tid >= off) ? sh[tid - off] : 0;
-    __syncthreads();
-    sh[tid] += v;
-    __syncthreads();
+  int base = 0, total = 0;
+#pragma unroll
+  for (int w = 0; w < 16; ++w) {
+    const int c = total_of[w];
+    if (w < wave) base += c;
+    total += c;
   }
-  int idx = sh[tid] - cnt;
-  for (int t = lo; t < hi; ++t) {
-    if (a.flag[t]) { a.rows[idx] = t; a.pos[t] = idx; ++idx; } else { a.pos[t] = -1; }
+  unsigned ahead = flags(lo + lane * 4);
+  for (int t0 = lo; t0 < hi; t0 += 256) {
+    const int t = t0 + lane * 4;
+    const unsigned f = ahead;
+    ahead = flags(t + 256);
+    const int c = __popc(f);
+    int incl = c;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const int v = __shfl_up(incl, off);
+      if (lane >= off) incl += v;
+    }
+    int idx = base + incl - c;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (t + e < hi) {
+        const bool on = (f >> (8 * e)) & 1u;
+        a.pos[t + e] = on ? idx : -1;
+        if (on) a.rows[idx++] = t + e;
+      }
+    base += __shfl(incl, 63);
   }
-  if (tid == 1023) {
-    const int total = sh[1023];
+  if (tid == 0) {
     a.ctl->n_active = total;
     a.ctl->n_pad = (total + 255) / 256 * 256;
     a.ctl->norm = a.norm_override > 0.f ? a.norm_override : (float)max(total, 1);
@@ -466,30 +496,33 @@ void launch_combine(const CombineArgs& a, hipStream_t s) {
   hipLaunchKernelGGL(combine_kernel, dim3((a.blk.cap_t > 0 ? a.blk.cap_t * BN : a.t_cap) / 64), dim3(64 * COMBINE_WAVES), 0, s, a);
 }
 
-// Single workgroup, fixed order, fp64: loss = (sum_t c_t l_t) / norm; publishes the counters.
-__global__ __launch_bounds__(1024) void finish_kernel(FinishArgs a) {
-  __shared__ double sh[1024];
+// One workgroup of 256, fixed order, fp64: loss = (sum_t c_t l_t) / norm; publishes the counters.  It runs as a
+// workgroup of the scatter, the first one there (a launch of its own was 4..17 us).
+__device__ __forceinline__ void finish_loss(const FinishArgs& a) {
+  __shared__ double sh[256];
   const Ctl ctl = *a.ctl;
   const int tid = threadIdx.x;
-  double acc = 0.0;
-  for (int i = tid; i < ctl.n_active; i += 1024) acc += (double)a.lossterm[i];
-  sh[tid] = acc;
+  double acc[4] = {0.0, 0.0, 0.0, 0.0};
+  int i = tid;
+  for (; i + 3 * 256 < ctl.n_active; i += 4 * 256)
+#pragma unroll
+    for (int k = 0; k < 4; ++k) acc[k] += (double)a.lossterm[i + k * 256];
+  for (; i < ctl.n_active; i += 256) acc[0] += (double)a.lossterm[i];
+  sh[tid] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
   __syncthreads();
-  for (int w = 512; w > 0; w >>= 1) {
+  for (int w = 128; w > 0; w >>= 1) {
     if (tid < w) sh[tid] += sh[tid + w];
     __syncthreads();
   }
   if (tid == 0 && a.loss_out) *a.loss_out = (float)(sh[0] / (double)ctl.norm);
   if (tid < 8 && a.counters_out) a.counters_out[tid] = (long long)a.counters[tid];
 }
-void launch_finish(const FinishArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(finish_kernel, dim3(1), dim3(1024), 0, s, a);
-}
 
 // ------------------------------------------------------------------ dH scatter
 // dH[t,:] = accumulated row of its compacted position, or zeros for rows that are not active.
-__global__ __launch_bounds__(256) void scatter_dh_kernel(ScatterArgs a) {
-  const int t = blockIdx.x;
+__global__ __launch_bounds__(256) void scatter_dh_kernel(ScatterArgs a, FinishArgs fin) {
+  const int t = (int)blockIdx.x - 1;
+  if (t < 0) return finish_loss(fin);
   const int p = a.pos[t];
   const float* src = a.acc + (size_t)(p < 0 ? 0 : p) * a.d;
   const int n_pad = a.ctl->n_pad;
@@ -592,9 +625,9 @@ void launch_dw_fold(const DwFoldArgs& a, hipStream_t s) {
   hipLaunchKernelGGL(dw_fold_kernel, dim3((unsigned)(blocks < 2048 ? blocks : 2048)), dim3(256), 0, s, a);
 }
 
-void launch_scatter_dh(const ScatterArgs& a, hipStream_t s) {
+void launch_scatter_dh(const ScatterArgs& a, const FinishArgs& fin, hipStream_t s) {
   if (a.T <= 0) return;
-  hipLaunchKernelGGL(scatter_dh_kernel, dim3(a.T), dim3(256), 0, s, a);
+  hipLaunchKernelGGL(scatter_dh_kernel, dim3(a.T + 1), dim3(256), 0, s, a, fin);
 }
 
 // ------------------------------------------------------------------ rewards (Eq. 1, Eq. 6-7)
@@ -1134,7 +1167,8 @@ void launch_norm_gather(const GatherArgs& g, const NormFuse& n, hipStream_t s) {
 // and g xhat is added to the thread's dgamma partial sums; rows that are not active are written as
 // zeros and nothing of theirs is read.  The workgroups' partials are folded by rmsnorm_dgamma_kernel.
 template <bool F32, int NC>
-__global__ __launch_bounds__(256) void scatter_dx_norm_kernel(ScatterArgs a, NormFuse n) {
+__global__ __launch_bounds__(256) void scatter_dx_norm_kernel(ScatterArgs a, NormFuse n, FinishArgs fin) {
+  if (blockIdx.x >= NORM_STRIPS) return finish_loss(fin);
   __shared__ float red[2][4];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const long long T = a.T;
@@ -1251,17 +1285,17 @@ __global__ __launch_bounds__(256) void scatter_dx_norm_kernel(ScatterArgs a, Nor
 }
 
 template <bool F32>
-static void launch_scatter_dx_norm_rows(const ScatterArgs& a, const NormFuse& n, hipStream_t s) {
+static void launch_scatter_dx_norm_rows(const ScatterArgs& a, const NormFuse& n, const FinishArgs& fin, hipStream_t s) {
   switch ((a.d + 2047) / 2048) {     // 8-column steps per thread; d <= NORM_MAX_D is checked by the caller
-    case 1: hipLaunchKernelGGL((scatter_dx_norm_kernel<F32, 1>), dim3(NORM_STRIPS), dim3(256), 0, s, a, n); break;
-    case 2: hipLaunchKernelGGL((scatter_dx_norm_kernel<F32, 2>), dim3(NORM_STRIPS), dim3(256), 0, s, a, n); break;
-    case 3: hipLaunchKernelGGL((scatter_dx_norm_kernel<F32, 3>), dim3(NORM_STRIPS), dim3(256), 0, s, a, n); break;
-    default: hipLaunchKernelGGL((scatter_dx_norm_kernel<F32, NORM_NC>), dim3(NORM_STRIPS), dim3(256), 0, s, a, n); break;
+    case 1: hipLaunchKernelGGL((scatter_dx_norm_kernel<F32, 1>), dim3(NORM_STRIPS + 1), dim3(256), 0, s, a, n, fin); break;
+    case 2: hipLaunchKernelGGL((scatter_dx_norm_kernel<F32, 2>), dim3(NORM_STRIPS + 1), dim3(256), 0, s, a, n, fin); break;
+    case 3: hipLaunchKernelGGL((scatter_dx_norm_kernel<F32, 3>), dim3(NORM_STRIPS + 1), dim3(256), 0, s, a, n, fin); break;
+    default: hipLaunchKernelGGL((scatter_dx_norm_kernel<F32, NORM_NC>), dim3(NORM_STRIPS + 1), dim3(256), 0, s, a, n, fin); break;
   }
 }
-void launch_scatter_dx_norm(const ScatterArgs& a, const NormFuse& n, hipStream_t s) {
-  if (a.out_f32) launch_scatter_dx_norm_rows<true>(a, n, s);
-  else launch_scatter_dx_norm_rows<false>(a, n, s);
+void launch_scatter_dx_norm(const ScatterArgs& a, const NormFuse& n, const FinishArgs& fin, hipStream_t s) {
+  if (a.out_f32) launch_scatter_dx_norm_rows<true>(a, n, fin, s);
+  else launch_scatter_dx_norm_rows<false>(a, n, fin, s);
   NormArgs f{};
   f.d = a.d; f.partial = n.partial; f.dgamma = n.dgamma;
   hipLaunchKernelGGL(rmsnorm_dgamma_kernel, dim3((a.d + 31) / 32), dim3(256), 0, s, f);
