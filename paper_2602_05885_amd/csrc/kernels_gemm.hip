@@ -265,10 +265,11 @@ struct DsColumn {
 // dS = c (onehot - p) is formed as  -sign(c) 2^(t2 - lse2 + log2|c|)  for every element (one fma
 // and one exp2 each; c = 0 gives 2^-inf = 0), the one-hot term c is added to the single element
 // that holds the sampled token (rare, wave-uniform branch), and the sign goes on with the bf16
-// packing.  LO (fp32 heads): the remainders dS - bf16(dS) instead.
-template <bool LO>
+// packing.  Fp32 heads also take the remainders dS - bf16(dS).
+enum DsPart { DS_VALUE, DS_REST, DS_EITHER };       // DS_EITHER: `rest` says which at run time
+template <DsPart PART>
 __device__ __forceinline__ void ds_pack(const DlogitsArgs& a, const DsColumn& col, int v_base, const f32x4 (&z)[GM],
-                                        uint32_t (&pk)[GM][2]) {
+                                        uint32_t (&pk)[GM][2], bool rest = false) {
   const int lane = threadIdx.x & 63;
   const bool ragged = v_base + WROWS > a.V;
   const int yrel = col.y - v_base;
@@ -295,9 +296,13 @@ __device__ __forceinline__ void ds_pack(const DlogitsArgs& a, const DsColumn& co
       bf16x2 two;
       two[0] = (__bf16)g[2 * h];
       two[1] = (__bf16)g[2 * h + 1];
-      if constexpr (LO) {
+      if constexpr (PART == DS_REST) {
         two[0] = (__bf16)(g[2 * h] - (float)two[0]);
         two[1] = (__bf16)(g[2 * h + 1] - (float)two[1]);
+      }
+      if constexpr (PART == DS_EITHER) {
+        two[0] = (__bf16)(g[2 * h] - (rest ? (float)two[0] : 0.f));
+        two[1] = (__bf16)(g[2 * h + 1] - (rest ? (float)two[1] : 0.f));
       }
       pk[i][h] = __builtin_bit_cast(uint32_t, two) ^ col.sgn;
     }
@@ -383,7 +388,7 @@ __device__ __forceinline__ void dlogits_tile(const DlogitsArgs& a, int tm, int t
     for (int i = 0; i < GM; ++i) z[i] = acc[i][j];
     const DsColumn col(a, tn * BN + wn * WCOLS + j * 16 + (lane & 15));
     uint32_t p[GM][2];
-    ds_pack<LO>(a, col, a.v0 + tm * BM + wm * WROWS, z, p);
+    ds_pack<LO ? DS_REST : DS_VALUE>(a, col, a.v0 + tm * BM + wm * WROWS, z, p);
 #pragma unroll
     for (int i = 0; i < GM; ++i) { pk[i][j][0] = p[i][0]; pk[i][j][1] = p[i][1]; }
   }
@@ -455,7 +460,7 @@ __global__ __launch_bounds__(KEPT_THREADS, 2) void dlogits_kept_kernel(DlogitsAr
   const int tiles_t = min(a.tiles_t, nt);
   if (tiles_t <= 0) return;
   a.yc += t0 * BN; a.lse2 += t0 * BN; a.coefc += t0 * BN;
-  const int total = 2 * kept_in_chunk(a, tiles_t) * tiles_t;
+  const int halves = 2 * kept_in_chunk(a, tiles_t) * tiles_t, total = SPLIT ? 2 * halves : halves;
   const int tid = threadIdx.x, lane = tid & 63, wm = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int tm0 = a.v0 / BM;
   f32x4 acc[GM][GN];
@@ -467,42 +472,33 @@ __global__ __launch_bounds__(KEPT_THREADS, 2) void dlogits_kept_kernel(DlogitsAr
 #pragma unroll
       for (int i = 0; i < GM; ++i) acc[i][j] = __builtin_nontemporal_load(kp + (j * GM + i) * 64);
   };
-  for (int h = blockIdx.x; h < total; h += gridDim.x) {
+  for (int item = blockIdx.x; item < total; item += gridDim.x) {
+    const bool rest = SPLIT && item >= halves;        // fp32 heads: the remainders as items of their own
+    const int h = rest ? item - halves : item;
     fetch(h);
     const int tm = (h >> 1) / tiles_t, tn = (h >> 1) - tm * tiles_t, half = h & 1;
     const size_t o_s = ((size_t)tn * BN + half * WCOLS) * a.ld_s + (size_t)tm * BM;
     const size_t o_t = ((size_t)tm * BM) * a.ld_t + (size_t)tn * BN + half * WCOLS;
     uint32_t pk[GM][GN][2];
-    auto pack = [&](auto lo) {
 #pragma unroll
-      for (int j = 0; j < GN; ++j) {
-        f32x4 z[GM];
+    for (int j = 0; j < GN; ++j) {
+      f32x4 z[GM];
 #pragma unroll
-        for (int i = 0; i < GM; ++i) z[i] = acc[i][j];
-        const DsColumn col(a, tn * BN + half * WCOLS + j * 16 + (lane & 15));
-        uint32_t p[GM][2];
-        ds_pack<decltype(lo)::value>(a, col, a.v0 + tm * BM + wm * WROWS, z, p);
+      for (int i = 0; i < GM; ++i) z[i] = acc[i][j];
+      const DsColumn col(a, tn * BN + half * WCOLS + j * 16 + (lane & 15));
+      uint32_t p[GM][2];
+      ds_pack<SPLIT ? DS_EITHER : DS_VALUE>(a, col, a.v0 + tm * BM + wm * WROWS, z, p, rest);
 #pragma unroll
-        for (int i = 0; i < GM; ++i) { pk[i][j][0] = p[i][0]; pk[i][j][1] = p[i][1]; }
-      }
-    };
-    auto flush = [&](__bf16* dS, __bf16* dST) {
-      ds_stage_rows<1>(pk, g_smem, wm, 0, lane);
-      lds_barrier();
-      ds_store<128, 512, EPI_STRIDE, KEPT_THREADS>(g_smem, dS, a.ld_s, tid);
-      lds_barrier();
-      ds_stage_cols(pk, g_smem, KEPT_STRIDE_T, wm, 0, lane);
-      lds_barrier();
-      ds_store<256, 256, KEPT_STRIDE_T, KEPT_THREADS>(g_smem, dST, a.ld_t, tid);
-      lds_barrier();
-    };
-    pack(std::false_type{});
-    flush(a.dS + o_s, a.dST + o_t);
-    if constexpr (SPLIT) {
-      fetch(h);                 // read again: held across the stores they would spill
-      pack(std::true_type{});
-      flush(a.dS_lo + o_s, a.dST_lo + o_t);
+      for (int i = 0; i < GM; ++i) { pk[i][j][0] = p[i][0]; pk[i][j][1] = p[i][1]; }
     }
+    ds_stage_rows<1>(pk, g_smem, wm, 0, lane);
+    lds_barrier();
+    ds_store<128, 512, EPI_STRIDE, KEPT_THREADS>(g_smem, (rest ? a.dS_lo : a.dS) + o_s, a.ld_s, tid);
+    lds_barrier();
+    ds_stage_cols(pk, g_smem, KEPT_STRIDE_T, wm, 0, lane);
+    lds_barrier();
+    ds_store<256, 256, KEPT_STRIDE_T, KEPT_THREADS>(g_smem, (rest ? a.dST_lo : a.dST) + o_t, a.ld_t, tid);
+    lds_barrier();
   }
 }
 
@@ -681,7 +677,7 @@ void launch_lmhead_fwd(const FwdArgs& a, hipStream_t s) {
 }
 void launch_lmhead_dlogits(const DlogitsArgs& a, hipStream_t s) {
   if (a.kept.cap > 0) {    // at most: every half tile of the launch's widest form
-    const long long halves = 2ll * (a.rc.enabled ? a.rc.tiles_v_all : a.tiles_v) * a.tiles_t;
+    const long long halves = (a.dS_lo ? 4ll : 2ll) * (a.rc.enabled ? a.rc.tiles_v_all : a.tiles_v) * a.tiles_t;
     const dim3 grid((unsigned)(halves < 2 * g_persistent_grid ? halves : 2 * g_persistent_grid));
     if (a.dS_lo) hipLaunchKernelGGL(dlogits_kept_kernel<true>, grid, dim3(KEPT_THREADS), KEPT_LDS_BYTES, s, a);
     else hipLaunchKernelGGL(dlogits_kept_kernel<false>, grid, dim3(KEPT_THREADS), KEPT_LDS_BYTES, s, a);
