@@ -247,7 +247,7 @@ struct GatherArgs {
   int d, t_cap;
   int is_f32;
   const int* rows;
-  __bf16* Hc;           // [t_cap, ldh]   bf16: ldh = d;  fp32: ldh = 3d = [hi | hi | lo]
+  __bf16* Hc;           // (null: only yc is written) [t_cap, ldh]   bf16: ldh = d;  fp32: ldh = 3d = [hi | hi | lo]
   __bf16* HcT;          // [d, ld_t] (nullable): transpose of the bf16 operand / of the hi parts
   __bf16* HcT_lo;       // [d, ld_t] (nullable, fp32 only): transpose of the lo parts
   int ld_t;             // leading dimension of HcT and HcT_lo

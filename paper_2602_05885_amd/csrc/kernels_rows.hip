@@ -240,8 +240,27 @@ __global__ __launch_bounds__(1024) void prep_compact_kernel(PrepArgs a) {
   }
 }
 
+// Every row active (no mask, no segments): the compaction is the identity, and the whole pre-pass one launch.
+__global__ void prep_all_rows_kernel(PrepArgs a) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < 8) a.counters[i] = i == 0 || i == 6 ? (unsigned long long)a.T : 0ull;      // active = loss rows = T
+  for (int w = i; w < a.queue_words; w += gridDim.x * blockDim.x) a.queue[w] = 0u;
+  if (i < a.t_cap) a.zy[i] = 0.f;
+  if (i < a.T) { a.rows[i] = i; a.pos[i] = i; }
+  if (i == 0) {
+    a.ctl->n_active = a.T;
+    a.ctl->n_pad = a.t_cap;
+    a.ctl->norm = a.norm_override > 0.f ? a.norm_override : (float)a.T;
+    a.ctl->pad_ = 0;
+  }
+}
+
 void launch_prepass(const PrepArgs& a, hipStream_t s) {
   const int n = a.t_cap > 8 ? a.t_cap : 8;
+  if (!a.cu && !a.mask) {
+    hipLaunchKernelGGL(prep_all_rows_kernel, dim3((n + 255) / 256), dim3(256), 0, s, a);
+    return;
+  }
   hipLaunchKernelGGL(prep_init_kernel, dim3((n + 255) / 256), dim3(256), 0, s, a);
   if (a.cu && a.S > 0) hipLaunchKernelGGL(prep_segment_kernel, dim3(a.S), dim3(256), 0, s, a);
   hipLaunchKernelGGL(prep_compact_kernel, dim3(1), dim3(1024), 0, s, a);
@@ -295,6 +314,7 @@ __global__ __launch_bounds__(256) void gather_kernel(GatherArgs a) {
     }
     a.yc[i] = yl;
   }
+  if (!a.Hc) return;      // the rows are read where they lie
   if (!a.is_f32) {
     const int chunk = tid & 7;
 #pragma unroll
@@ -352,7 +372,7 @@ __global__ __launch_bounds__(256) void gather_kernel(GatherArgs a) {
   }
 }
 void launch_gather(const GatherArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(gather_kernel, dim3(a.t_cap / 64, a.d / 64), dim3(256), 0, s, a);
+  hipLaunchKernelGGL(gather_kernel, dim3(a.t_cap / 64, a.Hc ? a.d / 64 : 1), dim3(256), 0, s, a);
 }
 
 __global__ void split_w_kernel(const float* W, __bf16* Wc, size_t n, int d) {
