@@ -43,11 +43,11 @@ def measured_mfma_only_tflops():
     return rates[-1] if rates else None
 
 # L2<->fabric bytes per gemm_store_kernel launch from the FETCH_SIZE / WRITE_SIZE counter runs
-# summarised in profiles/gemm_store_kernel_hbm_traffic.md (mean over a step's 14 launches, each
+# summarised in profiles/gemm_store_kernel_hbm_traffic.md (mean over a step's 30 launches, of which 20 have work, each
 # counter scaled by what it reads for a plain 1 GiB copy).  Valid only for the kernel sources the
 # counters were taken with: the digest below is of csrc/gemm_core.h + csrc/kernels_gemm.hip.
-TRAFFIC_GEMM_STORE = {"read_bytes": 5873740.1 * 1024 * 2.000, "write_bytes": 547145.8 * 1024 * 1.000,
-                      "sources_sha256": "b723ddea9561855eacbc87e3419af6609ef3501b8bad89cd1a341ee4c90ba681"}
+TRAFFIC_GEMM_STORE = {"read_bytes": 2572410.5 * 1024 * 2.000, "write_bytes": 312837.0 * 1024 * 1.000,
+                      "sources_sha256": "be584d520d0ebfe32b70fc8d159178e37b4a8d96c9f85aea8bcb8246bb9e9e1f"}
 
 
 def kernel_sources_digest() -> str:
@@ -150,7 +150,7 @@ def timed(torch, B, fn, steps, warmup):
     for _ in range(warmup):
         fn()
     torch.cuda.synchronize()
-    B.pg_profile_enable(True, 64 * max(steps, 1))
+    B.pg_profile_enable(True, 256 * max(steps, 1))
     t0 = time.perf_counter()
     for _ in range(steps):
         out = fn()
@@ -231,7 +231,7 @@ def main():
                          "share of the step (pg_head_shard_fwd + pg_head_partials_merge + pg_loss_shard_bwd); "
                          "bwd: pg_loss_shard_bwd on the whole head from the softmax states the old-policy "
                          "recompute left behind (valid while the weights are those of that recompute: the "
-                         "forward contraction is not repeated, 6dV instead of 8dV flops per token)")
+                         "forward contraction is not repeated: the logits are computed once, in the backward)")
     ap.add_argument("--vocab-shards", type=int, default=2, help="number of vocab shards for --workload shard")
     ap.add_argument("--no-others", dest="others", action="store_false",
                     help="skip the secondary workloads that the default run times after the headline "
@@ -337,7 +337,7 @@ def main():
     for _ in range(args.warmup):
         out = step()
     torch.cuda.synchronize()
-    B.pg_profile_enable(True, 64 * max(args.steps, 1))
+    B.pg_profile_enable(True, 256 * max(args.steps, 1))
     marks = [torch.cuda.Event(enable_timing=True) for _ in range(args.steps + 1)]   # step boundaries, same stream
     t0 = time.perf_counter()
     for i in range(args.steps):
@@ -378,15 +378,20 @@ def main():
     # ---- roofline of the dominant kernel ----
     # Algorithmic flops of each launch class per step: every class is one contraction over the whole
     # vocabulary, 2 d V flops per active token.
-    rows_of = {"fwd": V, "dlogits": V, "dw": V, "dh": V}
-    kernel_of = {"fwd": "lmhead_fwd_kernel", "dlogits": "lmhead_dlogits_kernel", "dw": "gemm_store_kernel",
+    # The calls that run the forward keep its fp32 logits (all of them at the sizes of the benchmark's configurations) and
+    # form dS from memory: 4 bytes read and 2 x 2 written per logit, no flops.  The others recompute the logits.
+    keeps = args.workload in ("pg", "sft")
+    rows_of = {"fwd": V, "dlogits": 0 if keeps else V, "dw": V, "dh": V}
+    kernel_of = {"fwd": "lmhead_fwd_kernel", "dlogits": "dlogits_kept_kernel" if keeps else "lmhead_dlogits_kernel", "dw": "gemm_store_kernel",
                  "dh": "gemm_store_kernel"}
     kern = {}
     for k, (ms, n) in prof.items():
         if n:
             fl = 2.0 * d * rows_of[k] * n_active                      # per step
             kern[k] = {"kernel": kernel_of[k], "launches_per_step": n / args.steps, "ms_per_step": ms / args.steps,
-                       "avg_launch_ms": ms / n, "flop_per_step": fl, "tflops": fl * args.steps / (ms * 1e-3) / 1e12}
+                       "avg_launch_ms": ms / n, "flop_per_step": fl, "tflops": fl * args.steps / (ms * 1e-3) / 1e12 if fl else None}
+            if k == "dlogits" and keeps:
+                kern[k]["GBps"] = 8.0 * V * n_active * args.steps / (ms * 1e-3) / 1e9
     by_kernel = {}
     for k, v in kern.items():
         b = by_kernel.setdefault(v["kernel"], {"ms": 0.0, "launches": 0.0, "flop": 0.0})
@@ -404,7 +409,7 @@ def main():
                 "traffic_source": TRAFFIC_SOURCE if measured_traffic(dom) is not None else None,
                 "flops_per_launch": b["flop"] / b["launches"], "avg_launch_ms": b["ms"] / b["launches"],
                 "launches_per_step": b["launches"]}
-    n_contractions = 3.0 if args.workload == "bwd" else 4.0       # logits (twice unless the forward is not repeated), dH, dW
+    n_contractions = 4.0 if args.workload == "shard" else 3.0     # logits (a second time where they are not kept), dH, dW
     executed = 2.0 * n_contractions * d * V * n_active / (ms_step * 1e-3) / 1e12
     useful = 6.0 * d * V * n_active / (ms_step * 1e-3) / 1e12
 
@@ -431,7 +436,7 @@ def main():
             B.trloo_advantage(rewards, valid, 1.0, want_returns=False, want_group_n=False)
             return B.pg_loss_fwd_bwd(H, W, y, loss_mask, cu, adv_flat, seg_sample, old_logp, rollout1, prm1, ws, dW=dW, out=outbuf)
         loss_entry("geometric_rejection", f"configs[{args.config}], mismatch_mode 1 (Sec. 5.1's rejection rule): "
-                   "trloo_advantage + pg_loss_fwd_bwd; tokens/s and % of peak count the tokens that stay active", step_mode1, 4.0)
+                   "trloo_advantage + pg_loss_fwd_bwd; tokens/s and % of peak count the tokens that stay active", step_mode1, 3.0)
 
         # the same with the W^T cache a trainer can keep while W is unchanged (further microbatches of one step)
         wt = B.alloc_w_transposed(d, V, dev)
@@ -443,7 +448,7 @@ def main():
             B.trloo_advantage(rewards, valid, 1.0, want_returns=False, want_group_n=False)
             return B.pg_loss_fwd_bwd(H, W, y, loss_mask, cu, adv_flat, seg_sample, old_logp, rollout1, prm1c, ws, dW=dW, out=outbuf)
         loss_entry("geometric_rejection_wt_cached", "as geometric_rejection, with pg_params.w_transposed filled by an earlier "
-                   "call on the same W (a microbatch after the first of an optimizer step)", step_mode1_cached, 4.0)
+                   "call on the same W (a microbatch after the first of an optimizer step)", step_mode1_cached, 3.0)
         del wt
 
         # loss + backward from the recompute stage's softmax states (the forward contraction is not repeated)
@@ -476,9 +481,9 @@ def main():
             B.pg_rmsnorm_bwd(H, gamma, o["dH"], 1e-6, out=dXn)
             return o
         loss_entry("with_rmsnorm_fused", f"configs[{args.config}] with the RMS normalisation of the hidden states in front of the head: "
-                   "trloo_advantage + pg_loss_fwd_bwd_normed (normalisation and its backward inside the call)", step_fused, 4.0)
+                   "trloo_advantage + pg_loss_fwd_bwd_normed (normalisation and its backward inside the call)", step_fused, 3.0)
         loss_entry("with_rmsnorm_separate_calls", "the same as trloo_advantage + pg_rmsnorm_fwd + pg_loss_fwd_bwd + pg_rmsnorm_bwd",
-                   step_separate, 4.0)
+                   step_separate, 3.0)
         del ws_n, Hn, dXn, gamma
 
     cpu = cpu_baseline(spec, args.cpu_rows) if args.cpu_rows > 0 and args.workload == "pg" else None
@@ -508,8 +513,8 @@ def main():
                             }[args.workload],
                    **({"vocab_shards": args.vocab_shards, "V_shard": V, "V": V_full} if args.workload == "shard" else {})},
         "packed_rows_per_s": T * args.steps / dt,          # value counts active (loss, not rejected) rows only
-        "pct_mfma_peak_executed_8dV": 100.0 * executed / PEAK_BF16_TFLOPS,      # of 6dV for --workload bwd
-        "executed_contractions_per_token": n_contractions,
+        "pct_mfma_peak_executed": 100.0 * executed / PEAK_BF16_TFLOPS,
+        "executed_contractions_per_token": n_contractions,      # of 2dV flops each: 8dV for --workload shard, else 6dV
         "pct_mfma_peak_useful_6dV": 100.0 * useful / PEAK_BF16_TFLOPS,
         "loss": loss, "counters": {n: int(c) for n, c in zip(B.COUNTER_NAMES, counters)},
         "kernels": kern, "roofline": roofline, "cpu_baseline": cpu, "aux_stages_us": aux,      # per call; the *_GBps entries are algorithmic bytes / time

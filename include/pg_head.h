@@ -118,7 +118,8 @@ typedef struct pg_params {
   void* w_transposed;    /* optional, loss calls only: DEVICE buffer of pg_w_transposed_bytes(d, V) bytes that
                             caches the transposed head weight the dH contraction reads (for fp32 heads its bf16
                             values; their remainders are rebuilt in the workspace on every call).  NULL: the
-                            transpose is rebuilt in the workspace on every call */
+                            transpose is rebuilt in the workspace on every call, or, with few
+                            active rows, W is read as it lies */
   int32_t w_transposed_valid; /* 0: this call fills w_transposed from W; 1: it already holds the transpose of
                             this very W (filled by an earlier call, W unchanged since: e.g. the further
                             microbatches of one optimizer step) and the call skips the transposition */
@@ -141,7 +142,8 @@ int32_t pg_init(void);
  * The workspace need not be initialised and holds nothing the caller may rely on.
  * For the loss calls its last part (at most 9.75 GiB) keeps fp32 logits between the forward and the backward
  * contractions.  A loss call also takes a workspace that is shorter by any part of it: it then
- * recomputes the logits that it cannot keep, with the same results, and refuses
+ * recomputes the logits that it cannot keep, with the same results up to the order of fp32 sums
+ * in dH and dW, and refuses
  * (PG_ERR_WORKSPACE_TOO_SMALL) only what is shorter than the rest.
  */
 size_t pg_workspace_bytes(int64_t T, int64_t d, int64_t V, int32_t S, const pg_params* h_params,

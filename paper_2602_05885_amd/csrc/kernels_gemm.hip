@@ -1,4 +1,5 @@
-// The three MFMA kernels of the policy-gradient head (see gemm_core.h for the tile engine).
+// The MFMA kernels of the policy-gradient head (see gemm_core.h for the tile engine), and the kernel that forms dS
+// from kept logits.
 //
 // Accumulator layout they all rely on: acc[i][j][r] of lane l is
 //   engine row     wm*64  + i*16 + 4*(l>>4) + r      (i < 4, r < 4)
@@ -32,9 +33,9 @@ __device__ __forceinline__ void merge_state(float& m, float& s, float& u, float 
 constexpr float NEG_BIG = -0x1p100f;
 
 // ------------------------------------------------------------------------------------
-// Forward: a tile is 256 vocab rows x 256 compacted tokens.  The logits live only in the
-// accumulators; what leaves the kernel is one (m, s, u) triple per token and vocab tile, plus the
-// scaled logit of the sampled token.
+// Forward: a tile is 256 vocab rows x 256 compacted tokens.  What leaves the kernel is one (m, s, u) triple
+// per token and vocab tile, plus the scaled logit of the sampled token, and for the loss calls the
+// accumulators of the tiles that are kept for the backward (Kept in kernels.h).
 // Persistent: one workgroup per compute unit takes tiles from the XCD-aware queue (gemm_core.h)
 // until none is left.  The operand loads of the next tile run ahead through the tile boundary
 // (mainloop_stream), so the statistics epilogue of a tile executes while the first two stages of
@@ -211,7 +212,7 @@ __device__ __forceinline__ void lmhead_fwd_body(FwdArgs a, bool steal, unsigned 
 __global__ __launch_bounds__(NTHREADS) void lmhead_fwd_kernel(FwdArgs a) { lmhead_fwd_body<false>(a, true, nullptr); }
 
 // ------------------------------------------------------------------------------------
-// Backward recompute: the same contraction, finished with
+// Backward recompute (of logits that were not kept): the same contraction, finished with
 //   dS[t,v] = c_t * (onehot(y_t)[v] - 2^(t2 - lse2_t)),  c_t = coef_t / tau,
 // rounded to bf16 and written for one vocab chunk in both orientations
 // (dS [t_cap, ld_s] for dH, dS^T [vc, ld_t] for dW).  Both go through an LDS transposition
