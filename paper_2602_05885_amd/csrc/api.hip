@@ -809,6 +809,16 @@ int32_t loss_fwd_bwd(int sft, const void* H, const void* W, const int32_t* y, co
   const pg::Ctl* ctl = at<pg::Ctl>(ws, pl.ctl);
   const int d_i = (int)pl.d;
   const int kc0 = (int)(((pl.V < pl.vc ? pl.V : pl.vc) + 255) / 256 * 256);      // contraction length of the first chunk
+  const bool direct = pl.direct_fits && !p.w_transposed, transposed = !direct || pl.t_cap > pg::DIRECT_MAX_ROWS;
+  pg::Rechunk few{};
+  few.enabled = pl.nchunks > 1; few.tiles_v_all = pl.tiles_v; few.ld_s_all = (int)pg::pad_ld((int64_t)pl.tiles_v * 256);
+  few.cap_s = (long long)pl.rows_b * pl.ld_v; few.cap_t = (long long)pl.vc * pl.ld_t;
+  few.V = (int)pl.V; few.dw_whole = !pl.dw_cap;
+  // (W as it lies, within RowsLoader's range, or a cached W^T span the vocabulary; the same for both, so that the cache
+  // does not change the order of the sums.  An fp32 head's remainders of W^T are held for one chunk.)
+  few.dh_whole = !pl.is_f32 && pl.direct_fits && (uint64_t)pl.V * pl.kd * 2 < FOUR_GIB;
+  if (p.w_transposed && !p.w_transposed_valid)       // the caller's cache is filled whole, before anything reads it
+    pg::launch_transpose_w(W, pl.is_f32, pl.V, d_i, d_i, 0, pl.tiles_v * 256, (int)wt_cache_ld(pl.V), static_cast<__bf16*>(p.w_transposed), pg::DirectRule{}, st);
   const int tiles_b = pl.cap_t ? pl.cap_t : pl.tiles_t;
   for (int b = 0; b < pl.nblocks; ++b) {      // token blocks; the backward of a block one vocab chunk at a time
     const pg::TokenBlocks blk{pl.cap_t, b};
@@ -821,7 +831,7 @@ int32_t loss_fwd_bwd(int sft, const void* H, const void* W, const int32_t* y, co
       const int tiles_c = (rows_valid + 255) / 256;
       const int kc = tiles_c * 256;
 
-      // W^T of this chunk: in the workspace, or a column range of the caller's cache (filled here unless valid)
+      // W^T of this chunk: in the workspace, or a column range of the caller's cache
       __bf16* wt = at<__bf16>(ws, pl.WT) + (pl.cap_t ? v0 : 0);
       int ld_wt = pl.ld_wt;
       if (p.w_transposed) {
@@ -829,10 +839,9 @@ int32_t loss_fwd_bwd(int sft, const void* H, const void* W, const int32_t* y, co
         ld_wt = (int)wt_cache_ld(pl.V);
       }
       // ... unless the dH launch reads W as it lies: for certain (every row count fits), or decided on the device
-      const bool direct = pl.direct_fits && !p.w_transposed, transposed = !direct || pl.t_cap > pg::DIRECT_MAX_ROWS;
       const pg::DirectRule rule{direct && transposed ? ctl : nullptr};
       if (transposed && b == 0) {
-        if (!p.w_transposed || !p.w_transposed_valid) pg::launch_transpose_w(W, pl.is_f32, pl.V, d_i, d_i, v0, kc, ld_wt, wt, rule, st);
+        if (!p.w_transposed) pg::launch_transpose_w(W, pl.is_f32, pl.V, d_i, d_i, v0, kc, ld_wt, wt, rule, st);
         if (pl.is_f32)   // the remainders W - bf16(W) are columns [d, 2d) of the split operand
           pg::launch_transpose_w(at<__bf16>(ws, pl.Wc) + d_i, 0, pl.V, d_i, pl.kd, v0, kc, pl.ld_v, at<__bf16>(ws, pl.WT_lo), rule, st);
       }
@@ -846,10 +855,8 @@ int32_t loss_fwd_bwd(int sft, const void* H, const void* W, const int32_t* y, co
       g.yc = at<int>(ws, pl.yc); g.lse2 = at<float>(ws, pl.lse2); g.coefc = at<float>(ws, pl.coefc);
       g.dS = at<__bf16>(ws, pl.dS); g.dST = at<__bf16>(ws, pl.dST); g.ctl = ctl;
       if (pl.is_f32) { g.dS_lo = at<__bf16>(ws, pl.dS_lo); g.dST_lo = at<__bf16>(ws, pl.dST_lo); }
-      pg::Rechunk rc{};
-      rc.enabled = pl.nchunks > 1; rc.chunk = c; rc.tiles_v_all = pl.tiles_v; rc.ld_s_all = (int)pg::pad_ld((int64_t)pl.tiles_v * 256);
-      rc.cap_s = (long long)pl.rows_b * pl.ld_v; rc.cap_t = (long long)pl.vc * pl.ld_t;
-      g.rc = rc; g.kept = kept; g.blk = blk; g.tiles_v_all = pl.tiles_v;
+      few.chunk = c;
+      g.rc = few; g.kept = kept; g.blk = blk; g.tiles_v_all = pl.tiles_v;
       unsigned* const queues = block_queue + pg::QUEUE_SET_WORDS * (1 + 4 * c);
       g.queue = queues; g.queue_lo = queues + 3 * pg::QUEUE_SET_WORDS;
       { ProfScope ps(PG_KERNEL_DLOGITS, st); pg::launch_lmhead_dlogits(g, st); }
@@ -863,7 +870,7 @@ int32_t loss_fwd_bwd(int sft, const void* H, const void* W, const int32_t* y, co
       w.C = static_cast<char*>(dW) + (size_t)v0 * pl.d * dw_elem; w.ldc = d_i;
       w.accumulate = p.accumulate_dW; w.out_bf16 = p.dW_dtype; w.k_from_ctl = 1; w.m_from_ctl = 0; w.ctl = ctl;
       w.queue = queues + pg::QUEUE_SET_WORDS;
-      w.rc = rc; w.rc_role = 1; w.v0 = v0; w.blk = blk;
+      w.rc = few; w.rc_role = 1; w.v0 = v0; w.blk = blk;
       if (pl.dw_cap) {
         pg::DwFoldArgs f{};
         f.slabs = at<float>(ws, pl.dWslabs); f.dW = w.C; f.n = (long long)rows_valid * d_i; f.slab = (long long)pl.vc * d_i;
@@ -887,7 +894,7 @@ int32_t loss_fwd_bwd(int sft, const void* H, const void* W, const int32_t* y, co
       h.accumulate = c > 0; h.out_bf16 = 0; h.k_from_ctl = 0; h.m_from_ctl = 1; h.split_k = 1; h.ctl = ctl;
       h.acc_rows = pl.acc_rows; h.split_stages = kc0 / 64;
       h.queue = queues + 2 * pg::QUEUE_SET_WORDS;
-      h.rc = rc; h.rc_role = 2; h.v0 = v0;
+      h.rc = few; h.rc_role = 2; h.v0 = v0;
       h.rule = rule; h.blk = blk;
       {
         ProfScope ps(PG_KERNEL_DH, st);
@@ -905,7 +912,7 @@ int32_t loss_fwd_bwd(int sft, const void* H, const void* W, const int32_t* y, co
   pg::FinishArgs fin{at<float>(ws, pl.lossterm), at<unsigned long long>(ws, pl.counters), loss_out,
                      reinterpret_cast<long long*>(counters_out), at<pg::Ctl>(ws, pl.ctl)};
   pg::ScatterArgs sc{at<float>(ws, pl.dHacc), at<int>(ws, pl.pos), dH, (int)pl.T, d_i, pl.is_f32 || shard.dH_f32,
-                     1, pl.acc_rows, (d_i + 255) / 256, kc0 / 64, pl.is_f32, pl.cap_t, ctl};
+                     1, pl.acc_rows, (d_i + 255) / 256, kc0 / 64, pl.is_f32, pl.cap_t, few, ctl};
   if (norm) pg::launch_scatter_dx_norm(sc, nf, fin, st);
   else pg::launch_scatter_dh(sc, fin, st);
   return guard.check(shard.what ? shard.what : sft ? "pg_sft_fwd_bwd" : norm ? "pg_loss_fwd_bwd_normed" : "pg_loss_fwd_bwd");

@@ -620,7 +620,16 @@ __global__ __launch_bounds__(NTHREADS) void gemm_store_kernel(StoreArgs a) {
   if (a.rule.ctl && (ctl.n_pad <= DIRECT_MAX_ROWS) != DIRECT) return;
   int ld_t_all;
   if (a.rc_role && rechunk_all(a.rc, ctl.n_pad, ld_t_all)) {   // few active rows, see Rechunk
-    if (a.rc_role == 1) {          // dW: this chunk's rows of the dS^T that spans the whole vocabulary
+    if (a.rc_role == 1 && a.rc.dw_whole) {                     // dW: the first chunk's launch does it all
+      if (a.rc.chunk > 0) return;
+      a.M = a.rc.V; a.tiles_m = a.rc.tiles_v_all; a.a_rows = a.rc.tiles_v_all * BM;
+      a.lda = ld_t_all;
+    } else if (a.rc_role == 2 && dh_runs_whole(a.rc, ctl.n_pad)) {      // dH: likewise
+      if (a.rc.chunk > 0) return;
+      a.K = a.rc.tiles_v_all * BM; a.split_stages = a.K / BK;
+      if (DIRECT) a.b_rows = a.rc.V;
+      a.lda = a.rc.ld_s_all;
+    } else if (a.rc_role == 1) {   // dW: this chunk's rows of the dS^T that spans the whole vocabulary
       a.A = static_cast<const char*>(a.A) + (size_t)a.v0 * ld_t_all * 2;
       if (a.A_lo) a.A_lo = static_cast<const char*>(a.A_lo) + (size_t)a.v0 * ld_t_all * 2;
       a.lda = ld_t_all;
@@ -693,7 +702,8 @@ void launch_lmhead_dlogits(const DlogitsArgs& a, hipStream_t s) {
 }
 void launch_gemm_store(const StoreArgs& a, hipStream_t s) {
   // (a split dH has at most acc_rows / 256 row tiles over all parts, a split dW dw_cap parts of every product)
-  const dim3 grid(persistent_grid(a.split_k ? max(a.tiles_m, a.acc_rows / BM) : a.tiles_m * max(1, a.dw_cap) * (a.dw_cap && a.A_lo ? 3 : 1), a.tiles_n));
+  const int tiles_m = a.rc_role == 1 && a.rc.enabled && a.rc.dw_whole ? a.rc.tiles_v_all : a.tiles_m;
+  const dim3 grid(persistent_grid(a.split_k ? max(a.tiles_m, a.acc_rows / BM) : tiles_m * max(1, a.dw_cap) * (a.dw_cap && a.A_lo ? 3 : 1), a.tiles_n));
   if (a.b_k_rows) hipLaunchKernelGGL(gemm_store_kernel<true>, grid, dim3(NTHREADS), PERSISTENT_LDS_BYTES, s, a);
   else hipLaunchKernelGGL(gemm_store_kernel<false>, grid, dim3(NTHREADS), PERSISTENT_LDS_BYTES, s, a);
 }
