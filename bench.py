@@ -46,8 +46,8 @@ def measured_mfma_only_tflops():
 # summarised in profiles/gemm_store_kernel_hbm_traffic.md (mean over a step's 30 launches, of which 20 have work, each
 # counter scaled by what it reads for a plain 1 GiB copy).  Valid only for the kernel sources the
 # counters were taken with: the digest below is of csrc/gemm_core.h + csrc/kernels_gemm.hip.
-TRAFFIC_GEMM_STORE = {"read_bytes": 2572410.5 * 1024 * 2.000, "write_bytes": 312837.0 * 1024 * 1.000,
-                      "sources_sha256": "be584d520d0ebfe32b70fc8d159178e37b4a8d96c9f85aea8bcb8246bb9e9e1f"}
+TRAFFIC_GEMM_STORE = {"read_bytes": 2573838.5 * 1024 * 2.000, "write_bytes": 312809.6 * 1024 * 1.000,
+                      "sources_sha256": "e190a2ce2550cf07cce5be57490527e1855fff2e8c65c7782eabff06ad5a4f43"}
 
 
 def kernel_sources_digest() -> str:
