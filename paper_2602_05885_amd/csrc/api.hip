@@ -158,10 +158,12 @@ int32_t make_plan(int64_t T, int64_t d, int64_t V, int32_t S, const pg_params* p
     // Token blocks: more logits than fit, blocks that are not too small, and a dW that can be added to without a
     // rounding in between (fp32; an fp32 head's split operands keep to one block).
     const int64_t td = (d + 255) / 256;
-    if (blocks && !pl.is_f32 && p->dW_dtype == 0 && kd >= pg::BLOCK_MIN_K && kept_all > kept_fit && kept_fit / tiles_v >= pg::BLOCK_MIN_TILES) {
-      pl.cap_t = (int)(kept_fit / tiles_v);
-      if (pl.cap_t * td >= 256) pl.cap_t = (int)(pl.cap_t * td / 256 * 256 / td);      // whole rounds of the dH launch
-      pl.nblocks = (pl.tiles_t + pl.cap_t - 1) / pl.cap_t;
+    if (blocks && !pl.is_f32 && p->dW_dtype == 0 && kd >= pg::BLOCK_MIN_K && kept_all > kept_fit) {
+      const int64_t rounds = kept_fit / tiles_v * td / 256, cap = rounds * 256 / td;
+      if (rounds >= pg::BLOCK_MIN_ROUNDS && cap >= pg::BLOCK_MIN_TILES) {
+        pl.cap_t = (int)cap;
+        pl.nblocks = (pl.tiles_t + pl.cap_t - 1) / pl.cap_t;
+      }
     }
     const int64_t rows_b = pl.cap_t ? (int64_t)pl.cap_t * 256 : t_cap;
     pl.rows_b = (int)rows_b;

@@ -81,11 +81,11 @@ __device__ inline bool dh_runs_whole(const Rechunk& r, int n_pad) {
 // number of rows over the whole vocabulary do, the rows are worked off in blocks of at most cap_t token tiles: forward,
 // row epilogue, dS, dW (added to the block before) and dH of a block, then the next one, so that nothing is ever
 // recomputed.  The active rows are known only on the device: the host launches as many blocks as its rows may need
-// and the launches of a block without any return at once.  cap_t is a whole number of rounds of the dH launch
-// (cap_t ceil(d / 256) tiles over 256 compute units), so that cutting the rows adds no half-empty round: dealt evenly, 133 tiles
-// at d = 2048 took 2 x 3 rounds instead of 5, and the call 41.6 ms against 41.0 ms in one block.
-// At d = 5120, V = 151936, 32768 rows, two blocks of 64 tiles took the call from 128.1 to 116.0 ms: the recompute of half of the
-// logits (16 ms) went, the second pass over dW cost 0.4 ms.
+// and the launches of a block without any return at once.  cap_t is the largest number of tiles that fits and whose
+// dH launch (cap_t ceil(d / 256) tiles over 256 compute units) does not reach into another round, so that cutting the
+// rows adds few half-empty rounds: dealt evenly, 133 tiles at d = 2048 took 2 x 3 rounds instead of 5, and the call
+// 41.6 ms against 41.0 ms in one block.  At d = 5120, V = 151936, 32768 rows, two blocks of 64 tiles took the call from
+// 128.1 to 116.0 ms: the recompute of half of the logits (16 ms) went, the second pass over dW cost 0.4 ms.
 struct TokenBlocks {
   int cap_t;            // token tiles per block at most; 0: one block holds every row
   int b;                // this launch's block
@@ -94,9 +94,16 @@ struct TokenBlocks {
 // head): K = 512 1990 us kept against 1811 us recomputed, 768 2440 / 2390, 1024 2866 / 2990, 2048 4620 / 5370 (4000 rows,
 // V = 103936); and always where no workgroup has more than one tile to recompute (latency).  Token blocks pass over
 // dW and W once more per block: 33912 rows, K = 1024 27.3 ms in blocks against 24.9 ms in one, 1536 31.3 / 33.1,
-// 3072 55.8 / 58.5.
+// 3072 55.8 / 58.5.  And the dH contraction of a block runs over the whole vocabulary however few tiles the block has
+// (the rows that remain in the last block above all), so a full block has to fill the chip well, two rounds at least.
+// In blocks against in one, one tile more than whole blocks and every row active:
+//   one round:  K = 1536, V = 512000  37.8 / 23.0 and 63.7 / 45.3 ms;  V = 256000  28.6 / 22.5 and 50.2 / 45.7;
+//               V = 151936  31.6 / 29.1 and 58.9 / 61.8;  K = 5120, V = 512000  55.4 / 42.9 and 94.8 / 82.0
+//   two rounds: K = 1536, V = 100000  21.3 / 20.1 and 43.1 / 45.2;  K = 2048, V = 151936  30.0 / 28.7 and 69.5 / 77.4;
+//               K = 8192, V = 512000  96.6 / 83.3 and 303 / 353
 constexpr int KEEP_MIN_K = 1024, KEEP_ANY_TILES = 256;
 constexpr int BLOCK_MIN_K = 1536;
+constexpr int BLOCK_MIN_ROUNDS = 2;     // rounds of a block's dH launch
 constexpr int BLOCK_MIN_TILES = 16;     // smaller blocks would make the passes over dW and W dearer than a recompute
 // Token tiles [t0, t0 + nt) of block k.b when `live` tiles are live.
 __host__ __device__ inline void token_block(const TokenBlocks& k, int live, int& t0, int& nt) {

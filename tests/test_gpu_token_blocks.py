@@ -9,7 +9,9 @@ from paper_2602_05885_amd import synth
 from tests._cases import block_rel_fro, np64
 
 pytestmark = pytest.mark.gpu
-T, V, BLOCK = 9000, 515, 4096          # three vocab tiles; 48 kept tiles: blocks of 16 token tiles, three of them
+# three vocab tiles; 48 kept tiles: blocks of 16 token tiles, three of them; d: 512 dH tiles per block, the two rounds over
+# 256 compute units from which a call is planned in blocks
+T, V, BLOCK, D = 9000, 515, 4096, 8192
 
 
 @pytest.fixture()
@@ -26,7 +28,7 @@ def _mask(active, dev):
 @pytest.mark.parametrize("active", [0, 1, BLOCK, BLOCK + 1, 2 * BLOCK, 2 * BLOCK + 1, T])
 @pytest.mark.parametrize("accumulate,cache", [(0, False), (1, True)])
 def test_sft_in_token_blocks(budget, active, accumulate, cache):
-    dev, d = torch.device("cuda:0"), 1536
+    dev, d = torch.device("cuda:0"), D
     H, W, y = synth.make_head(T, d, V, "bf16", 11, dev)
     mask = _mask(active, dev)
     prm = B.Params(accumulate_dW=accumulate, w_transposed=B.alloc_w_transposed(d, V, dev) if cache else None)
@@ -48,7 +50,7 @@ def test_sft_in_token_blocks(budget, active, accumulate, cache):
 def test_normed_loss_in_token_blocks_repeats_and_replays(budget):
     """Fused normalisation, off-policy surrogate with weights, three live blocks: against the one-block plan (fp32 sums in
     another order), bit for bit on a second call with a scrambled workspace and on replays of a captured graph."""
-    dev, d, S = torch.device("cuda:0"), 1600, 3
+    dev, d, S = torch.device("cuda:0"), D, 3
     H, W, y = synth.make_head(T, d, V, "bf16", 12, dev)
     g = torch.Generator(device=dev).manual_seed(1)
     gamma = (1 + 0.1 * torch.randn(d, generator=g, device=dev)).to(torch.bfloat16)
