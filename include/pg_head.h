@@ -141,13 +141,19 @@ int32_t pg_init(void);
  * PG_CALL_LOGPROB_FWD).  Returns 0 if the arguments are invalid or unsupported.
  * The workspace need not be initialised and holds nothing the caller may rely on.
  * For the loss calls its last part (at most 9.75 GiB) keeps fp32 logits between the forward and the backward
- * contractions.  A loss call also takes a workspace that is shorter by any part of it: it then
+ * contractions.  A loss call also takes a shorter workspace, down to pg_workspace_min_bytes(): it then
  * recomputes the logits that it cannot keep, with the same results up to the order of fp32 sums
- * in dH and dW, and refuses
- * (PG_ERR_WORKSPACE_TOO_SMALL) only what is shorter than the rest.
+ * in dH and dW, and refuses (PG_ERR_WORKSPACE_TOO_SMALL) only what is shorter than that.
+ * Neither size grows steadily with T (the scratch is cut in whole tiles and rounds, and calls of many rows keep
+ * the logits of a part of them at a time): a workspace that serves calls of several sizes should have the largest
+ * of their sizes, and must have the largest of their least ones.
  */
 size_t pg_workspace_bytes(int64_t T, int64_t d, int64_t V, int32_t S, const pg_params* h_params,
                           int32_t which_call);
+
+/* The least bytes of device workspace that the call takes; 0 as pg_workspace_bytes(). */
+size_t pg_workspace_min_bytes(int64_t T, int64_t d, int64_t V, int32_t S, const pg_params* h_params,
+                              int32_t which_call);
 
 /* Bytes of the optional W^T cache (pg_params.w_transposed) for a [V, d] head; 0 if unsupported. */
 size_t pg_w_transposed_bytes(int64_t d, int64_t V);

@@ -22,7 +22,7 @@ CALL_LOSS_FWD_BWD = 1
 CALL_LOSS_FWD_BWD_NORMED = 2
 COUNTER_NAMES = ("active", "clip_hi", "clip_lo", "seg_geo", "seg_veto", "truncated", "loss_tokens", "seg_dropped")
 
-EXPORTS = ("pg_last_error", "pg_init", "pg_workspace_bytes", "pg_backward_chunk_rows", "pg_w_transposed_bytes", "trloo_advantage", "pg_logprob_fwd", "pg_loss_fwd_bwd", "pg_loss_fwd_bwd_normed",
+EXPORTS = ("pg_last_error", "pg_init", "pg_workspace_bytes", "pg_workspace_min_bytes", "pg_backward_chunk_rows", "pg_w_transposed_bytes", "trloo_advantage", "pg_logprob_fwd", "pg_loss_fwd_bwd", "pg_loss_fwd_bwd_normed",
            "pg_sft_fwd_bwd", "pg_head_shard_fwd", "pg_head_partials_merge", "pg_head_partials_finish", "pg_loss_shard_bwd", "grpo_advantage",
            "turn_reward", "prs_retain", "pg_monitors_workspace_bytes", "pg_monitors", "pg_monitors_static", "pg_rmsnorm_fwd", "pg_rmsnorm_bwd_workspace_bytes", "pg_rmsnorm_bwd",
            "pg_profile_enable", "pg_profile_read")
@@ -85,6 +85,8 @@ def lib() -> C.CDLL:
         L.pg_last_error.argtypes = []
         L.pg_workspace_bytes.restype = C.c_size_t
         L.pg_workspace_bytes.argtypes = [C.c_int64, C.c_int64, C.c_int64, C.c_int32, C.POINTER(PgParams), C.c_int32]
+        L.pg_workspace_min_bytes.restype = C.c_size_t
+        L.pg_workspace_min_bytes.argtypes = L.pg_workspace_bytes.argtypes
         L.pg_w_transposed_bytes.restype = C.c_size_t
         L.pg_w_transposed_bytes.argtypes = [C.c_int64, C.c_int64]
         L.pg_backward_chunk_rows.restype = C.c_int64
@@ -288,6 +290,12 @@ def pg_profile_read():
 def pg_workspace_bytes(T: int, d: int, V: int, S: int, params: Params, which_call: int) -> int:
     p = params.c_struct()
     return int(lib().pg_workspace_bytes(T, d, V, S, C.byref(p), which_call))
+
+
+def pg_workspace_min_bytes(T: int, d: int, V: int, S: int, params: Params, which_call: int) -> int:
+    """The shortest workspace that the call takes (the loss calls then recompute the logits they cannot keep)."""
+    p = params.c_struct()
+    return int(lib().pg_workspace_min_bytes(T, d, V, S, C.byref(p), which_call))
 
 
 def pg_backward_chunk_rows(T: int, d: int, V: int, S: int, params: Params) -> int:

@@ -103,8 +103,11 @@ int32_t check_params(const pg_params* p) {
   return PG_OK;
 }
 
-// blocks: plan a loss call in token blocks if it is one that pays (see TokenBlocks); pl.cap_t says whether it did.
-int32_t make_plan(int64_t T, int64_t d, int64_t V, int32_t S, const pg_params* p, int which, Plan& pl, bool blocks = false) {
+// How a loss call may be planned: in token blocks if it is one that pays (see TokenBlocks; pl.cap_t says whether it did),
+// in one block, or in one block with half of the dS scratch (what a block plan has).
+enum Form { BLOCKS, ONE_BLOCK, ONE_BLOCK_HALF };
+
+int32_t make_plan(int64_t T, int64_t d, int64_t V, int32_t S, const pg_params* p, int which, Plan& pl, Form form = ONE_BLOCK) {
   pl = Plan{};
   int32_t rc = check_params(p);
   if (rc) return rc;
@@ -158,7 +161,7 @@ int32_t make_plan(int64_t T, int64_t d, int64_t V, int32_t S, const pg_params* p
     // Token blocks: more logits than fit, blocks that are not too small, and a dW that can be added to without a
     // rounding in between (fp32; an fp32 head's split operands keep to one block).
     const int64_t td = (d + 255) / 256;
-    if (blocks && !pl.is_f32 && p->dW_dtype == 0 && kd >= pg::BLOCK_MIN_K && kept_all > kept_fit) {
+    if (form == BLOCKS && !pl.is_f32 && p->dW_dtype == 0 && kd >= pg::BLOCK_MIN_K && kept_all > kept_fit) {
       const int64_t rounds = kept_fit / tiles_v * td / 256, cap = rounds * 256 / td;
       if (rounds >= pg::BLOCK_MIN_ROUNDS && cap >= pg::BLOCK_MIN_TILES) {
         pl.cap_t = (int)cap;
@@ -168,7 +171,7 @@ int32_t make_plan(int64_t T, int64_t d, int64_t V, int32_t S, const pg_params* p
     const int64_t rows_b = pl.cap_t ? (int64_t)pl.cap_t * 256 : t_cap;
     pl.rows_b = (int)rows_b;
     // (a block has fewer rows and gets half the scratch for them; W^T is then held in full, for all blocks)
-    const uint64_t budget = pl.cap_t ? ds_budget() / 2 : ds_budget();
+    const uint64_t budget = pl.cap_t || form == ONE_BLOCK_HALF ? ds_budget() / 2 : ds_budget();
     int64_t max_tiles = t_cap > 0 ? (int64_t)(budget / ((uint64_t)rows_b * 2 * 256)) : tiles_v;
     if (max_tiles < 1) max_tiles = 1;
     if (max_tiles > tiles_v) max_tiles = tiles_v;
@@ -225,6 +228,17 @@ int32_t make_plan(int64_t T, int64_t d, int64_t V, int32_t S, const pg_params* p
   }
   pl.total = pl.kept + (size_t)pl.kept_cap * pg::KEPT_TILE_FLOATS * sizeof(float);
   return PG_OK;
+}
+
+// The plan of a call on a workspace of `room` bytes.  Token blocks keep all their logits: a workspace that has no room for
+// that gets the one-block plan, and one that is too short for that too gets it with half of the dS scratch: about what the
+// block plan has beside its kept logits (its W^T is the whole one; 0.3 to 1.16 times over d <= 8192).  Whether the room suffices is the caller's check (pl.required).
+int32_t make_plan_for(size_t room, int64_t T, int64_t d, int64_t V, int32_t S, const pg_params* p, int which, Plan& pl) {
+  int32_t rc = make_plan(T, d, V, S, p, which, pl, BLOCKS);
+  if (rc || !pl.cap_t || room >= pl.total) return rc;
+  rc = make_plan(T, d, V, S, p, which, pl, ONE_BLOCK);
+  if (rc || room >= pl.required) return rc;
+  return make_plan(T, d, V, S, p, which, pl, ONE_BLOCK_HALF);
 }
 
 bool misaligned(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) != 0; }
@@ -462,12 +476,17 @@ int32_t pg_profile_read(double* h_ms, int64_t* h_launches) {
 
 size_t pg_workspace_bytes(int64_t T, int64_t d, int64_t V, int32_t S, const pg_params* h_params, int32_t which_call) {
   Plan pl;
-  if (make_plan(T, d, V, S, h_params, which_call, pl, true) != PG_OK) return 0;
+  if (make_plan(T, d, V, S, h_params, which_call, pl, BLOCKS) != PG_OK) return 0;
   const size_t total = pl.total;
   if (!pl.cap_t) return total;
   // (a call that cannot work in blocks, as pg_loss_shard_bwd, uses the one-block plan on the same workspace)
-  if (make_plan(T, d, V, S, h_params, which_call, pl, false) != PG_OK) return 0;
+  if (make_plan(T, d, V, S, h_params, which_call, pl, ONE_BLOCK) != PG_OK) return 0;
   return std::max(total, pl.required);
+}
+
+size_t pg_workspace_min_bytes(int64_t T, int64_t d, int64_t V, int32_t S, const pg_params* h_params, int32_t which_call) {
+  Plan pl;
+  return make_plan_for(0, T, d, V, S, h_params, which_call, pl) == PG_OK ? pl.required : 0;
 }
 
 size_t pg_w_transposed_bytes(int64_t d, int64_t V) {
@@ -479,7 +498,7 @@ size_t pg_w_transposed_bytes(int64_t d, int64_t V) {
 
 int64_t pg_backward_chunk_rows(int64_t T, int64_t d, int64_t V, int32_t S, const pg_params* h_params) {
   Plan pl;
-  if (make_plan(T, d, V, S, h_params, PG_CALL_LOSS_FWD_BWD, pl, true) != PG_OK) return 0;
+  if (make_plan(T, d, V, S, h_params, PG_CALL_LOSS_FWD_BWD, pl, BLOCKS) != PG_OK) return 0;
   return pl.vc;
 }
 
@@ -742,10 +761,8 @@ int32_t loss_fwd_bwd(int sft, const void* H, const void* W, const int32_t* y, co
                      const Shard& shard, const NormIn* norm) {
   Plan pl;
   const int which = norm ? PG_CALL_LOSS_FWD_BWD_NORMED : PG_CALL_LOSS_FWD_BWD;
-  int32_t rc = make_plan(T, d, V, S, h_params, which, pl, !shard.partials);
+  int32_t rc = shard.partials ? make_plan(T, d, V, S, h_params, which, pl) : make_plan_for(workspace_bytes, T, d, V, S, h_params, which, pl);
   if (rc) return rc;
-  // (token blocks keep all their logits: a workspace that has no room for that gets the one-block plan)
-  if (pl.cap_t && workspace_bytes < pl.total && (rc = make_plan(T, d, V, S, h_params, which, pl))) return rc;
   const pg_params& p = *h_params;
   if (!W || !loss_out || !dW) return fail(PG_ERR_INVALID_ARG, "W, loss_out and dW must not be NULL");
   if (misaligned(W) || misaligned(dW)) return fail(PG_ERR_INVALID_ARG, "W and dW must be 16-byte aligned");

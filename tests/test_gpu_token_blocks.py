@@ -81,3 +81,26 @@ def test_normed_loss_in_token_blocks_repeats_and_replays(budget):
         torch.cuda.synchronize()
         for q in a:
             assert torch.equal(a[q], c[q]), q
+
+
+def test_shorter_workspaces_down_to_the_least(monkeypatch):
+    """Token blocks; one block with part of the logits; with none; with half of the dS scratch (one vocab tile per chunk
+    instead of two), at the least workspace the call takes."""
+    dev, d, V2 = torch.device("cuda:0"), D, 2600
+    monkeypatch.setenv("PG_HEAD_DS_BUDGET_BYTES", "9500000")      # 176 kept tiles, of 11 vocab tiles: again 16 token tiles
+    H, W, y = synth.make_head(T, d, V2, "bf16", 13, dev)
+    prm, mask = B.Params(), _mask(8800, dev)
+    full, least = (f(T, d, V2, 0, prm, B.CALL_LOSS_FWD_BWD) for f in (B.pg_workspace_bytes, B.pg_workspace_min_bytes))
+    row_tile = 9216 * 2 * 256 * 2                                 # a vocab tile of both orientations of dS
+    outs = []
+    for n in (full, full - 1, least + row_tile // 2, least):
+        outs.append(B.pg_sft_fwd_bwd(H, W, y, mask, prm, torch.full((n,), 0xFF, dtype=torch.uint8, device=dev)))
+    torch.cuda.synchronize()
+    for o in outs[1:]:
+        for q in ("loss", "logp", "entropy", "counters"):
+            assert torch.equal(o[q], outs[0][q]), q
+        for q in ("dH", "dW"):
+            e = ((o[q].double() - outs[0][q].double()).norm() / outs[0][q].double().norm()).item()
+            assert e <= (1e-3 if q == "dH" else 1e-5), (q, e)     # dH is rounded to bf16, dW is fp32 sums in another order
+    with pytest.raises(B.PgError, match="needed"):
+        B.pg_sft_fwd_bwd(H, W, y, mask, prm, torch.empty(least - 1, dtype=torch.uint8, device=dev))
