@@ -304,7 +304,7 @@ def main():
         merged = B.pg_head_shard_fwd(H, W, y, loss_mask, 0, prm, wsk)
         torch.cuda.synchronize()
         del wsk
-    ws = B.alloc_workspace(T, d, V, S, prm, B.CALL_LOSS_FWD_BWD, dev)
+    ws = B.alloc_workspace(T, d, V, S, prm, B.CALL_LOSS_SHARD_BWD if args.workload in ("shard", "bwd") else B.CALL_LOSS_FWD_BWD, dev)
     dW = torch.empty((V, d), dtype=torch.float32, device=dev)
     outbuf = (torch.empty(1, dtype=torch.float32, device=dev),
               torch.empty((T, d), dtype=torch.float32, device=dev) if args.workload in ("shard", "bwd") else torch.empty_like(H),

@@ -85,6 +85,7 @@ extern "C" {
 #define PG_CALL_LOGPROB_FWD 0
 #define PG_CALL_LOSS_FWD_BWD 1
 #define PG_CALL_LOSS_FWD_BWD_NORMED 2
+#define PG_CALL_LOSS_SHARD_BWD 3 /* workspace queries of pg_loss_shard_bwd, which keeps no logits */
 
 /* indices into counters_out[8] */
 #define PG_CNT_ACTIVE 0      /* loss tokens of kept samples */
@@ -140,13 +141,14 @@ int32_t pg_init(void);
  * Bytes of device workspace the given call needs for these sizes (S is ignored for
  * PG_CALL_LOGPROB_FWD).  Returns 0 if the arguments are invalid or unsupported.
  * The workspace need not be initialised and holds nothing the caller may rely on.
- * For the loss calls its last part (at most 9.75 GiB) keeps fp32 logits between the forward and the backward
- * contractions.  A loss call also takes a shorter workspace, down to pg_workspace_min_bytes(): it then
- * recomputes the logits that it cannot keep, with the same results up to the order of fp32 sums
- * in dH and dW, and refuses (PG_ERR_WORKSPACE_TOO_SMALL) only what is shorter than that.
- * Neither size grows steadily with T (the scratch is cut in whole tiles and rounds, and calls of many rows keep
- * the logits of a part of them at a time): a workspace that serves calls of several sizes should have the largest
- * of their sizes, and must have the largest of their least ones.
+ * For the loss calls that run the forward contraction its last part (at most 9.75 GiB) keeps fp32
+ * logits between the forward and the backward contractions.  Such a call also takes a shorter
+ * workspace, down to pg_workspace_min_bytes(): it then recomputes the logits that it cannot keep,
+ * with the same results up to the order of fp32 sums in dH and dW, and refuses
+ * (PG_ERR_WORKSPACE_TOO_SMALL) only what is shorter than that.
+ * Neither size grows steadily with T (the scratch is cut in whole tiles and rounds, and calls of
+ * many rows keep the logits of a part of them at a time): a workspace that serves calls of several
+ * sizes should have the largest of their sizes, and must have the largest of their least ones.
  */
 size_t pg_workspace_bytes(int64_t T, int64_t d, int64_t V, int32_t S, const pg_params* h_params,
                           int32_t which_call);
@@ -160,8 +162,9 @@ size_t pg_w_transposed_bytes(int64_t d, int64_t V);
 
 /*
  * Inspection hook (tests, tuning): the number of vocabulary rows per chunk of the backward pass of
- * pg_loss_fwd_bwd / pg_sft_fwd_bwd for these sizes (chunk c covers rows [c n, (c+1) n) of W and dW;
- * it follows from the scratch budget, PG_HEAD_DS_BUDGET_BYTES).  0 if the arguments are invalid.
+ * pg_loss_fwd_bwd / pg_sft_fwd_bwd on a workspace of pg_workspace_bytes() for these sizes (chunk c
+ * covers rows [c n, (c+1) n) of W and dW; it follows from the scratch budget,
+ * PG_HEAD_DS_BUDGET_BYTES).  0 if the arguments are invalid.
  */
 int64_t pg_backward_chunk_rows(int64_t T, int64_t d, int64_t V, int32_t S, const pg_params* h_params);
 
@@ -396,7 +399,8 @@ int32_t pg_loss_fwd_bwd_normed(const void* X, const void* gamma, float norm_eps,
  * With the whole head as the one shard (v_offset = 0, V_shard = V) this is pg_loss_fwd_bwd without its
  * forward contraction: a caller whose old-policy recompute (pg_head_shard_fwd + pg_head_partials_finish)
  * ran on the same H and W can hand its states over and save a quarter of the step's flops.
- * Workspace: pg_workspace_bytes(T, d, V_shard, S, params, PG_CALL_LOSS_FWD_BWD).
+ * Workspace: pg_workspace_bytes(T, d, V_shard, S, params, PG_CALL_LOSS_SHARD_BWD) (what PG_CALL_LOSS_FWD_BWD
+ * gives is enough too: it has room for logits that this call does not keep).
  * Errors as for pg_loss_fwd_bwd; partials and partials_out must be 16-byte aligned.
  */
 int32_t pg_head_shard_fwd(const void* H, const void* W_shard, const int32_t* y, const uint8_t* row_mask, int64_t T,

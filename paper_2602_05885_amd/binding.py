@@ -20,6 +20,7 @@ PG_OK = 0
 CALL_LOGPROB_FWD = 0
 CALL_LOSS_FWD_BWD = 1
 CALL_LOSS_FWD_BWD_NORMED = 2
+CALL_LOSS_SHARD_BWD = 3
 COUNTER_NAMES = ("active", "clip_hi", "clip_lo", "seg_geo", "seg_veto", "truncated", "loss_tokens", "seg_dropped")
 
 EXPORTS = ("pg_last_error", "pg_init", "pg_workspace_bytes", "pg_workspace_min_bytes", "pg_backward_chunk_rows", "pg_w_transposed_bytes", "trloo_advantage", "pg_logprob_fwd", "pg_loss_fwd_bwd", "pg_loss_fwd_bwd_normed",

@@ -111,7 +111,7 @@ int32_t make_plan(int64_t T, int64_t d, int64_t V, int32_t S, const pg_params* p
   pl = Plan{};
   int32_t rc = check_params(p);
   if (rc) return rc;
-  if (which != PG_CALL_LOGPROB_FWD && which != PG_CALL_LOSS_FWD_BWD && which != PG_CALL_LOSS_FWD_BWD_NORMED)
+  if (which != PG_CALL_LOGPROB_FWD && which != PG_CALL_LOSS_FWD_BWD && which != PG_CALL_LOSS_FWD_BWD_NORMED && which != PG_CALL_LOSS_SHARD_BWD)
     return fail(PG_ERR_INVALID_ARG, "unknown call id %d", which);
   if (T < 0 || d < 1 || V < 1 || S < 0) return fail(PG_ERR_INVALID_ARG, "negative or zero extent (T=%lld d=%lld V=%lld S=%d)", (long long)T, (long long)d, (long long)V, S);
   if (d % 64 != 0) return fail(PG_ERR_UNSUPPORTED_SHAPE, "d=%lld is not a multiple of 64", (long long)d);
@@ -155,7 +155,8 @@ int32_t make_plan(int64_t T, int64_t d, int64_t V, int32_t S, const pg_params* p
     pl.norm_partial = take((size_t)pg::NORM_STRIPS * d * 4);
   }
   const uint64_t kept_tile = (uint64_t)pg::KEPT_TILE_FLOATS * sizeof(float);
-  const bool keep = which != PG_CALL_LOGPROB_FWD && (kd * (pl.is_f32 ? 2 : 1) >= pg::KEEP_MIN_K || tiles_v * pl.tiles_t <= pg::KEEP_ANY_TILES);
+  // (a shard's backward starts from the rows' states: no forward contraction of the same call leaves logits behind)
+  const bool keep = which != PG_CALL_LOGPROB_FWD && which != PG_CALL_LOSS_SHARD_BWD && (kd * (pl.is_f32 ? 2 : 1) >= pg::KEEP_MIN_K || tiles_v * pl.tiles_t <= pg::KEEP_ANY_TILES);
   const int64_t kept_all = keep ? tiles_v * pl.tiles_t : 0, kept_fit = std::min<int64_t>((int64_t)(kept_budget() / kept_tile), INT32_MAX);
   if (which != PG_CALL_LOGPROB_FWD) {
     // Token blocks: more logits than fit, blocks that are not too small, and a dW that can be added to without a
@@ -479,7 +480,7 @@ size_t pg_workspace_bytes(int64_t T, int64_t d, int64_t V, int32_t S, const pg_p
   if (make_plan(T, d, V, S, h_params, which_call, pl, BLOCKS) != PG_OK) return 0;
   const size_t total = pl.total;
   if (!pl.cap_t) return total;
-  // (a call that cannot work in blocks, as pg_loss_shard_bwd, uses the one-block plan on the same workspace)
+  // (pg_loss_shard_bwd may be given this workspace too, and has the one-block plan)
   if (make_plan(T, d, V, S, h_params, which_call, pl, ONE_BLOCK) != PG_OK) return 0;
   return std::max(total, pl.required);
 }
@@ -760,8 +761,8 @@ int32_t loss_fwd_bwd(int sft, const void* H, const void* W, const int32_t* y, co
                      float* entropy_out, int64_t* counters_out, void* workspace, size_t workspace_bytes, void* stream,
                      const Shard& shard, const NormIn* norm) {
   Plan pl;
-  const int which = norm ? PG_CALL_LOSS_FWD_BWD_NORMED : PG_CALL_LOSS_FWD_BWD;
-  int32_t rc = shard.partials ? make_plan(T, d, V, S, h_params, which, pl) : make_plan_for(workspace_bytes, T, d, V, S, h_params, which, pl);
+  const int which = norm ? PG_CALL_LOSS_FWD_BWD_NORMED : shard.what ? PG_CALL_LOSS_SHARD_BWD : PG_CALL_LOSS_FWD_BWD;
+  int32_t rc = make_plan_for(workspace_bytes, T, d, V, S, h_params, which, pl);
   if (rc) return rc;
   const pg_params& p = *h_params;
   if (!W || !loss_out || !dW) return fail(PG_ERR_INVALID_ARG, "W, loss_out and dW must not be NULL");
@@ -793,11 +794,9 @@ int32_t loss_fwd_bwd(int sft, const void* H, const void* W, const int32_t* y, co
   if (workspace_bytes < pl.required) return fail(PG_ERR_WORKSPACE_TOO_SMALL, "workspace has %zu bytes, %zu needed", workspace_bytes, pl.required);
   if ((rc = ensure_init())) return rc;
   void* ws = workspace;
-  // A workspace of less than pg_workspace_bytes() keeps fewer logits (none: the backward recomputes them all, as it
-  // does when the rows' states come from elsewhere and no forward contraction runs).
+  // A workspace of less than pg_workspace_bytes() keeps fewer logits (none: the backward recomputes them all).
   pg::Kept kept{};
   kept.cap = (int)std::min<size_t>(pl.kept_cap, (workspace_bytes - pl.required) / (pg::KEPT_TILE_FLOATS * sizeof(float)));
-  if (shard.partials) kept.cap = 0;
   if (kept.cap > 0) kept.tiles = at<float>(ws, pl.kept);
   const LaunchGuard guard;
 

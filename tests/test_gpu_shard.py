@@ -186,6 +186,26 @@ def test_shard_backward_bf16_dH_accumulate_and_one_shard_equals_unsharded(dev):
     assert rel_fro(np64(b["dH"]), np64(a["dH"])) <= 1e-2        # bf16 outputs: one ulp flips
 
 
+@pytest.mark.parametrize("T,d,V", [(300, 64, 500), (700, 1088, 1300)])
+def test_shard_backward_in_its_own_workspace(dev, T, d, V):
+    """The size of PG_CALL_LOSS_SHARD_BWD has no room for kept logits: same bits as in the loss call's workspace."""
+    H, W, y = synth.make_head(T, d, V, "bf16", 72, dev, unit_rms=True)
+    prm = B.Params()
+    mask = torch.ones(T, dtype=torch.uint8, device=dev)
+    cu = torch.tensor([0, T], dtype=torch.int32, device=dev)
+    adv = torch.ones(1, dtype=torch.float64, device=dev)
+    outs = []
+    for which in (B.CALL_LOSS_FWD_BWD, B.CALL_LOSS_SHARD_BWD):
+        ws = torch.full((B.pg_workspace_bytes(T, d, V, 1, prm, which),), 0xFF, dtype=torch.uint8, device=dev)
+        part = B.pg_head_shard_fwd(H, W, y, mask, 0, prm, ws)
+        outs.append(B.pg_loss_shard_bwd(H, W, y, mask, cu, adv, None, None, None, part, 0, prm, ws))
+    torch.cuda.synchronize()
+    for q in outs[0]:
+        assert torch.equal(outs[0][q], outs[1][q]), q
+    with pytest.raises(B.PgError, match="needed"):
+        B.pg_loss_shard_bwd(H, W, y, mask, cu, adv, None, None, None, part, 0, prm, ws[:-256])
+
+
 def test_shard_empty_and_all_masked(dev):
     T, d, Vs = 300, 64, 500
     H, W, y = synth.make_head(T, d, Vs, "bf16", 71, dev, unit_rms=True)

@@ -25,7 +25,10 @@ def test_blocks_only_where_their_dh_fills_the_chip_twice(T, d, V, blocks):
 def _needed(T, d, V, which, nbytes, prm):
     """What a loss call says it needs when it is given `nbytes` (refused before any HIP call), None if it does not refuse."""
     lib, p, one = B.lib(), prm.c_struct(), C.c_void_p(16)
-    if which == B.CALL_LOSS_FWD_BWD_NORMED:
+    if which == B.CALL_LOSS_SHARD_BWD:
+        rc = lib.pg_loss_shard_bwd(one, one, one, one, one, 1, one, None, None, None, None, one, T, d, V, 0, C.byref(p), one, one, 1, one,
+                                   None, None, None, one, nbytes, None)
+    elif which == B.CALL_LOSS_FWD_BWD_NORMED:
         rc = lib.pg_loss_fwd_bwd_normed(one, one, 1e-6, one, one, one, one, 1, one, None, None, None, None, T, d, V, C.byref(p), one, one,
                                         one, one, None, None, None, one, nbytes, None)
     else:
@@ -58,3 +61,18 @@ def test_the_minimum_of_the_other_calls_is_their_size():
     args = (5000, 5120, 151936, 0, B.Params(), B.CALL_LOGPROB_FWD)
     assert B.pg_workspace_min_bytes(*args) == B.pg_workspace_bytes(*args) > 0
     assert B.pg_workspace_min_bytes(1024, 100, 1000, 1, B.Params(), 1) == 0 and "multiple of 64" in B.pg_last_error()
+
+
+def test_the_shard_backward_reserves_no_logits():
+    """It starts from states of another call, so its size is what a loss call needs beside the kept logits, and the least it
+    takes; the size of the loss call is enough for it as well."""
+    for T, d, V in SHAPES:
+        for dw in (0, 1):
+            prm = B.Params(dW_dtype=dw)
+            n = B.pg_workspace_bytes(T, d, V, 1, prm, B.CALL_LOSS_SHARD_BWD)
+            assert 0 < n == B.pg_workspace_min_bytes(T, d, V, 1, prm, B.CALL_LOSS_SHARD_BWD)
+            assert n <= B.pg_workspace_bytes(T, d, V, 1, prm, B.CALL_LOSS_FWD_BWD), (T, d, V)
+            assert n >= B.pg_workspace_bytes(T, d, V, 1, prm, B.CALL_LOGPROB_FWD), (T, d, V)
+            assert _needed(T, d, V, B.CALL_LOSS_SHARD_BWD, n - 1, prm) == n
+    n = B.pg_workspace_bytes(16411, 5120, 18992, 30, B.Params(), B.CALL_LOSS_SHARD_BWD)      # one of eight shards of a 14B head
+    assert n < 2.4 * (1 << 30) < 3.4 * (1 << 30) < B.pg_workspace_bytes(16411, 5120, 18992, 30, B.Params(), B.CALL_LOSS_FWD_BWD)
