@@ -120,7 +120,8 @@ typedef struct pg_params {
                             caches the transposed head weight the dH contraction reads (for fp32 heads its bf16
                             values; their remainders are rebuilt in the workspace on every call).  NULL: the
                             transpose is rebuilt in the workspace on every call, or, with few
-                            active rows, W is read as it lies */
+                            active rows, W is read as it lies.  The workspace queries only look
+                            whether it is NULL: a call of many rows needs less with the cache */
   int32_t w_transposed_valid; /* 0: this call fills w_transposed from W; 1: it already holds the transpose of
                             this very W (filled by an earlier call, W unchanged since: e.g. the further
                             microbatches of one optimizer step) and the call skips the transposition */

@@ -201,7 +201,8 @@ int32_t make_plan(int64_t T, int64_t d, int64_t V, int32_t S, const pg_params* p
     pl.dST = take((size_t)vc * ld_t * 2);
     pl.direct_fits = (uint64_t)vc * kd * 2 < FOUR_GIB;      // RowsLoader's range
     pl.ld_wt = (int)(pl.cap_t ? wt_cache_ld(V) : ld_v);
-    if (!pl.direct_fits || t_cap > pg::DIRECT_MAX_ROWS) pl.WT = take((size_t)d * pl.ld_wt * 2);
+    // (a whole W^T only where the caller has none; a chunk's stays, so that a size asked for with the cache does without it)
+    if ((!pl.direct_fits || t_cap > pg::DIRECT_MAX_ROWS) && !(pl.cap_t && p->w_transposed)) pl.WT = take((size_t)d * pl.ld_wt * 2);
     if (pl.is_f32) {   // bf16 remainders of the four backward operands
       pl.HcT_lo = take((size_t)d * ld_h * 2);
       pl.dS_lo = take((size_t)rows_b * ld_v * 2);

@@ -76,3 +76,18 @@ def test_the_shard_backward_reserves_no_logits():
             assert _needed(T, d, V, B.CALL_LOSS_SHARD_BWD, n - 1, prm) == n
     n = B.pg_workspace_bytes(16411, 5120, 18992, 30, B.Params(), B.CALL_LOSS_SHARD_BWD)      # one of eight shards of a 14B head
     assert n < 2.4 * (1 << 30) < 3.4 * (1 << 30) < B.pg_workspace_bytes(16411, 5120, 18992, 30, B.Params(), B.CALL_LOSS_FWD_BWD)
+
+
+def test_no_second_w_transposed_beside_the_callers():
+    """Token blocks hold the whole W^T, unless the caller keeps it."""
+    for T, d, V in SHAPES:
+        lib, sizes, least = B.lib(), [], []
+        for cache in (None, 256):
+            p = B.Params().c_struct()
+            p.w_transposed = cache
+            sizes.append(int(lib.pg_workspace_bytes(T, d, V, 1, C.byref(p), B.CALL_LOSS_FWD_BWD)))
+            least.append(int(lib.pg_workspace_min_bytes(T, d, V, 1, C.byref(p), B.CALL_LOSS_FWD_BWD)))
+        assert least[0] == least[1] <= sizes[1]          # a call without the cache takes the size asked for with it
+        one = B.pg_workspace_bytes(T, d, V, 1, B.Params(), B.CALL_LOSS_SHARD_BWD)      # enough for that call, too
+        saved = min(int(lib.pg_w_transposed_bytes(d, V)), sizes[0] - one) if _in_blocks(T, d, V) else 0
+        assert sizes[0] - sizes[1] == saved, (T, d, V)
