@@ -261,10 +261,12 @@ def _ptr(t: Optional[torch.Tensor]):
 def _stream(stream=None):
     if stream is not None:
         return stream.cuda_stream
-    # torch.cuda.current_stream().cuda_stream without the Stream object: a call of the small stages is host time only
-    # (three of them on a 16x8x3 rollout batch: 36.9 us through the object, 28.3 us so)
-    torch.cuda.init()
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    # torch.cuda.current_stream().cuda_stream without the Stream object where torch has the (private) short cut: a call of
+    # the small stages is host time only (three of them on a 16x8x3 rollout batch: 36.9 us through the object, 28.3 us so)
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None:
+        return torch.cuda.current_stream().cuda_stream
+    return raw(torch.cuda.current_device())
 
 
 def _check(rc: int):

@@ -253,3 +253,15 @@ def test_binding_rejects_wrong_dtypes_shapes_and_devices():
         B._want_loss_out(out[:4] + (torch.zeros(8, dtype=torch.int32),), T, d, V, cpu, torch.bfloat16, None, P)
     with pytest.raises(ValueError, match="shape"):
         B._want_loss_out(out, T, d, V, cpu, torch.bfloat16, torch.zeros((V + 1, d)), P)
+
+
+def test_current_stream_without_the_private_short_cut(monkeypatch):
+    import torch
+    from types import SimpleNamespace
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda device=None: SimpleNamespace(cuda_stream=77))
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 1000 + device, raising=False)
+    assert B._stream() == 1003
+    assert B._stream(SimpleNamespace(cuda_stream=5)) == 5
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream")
+    assert B._stream() == 77
