@@ -91,10 +91,22 @@ def pad_ld(n: int) -> int:
     return n + 64 if (n // 64) % 2 == 0 else n
 
 
-def recompute_covers_vocabulary(T: int, V: int, n_pad: int, chunk_rows: int) -> bool:
+def block_rows(T: int, d: int, V: int, budget: int = 2 << 30) -> int:
+    """Rows that the dS scratch of a bf16 loss call with an fp32 dW holds: all of them, or those of a token block (the
+    library's rule, restated for the tests: the logits of all rows do not fit 39/8 of the budget, d >= 1536, and the dH
+    launch of the block has at least two rounds of 256 tiles)."""
+    tiles_t, tiles_v, td = (T + 255) // 256, (V + 255) // 256, (d + 255) // 256
+    fit = budget // 8 * 39 >> 18
+    rounds = fit // tiles_v * td // 256
+    cap = rounds * 256 // td
+    return cap * 256 if tiles_t * tiles_v > fit and d >= 1536 and rounds >= 2 and cap >= 16 else tiles_t * 256
+
+
+def recompute_covers_vocabulary(T: int, V: int, n_pad: int, chunk_rows: int, rows=None) -> bool:
     """The library's device-side rule for few active rows, restated for the tests: dS of the whole vocabulary fits
-    the chunk scratch (sized for t_cap rows and chunk_rows columns) at n_pad rows, in both orientations."""
-    t_cap, v_pad = (T + 255) // 256 * 256, (V + 255) // 256 * 256
+    the chunk scratch (sized for `rows` rows, by default all of them, and chunk_rows columns) at n_pad rows, in both
+    orientations."""
+    t_cap, v_pad = rows or (T + 255) // 256 * 256, (V + 255) // 256 * 256
     if chunk_rows >= v_pad or n_pad <= 0:
         return False                                  # one chunk anyway / nothing to do
     return n_pad * pad_ld(v_pad) <= t_cap * pad_ld(chunk_rows) and v_pad * pad_ld(n_pad) <= chunk_rows * pad_ld(t_cap)

@@ -258,16 +258,11 @@ def test_full_all_rows_against_library_gradients(full_case):
     del lib_dW, lib_dH
 
 
-def dh_split_parts(n_pad, t_cap, tiles_n, k_stages):
-    """The device's choice of how many parts the dH contraction is cut into (restated from the header's
-    description: enough parts to fill 256 compute units, at most 8, at least 8 stages each, and the parts'
-    accumulator slabs must fit into the [t_cap, d] accumulator)."""
-    if n_pad <= 0:
-        return 1
-    tiles = (n_pad // 256) * tiles_n
-    ks = 256 // max(tiles, 1)
-    ks = min(ks, t_cap // n_pad, k_stages // 8, 8)
-    return max(ks, 1)
+def dh_split_parts(n_pad, acc_rows, tiles_n, k_stages):
+    """The device's choice of how many parts the dH contraction is cut into, restated: the least rounds of 256 tiles times
+    (stages of a part + 24), at most 8 parts of at least 8 stages, whose slabs fit the accumulator."""
+    fits = [ks for ks in range(1, 9) if ks == 1 or (ks * n_pad <= acc_rows and ks * 8 <= k_stages)]
+    return min(fits, key=lambda ks: (-(-n_pad // 256 * tiles_n * ks // 256) * (-(-k_stages // ks) + 24), ks))
 
 
 def test_full_geometric_rejection_few_rows_split_contraction(full_case):
@@ -306,12 +301,13 @@ def test_full_geometric_rejection_few_rows_split_contraction(full_case):
     # the launch really is the split one
     vc = B.pg_backward_chunk_rows(T, d, V, S, prm)
     t_cap, n_pad = (T + 255) // 256 * 256, (n_act + 255) // 256 * 256
-    parts = dh_split_parts(n_pad, t_cap, (d + 255) // 256, vc // 64)
+    # (few rows: one launch over the whole vocabulary; the accumulator has t_cap rows from 32768 on)
+    parts = dh_split_parts(n_pad, t_cap, (d + 255) // 256, (V + 255) // 256 * 4)
     print(f"[fullsize] geometric rejection keeps {n_act} rows (padded {n_pad}): dH contraction in {parts} parts", flush=True)
     assert parts >= 2
     # ... and the recompute of the whole vocabulary runs in the first chunk's launch
-    from tests._cases import recompute_covers_vocabulary
-    assert vc < V and recompute_covers_vocabulary(T, V, n_pad, vc)
+    from tests._cases import block_rows, recompute_covers_vocabulary
+    assert vc < V and recompute_covers_vocabulary(T, V, n_pad, vc, block_rows(T, d, V))
     # per-row outputs against the oracle on sampled active rows; inactive rows are zero
     act = np.nonzero(active)[0]
     rows = np.sort(rng.choice(act, 24, replace=False))

@@ -6,7 +6,7 @@ import torch
 from oracle import pg_oracle as O
 from paper_2602_05885_amd import binding as B
 from paper_2602_05885_amd import synth
-from tests._cases import block_rel_fro, np64
+from tests._cases import block_rel_fro, np64, recompute_covers_vocabulary
 
 pytestmark = pytest.mark.gpu
 
@@ -54,3 +54,31 @@ def test_direct_dh_is_chosen_by_the_active_rows(active, dtype):
         rows = mask.nonzero()[:40, 0].cpu().numpy()
         ref = O.sft_ce_fwd_bwd(np64(H)[rows], np64(W), y.cpu().numpy()[rows], [1] * len(rows), norm_override=float(active))
         assert block_rel_fro(np64(outs[0]["dH"])[rows], ref["dH"]) <= (5e-5 if dtype == "f32" else 1e-2)
+
+
+# the same choice where the rows are few enough that dS spans the vocabulary (planned in two chunks): up to 8192 rows dH is
+# one launch that reads W as it lies, beyond it keeps its chunks, with their W^T and their columns of the wide dS.  Kept
+# logits (201 tiles, at most 256) and recomputed ones (335).
+@pytest.mark.parametrize("V,chunk_tiles", [(515, 2), (1027, 3)])
+@pytest.mark.parametrize("active", [8192, 8193, 8700])
+def test_wide_ds_with_chunked_and_whole_dh(active, V, chunk_tiles, monkeypatch):
+    dev = torch.device("cuda:0")
+    T, d = 17000, 192
+    monkeypatch.setenv("PG_HEAD_DS_BUDGET_BYTES", str((T + 255) // 256 * 256 * 2 * 256 * chunk_tiles))
+    n_pad = (active + 255) // 256 * 256
+    assert B.pg_backward_chunk_rows(T, d, V, 0, B.Params()) == 256 * chunk_tiles
+    assert recompute_covers_vocabulary(T, V, n_pad, 256 * chunk_tiles)
+    H, W, y = synth.make_head(T, d, V, "bf16", 8, dev)
+    mask = torch.zeros(T, dtype=torch.uint8, device=dev)
+    mask[torch.randperm(T, generator=torch.Generator().manual_seed(2))[:active].to(dev)] = 1
+    outs = []
+    for cache in (None, B.alloc_w_transposed(d, V, dev)):
+        prm = B.Params(w_transposed=cache)
+        ws = torch.full((B.pg_workspace_bytes(T, d, V, 0, prm, B.CALL_LOSS_FWD_BWD),), 0xFF, dtype=torch.uint8, device=dev)
+        outs.append(B.pg_sft_fwd_bwd(H, W, y, mask, prm, ws))
+    torch.cuda.synchronize()
+    for q in outs[0]:
+        assert torch.equal(outs[0][q], outs[1][q]), q
+    ref = O.sft_ce_fwd_bwd(np64(H), np64(W), y.cpu().numpy(), mask.cpu().numpy())
+    for q in ("dH", "dW"):                  # bf16 dS: 2^-9 per element
+        assert block_rel_fro(np64(outs[0][q]), ref[q]) <= 1e-2, q
