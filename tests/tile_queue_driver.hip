@@ -3,10 +3,12 @@
 // For every tile count swept and both orders: the entries i < share(y) of the 8 XCDs, decoded with the
 // order's map, hand out every tile (tm, tn) exactly once; entries at and beyond share(y) map to no tile;
 // 32 consecutive entries of one XCD form a block of at most 4 x 8 neighbouring tiles (what the L2 sharing
-// relies on); and dh_split keeps its parts inside the accumulator.
+// relies on); dh_split and dh_slabs keep their parts inside the accumulator; dw_split's parts are no shorter than
+// its least; token blocks cut the live tiles without a gap or an overlap; and the kept tiles fit their region.
 #include <cstdio>
 #include <vector>
 #include "../paper_2602_05885_amd/csrc/gemm_core.h"
+#include "../paper_2602_05885_amd/csrc/kernels.h"
 using namespace pg;
 
 static int fails = 0;
@@ -62,7 +64,51 @@ int main() {
           const int ks = dh_split(n_pad, t_cap, tiles_n, stages);
           CHECK(ks >= 1 && ks <= 8 && (long long)ks * n_pad <= (long long)imax(t_cap, n_pad) && (ks == 1 || stages / ks >= 8),
                 "dh_split(%d, %d, %d, %d) = %d", n_pad, t_cap, tiles_n, stages, ks);
+          for (int f32 = 0; f32 < 2; ++f32) {
+            int parts = 0;
+            const int slabs = dh_slabs(n_pad, t_cap, tiles_n, stages, f32, parts), products = slabs / parts;
+            CHECK(parts == ks && slabs == parts * products && (products == 1 || (products == 3 && f32)) && (long long)slabs * n_pad <= t_cap,
+                  "dh_slabs(%d, %d, %d, %d, %d) = %d of %d parts", n_pad, t_cap, tiles_n, stages, f32, slabs, parts);
+            CHECK(products == 1 || (n_pad / 256) * tiles_n * slabs <= 256, "dh_slabs(%d, %d, %d, %d, 1): %d slabs are more than one round", n_pad, t_cap, tiles_n, stages, slabs);
+          }
         }
+  for (int stages = 0; stages <= 300; ++stages)
+    for (int cap = 1; cap <= DW_SPLIT_MAX; ++cap) {
+      const int ks = dw_split(stages, cap);
+      CHECK(ks >= 1 && ks <= cap && (ks == 1 || stages / ks >= DW_MIN_STAGES) && (ks == cap || (ks + 1) * DW_MIN_STAGES > stages),
+            "dw_split(%d, %d) = %d", stages, cap, ks);
+      int at = 0;       // the parts of gemm_store_tile
+      for (int p = 0; p < ks; ++p) {
+        const int s0 = (int)((long long)p * stages / ks), s1 = (int)((long long)(p + 1) * stages / ks);
+        CHECK(s0 == at && s1 >= s0 && (ks == 1 || s1 - s0 >= DW_MIN_STAGES), "part %d of %d: stages %d .. %d of %d", p, ks, s0, s1, stages);
+        at = s1;
+      }
+      CHECK(at == stages, "%d parts end at stage %d of %d", ks, at, stages);
+    }
+  for (int host_tiles = 1; host_tiles <= 80; ++host_tiles)        // what the host launches: blocks for all of its tiles
+    for (int cap_t = 0; cap_t <= 40; ++cap_t) {
+      const int nblocks = cap_t ? (host_tiles + cap_t - 1) / cap_t : 1;
+      for (int live = 0; live <= host_tiles; ++live) {
+        int at = 0;
+        for (int b = 0; b < nblocks; ++b) {
+          int t0 = -1, nt = -1;
+          token_block(TokenBlocks{cap_t, b}, live, t0, nt);
+          CHECK(t0 == at && nt >= 0 && (!cap_t || nt <= cap_t) && (nt == cap_t || t0 + nt == live),
+                "block %d of %d (cap %d): tiles %d + %d of %d", b, nblocks, cap_t, t0, nt, live);
+          at = t0 + nt;
+        }
+        CHECK(at == live, "%d blocks of %d end at tile %d of %d", nblocks, cap_t, at, live);
+      }
+    }
+  float region = 0.f;
+  for (int cap : {0, 1, 47, 48, 594, 38016, 39936})
+    for (int tiles_v : {1, 2, 75, 594, 2000})
+      for (int live = 0; live <= 200; ++live) {
+        const int n = kept_vocab_tiles(Kept{&region, cap}, tiles_v, live);
+        CHECK(n >= 0 && n <= tiles_v && (long long)n * live <= cap && (live == 0 ? n == 0 : n == tiles_v || (long long)(n + 1) * live > cap),
+              "kept_vocab_tiles(%d, %d, %d) = %d", cap, tiles_v, live, n);
+        CHECK(kept_vocab_tiles(Kept{nullptr, cap}, tiles_v, live) == 0, "nothing is kept without a region");
+      }
   printf(fails ? "tile queue driver: %d FAILED\n" : "tile queue driver: every tile handed out exactly once (%d failures)\n", fails);
   return fails != 0;
 }
