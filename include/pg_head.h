@@ -2,9 +2,9 @@
  * pg_head.h -- C ABI of the MI355X policy-gradient head.
  *
  * The library computes, for one packed microbatch of a multi-turn RL step, the
- * per-token policy-gradient quantities over the vocabulary without ever holding
- * the [tokens x vocab] logits: the forward-only calls write none of them, the loss calls
- * park a bounded number of 256 x 256 logits tiles in the workspace for their backward:
+ * per-token policy-gradient quantities over the vocabulary.  The forward-only calls write none of
+ * the [tokens x vocab] logits; the loss calls keep up to 9.75 GiB of them in fp32 (those of every
+ * row, where the microbatch is small enough) in the workspace for their backward:
  *
  *   trloo_advantage   turn returns and leave-one-out advantages   (Sec. 4.2, Eq. 2 and 5)
  *   pg_logprob_fwd    LM-head log-prob / entropy / logsumexp of the sampled tokens
@@ -420,15 +420,16 @@ int32_t pg_loss_shard_bwd(const void* H, const void* W_shard, const int32_t* y, 
 /*
  * Measurement hooks (host-side state, not thread-safe; the only calls that create HIP events
  * or wait on the device).  pg_profile_enable(1, n) creates a pool for n kernel launches; from
- * then on each launch of the MFMA kernels is bracketed by two events on the caller's stream.
+ * then on each launch of the MFMA kernels (the launches of one class that follow each other count
+ * as one) is bracketed by two events on the caller's stream.
  * pg_profile_read waits for the recorded events, returns the summed durations in milliseconds
  * and the launch counts per kernel class (host arrays of PG_KERNEL_CLASSES entries), and
  * empties the pool.  pg_profile_enable(0, 0) releases the events.
  */
 #define PG_KERNEL_FWD 0      /* logits + online softmax statistics               */
-#define PG_KERNEL_DLOGITS 1  /* logits recompute + dS in both orientations       */
-#define PG_KERNEL_DW 2       /* dW = dS^T H   (gemm_store_kernel)                */
-#define PG_KERNEL_DH 3       /* dH = dS W     (gemm_store_kernel)                */
+#define PG_KERNEL_DLOGITS 1  /* dS in both orientations, from kept and from recomputed logits */
+#define PG_KERNEL_DW 2       /* dW = dS^T H   (gemm_store_kernel; the fold of a split dW) */
+#define PG_KERNEL_DH 3       /* dH = dS W     (gemm_store_kernel, in both of its forms) */
 #define PG_KERNEL_CLASSES 4
 int32_t pg_profile_enable(int32_t on, int32_t max_launches);
 int32_t pg_profile_read(double* h_ms, int64_t* h_launches);

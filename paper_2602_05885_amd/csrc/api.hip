@@ -34,7 +34,7 @@ constexpr int64_t ACC_ROWS_SPLIT = 32768;
 constexpr double LOG2E = 1.4426950408889634;
 
 // Tuning knob: PG_HEAD_DS_BUDGET_BYTES overrides the size of the dS chunk scratch (and with
-// it the number of vocab chunks of the backward pass).
+// it the number of vocab chunks of the backward pass, and the room for kept logits).
 uint64_t ds_budget() {
   if (const char* e = std::getenv("PG_HEAD_DS_BUDGET_BYTES")) {
     const unsigned long long v = std::strtoull(e, nullptr, 10);
@@ -46,8 +46,11 @@ uint64_t ds_budget() {
 inline size_t align_up(size_t x) { return (x + ALIGN - 1) / ALIGN * ALIGN; }
 
 // Bytes of fp32 logits that a loss call keeps for its backward (Kept in kernels.h): 39/8 of the dS scratch of one
-// orientation (9.75 GiB), so one knob bounds all scratch.  A 14B head with 44k rows then needs 15.7 GiB in all,
-// 5 % of the card, and keeps half of its 32768 active rows' logits; every further GiB is worth 1.2 ms of 128 there.
+// orientation (9.75 GiB), so one knob bounds all scratch.  At V = 151936 that holds 67 token tiles, and token blocks of 64
+// tiles (five dH rounds at d = 5120, four at d = 4096), into which batches of a power of two of rows fall evenly.  32768
+// active rows of 43697, with a budget of 8, 9.75 and 12 GiB: d = 5120 119.1, 114.2, 119.9 ms, d = 4096 94.3, 93.8, 94.4;
+// d = 5120, V = 256000, 20000 rows 129.4, 128.1, 128.1; d = 2048, V = 50000, 60000 rows 33.6, 34.4, 34.1.  The first of
+// these needs 14.7 GiB in all, 5 % of the card.
 uint64_t kept_budget() { return ds_budget() / 8 * 39; }
 
 // Leading dimension of the caller-owned W^T cache [d, ld]: the vocabulary rounded up to whole tiles.
@@ -311,8 +314,8 @@ int32_t check_monitor_args(const float* logp_train, const uint8_t* loss_mask, in
 }
 
 // ---- optional per-kernel timing (measurement hook; off by default) ----
-// When enabled, every launch of the three MFMA kernels is bracketed by a pair of events on the
-// caller's stream, taken from a pool created up front.  Not thread-safe.
+// When enabled, the launches of each kernel class (pg_head.h) of a chunk are bracketed by a pair of events
+// on the caller's stream, taken from a pool created up front.  Not thread-safe.
 struct Profiler {
   bool on = false;
   std::vector<hipEvent_t> ev;     // 2 per recorded launch

@@ -65,8 +65,9 @@ __host__ __device__ inline int kept_vocab_tiles(const Kept& k, int tiles_v, int 
 // 8 consecutive k per lane; without, its fragments are read from LDS transposed (RowsLoader in gemm_core.h), which
 // makes the contraction 3..5 % slower but saves writing and reading W^T, a cost that does not depend on the rows.
 // Measured, dH and transposition per call: V = 151936, d = 5120, 768 rows 615 + 574 us against 694 us; d = 4096,
-// 4100 rows 3585 + 457 us against 3752 us; d = 5120, 32768 rows 37.3 + 0.48 ms against 38.1 ms.  The two meet at
-// about 11000 rows.  The active rows are known only on the device: where they may lie on either side, both forms are launched
+// 4100 rows 3585 + 457 us against 3752 us; d = 5120, 32768 rows 37.3 + 0.48 ms against 38.1 ms.  Around the line the
+// two are equal for the call: W as it lies takes 0.997 of its time at 8448 to 10752 rows and 0.999 at 12032 (d = 4096), 0.997
+// at 8448, 1.000 at 10752 and 1.004 at 12032 (d = 5120), 1.002, 1.004 and 1.004 at V = 18992.  The active rows are known only on the device: where they may lie on either side, both forms are launched
 // and one returns at once (ctl != null).
 constexpr int DIRECT_MAX_ROWS = 8192;
 struct DirectRule {

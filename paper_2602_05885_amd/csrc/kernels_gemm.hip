@@ -127,7 +127,8 @@ __device__ __forceinline__ void lmhead_fwd_body(FwdArgs a, bool steal, unsigned 
     const int v_base = tm * BM + wm * WROWS;            // first vocab row of this wavefront's block
     const bool ragged = (tm * BM + BM > a.V);
     // park the accumulators for the backward, 1 KiB per instruction, before the statistics, so that the stores drain
-    // under them (d = 5120, V = 151936: 609 -> 640 us at 768 rows, all tiles kept; nothing at 32768 rows, 43 % kept)
+    // under them (d = 5120, V = 151936, all tiles kept: 609 -> 640 us at 768 rows; at 32768 rows in two token blocks
+    // 36.4 -> 36.5 ms)
     if (tm < kept_v) {
       f32x4* kp = reinterpret_cast<f32x4*>(a.kept.tiles + ((size_t)tm * tiles_t + tn) * KEPT_TILE_FLOATS) + wave * (GM * GN * 64) + lane;
 #pragma unroll
@@ -441,8 +442,8 @@ __global__ __launch_bounds__(NTHREADS) void lmhead_dlogits_kernel(DlogitsArgs a)
 // workgroup takes 256 vocab rows x 128 tokens, i.e. four wavefronts of a kept tile, so that two fit a
 // compute unit (72 KiB of LDS each) and one's loads run under the other's stores.  Measured at d = 5120,
 // V = 151936: 768 rows 119 us (recompute 639 us; 7.8 TB/s, part of the kept tiles still sits in the
-// memory-side cache), 32768 rows 4.8 TB/s, the rate of a plain copy (recompute of the same tiles 4.2 times as
-// long).  Requesting a quarter or half of the next half tile before the stores: 126 us at 768 rows.
+// memory-side cache), 32768 rows in two token blocks 7.7 ms, 5.2 TB/s, above the rate of a plain copy (recompute
+// 36 ms).  Requesting a quarter or half of the next half tile before the stores: 126 us at 768 rows.
 constexpr int KEPT_STRIDE_T = 288;                          // 128 tokens + pad: 72 dwords, see EPI_STRIDE_T
 constexpr int KEPT_THREADS = 256;
 constexpr int KEPT_LDS_BYTES = 256 * KEPT_STRIDE_T;

@@ -1,7 +1,9 @@
-// Stand-alone timeline of one vocab chunk's three persistent launches at the 14B head shape (d=5120,
-// 32 768 tokens, a chunk of 89 vocab tiles): the recompute (logits tile -> dS in both orientations), the dW
-// contraction and the dH contraction, each as the library launches it (one workgroup per compute unit,
-// tiles from the per-XCD queue), with the 100 MHz wall clock read inside the kernel
+// Stand-alone timeline of one vocab chunk's three persistent launches at the 14B head shape in one block of rows
+// (d=5120, 32 768 tokens, a chunk of 89 vocab tiles): the recompute (logits tile -> dS in both orientations), the
+// dW contraction and the dH contraction, each as the library launches it (one workgroup per compute unit,
+// tiles from the per-XCD queue) where a step starts from the softmax states of another call (pg_loss_shard_bwd on
+// the whole head).  A loss call with its own forward takes that many rows in two blocks of 16 384, with chunks
+// of 128 tiles and without the recompute.  The 100 MHz wall clock is read inside the kernel
 //   * per workgroup at its start, at the start of its last tile and at its end: how long the workgroups
 //     idle at the end of a launch, per XCD, and how long the last tile was;
 //   * for the recompute, per tile at the end of the main loop and at the end of the epilogue, for the first
@@ -118,7 +120,7 @@ static void report(const char* name, const std::vector<unsigned long long>& t, i
 
 int main(int argc, char** argv) {
   const int reps = argc > 1 ? atoi(argv[1]) : 2;
-  const int T = 32768, d = 5120, vc = 22784, V = 151936;     // one full chunk of the headline plan: 89 vocab tiles
+  const int T = 32768, d = 5120, vc = 22784, V = 151936;     // one full chunk of the one-block plan: 89 vocab tiles
   CK(init_gemm_kernels());
   CK(hipFuncSetAttribute(reinterpret_cast<const void*>(store_timeline_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, PERSISTENT_LDS_BYTES));
   CK(hipFuncSetAttribute(reinterpret_cast<const void*>(dlogits_timeline_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, PERSISTENT_LDS_BYTES));
