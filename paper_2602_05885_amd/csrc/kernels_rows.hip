@@ -558,7 +558,7 @@ __global__ __launch_bounds__(256) void scatter_dh_kernel(ScatterArgs a, FinishAr
   const float* src = a.acc + (size_t)(p < 0 ? 0 : p) * a.d;
   const int n_pad = a.ctl->n_pad;
   int ks = 1;                                       // slabs
-  if (a.split_k && (a.cap_t <= 0 || n_pad <= a.cap_t * BM)) ks = dh_slabs(n_pad, a.acc_rows, a.tiles_n, dh_runs_whole(a.rc, n_pad) ? a.rc.tiles_v_all * BM / BK : a.k_stages, a.split_f32, ks);
+  if (p >= 0 && a.split_k && (a.cap_t <= 0 || n_pad <= a.cap_t * BM)) ks = dh_slabs(n_pad, a.acc_rows, a.tiles_n, dh_runs_whole(a.rc, n_pad) ? a.rc.tiles_v_all * BM / BK : a.k_stages, a.split_f32, ks);
   const size_t slab = (size_t)n_pad * a.d;
   for (int j = threadIdx.x * 4; j < a.d; j += 256 * 4) {
     float4 v = make_float4(0.f, 0.f, 0.f, 0.f);

@@ -64,6 +64,13 @@ int main() {
           const int ks = dh_split(n_pad, t_cap, tiles_n, stages);
           CHECK(ks >= 1 && ks <= 8 && (long long)ks * n_pad <= (long long)imax(t_cap, n_pad) && (ks == 1 || stages / ks >= 8),
                 "dh_split(%d, %d, %d, %d) = %d", n_pad, t_cap, tiles_n, stages, ks);
+          int least = 1;           // the least modelled rounds, the fewest parts among equals
+          long long least_cost = 0;
+          for (int q = 1; q <= 8 && (q == 1 || ((long long)q * n_pad <= t_cap && q * 8 <= stages)); ++q) {
+            const long long cost = ((long long)(n_pad / 256) * tiles_n * q + 255) / 256 * ((stages + q - 1) / q + 24);
+            if (q == 1 || cost < least_cost) { least = q; least_cost = cost; }
+          }
+          CHECK(ks == least, "dh_split(%d, %d, %d, %d) = %d, not %d", n_pad, t_cap, tiles_n, stages, ks, least);
           for (int f32 = 0; f32 < 2; ++f32) {
             int parts = 0;
             const int slabs = dh_slabs(n_pad, t_cap, tiles_n, stages, f32, parts), products = slabs / parts;
