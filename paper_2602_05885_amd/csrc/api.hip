@@ -214,7 +214,8 @@ int32_t make_plan(int64_t T, int64_t d, int64_t V, int32_t S, const pg_params* p
     }
     // A head of so few dW tiles that half of the compute units would idle: parts of the contraction side by side
     const int64_t dw_tiles = chunk_tiles * ((d + 255) / 256), products = pl.is_f32 ? 3 : 1;
-    if (dw_tiles * products * 2 <= 256 && !pl.cap_t) {
+    // (unless the rows are too few for two)
+    if (dw_tiles * products * 2 <= 256 && !pl.cap_t && products * pg::dw_split((int)(rows_b / 64), pg::DW_SPLIT_MAX) > 1) {
       pl.dw_cap = (int)std::min<int64_t>(pg::DW_SPLIT_MAX, 256 / (dw_tiles * products));
       pl.dWslabs = take((size_t)pl.dw_cap * products * vc * d * 4);
     }
@@ -897,7 +898,7 @@ int32_t loss_fwd_bwd(int sft, const void* H, const void* W, const int32_t* y, co
         pg::DwFoldArgs f{};
         f.slabs = at<float>(ws, pl.dWslabs); f.dW = w.C; f.n = (long long)rows_valid * d_i; f.slab = (long long)pl.vc * d_i;
         f.dw_cap = pl.dw_cap; f.products = pl.is_f32 ? 3 : 1; f.accumulate = w.accumulate; f.out_bf16 = w.out_bf16; f.ctl = ctl;
-        w.C = at<float>(ws, pl.dWslabs); w.accumulate = 0; w.out_bf16 = 0; w.dw_cap = pl.dw_cap; w.slab_rows = pl.vc;
+        w.slabs = at<float>(ws, pl.dWslabs); w.dw_cap = pl.dw_cap; w.slab_rows = pl.vc;
         ProfScope ps(PG_KERNEL_DW, st);
         pg::launch_gemm_store(w, st);
         pg::launch_dw_fold(f, st);

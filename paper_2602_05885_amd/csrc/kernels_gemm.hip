@@ -646,6 +646,7 @@ __global__ __launch_bounds__(NTHREADS) void gemm_store_kernel(StoreArgs a) {
     if (sh.nt <= 0) return;
     if (a.k_from_ctl) a.accumulate = 1;                              // dW: on top of the blocks before
   }
+  if (a.dw_cap > 0 && sh.ks * sh.products > 1) { a.C = a.slabs; a.accumulate = 0; a.out_bf16 = 0; }
   if (a.m_from_ctl) a.C = static_cast<float*>(a.C) + (size_t)sh.t0 * BM * a.ldc;      // dH: this block's rows of the accumulator
   TileQueue Q;
   Q.init(a.queue, sh.total, 1);

@@ -630,6 +630,7 @@ void launch_finish_partials(const float* parts, long long T, float* logp, float*
 // Adds the slabs of a split dW contraction (dw_split) in order, and the gradient that was there if it accumulates.
 __global__ __launch_bounds__(256) void dw_fold_kernel(DwFoldArgs a) {
   const int slabs = dw_split(a.ctl->n_pad / BK, a.dw_cap) * a.products;
+  if (slabs == 1) return;                           // the contraction wrote dW itself
   for (long long e = ((long long)blockIdx.x * 256 + threadIdx.x) * 4; e < a.n; e += (long long)gridDim.x * 256 * 4) {
     f32x4 v = *reinterpret_cast<const f32x4*>(a.slabs + e);
     for (int q = 1; q < slabs; ++q) v += *reinterpret_cast<const f32x4*>(a.slabs + q * a.slab + e);

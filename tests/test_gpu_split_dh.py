@@ -56,6 +56,32 @@ def test_direct_dh_is_chosen_by_the_active_rows(active, dtype):
         assert block_rel_fro(np64(outs[0]["dH"])[rows], ref["dH"]) <= (5e-5 if dtype == "f32" else 1e-2)
 
 
+# a small head's dW: one part (written to dW itself; no active row at all among them), two and more, over one vocab chunk
+# and several, added to what is there or not
+@pytest.mark.parametrize("T,active", [(1100, 0), (1100, 1), (1100, 256), (1100, 257), (1100, 1100), (200, 200)])
+@pytest.mark.parametrize("dtype,dw16,acc,budget", [("bf16", 1, 1, None), ("bf16", 0, 1, 2), ("bf16", 1, 0, 2), ("f32", 0, 1, None)])
+def test_split_dw_of_small_heads(T, active, dtype, dw16, acc, budget, monkeypatch):
+    dev = torch.device("cuda:0")
+    d, V = 320, 1500
+    if budget:
+        monkeypatch.setenv("PG_HEAD_DS_BUDGET_BYTES", str((T + 255) // 256 * 256 * 2 * 256 * budget))
+    H, W, y = synth.make_head(T, d, V, dtype, 17, dev)
+    mask = torch.zeros(T, dtype=torch.uint8, device=dev)
+    mask[torch.randperm(T, generator=torch.Generator().manual_seed(4))[:active].to(dev)] = 1
+    prm = B.Params(dtype=int(dtype == "f32"), dW_dtype=dw16, accumulate_dW=acc)
+    start = (torch.randn((V, d), generator=torch.Generator().manual_seed(5)) * 1e-3).to(torch.bfloat16 if dw16 else torch.float32).to(dev)
+    dW = start.clone() if acc else torch.full_like(start, float("nan"))
+    ws = torch.full((B.pg_workspace_bytes(T, d, V, 0, prm, B.CALL_LOSS_FWD_BWD),), 0xFF, dtype=torch.uint8, device=dev)
+    out = B.pg_sft_fwd_bwd(H, W, y, mask, prm, ws, dW=dW)
+    torch.cuda.synchronize()
+    ref = O.sft_ce_fwd_bwd(np64(H), np64(W), y.cpu().numpy(), mask.cpu().numpy(), dW_prev=np64(start) if acc else None)
+    tol = 1e-2 if dtype == "bf16" else 5e-5      # bf16 dS and dW: 2^-9 per element each; fp32 heads carry about 16 mantissa bits
+    for q in ("dH", "dW"):
+        assert block_rel_fro(np64(out[q]), ref[q]) <= tol, q
+    if acc and active == 0:
+        assert torch.equal(out["dW"], start)
+
+
 # the same choice where the rows are few enough that dS spans the vocabulary (planned in two chunks): up to 8192 rows dH is
 # one launch that reads W as it lies, beyond it keeps its chunks, with their W^T and their columns of the wide dS.  Kept
 # logits (201 tiles, at most 256) and recomputed ones (335).
