@@ -843,6 +843,7 @@ int32_t loss_fwd_bwd(int sft, const void* H, const void* W, const int32_t* y, co
   if (p.w_transposed && !p.w_transposed_valid)       // the caller's cache is filled whole, before anything reads it
     pg::launch_transpose_w(W, pl.is_f32, pl.V, d_i, d_i, 0, pl.tiles_v * 256, (int)wt_cache_ld(pl.V), static_cast<__bf16*>(p.w_transposed), pg::DirectRule{}, st);
   const int tiles_b = pl.cap_t ? pl.cap_t : pl.tiles_t;
+  pg::DwFoldArgs fold{};                            // of a dW that was split in a single chunk
   for (int b = 0; b < pl.nblocks; ++b) {      // token blocks; the backward of a block one vocab chunk at a time
     const pg::TokenBlocks blk{pl.cap_t, b};
     unsigned* const block_queue = at<unsigned>(ws, pl.queue) + (size_t)pg::QUEUE_SET_WORDS * pg::queue_sets(pl.nchunks) * b;
@@ -895,13 +896,13 @@ int32_t loss_fwd_bwd(int sft, const void* H, const void* W, const int32_t* y, co
       w.queue = queues + pg::QUEUE_SET_WORDS;
       w.rc = few; w.rc_role = 1; w.v0 = v0; w.blk = blk;
       if (pl.dw_cap) {
-        pg::DwFoldArgs f{};
+        pg::DwFoldArgs& f = fold;
         f.slabs = at<float>(ws, pl.dWslabs); f.dW = w.C; f.n = (long long)rows_valid * d_i; f.slab = (long long)pl.vc * d_i;
         f.dw_cap = pl.dw_cap; f.products = pl.is_f32 ? 3 : 1; f.accumulate = w.accumulate; f.out_bf16 = w.out_bf16; f.ctl = ctl;
         w.slabs = at<float>(ws, pl.dWslabs); w.dw_cap = pl.dw_cap; w.slab_rows = pl.vc;
         ProfScope ps(PG_KERNEL_DW, st);
         pg::launch_gemm_store(w, st);
-        pg::launch_dw_fold(f, st);
+        if (pl.nchunks > 1) { pg::launch_dw_fold(f, st); f = pg::DwFoldArgs{}; }      // (the next chunk writes the slabs anew)
       } else {
         ProfScope ps(PG_KERNEL_DW, st);
         pg::launch_gemm_store(w, st);
@@ -936,8 +937,8 @@ int32_t loss_fwd_bwd(int sft, const void* H, const void* W, const int32_t* y, co
                      reinterpret_cast<long long*>(counters_out), at<pg::Ctl>(ws, pl.ctl)};
   pg::ScatterArgs sc{at<float>(ws, pl.dHacc), at<int>(ws, pl.pos), dH, (int)pl.T, d_i, pl.is_f32 || shard.dH_f32,
                      1, pl.acc_rows, (d_i + 255) / 256, kc0 / 64, pl.is_f32, pl.cap_t, few, ctl};
-  if (norm) pg::launch_scatter_dx_norm(sc, nf, fin, st);
-  else pg::launch_scatter_dh(sc, fin, st);
+  if (norm) pg::launch_scatter_dx_norm(sc, nf, fin, fold, st);
+  else pg::launch_scatter_dh(sc, fin, fold, st);
   return guard.check(shard.what ? shard.what : sft ? "pg_sft_fwd_bwd" : norm ? "pg_loss_fwd_bwd_normed" : "pg_loss_fwd_bwd");
 }
 

@@ -173,10 +173,13 @@ __host__ __device__ inline int dh_split(int n_pad, int acc_rows, int tiles_n, in
 __host__ __device__ inline int split_products(int split_f32, int tiles, int ks, long long slab_rows, long long acc_rows) {
   return split_f32 && 3 * ks * tiles <= 256 && 3 * ks * slab_rows <= acc_rows ? 3 : 1;
 }
+__host__ __device__ inline int dh_products(int n_pad, int acc_rows, int tiles_n, int ks, int split_f32) {
+  return split_products(split_f32, (n_pad / 256) * tiles_n, ks, n_pad, acc_rows);
+}
 // Slabs of the dH accumulator.
 __host__ __device__ inline int dh_slabs(int n_pad, int acc_rows, int tiles_n, int k_stages, int split_f32, int& ks) {
   ks = dh_split(n_pad, acc_rows, tiles_n, k_stages);
-  return ks * split_products(split_f32, (n_pad / 256) * tiles_n, ks, n_pad, acc_rows);
+  return ks * dh_products(n_pad, acc_rows, tiles_n, ks, split_f32);
 }
 
 // Split-K factor of the dW contraction (over the padded active rows) of a head so small that its tiles leave most

@@ -330,8 +330,8 @@ struct ScatterArgs {
   Rechunk rc;           // see dh_runs_whole: the contraction is then as long as the vocabulary
   const Ctl* ctl;
 };
-// (the loss and the counters come from the same launch)
-void launch_scatter_dh(const ScatterArgs& a, const FinishArgs& fin, hipStream_t s);
+// (the loss and the counters, and the fold of a dW split over one vocab chunk, come from the same launch; fold.n = 0: none)
+void launch_scatter_dh(const ScatterArgs& a, const FinishArgs& fin, const DwFoldArgs& fold, hipStream_t s);
 
 // RMS normalisation fused around the head (h = x rstd gamma in front of it, its backward behind dH):
 // the forward is applied while the active rows are compacted, the backward while dH is scattered.
@@ -346,7 +346,7 @@ struct NormFuse {
 // Hc[i, :] = normalised row rows[i] of X (zeros on padding), yc[i] as launch_gather; then Hc -> HcT.
 void launch_norm_gather(const GatherArgs& g, const NormFuse& n, hipStream_t s);
 // dX[t, :] = RMSNorm backward of the accumulated dH row of t (zeros for rows that are not active); dgamma.
-void launch_scatter_dx_norm(const ScatterArgs& a, const NormFuse& n, const FinishArgs& fin, hipStream_t s);
+void launch_scatter_dx_norm(const ScatterArgs& a, const NormFuse& n, const FinishArgs& fin, const DwFoldArgs& fold, hipStream_t s);
 
 // out[t] = merge(a[t], b[t]) of two per-row softmax states (m, s, u, z_y), [T][4] each.
 void launch_merge_partials(const float* a, const float* b, float* out, long long T, hipStream_t s);

@@ -560,7 +560,8 @@ struct StoreShape {
     b_off = a.k_from_ctl ? (uint32_t)t0 * BM * 2u : 0u;
     ks = 1; products = 1; slab_rows = ctl.n_pad;
     if (a.split_k && a.m_from_ctl && nt * BM == ctl.n_pad) {
-      products = dh_slabs(ctl.n_pad, a.acc_rows, a.tiles_n, a.split_stages, a.A_lo != nullptr, ks) / ks;
+      ks = dh_split(ctl.n_pad, a.acc_rows, a.tiles_n, a.split_stages);
+      products = dh_products(ctl.n_pad, a.acc_rows, a.tiles_n, ks, a.A_lo != nullptr);
     } else if (a.dw_cap > 0) {
       ks = dw_split(K / BK, a.dw_cap);
       products = a.A_lo ? 3 : 1;
@@ -576,12 +577,19 @@ __device__ __forceinline__ void gemm_store_tile(StoreArgs a, const StoreShape& s
   const int tid = threadIdx.x;
   int tm, tn;
   map_tile_interleaved(b, sh.tiles_m * sh.ks * sh.products, a.tiles_n, tm, tn);
-  const int slab = tm / sh.tiles_m;                    // 0 unless the contraction is split
-  tm -= slab * sh.tiles_m;
-  const int part = slab / sh.products, product = slab - part * sh.products;
-  if (product == 1) { a.B = a.B_lo; a.ldb = a.ldb_lo; }
-  if (product == 2) a.A = a.A_lo;
-  const int s0 = (int)((long long)part * (sh.K / BK) / sh.ks), s1 = (int)((long long)(part + 1) * (sh.K / BK) / sh.ks);
+  // (divisions only where the contraction is split, and in 32 bits: they run in front of every tile's first load)
+  int slab = 0, part = 0, s0 = 0, s1 = sh.K / BK;
+  if (sh.ks * sh.products > 1) {
+    slab = tm / sh.tiles_m;
+    tm -= slab * sh.tiles_m;
+    part = sh.products == 3 ? slab / 3 : slab;
+    const int product = slab - part * sh.products;
+    if (product == 1) { a.B = a.B_lo; a.ldb = a.ldb_lo; }
+    if (product == 2) a.A = a.A_lo;
+    const unsigned stages = (unsigned)s1;              // below 2^23 (V or T in stages of 64), at most DW_SPLIT_MAX parts
+    s0 = (int)((unsigned)part * stages / (unsigned)sh.ks);
+    s1 = (int)((unsigned)(part + 1) * stages / (unsigned)sh.ks);
+  }
   const uint32_t kb = (uint32_t)s0 * BK * 2u;          // byte offset of this part's first k
 
   // (a tile here is hundreds of stages long: the claim for the next one simply travels under the main loop)

@@ -549,11 +549,48 @@ __device__ __forceinline__ void finish_loss(const FinishArgs& a) {
   if (tid < 8 && a.counters_out) a.counters_out[tid] = (long long)a.counters[tid];
 }
 
+// Adds the slabs of a split dW contraction (dw_split) in order, and the gradient that was there if it accumulates:
+// workgroup `group` of `groups` of 256.  With one vocab chunk they are workgroups of the scatter, behind the finish (a launch of
+// its own, which a call of few active rows makes for nothing, was 4.6 us).
+__device__ __forceinline__ void dw_fold(const DwFoldArgs& a, int group, int groups) {
+  const int slabs = dw_split(a.ctl->n_pad / BK, a.dw_cap) * a.products;
+  if (slabs == 1) return;                           // the contraction wrote dW itself
+  for (long long e = ((long long)group * 256 + threadIdx.x) * 4; e < a.n; e += (long long)groups * 256 * 4) {
+    f32x4 v = *reinterpret_cast<const f32x4*>(a.slabs + e);
+    for (int q = 1; q < slabs; ++q) v += *reinterpret_cast<const f32x4*>(a.slabs + q * a.slab + e);
+    if (a.out_bf16) {
+      bf16x4* p = reinterpret_cast<bf16x4*>(reinterpret_cast<__bf16*>(a.dW) + e);
+      if (a.accumulate) {
+        const bf16x4 old = *p;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[r] += (float)old[r];
+      }
+      bf16x4 o;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) o[r] = (__bf16)v[r];
+      *p = o;
+    } else {
+      f32x4* p = reinterpret_cast<f32x4*>(reinterpret_cast<float*>(a.dW) + e);
+      if (a.accumulate) v += *p;
+      *p = v;
+    }
+  }
+}
+__global__ __launch_bounds__(256) void dw_fold_kernel(DwFoldArgs a) { dw_fold(a, (int)blockIdx.x, (int)gridDim.x); }
+static int dw_fold_groups(const DwFoldArgs& a) {
+  const long long groups = (a.n / 4 + 255) / 256;
+  return (int)(groups < 2048 ? groups : 2048);
+}
+void launch_dw_fold(const DwFoldArgs& a, hipStream_t s) {
+  hipLaunchKernelGGL(dw_fold_kernel, dim3(dw_fold_groups(a)), dim3(256), 0, s, a);
+}
+
 // ------------------------------------------------------------------ dH scatter
 // dH[t,:] = accumulated row of its compacted position, or zeros for rows that are not active.
-__global__ __launch_bounds__(256) void scatter_dh_kernel(ScatterArgs a, FinishArgs fin) {
-  const int t = (int)blockIdx.x - 1;
-  if (t < 0) return finish_loss(fin);
+__global__ __launch_bounds__(256) void scatter_dh_kernel(ScatterArgs a, FinishArgs fin, DwFoldArgs fold, int fold_groups) {
+  const int t = (int)blockIdx.x - 1 - fold_groups;
+  if (blockIdx.x == 0) return finish_loss(fin);
+  if (t < 0) return dw_fold(fold, (int)blockIdx.x - 1, fold_groups);
   const int p = a.pos[t];
   const float* src = a.acc + (size_t)(p < 0 ? 0 : p) * a.d;
   const int n_pad = a.ctl->n_pad;
@@ -627,39 +664,10 @@ void launch_finish_partials(const float* parts, long long T, float* logp, float*
   hipLaunchKernelGGL(finish_partials_kernel, dim3((unsigned)((T + 255) / 256)), dim3(256), 0, s, parts, T, logp, ent, lse);
 }
 
-// Adds the slabs of a split dW contraction (dw_split) in order, and the gradient that was there if it accumulates.
-__global__ __launch_bounds__(256) void dw_fold_kernel(DwFoldArgs a) {
-  const int slabs = dw_split(a.ctl->n_pad / BK, a.dw_cap) * a.products;
-  if (slabs == 1) return;                           // the contraction wrote dW itself
-  for (long long e = ((long long)blockIdx.x * 256 + threadIdx.x) * 4; e < a.n; e += (long long)gridDim.x * 256 * 4) {
-    f32x4 v = *reinterpret_cast<const f32x4*>(a.slabs + e);
-    for (int q = 1; q < slabs; ++q) v += *reinterpret_cast<const f32x4*>(a.slabs + q * a.slab + e);
-    if (a.out_bf16) {
-      bf16x4* p = reinterpret_cast<bf16x4*>(reinterpret_cast<__bf16*>(a.dW) + e);
-      if (a.accumulate) {
-        const bf16x4 old = *p;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) v[r] += (float)old[r];
-      }
-      bf16x4 o;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) o[r] = (__bf16)v[r];
-      *p = o;
-    } else {
-      f32x4* p = reinterpret_cast<f32x4*>(reinterpret_cast<float*>(a.dW) + e);
-      if (a.accumulate) v += *p;
-      *p = v;
-    }
-  }
-}
-void launch_dw_fold(const DwFoldArgs& a, hipStream_t s) {
-  const long long blocks = (a.n / 4 + 255) / 256;
-  hipLaunchKernelGGL(dw_fold_kernel, dim3((unsigned)(blocks < 2048 ? blocks : 2048)), dim3(256), 0, s, a);
-}
-
-void launch_scatter_dh(const ScatterArgs& a, const FinishArgs& fin, hipStream_t s) {
+void launch_scatter_dh(const ScatterArgs& a, const FinishArgs& fin, const DwFoldArgs& fold, hipStream_t s) {
   if (a.T <= 0) return;
-  hipLaunchKernelGGL(scatter_dh_kernel, dim3(a.T + 1), dim3(256), 0, s, a, fin);
+  const int f = dw_fold_groups(fold);
+  hipLaunchKernelGGL(scatter_dh_kernel, dim3(a.T + 1 + f), dim3(256), 0, s, a, fin, fold, f);
 }
 
 // ------------------------------------------------------------------ rewards (Eq. 1, Eq. 6-7)
@@ -1199,8 +1207,9 @@ void launch_norm_gather(const GatherArgs& g, const NormFuse& n, hipStream_t s) {
 // and g xhat is added to the thread's dgamma partial sums; rows that are not active are written as
 // zeros and nothing of theirs is read.  The workgroups' partials are folded by rmsnorm_dgamma_kernel.
 template <bool F32, int NC>
-__global__ __launch_bounds__(256) void scatter_dx_norm_kernel(ScatterArgs a, NormFuse n, FinishArgs fin) {
-  if (blockIdx.x >= NORM_STRIPS) return finish_loss(fin);
+__global__ __launch_bounds__(256) void scatter_dx_norm_kernel(ScatterArgs a, NormFuse n, FinishArgs fin, DwFoldArgs fold) {
+  if (blockIdx.x == NORM_STRIPS) return finish_loss(fin);
+  if (blockIdx.x > NORM_STRIPS) return dw_fold(fold, (int)blockIdx.x - NORM_STRIPS - 1, (int)gridDim.x - NORM_STRIPS - 1);
   __shared__ float red[2][4];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const long long T = a.T;
@@ -1317,17 +1326,18 @@ __global__ __launch_bounds__(256) void scatter_dx_norm_kernel(ScatterArgs a, Nor
 }
 
 template <bool F32>
-static void launch_scatter_dx_norm_rows(const ScatterArgs& a, const NormFuse& n, const FinishArgs& fin, hipStream_t s) {
+static void launch_scatter_dx_norm_rows(const ScatterArgs& a, const NormFuse& n, const FinishArgs& fin, const DwFoldArgs& fold, hipStream_t s) {
+  const dim3 grid(NORM_STRIPS + 1 + dw_fold_groups(fold));
   switch ((a.d + 2047) / 2048) {     // 8-column steps per thread; d <= NORM_MAX_D is checked by the caller
-    case 1: hipLaunchKernelGGL((scatter_dx_norm_kernel<F32, 1>), dim3(NORM_STRIPS + 1), dim3(256), 0, s, a, n, fin); break;
-    case 2: hipLaunchKernelGGL((scatter_dx_norm_kernel<F32, 2>), dim3(NORM_STRIPS + 1), dim3(256), 0, s, a, n, fin); break;
-    case 3: hipLaunchKernelGGL((scatter_dx_norm_kernel<F32, 3>), dim3(NORM_STRIPS + 1), dim3(256), 0, s, a, n, fin); break;
-    default: hipLaunchKernelGGL((scatter_dx_norm_kernel<F32, NORM_NC>), dim3(NORM_STRIPS + 1), dim3(256), 0, s, a, n, fin); break;
+    case 1: hipLaunchKernelGGL((scatter_dx_norm_kernel<F32, 1>), grid, dim3(256), 0, s, a, n, fin, fold); break;
+    case 2: hipLaunchKernelGGL((scatter_dx_norm_kernel<F32, 2>), grid, dim3(256), 0, s, a, n, fin, fold); break;
+    case 3: hipLaunchKernelGGL((scatter_dx_norm_kernel<F32, 3>), grid, dim3(256), 0, s, a, n, fin, fold); break;
+    default: hipLaunchKernelGGL((scatter_dx_norm_kernel<F32, NORM_NC>), grid, dim3(256), 0, s, a, n, fin, fold); break;
   }
 }
-void launch_scatter_dx_norm(const ScatterArgs& a, const NormFuse& n, const FinishArgs& fin, hipStream_t s) {
-  if (a.out_f32) launch_scatter_dx_norm_rows<true>(a, n, fin, s);
-  else launch_scatter_dx_norm_rows<false>(a, n, fin, s);
+void launch_scatter_dx_norm(const ScatterArgs& a, const NormFuse& n, const FinishArgs& fin, const DwFoldArgs& fold, hipStream_t s) {
+  if (a.out_f32) launch_scatter_dx_norm_rows<true>(a, n, fin, fold, s);
+  else launch_scatter_dx_norm_rows<false>(a, n, fin, fold, s);
   NormArgs f{};
   f.d = a.d; f.partial = n.partial; f.dgamma = n.dgamma;
   hipLaunchKernelGGL(rmsnorm_dgamma_kernel, dim3((a.d + 31) / 32), dim3(256), 0, s, f);
