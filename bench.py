@@ -46,8 +46,8 @@ def measured_mfma_only_tflops():
 # summarised in profiles/gemm_store_kernel_hbm_traffic.md (mean over a step's 30 launches, of which 20 have work, each
 # counter scaled by what it reads for a plain 1 GiB copy).  Valid only for the kernel sources the
 # counters were taken with: the digest below is of csrc/gemm_core.h + csrc/kernels_gemm.hip.
-TRAFFIC_GEMM_STORE = {"read_bytes": 2571695.4 * 1024 * 2.000, "write_bytes": 312816.2 * 1024 * 1.000,
-                      "sources_sha256": "85136be90727f0e6ffea030ec2f677e0f1b0f2d540f0eee691b0d1c6e224e2e1"}
+TRAFFIC_GEMM_STORE = {"read_bytes": 2576718.2 * 1024 * 2.000, "write_bytes": 312800.9 * 1024 * 1.000,
+                      "sources_sha256": "fa7b9aa27c970ea64edd464849a5abadef2f25758da5a2dabbc3c7685c1c7a45"}
 
 
 def kernel_sources_digest() -> str:

@@ -93,7 +93,9 @@ struct TokenBlocks {
 };
 // Where keeping pays, by the contraction length K that a recompute would repeat (once more for the remainders of an fp32
 // head): K = 512 1990 us kept against 1811 us recomputed, 768 2440 / 2390, 1024 2866 / 2990, 2048 4620 / 5370 (4000 rows,
-// V = 103936); and always where no workgroup has more than one tile to recompute (latency).  Token blocks pass over
+// V = 103936); and always where no workgroup has more than one tile to recompute, which is a latency: recomputed against kept,
+// 3 tiles K = 64 71 / 74 us, 256 88 / 88, 1024 115 / 101, fp32 d = 64 102 / 85; 256 tiles K = 64 110 / 120, 512 164 / 166, 1024
+// 207 / 200, fp32 d = 64 174 / 181 (not worth a rule of its own: the heads that are trained have K of 1024 and more).  Token blocks pass over
 // dW and W once more per block: 33912 rows, K = 1024 27.3 ms in blocks against 24.9 ms in one, 1536 31.3 / 33.1,
 // 3072 55.8 / 58.5.  And the dH contraction of a block runs over the whole vocabulary however few tiles the block has
 // (the rows that remain in the last block above all), so a full block has to fill the chip well, two rounds at least.

@@ -19,7 +19,8 @@ int main() {
   EXPECT(pg_logprob_fwd(one, one, (const int32_t*)one, nullptr, 8, 72, 100, &p, (float*)one, nullptr, nullptr, one, big, nullptr), PG_ERR_UNSUPPORTED_SHAPE);
   for (int64_t T : {0ll, 1ll, 255ll, 43697ll, (1ll << 30)})
     for (int64_t V : {1ll, 1000ll, 151936ll})
-      for (int dt = 0; dt < 2; ++dt) { p.dtype = dt; (void)pg_workspace_bytes(T, 5120, V, 50, &p, PG_CALL_LOSS_FWD_BWD); (void)pg_workspace_bytes(T, 64, V, 0, &p, PG_CALL_LOGPROB_FWD); }
+      for (int dt = 0; dt < 2; ++dt) { p.dtype = dt; (void)pg_workspace_bytes(T, 5120, V, 50, &p, PG_CALL_LOSS_FWD_BWD); (void)pg_workspace_bytes(T, 64, V, 0, &p, PG_CALL_LOGPROB_FWD);
+        for (int call = 0; call < 5; ++call) (void)pg_workspace_min_bytes(T, 5120, V, 50, &p, call); }
   p.dtype = 0;
   p.mismatch_mode = 1;
   EXPECT(pg_loss_fwd_bwd(one, one, (const int32_t*)one, (const uint8_t*)one, (const int32_t*)one, 1, (const double*)one, nullptr, nullptr, (const float*)one, nullptr, 8, 64, 100, &p, (float*)one, one, one, nullptr, nullptr, nullptr, one, big, nullptr), PG_ERR_INVALID_ARG);
