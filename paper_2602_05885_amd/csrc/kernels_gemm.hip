@@ -556,7 +556,7 @@ struct StoreShape {
     token_block(a.blk, ctl.n_pad / BM, t0, nt);
     m_lim = a.m_from_ctl ? min(a.M, nt * BM) : a.M;
     tiles_m = min(a.tiles_m, (m_lim + BM - 1) / BM);
-    K = a.k_from_ctl ? nt * BM : a.K;
+    K = a.k_from_ctl ? min(nt * BM, dw_stages(ctl.n_active - t0 * BM) * BK) : a.K;
     b_off = a.k_from_ctl ? (uint32_t)t0 * BM * 2u : 0u;
     ks = 1; products = 1; slab_rows = ctl.n_pad;
     if (a.split_k && a.m_from_ctl && nt * BM == ctl.n_pad) {

@@ -553,7 +553,7 @@ __device__ __forceinline__ void finish_loss(const FinishArgs& a) {
 // workgroup `group` of `groups` of 256.  With one vocab chunk they are workgroups of the scatter, behind the finish (a launch of
 // its own, which a call of few active rows makes for nothing, was 4.6 us).
 __device__ __forceinline__ void dw_fold(const DwFoldArgs& a, int group, int groups) {
-  const int slabs = dw_split(a.ctl->n_pad / BK, a.dw_cap) * a.products;
+  const int slabs = dw_split(dw_stages(a.ctl->n_active), a.dw_cap) * a.products;
   if (slabs == 1) return;                           // the contraction wrote dW itself
   for (long long e = ((long long)group * 256 + threadIdx.x) * 4; e < a.n; e += (long long)groups * 256 * 4) {
     f32x4 v = *reinterpret_cast<const f32x4*>(a.slabs + e);
