@@ -514,34 +514,52 @@ __global__ __launch_bounds__(KEPT_THREADS, 2) void dlogits_kept_kernel(DlogitsAr
 // lane owns 4 consecutive n of one m and C[m, n..n+3] leaves as one 16-byte (fp32) or 8-byte (bf16)
 // access; N is a multiple of 4.  (Accumulating with fp32 adds performed at the L2 instead of the
 // read-modify-write below was measured 6 % slower on the dH contraction.)
-template <typename OutT>
+// A lane pair (columns 2q, 2q + 1) swaps half of two MFMA tiles first, so that an instruction writes 128 bytes of each of 8
+// rows: pieces of 64 bytes go through a compute unit at half the rate (256 KiB of stores alone, at any number of active
+// compute units: 16 rows x 64 B 7.6 us, whole rows 3.7 us; all 256 at once 12 us, the HBM's rate).  STORE_FIGURES
+// The old values of an accumulated output are requested one column ahead of the stores.
+__device__ __forceinline__ float of_lane_pair(float x) {      // x of lane ^ 1
+  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), 0xB1, 0xf, 0xf, true));
+}
+template <typename OutT, bool ACCUMULATE>
 __device__ __forceinline__ void store_tile(const StoreArgs& a, int tm, int tn, int m_lim, f32x4 (&acc)[GM][GN]) {
+  typedef __attribute__((ext_vector_type(4))) OutT out4;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave / WN, wn = wave % WN;
-  OutT* C = reinterpret_cast<OutT*>(a.C);
+  const bool odd = lane & 1;
+  const int n_w = tn * BN + wm * WROWS;
+  if (n_w >= a.N) return;                              // (N is a multiple of 64)
+  const int m0 = tm * BM + wn * WCOLS + (lane & 14);
+  OutT* const C = reinterpret_cast<OutT*>(a.C) + (size_t)m0 * a.ldc + n_w + (odd ? 16 : 0) + ((lane >> 4) << 2);
+  out4 old[2][GM];
+  auto fetch = [&](int j) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      if (m0 + j * 16 + h < m_lim)
+#pragma unroll
+        for (int i = 0; i < GM; i += 2) old[j & 1][i + h] = *reinterpret_cast<const out4*>(C + (size_t)(j * 16 + h) * a.ldc + i * 16);
+  };
+  if (ACCUMULATE) fetch(0);
 #pragma unroll
   for (int j = 0; j < GN; ++j) {
-    const int m = tm * BM + wn * WCOLS + j * 16 + (lane & 15);
-    if (m >= m_lim) continue;
+    if (ACCUMULATE && j + 1 < GN) fetch(j + 1);
 #pragma unroll
-    for (int i = 0; i < GM; ++i) {
-      const int n0 = tn * BN + wm * WROWS + i * 16 + ((lane >> 4) << 2);
-      if (n0 >= a.N) continue;
-      OutT* p = C + (size_t)m * a.ldc + n0;
-      f32x4 v = acc[i][j];
-      if constexpr (sizeof(OutT) == 4) {
-        if (a.accumulate) v += *reinterpret_cast<const f32x4*>(p);
-        *reinterpret_cast<f32x4*>(p) = v;
-      } else {
-        if (a.accumulate) {
-          const bf16x4 old = *reinterpret_cast<const bf16x4*>(p);
+    for (int i = 0; i < GM; i += 2) {
+      f32x4 v[2];                                      // columns 2q and 2q + 1; even lanes MFMA tile i of both, odd lanes i + 1
 #pragma unroll
-          for (int r = 0; r < 4; ++r) v[r] += (float)old[r];
-        }
-        bf16x4 o;
+      for (int r = 0; r < 4; ++r) {
+        const float lo = acc[i][j][r], hi = acc[i + 1][j][r];
+        const float lo_x = of_lane_pair(lo), hi_x = of_lane_pair(hi);
+        v[0][r] = odd ? hi_x : lo;
+        v[1][r] = odd ? hi : lo_x;
+      }
 #pragma unroll
-        for (int r = 0; r < 4; ++r) o[r] = (__bf16)v[r];
-        *reinterpret_cast<bf16x4*>(p) = o;
+      for (int h = 0; h < 2; ++h) {
+        if (m0 + j * 16 + h >= m_lim) continue;
+        out4 o;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) o[r] = (OutT)(ACCUMULATE ? v[h][r] + (float)old[j & 1][i + h][r] : v[h][r]);
+        *reinterpret_cast<out4*>(C + (size_t)(j * 16 + h) * a.ldc + i * 16) = o;
       }
     }
   }
@@ -617,10 +635,13 @@ __device__ __forceinline__ void gemm_store_tile(StoreArgs a, const StoreShape& s
   before_stores();
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // the claim is visible behind this barrier
   a.C = static_cast<char*>(a.C) + (size_t)slab * sh.slab_rows * a.ldc * (a.out_bf16 ? 2 : 4);
-  if (a.out_bf16)
-    store_tile<__bf16>(a, tm, tn, sh.m_lim, acc);
-  else
-    store_tile<float>(a, tm, tn, sh.m_lim, acc);
+  if (a.out_bf16) {
+    if (a.accumulate) store_tile<__bf16, true>(a, tm, tn, sh.m_lim, acc);
+    else store_tile<__bf16, false>(a, tm, tn, sh.m_lim, acc);
+  } else {
+    if (a.accumulate) store_tile<float, true>(a, tm, tn, sh.m_lim, acc);
+    else store_tile<float, false>(a, tm, tn, sh.m_lim, acc);
+  }
 }
 
 template <bool DIRECT>
