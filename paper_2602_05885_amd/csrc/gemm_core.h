@@ -61,7 +61,7 @@ constexpr int EPI_STRIDE = 528;                  // 132 dwords
 constexpr int EPI_STRIDE_T = 544;                // 136 dwords
 constexpr int GEMM_LDS_BYTES = 256 * EPI_STRIDE_T; // 136 KiB >= the 128 KiB double-buffered main loop
 static_assert(GEMM_LDS_BYTES >= 2 * STAGE_BYTES, "LDS budget");
-static_assert(GM == 4 && GN == 8, "the main loop's 16-step schedule is written for 4 x 8 MFMA tiles per wavefront");
+static_assert(GM == 4 && GN == 8, "the main loop's schedule is written for 4 x 8 MFMA tiles per wavefront");
 
 // ---- control block written by the row-compaction kernel (device memory) ----
 struct Ctl {
@@ -477,7 +477,35 @@ __device__ __forceinline__ void pick_stage(const TileSrc cur, const TileSrc nxt,
   r = t.rsrc();
 }
 
-// One tile of the stream: acc += A(256 x K) B(256 x K)^T with K = 64 nk.
+// The last token tile of the forward may hold few rows.  A tile of `cols` live columns runs NJ = 8, 6 or 4 of the 8 MFMA columns
+// of every wavefront.  A stage of NJ = 4 is as long as its loads, so nothing shorter; and where a vocab tile has more than two
+// token tiles, one that ends early starts the next before the others are there and their W no longer meets in the L2
+// (d = 4096, V = 151936, 677 rows: 3.7 GB read instead of 1.8), so NJ = 6 loses what it saves.  Forward-only call, whole
+// tiles against this: 128 rows 300 -> 272 us, 192 318 -> 290, 384 500 -> 488, 448 527 -> 520, 640 727 -> 720, 2176 2156 -> 2081; NJ = 6
+// at 704 rows 743 -> 755, at 1216 1208 -> 1233.  (The dH contraction and the recompute of the logits gained nothing: +-0.3 %.)
+__host__ __device__ inline int fwd_nj(int cols, int tiles_t) { return cols > (tiles_t > 2 ? 128 : 192) ? 8 : cols > 128 ? 6 : 4; }
+
+// The two wavefronts of a row take the 16-column groups of the tile in turn, so that the first NJ MFMA columns of both are its
+// first 32 NJ columns:
+__device__ __forceinline__ int stream_col(int j, int wn, int lane) { return j * (16 * WN) + wn * 16 + (lane & 15); }
+
+// The schedule: NJ = 6 leaves out four of the 16 steps; NJ = 4 has half of them, reads two A fragments per step, passes X after
+// step 2 and issues the A loads in steps 3..5.  The loads are those of a whole tile (columns beyond the operand read as zero).
+template <int NJ>
+struct Steps {
+  static constexpr int NS = 2 * NJ;          // steps per stage
+  static constexpr int TAIL = 2;             // steps behind barrier Y
+  static constexpr int A_READS = NJ == 4 ? 2 : 1;      // A fragments of the second k-half read per step
+  static constexpr int XS = NJ == 4 ? 2 : 4; // barrier X follows this step
+  static constexpr int BH = CHUNKS / 2;      // B loads per half
+  // A loads [first, last) of step s
+  static constexpr int a_first(int s) { return s <= XS ? 0 : NJ == 4 ? (s == XS + 1 ? 0 : s - XS) : s - XS - 1; }
+  static constexpr int a_last(int s) { return s <= XS ? 0 : NJ == 4 ? s - XS + 1 : s - XS; }
+  static_assert(NJ == 4 || NJ == 6 || NJ == 8, "steps in multiples of four: B fragments rotate through four registers");
+  static_assert(CHUNKS == 4 && GM == 4 && BH <= XS && a_last(NS - TAIL - 1) >= CHUNKS && GM / A_READS <= XS && GM / A_READS <= NJ, "schedule");
+};
+
+// One tile of the stream: acc += A(256 x K) B(256 x K)^T with K = 64 nk, for the first 32 NJ columns.
 //   A0, B0    operand sources of this tile; A1, B1 of the next one (bytes = 0 where the stream
 //             ends).  A tile of a single stage (nk = 1) cannot run ahead by two stages: the caller
 //             then passes switched-off next sources, cold = true for every tile, and waits for
@@ -488,19 +516,20 @@ __device__ __forceinline__ void pick_stage(const TileSrc cur, const TileSrc nxt,
 // On return the first two stages of the next tile are in the stage buffers or on their way (this
 // wavefront's newest CHUNKS + BH loads may still be in flight) and nobody reads the buffers until the
 // next call's opening barrier.
+template <int NJ>
 __device__ __forceinline__ void mainloop_stream(const OperandLanes& VA, const OperandLanes& VB, const TileSrc A0,
                                                 const TileSrc B0, const TileSrc A1, const TileSrc B1, int nk,
                                                 bool cold, int par0, char* smem,
                                                 f32x4 (&acc)[GM][GN]) {
-  constexpr int NS = 2 * GN, TAIL = 2, XS = 4, BH = CHUNKS / 2;
-  static_assert(CHUNKS == 4 && BH <= XS && XS + CHUNKS < NS - TAIL, "load schedule");
+  typedef Steps<NJ> St;
+  constexpr int NS = St::NS, TAIL = St::TAIL, XS = St::XS, BH = St::BH;
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WN, wn = wave % WN;
   const int lrow = lane & 15;
   const int xr = (lane >> 1) & 7;
   const uint32_t a_off = (uint32_t)(wm * WROWS + lrow) * 128u;
-  const uint32_t b_off = (uint32_t)(wn * WCOLS + lrow) * 128u + SLAB_BYTES;
+  const uint32_t b_off = (uint32_t)(wn * 16 + lrow) * 128u + SLAB_BYTES;
   uint32_t koff[2];
 #pragma unroll
   for (int ks = 0; ks < 2; ++ks) koff[ks] = (uint32_t)(((ks * 4 + (lane >> 4)) ^ xr) << 4);
@@ -510,7 +539,7 @@ __device__ __forceinline__ void mainloop_stream(const OperandLanes& VA, const Op
     return *reinterpret_cast<const bf16x8*>(st + a_off + i * (16 * 128) + koff[ks]);
   };
   auto rdB = [&](const char* st, int s) -> bf16x8 {
-    return *reinterpret_cast<const bf16x8*>(st + b_off + (s % GN) * (16 * 128) + koff[s / GN]);
+    return *reinterpret_cast<const bf16x8*>(st + b_off + (s % NJ) * (32 * 128) + koff[s / NJ]);
   };
 
   if (cold) {   // stage 0 complete, A and the first half of B of stage 1
@@ -551,11 +580,13 @@ __device__ __forceinline__ void mainloop_stream(const OperandLanes& VA, const Op
     pick_stage(B0, B1, kt + 2, nk, rb2, kb2b);
 #pragma unroll
     for (int s = 0; s < NS - TAIL; ++s) {
-      const int ks = s / GN, j = s % GN;
+      const int ks = s / NJ, j = s % NJ;
       bq[(s + 2) & 3] = rdB(cur, s + 2);
-      if (s < GM) a[1][s] = rdA(cur, 1, s);
+#pragma unroll
+      for (int q = s * St::A_READS; q < (s + 1) * St::A_READS && q < GM; ++q) a[1][q] = rdA(cur, 1, q);
       if (s < BH) issue_lds(rb1, VB, BH + s, kb1, nxt + SLAB_BYTES, wave);
-      if (s > XS && s <= XS + CHUNKS) issue_lds(ra2, VA, s - XS - 1, kb2, cur, wave);
+#pragma unroll
+      for (int q = St::a_first(s); q < St::a_last(s) && q < CHUNKS; ++q) issue_lds(ra2, VA, q, kb2, cur, wave);
 #pragma unroll
       for (int i = 0; i < GM; ++i)
         acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[ks][i], bq[s & 3], acc[i][j], 0, 0, 0);
@@ -566,7 +597,7 @@ __device__ __forceinline__ void mainloop_stream(const OperandLanes& VA, const Op
 #pragma unroll
     for (int m = 0; m < TAIL * GM; ++m) {
       const int s = NS - TAIL + m / GM, i = m % GM;
-      const int ks = s / GN, j = s % GN;
+      const int ks = s / NJ, j = s % NJ;
       if (m == 0) bq[0] = rdB(nxt, 0);
       else if (m <= GM) a[0][m - 1] = rdA(nxt, 0, m - 1);
       else if (m == GM + 1) bq[1] = rdB(nxt, 1);
@@ -575,6 +606,13 @@ __device__ __forceinline__ void mainloop_stream(const OperandLanes& VA, const Op
       __builtin_amdgcn_sched_barrier(0);
     }
   }
+}
+__device__ __forceinline__ void mainloop_stream(const OperandLanes& VA, const OperandLanes& VB, const TileSrc A0, const TileSrc B0,
+                                                const TileSrc A1, const TileSrc B1, int nk, bool cold, int par0, int nj, char* smem,
+                                                f32x4 (&acc)[GM][GN]) {
+  if (nj == 8) mainloop_stream<8>(VA, VB, A0, B0, A1, B1, nk, cold, par0, smem, acc);
+  else if (nj == 6) mainloop_stream<6>(VA, VB, A0, B0, A1, B1, nk, cold, par0, smem, acc);
+  else mainloop_stream<4>(VA, VB, A0, B0, A1, B1, nk, cold, par0, smem, acc);
 }
 
 // ---- tile queue of the persistent kernels ----------------------------------------------------------

@@ -3,7 +3,7 @@
 //
 // Accumulator layout they all rely on: acc[i][j][r] of lane l is
 //   engine row     wm*64  + i*16 + 4*(l>>4) + r      (i < 4, r < 4)
-//   engine column  wn*128 + j*16 + (l & 15)          (j < 8)
+//   engine column  wn*128 + j*16 + (l & 15)          (j < 8; in the forward j*32 + wn*16 + (l & 15))
 // so one lane holds 16 rows of each of its 8 columns, and the four 16-lane groups of a
 // wavefront hold the other 48 rows of the same columns.  The two logits kernels put the
 // vocabulary on the rows (a token's statistics then reduce inside a lane first); the store
@@ -50,6 +50,9 @@ constexpr int FWD_STASH_OFF = FWD_RED_OFF + WM * 256 * 3 * 4; // [2][256] ints
 constexpr int FWD_CLAIM_OFF = FWD_STASH_OFF + 2 * 256 * 4;    // [4] ints
 constexpr int FWD_LDS_BYTES = FWD_CLAIM_OFF + 16;
 
+// Kept tiles, in units of f32x4: 16 (4 i + r-groups of lanes) x 16-column groups c of every 64-row group wm, 64 lanes each.
+__device__ __forceinline__ int kept_column(int wm, int c) { return (wm * (BN / 16) + c) * (GM * 64); }
+
 // PROBE = true (the stand-alone measurement tool only) records wall-clock and shader-clock stamps of
 // tiles PROBE_FIRST .. PROBE_FIRST + PROBE_TILES - 1 of every workgroup in tl[wg][tile][4] (main loop
 // start, main loop end, epilogue end, shader clock at the epilogue's end) and lets the tool switch the
@@ -63,7 +66,8 @@ __device__ __forceinline__ void lmhead_fwd_body(FwdArgs a, bool steal, unsigned 
   token_block(a.blk, ctl.n_pad / BN, t0, nt);
   const int tiles_t = min(a.tiles_t, nt);                      // live token tiles: known only on the device
   if (tiles_t <= 0) return;
-  a.Hc = static_cast<const char*>(a.Hc) + (size_t)t0 * BN * a.ldh * 2; a.h_rows -= t0 * BN;
+  const int live_rows = ctl.n_active - t0 * BN;                // of this block and those behind it
+  a.Hc = static_cast<const char*>(a.Hc) + (size_t)t0 * BN * a.ldh * 2; a.h_rows = min(a.h_rows - t0 * BN, live_rows);
   a.yc += t0 * BN; a.zy += t0 * BN;
   a.part_m += t0 * BN; a.part_s += t0 * BN; a.part_u += t0 * BN;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -109,7 +113,8 @@ __device__ __forceinline__ void lmhead_fwd_body(FwdArgs a, bool steal, unsigned 
     const bool probe = PROBE && tl && tid == 0 && n >= PROBE_FIRST && n < PROBE_FIRST + PROBE_TILES;
     unsigned long long* stamp = probe ? tl + ((size_t)blockIdx.x * PROBE_TILES + (n - PROBE_FIRST)) * 4 : nullptr;
     if (probe) stamp[0] = wall_clock64();
-    mainloop_stream(VA, VB, A0, B0, A1, B1, nk, n == 0 || !ahead, par, g_smem, acc);
+    const int nj = fwd_nj(live_rows - tn * BN, tiles_t);
+    mainloop_stream(VA, VB, A0, B0, A1, B1, nk, n == 0 || !ahead, par, nj, g_smem, acc);
     par = (par + nk) & 1;
     if (probe) stamp[1] = wall_clock64();
     if (!ahead) asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
@@ -130,15 +135,17 @@ __device__ __forceinline__ void lmhead_fwd_body(FwdArgs a, bool steal, unsigned 
     // under them (d = 5120, V = 151936, all tiles kept: 609 -> 640 us at 768 rows; at 32768 rows in two token blocks
     // 36.4 -> 36.5 ms)
     if (tm < kept_v) {
-      f32x4* kp = reinterpret_cast<f32x4*>(a.kept.tiles + ((size_t)tm * tiles_t + tn) * KEPT_TILE_FLOATS) + wave * (GM * GN * 64) + lane;
+      f32x4* kp = reinterpret_cast<f32x4*>(a.kept.tiles + ((size_t)tm * tiles_t + tn) * KEPT_TILE_FLOATS) + kept_column(wm, wn) + lane;
 #pragma unroll
-      for (int j = 0; j < GN; ++j)
+      for (int j = 0; j < GN; ++j) {
+        if (j >= nj) continue;
 #pragma unroll
-        for (int i = 0; i < GM; ++i) __builtin_nontemporal_store(acc[i][j], kp + (j * GM + i) * 64);
+        for (int i = 0; i < GM; ++i) __builtin_nontemporal_store(acc[i][j], kp + (kept_column(0, j * WN) + i * 64));
+      }
     }
 #pragma unroll
     for (int j = 0; j < GN; ++j) {
-      const int tok_l = wn * WCOLS + j * 16 + (lane & 15);
+      const int tok_l = stream_col(j, wn, lane);
       const int tok = tn * BN + tok_l;
       float mr = NEG_BIG;
 #pragma unroll
@@ -421,6 +428,7 @@ __global__ __launch_bounds__(NTHREADS) void lmhead_dlogits_kernel(DlogitsArgs a)
     a.v0 = 0; a.tiles_v = a.rc.tiles_v_all; a.ld_s = a.rc.ld_s_all; a.ld_t = ld_t_all;
   }
   const int tiles_t = min(a.tiles_t, ctl.n_pad / BN);   // live token tiles: known only on the device
+  a.h_rows = min(a.h_rows, ctl.n_active);
   const int skip = kept_in_chunk(a, tiles_t);           // these are finished by dlogits_kept_kernel
   a.v0 += skip * BM; a.tiles_v -= skip;
   a.dS += skip * BM; a.dST += (size_t)skip * BM * a.ld_t;
@@ -439,7 +447,7 @@ __global__ __launch_bounds__(NTHREADS) void lmhead_dlogits_kernel(DlogitsArgs a)
 
 // dS of the vocab tiles whose logits the forward kept: the epilogue of the recompute with the accumulators
 // read back instead of computed.  Bound by HBM (256 KiB read and 256 KiB written per 256 x 256 tile); a
-// workgroup takes 256 vocab rows x 128 tokens, i.e. four wavefronts of a kept tile, so that two fit a
+// workgroup takes 256 vocab rows x 128 tokens, i.e. half of a kept tile, so that two fit a
 // compute unit (72 KiB of LDS each) and one's loads run under the other's stores.  Measured at d = 5120,
 // V = 151936: 768 rows 119 us (recompute 639 us; 7.8 TB/s, part of the kept tiles still sits in the
 // memory-side cache), 32768 rows in two token blocks 7.7 ms, 5.2 TB/s, above the rate of a plain copy (recompute
@@ -466,19 +474,27 @@ __global__ __launch_bounds__(KEPT_THREADS, 2) void dlogits_kept_kernel(DlogitsAr
   const int tid = threadIdx.x, lane = tid & 63, wm = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int tm0 = a.v0 / BM;
   f32x4 acc[GM][GN];
-  auto fetch = [&](int h) {
+  // 16-column groups [8 half, 8 half + 8) of kept tile h / 2; those beyond the live ones were not parked and count as zero
+  auto fetch = [&](int h, int groups) {
     const f32x4* kp = reinterpret_cast<const f32x4*>(a.kept.tiles + ((size_t)tm0 * tiles_t + (h >> 1)) * KEPT_TILE_FLOATS) +
-                      (wm * WN + (h & 1)) * (GM * GN * 64) + lane;
+                      kept_column(wm, (h & 1) * GN) + lane;
 #pragma unroll
     for (int j = 0; j < GN; ++j)
+      if (j < groups) {
 #pragma unroll
-      for (int i = 0; i < GM; ++i) acc[i][j] = __builtin_nontemporal_load(kp + (j * GM + i) * 64);
+        for (int i = 0; i < GM; ++i) acc[i][j] = __builtin_nontemporal_load(kp + (kept_column(0, j) + i * 64));
+      } else {
+#pragma unroll
+        for (int i = 0; i < GM; ++i) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
   };
   for (int item = blockIdx.x; item < total; item += gridDim.x) {
     const bool rest = SPLIT && item >= halves;        // fp32 heads: the remainders as items of their own
     const int h = rest ? item - halves : item;
-    fetch(h);
     const int tm = (h >> 1) / tiles_t, tn = (h >> 1) - tm * tiles_t, half = h & 1;
+    const int groups = WN * fwd_nj(ctl.n_active - (t0 + tn) * BN, tiles_t) - half * GN;
+    if (groups <= 0) continue;                        // 128 columns without a row: nobody reads their dS
+    fetch(h, groups);
     const size_t o_s = ((size_t)tn * BN + half * WCOLS) * a.ld_s + (size_t)tm * BM;
     const size_t o_t = ((size_t)tm * BM) * a.ld_t + (size_t)tn * BN + half * WCOLS;
     uint32_t pk[GM][GN][2];
@@ -572,7 +588,7 @@ struct StoreShape {
   uint32_t b_off;         // dW: byte offset of the block's first column in a row of H^T
   __device__ __forceinline__ void init(const StoreArgs& a, const Ctl& ctl) {
     token_block(a.blk, ctl.n_pad / BM, t0, nt);
-    m_lim = a.m_from_ctl ? min(a.M, nt * BM) : a.M;
+    m_lim = a.m_from_ctl ? min(a.M, max(0, min(nt * BM, ctl.n_active - t0 * BM))) : a.M;      // (rows beyond the active ones: nobody reads them)
     tiles_m = min(a.tiles_m, (m_lim + BM - 1) / BM);
     K = a.k_from_ctl ? min(nt * BM, dw_stages(ctl.n_active - t0 * BM) * BK) : a.K;
     b_off = a.k_from_ctl ? (uint32_t)t0 * BM * 2u : 0u;
