@@ -73,7 +73,7 @@ struct Ctl {
 
 // ---- workgroup -> tile mapping -------------------------------------------------
 // Workgroups are dealt round-robin to the 8 XCDs, each with a private L2.  The flattened tile
-// order (panels of 8 n-tiles; inside a panel, groups of 4 m-tiles, so 32 consecutive tiles form
+// order (panels of n-tiles; inside a panel, groups of 4 m-tiles, so 32 consecutive tiles form
 // a 4 x 8 block whose A slabs are shared by 8 and B slabs by 4 workgroups) is cut into 8 equal
 // contiguous ranges, one per XCD: the 32 workgroups resident on an XCD work on one such block
 // out of that XCD's L2, and every XCD gets the same number of tiles to within one.
@@ -89,21 +89,34 @@ __host__ __device__ inline int grid_for_tiles(int tiles_m, int tiles_n) {
 __host__ __device__ inline int imin(int a, int b) { return a < b ? a : b; }
 __host__ __device__ inline int imax(int a, int b) { return a > b ? a : b; }
 
-__host__ __device__ inline bool map_tile(int bid, int tiles_m, int tiles_n, int& tm, int& tn) {
+// Entry t of the flattened order: panels of `width` n-tiles, inside a panel groups of SB_M m-tiles with m running fastest, or
+// (n_first) one m-tile after the other.  A block of 32 is 4 x 8 tiles either way; what differs is which operand is asked for by
+// workgroups that start close in time, and so is still in the 4 MiB L2 when the last of them gets to it.
+__host__ __device__ inline void flat_tile(int t, int tiles_m, int tiles_n, int width, bool n_first, int& tm, int& tn) {
+  const int panel_tiles = width * tiles_m;
+  const int p = t / panel_tiles;
+  const int w = imin(width, tiles_n - p * width);
+  const int idx = t - p * panel_tiles;
+  if (n_first) {
+    tm = idx / w;
+    tn = p * width + (idx - tm * w);
+    return;
+  }
+  const int mg = idx / (SB_M * w);
+  const int rig = imin(SB_M, tiles_m - mg * SB_M);
+  const int rem = idx - mg * SB_M * w;
+  tm = mg * SB_M + rem % rig;
+  tn = p * width + rem / rig;
+}
+
+// (a panel is SB_N token tiles wide)
+__host__ __device__ inline bool map_tile(int bid, int tiles_m, int tiles_n, int& tm, int& tn, bool n_first = false) {
   const int total = tiles_m * tiles_n;   // may be smaller than what the grid was sized for
   const int per = (total + 7) / 8;
   const int xcd = bid & 7, q = bid >> 3;
   const int t = xcd * per + q;
   if (q >= per || t >= total) return false;
-  const int panel_tiles = SB_N * tiles_m;
-  const int p = t / panel_tiles;
-  const int w = imin(SB_N, tiles_n - p * SB_N);
-  const int idx = t - p * panel_tiles;
-  const int mg = idx / (SB_M * w);
-  const int rig = imin(SB_M, tiles_m - mg * SB_M);
-  const int rem = idx - mg * SB_M * w;
-  tm = mg * SB_M + rem % rig;
-  tn = p * SB_N + rem / rig;
+  flat_tile(t, tiles_m, tiles_n, SB_N, n_first, tm, tn);
   return true;
 }
 
@@ -113,8 +126,13 @@ __host__ __device__ inline bool map_tile(int bid, int tiles_m, int tiles_n, int&
 // The last (< 256) tiles are split evenly.  Pays when the n-panel (B rows x K) is too large to
 // stay cached while an XCD walks the whole M extent on its own: measured +1..3 % on the dW and
 // dH contractions, -1.5 % on the logits contraction (whose token panels do stay cached).
-__host__ __device__ inline bool map_tile_interleaved(int bid, int tiles_m, int tiles_n, int& tm, int& tn) {
-  const int total = tiles_m * tiles_n;
+// d <= 8192 is one panel: panels of 8 took the loss calls of d = 4096, 4100 rows from 12.98 to 13.06 ms, of d = 5120, 32768
+// rows from 114.5 to 115.5.
+// A contraction cut into `slabs` parts has the tiles of one part after those of the other (parts share no operand): dH of
+// 675 rows, d = 5120, 3.5 -> 2.8 GB read, 630 -> 570 us.
+constexpr int STORE_PANEL = 32;
+__host__ __device__ inline bool map_tile_interleaved(int bid, int tiles_m, int tiles_n, int slabs, int& slab, int& tm, int& tn) {
+  const int per_slab = tiles_m * tiles_n, total = per_slab * slabs;
   const int full = (total / 256) * 256;
   const int xcd = bid & 7, q = bid >> 3;
   int t;
@@ -125,16 +143,17 @@ __host__ __device__ inline bool map_tile_interleaved(int bid, int tiles_m, int t
     t = full + xcd * per + qq;
     if (qq >= per || t >= total) return false;
   }
-  const int panel_tiles = SB_N * tiles_m;
-  const int p = t / panel_tiles;
-  const int w = imin(SB_N, tiles_n - p * SB_N);
-  const int idx = t - p * panel_tiles;
-  const int mg = idx / (SB_M * w);
-  const int rig = imin(SB_M, tiles_m - mg * SB_M);
-  const int rem = idx - mg * SB_M * w;
-  tm = mg * SB_M + rem % rig;
-  tn = p * SB_N + rem / rig;
+  slab = 0;
+  if (slabs > 1) {
+    slab = t / per_slab;
+    t -= slab * per_slab;
+  }
+  flat_tile(t, tiles_m, tiles_n, STORE_PANEL, false, tm, tn);
   return true;
+}
+__host__ __device__ inline bool map_tile_interleaved(int bid, int tiles_m, int tiles_n, int& tm, int& tn) {
+  int slab;
+  return map_tile_interleaved(bid, tiles_m, tiles_n, 1, slab, tm, tn);
 }
 
 // Split-K factor of the dH contraction.  Its row extent is the padded number of active tokens, known only on

@@ -75,6 +75,11 @@ __device__ __forceinline__ void lmhead_fwd_body(FwdArgs a, bool steal, unsigned 
   TileQueue Q;
   Q.init(a.queue, a.tiles_v * tiles_t, 0);
   const int kept_v = kept_vocab_tiles(a.kept, a.tiles_v, tiles_t);
+  // Tile order: W is shared by more tiles than H and comes first, unless tiles are parked: the block's stores are then spread
+  // better with the vocabulary running fastest.  Forward-only calls, vocabulary first against tokens first: d = 4096, 768 rows
+  // 732 -> 722 us, 4100 rows 3796 -> 3764, 16384 rows 14.24 -> 13.93 ms; d = 5120, 131072 rows 143.2 -> 139.8 ms.  The forward of a
+  // loss call that keeps its logits: d = 5120, 32768 rows 36.4 against 37.4 ms, d = 4096, 2869 rows 2.81 against 2.86.
+  const bool tokens_first = a.kept.tiles == nullptr;
   float* red = reinterpret_cast<float*>(g_smem + FWD_RED_OFF);
   int* stash = reinterpret_cast<int*>(g_smem + FWD_STASH_OFF);
   volatile int* claim = reinterpret_cast<volatile int*>(g_smem + FWD_CLAIM_OFF);
@@ -90,9 +95,9 @@ __device__ __forceinline__ void lmhead_fwd_body(FwdArgs a, bool steal, unsigned 
   const int b_cur = __builtin_amdgcn_readfirstlane(claim[0]), b_nxt = __builtin_amdgcn_readfirstlane(claim[1]);
   if (b_cur < 0) return;
   int tm, tn, tm1 = 0, tn1 = 0;
-  map_tile(b_cur, a.tiles_v, tiles_t, tm, tn);
+  map_tile(b_cur, a.tiles_v, tiles_t, tm, tn, tokens_first);
   bool more = b_nxt >= 0;
-  if (more) map_tile(b_nxt, a.tiles_v, tiles_t, tm1, tn1);
+  if (more) map_tile(b_nxt, a.tiles_v, tiles_t, tm1, tn1, tokens_first);
   OperandLanes VA, VB;
   VA.init(a.ldw, tid);
   VB.init(a.ldh, tid);
@@ -211,7 +216,7 @@ __device__ __forceinline__ void lmhead_fwd_body(FwdArgs a, bool steal, unsigned 
     A0.set(a.W, a.w_rows, tm * BM, a.ldw, 0u);
     B0.set(a.Hc, a.h_rows, tn * BN, a.ldh, 0u);
     more = b_nn >= 0;
-    if (more) map_tile(b_nn, a.tiles_v, tiles_t, tm1, tn1);
+    if (more) map_tile(b_nn, a.tiles_v, tiles_t, tm1, tn1, tokens_first);
     A1.set(a.W, (more && ahead) ? a.w_rows : 0, tm1 * BM, a.ldw, 0u);
     B1.set(a.Hc, (more && ahead) ? a.h_rows : 0, tn1 * BN, a.ldh, 0u);
   }
@@ -609,13 +614,11 @@ template <bool DIRECT, class AfterLoop, class BeforeStores>
 __device__ __forceinline__ void gemm_store_tile(StoreArgs a, const StoreShape& sh, int b, AfterLoop&& after_loop,
                                                 BeforeStores&& before_stores) {
   const int tid = threadIdx.x;
-  int tm, tn;
-  map_tile_interleaved(b, sh.tiles_m * sh.ks * sh.products, a.tiles_n, tm, tn);
+  int tm, tn, slab;
+  map_tile_interleaved(b, sh.tiles_m, a.tiles_n, sh.ks * sh.products, slab, tm, tn);
   // (divisions only where the contraction is split, and in 32 bits: they run in front of every tile's first load)
-  int slab = 0, part = 0, s0 = 0, s1 = sh.K / BK;
+  int part = 0, s0 = 0, s1 = sh.K / BK;
   if (sh.ks * sh.products > 1) {
-    slab = tm / sh.tiles_m;
-    tm -= slab * sh.tiles_m;
     part = sh.products == 3 ? slab / 3 : slab;
     const int product = slab - part * sh.products;
     if (product == 1) { a.B = a.B_lo; a.ldb = a.ldb_lo; }
