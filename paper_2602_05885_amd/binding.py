@@ -1,7 +1,8 @@
-"""ctypes binding of libpg_head.so: same names as the C ABI, argument marshalling only.
+"""Binding of libpg_head.so: same names as the C ABI, argument marshalling only (ctypes; the small stages, whose calls are
+host time only, go through _stage_calls.so first).
 
 Every computation happens in the HIP kernels behind the C entry points.  torch is used
-for device memory, data pointers and the current stream.  There is no fallback: if the
+for device memory, data pointers and the current stream.  There is no fallback: if a
 library is missing or a call fails, an exception is raised.
 """
 from __future__ import annotations
@@ -73,11 +74,12 @@ class PgError(RuntimeError):
 
 
 _lib = None
+_stage = None        # csrc/stage_calls.cpp, bound to the entry points of _lib
 
 
 def lib() -> C.CDLL:
     """Loads the shared library (once).  Raises if it has not been built."""
-    global _lib
+    global _lib, _stage
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise RuntimeError(f"{LIB_PATH} is missing: build it with `python -m paper_2602_05885_amd.build`")
@@ -157,8 +159,24 @@ def lib() -> C.CDLL:
         L.pg_profile_enable.argtypes = [C.c_int32, C.c_int32]
         L.pg_profile_read.restype = C.c_int32
         L.pg_profile_read.argtypes = [C.POINTER(C.c_double), C.POINTER(C.c_int64)]
+        try:
+            from . import _stage_calls
+        except ImportError as e:
+            raise RuntimeError(f"_stage_calls.so does not load ({e}): build it with `python -m paper_2602_05885_amd.build`") from e
+        _stage_calls.bind(*(C.cast(f, C.c_void_p).value for f in (L.turn_reward, L.prs_retain, L.trloo_advantage, L.grpo_advantage)))
+        _stage = _stage_calls
         _lib = L
     return _lib
+
+
+def _staged(call: str, *args, stream):
+    """The native step of a small stage: its outputs, or None where the general path below it has to look at the arguments."""
+    if _stage is None:
+        lib()
+    r = getattr(_stage, call)(*args, None if stream is None else stream.cuda_stream)
+    if type(r) is int:
+        _check(r)
+    return r
 
 
 _HEAD_DTYPES = {0: torch.bfloat16, 1: torch.float32}
@@ -325,6 +343,9 @@ def alloc_workspace(T: int, d: int, V: int, S: int, params: Params, which_call: 
 def trloo_advantage(rewards: torch.Tensor, valid: torch.Tensor, gamma: float = 1.0, want_returns=True,
                     want_group_n=True, stream=None):
     """rewards float32 [P,K,Tmax], valid uint8 [P,K,Tmax] (device).  Returns (adv f64, returns f64|None, N i32|None)."""
+    r = _staged("turn_advantage", rewards, valid, gamma, want_returns, want_group_n, False, stream=stream)
+    if r is not None:
+        return r
     P, K, Tm = rewards.shape
     assert rewards.dtype == torch.float32 and valid.dtype == torch.uint8 and valid.shape == rewards.shape
     adv = torch.empty((P, K, Tm), dtype=torch.float64, device=rewards.device)
@@ -338,6 +359,9 @@ def trloo_advantage(rewards: torch.Tensor, valid: torch.Tensor, gamma: float = 1
 def grpo_advantage(rewards: torch.Tensor, valid: torch.Tensor, gamma: float = 1.0, want_returns=True,
                    want_group_n=True, stream=None):
     """As trloo_advantage, with the group-mean baseline of Eq. (3)."""
+    r = _staged("turn_advantage", rewards, valid, gamma, want_returns, want_group_n, True, stream=stream)
+    if r is not None:
+        return r
     P, K, Tm = rewards.shape
     assert rewards.dtype == torch.float32 and valid.dtype == torch.uint8 and valid.shape == rewards.shape
     adv = torch.empty((P, K, Tm), dtype=torch.float64, device=rewards.device)
@@ -351,6 +375,9 @@ def grpo_advantage(rewards: torch.Tensor, valid: torch.Tensor, gamma: float = 1.
 def turn_reward(correct, t_reference, t_kernel, t_generated=None, t_total=None, speedup_cap: float = 3.0,
                 want_pr=True, stream=None):
     """correct uint8 [n], times float32 [n] (device).  Returns (rewards f32 [n], C*PR f32 [n] | None)."""
+    r = _staged("turn_reward", correct, t_reference, t_kernel, t_generated, t_total, speedup_cap, want_pr, stream=stream)
+    if r is not None:
+        return r
     n = correct.numel()
     assert correct.dtype == torch.uint8
     for t in (t_reference, t_kernel, t_generated, t_total):
@@ -364,6 +391,9 @@ def turn_reward(correct, t_reference, t_kernel, t_generated=None, t_total=None, 
 
 def prs_retain(pr, valid, seed: int, tau: float = 0.3, s: float = 0.1, hard: bool = False, want_p=True, stream=None):
     """pr float32 [n], valid uint8 [n] | None (device).  Returns (keep u8 [n], p f32 [n] | None)."""
+    r = _staged("prs_retain", pr, valid, seed, tau, s, hard, want_p, stream=stream)
+    if r is not None:
+        return r
     n = pr.numel()
     assert pr.dtype == torch.float32 and (valid is None or (valid.dtype == torch.uint8 and valid.numel() == n))
     keep = torch.empty(n, dtype=torch.uint8, device=pr.device)

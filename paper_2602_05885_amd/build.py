@@ -1,14 +1,16 @@
-"""Builds the HIP library in-tree: python -m paper_2602_05885_amd.build"""
+"""Builds the HIP library and the native stage calls in-tree: python -m paper_2602_05885_amd.build"""
 from __future__ import annotations
 
 import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libpg_head.so")
+STAGE_CALLS = os.path.join(PKG, "_stage_calls.so")      # imported as paper_2602_05885_amd._stage_calls
 SOURCES = ["api.hip", "kernels_gemm.hip", "kernels_rows.hip"]
 FLAGS = ["-O3", "--offload-arch=gfx950", "-fPIC", "-std=c++17", "-fno-gpu-rdc",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wall", "-Wno-unused-function"]
@@ -21,8 +23,20 @@ def hipcc() -> str:
     raise RuntimeError("hipcc not found")
 
 
+def stage_calls_command() -> list:
+    """Host code only: the marshalling of the small stages, against torch's own headers."""
+    import torch
+    root = os.path.dirname(torch.__file__)
+    rocm = os.path.dirname(os.path.dirname(os.path.realpath(hipcc())))
+    include = [os.path.join(root, "include"), os.path.join(root, "include", "torch", "csrc", "api", "include"), os.path.join(rocm, "include"),
+               sysconfig.get_paths()["include"]]
+    return ["g++", "-O2", "-shared", "-fPIC", "-std=c++17", "-Wall", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *[f for i in include for f in ("-isystem", i)],
+            os.path.join(CSRC, "stage_calls.cpp"), "-o", STAGE_CALLS, "-L" + os.path.join(root, "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
+
+
 def build(verbose: bool = True) -> str:
-    """Compiles every source for gfx950 and links libpg_head.so next to this file."""
+    """Compiles every source for gfx950 and links libpg_head.so next to this file, and _stage_calls.so beside it."""
     objdir = os.path.join(PKG, "_build")
     os.makedirs(objdir, exist_ok=True)
     cc = hipcc()
@@ -33,6 +47,10 @@ def build(verbose: bool = True) -> str:
         if verbose:
             print(" ".join(cmd), flush=True)
         procs.append((src, obj, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
+    cmd = stage_calls_command()
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
     objs = []
     for src, obj, p in procs:
         out, _ = p.communicate()
