@@ -28,6 +28,19 @@ __device__ __forceinline__ void merge_state(float& m, float& s, float& u, float 
   m = mm;
 }
 
+// Two registers after an exchange of lanes.  swap_halves: a = {first half of a, first half of b}, b = {second half of a, second
+// half of b}.  swap_rows: a = rows {a0, b0, a2, b2}, b = rows {a1, b1, a3, b3} of 16 lanes.
+struct Two { float a, b; };
+__device__ __forceinline__ Two swap_halves(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, a), __builtin_bit_cast(unsigned, b), false, false);
+  const unsigned x = r[0], y = r[1];      // (a bit cast of the vector's element itself would take element 0)
+  return {__builtin_bit_cast(float, x), __builtin_bit_cast(float, y)};
+}
+__device__ __forceinline__ Two swap_rows(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, a), __builtin_bit_cast(unsigned, b), false, false);
+  const unsigned x = r[0], y = r[1];      // (a bit cast of the vector's element itself would take element 0)
+  return {__builtin_bit_cast(float, x), __builtin_bit_cast(float, y)};
+}
 // Finite stand-in for -inf (keeps 0 * (t - m) finite).  A power of two, so that its product
 // with the logit scale is exact and "t - max" of an all-masked column is exactly zero.
 constexpr float NEG_BIG = -0x1p100f;
@@ -45,7 +58,7 @@ constexpr float NEG_BIG = -0x1p100f;
 // of the tile (double-buffered; loaded one tile ahead so that the epilogue waits on no global load)
 // and the words that hand the claimed tiles to all wavefronts.
 // ------------------------------------------------------------------------------------
-constexpr int FWD_RED_OFF = 2 * STAGE_BYTES;                 // [WM][256 tokens][3] floats
+constexpr int FWD_RED_OFF = 2 * STAGE_BYTES;                 // [m, s, u][WM][256 tokens] floats
 constexpr int FWD_STASH_OFF = FWD_RED_OFF + WM * 256 * 3 * 4; // [2][256] ints
 constexpr int FWD_CLAIM_OFF = FWD_STASH_OFF + 2 * 256 * 4;    // [4] ints
 constexpr int FWD_LDS_BYTES = FWD_CLAIM_OFF + 16;
@@ -148,10 +161,12 @@ __device__ __forceinline__ void lmhead_fwd_body(FwdArgs a, bool steal, unsigned 
         for (int i = 0; i < GM; ++i) __builtin_nontemporal_store(acc[i][j], kp + (kept_column(0, j * WN) + i * 64));
       }
     }
+    // Statistics of this wavefront's 64 vocab rows, per token: their maximum first, known to all four lanes of a token, so that
+    // the sums over the lanes are plain additions.  Cross-lane steps are half-wavefront and row swaps (no LDS latency); a swap
+    // of two different values reduces both at once.
+    float mx[GN];
 #pragma unroll
     for (int j = 0; j < GN; ++j) {
-      const int tok_l = stream_col(j, wn, lane);
-      const int tok = tn * BN + tok_l;
       float mr = NEG_BIG;
 #pragma unroll
       for (int i = 0; i < GM; ++i)
@@ -160,39 +175,49 @@ __device__ __forceinline__ void lmhead_fwd_body(FwdArgs a, bool steal, unsigned 
           if (ragged && (v_base + i * 16 + acc_row(r, lane) >= a.V)) acc[i][j][r] = NEG_BIG;
           mr = fmaxf(mr, acc[i][j][r]);
         }
-      float mx = mr * a.scale;
-      const float nmx = -mx;
-      float s = 0.f, u = 0.f;
+      const Two h = swap_halves(mr, mr);
+      mr = fmaxf(h.a, h.b);
+      const Two q = swap_rows(mr, mr);
+      mx[j] = fmaxf(q.a, q.b) * a.scale;
+    }
 #pragma unroll
-      for (int i = 0; i < GM; ++i)
+    for (int j0 = 0; j0 < GN; j0 += 2) {
+      float su[2];          // lanes 0..31 s, lanes 32..63 u of token column j0 + h
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const float dlt = fmaf(acc[i][j][r], a.scale, nmx);
-          const float e = __builtin_amdgcn_exp2f(dlt);
-          s += e;
-          u = fmaf(e, dlt, u);
-        }
-      const int ytok = ys[tok_l];
-      const int yrel = ytok - v_base;
-      const bool mine = (yrel >= 0) && (yrel < WROWS) && (ytok < a.V) && (((yrel >> 2) & 3) == (lane >> 4));
-      if (__any(mine)) {
-        float zy = 0.f;
+      for (int h = 0; h < 2; ++h) {
+        const int j = j0 + h;
+        const float nmx = -mx[j];
+        float s = 0.f, u = 0.f;
 #pragma unroll
         for (int i = 0; i < GM; ++i)
 #pragma unroll
-          for (int r = 0; r < 4; ++r)
-            if (yrel == i * 16 + acc_row(r, lane)) zy = acc[i][j][r] * a.scale;
-        if (mine) a.zy[tok] = zy;
-      }
+          for (int r = 0; r < 4; ++r) {
+            const float dlt = fmaf(acc[i][j][r], a.scale, nmx);
+            const float e = __builtin_amdgcn_exp2f(dlt);
+            s += e;
+            u = fmaf(e, dlt, u);
+          }
+        const Two x = swap_halves(s, u);
+        su[h] = x.a + x.b;
+        const int tok_l = stream_col(j, wn, lane);
+        const int ytok = ys[tok_l];
+        const int yrel = ytok - v_base;
+        const bool mine = (yrel >= 0) && (yrel < WROWS) && (ytok < a.V) && (((yrel >> 2) & 3) == (lane >> 4));
+        if (__any(mine)) {
+          float zy = 0.f;
 #pragma unroll
-      for (int sh = 16; sh <= 32; sh <<= 1) {
-        const float m2 = __shfl_xor(mx, sh), s2 = __shfl_xor(s, sh), u2 = __shfl_xor(u, sh);
-        merge_state(mx, s, u, m2, s2, u2);
+          for (int i = 0; i < GM; ++i)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+              if (yrel == i * 16 + acc_row(r, lane)) zy = acc[i][j][r] * a.scale;
+          if (mine) a.zy[tn * BN + tok_l] = zy;
+        }
       }
-      if (lane < 16) {
-        float* p = red + (wm * 256 + tok_l) * 3;
-        p[0] = mx; p[1] = s; p[2] = u;
-      }
+      // rows of 16 lanes: s of j0, s of j0 + 1, u of j0, u of j0 + 1
+      const Two y = swap_rows(su[0], su[1]);
+      const int tok_l = stream_col(j0 + ((lane >> 4) & 1), wn, lane);
+      red[(1 + (lane >> 5)) * (WM * BN) + wm * BN + tok_l] = y.a + y.b;
+      if (lane < 32) red[wm * BN + tok_l] = lane < 16 ? mx[j0] : mx[j0 + 1];
     }
     if (tid == 0) claim[2] = more ? Q.resolve(ticket, steal) : -1;
     // LDS-only synchronisation: a full __syncthreads() would also wait for the next tile's loads
@@ -200,13 +225,10 @@ __device__ __forceinline__ void lmhead_fwd_body(FwdArgs a, bool steal, unsigned 
     const int b_nn = __builtin_amdgcn_readfirstlane(claim[2]);
     if (tid < BN) {
       stash[((n + 1) & 1) * BN + tid] = y_next;
-      const float* p0 = red + tid * 3;
-      float m = p0[0], s = p0[1], u = p0[2];
+      const float* p = red + tid;
+      float m = p[0], s = p[WM * BN], u = p[2 * WM * BN];
 #pragma unroll
-      for (int w = 1; w < WM; ++w) {
-        const float* p1 = red + (w * 256 + tid) * 3;
-        merge_state(m, s, u, p1[0], p1[1], p1[2]);
-      }
+      for (int w = 1; w < WM; ++w) merge_state(m, s, u, p[w * BN], p[(WM + w) * BN], p[(2 * WM + w) * BN]);
       const size_t o = (size_t)tm * a.t_cap + (size_t)tn * BN + tid;
       a.part_m[o] = m; a.part_s[o] = s; a.part_u[o] = u;
     }
