@@ -86,7 +86,7 @@ __device__ __forceinline__ void lmhead_fwd_body(FwdArgs a, bool steal, unsigned 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave / WN, wn = wave % WN;
   TileQueue Q;
-  Q.init(a.queue, a.tiles_v * tiles_t, 0);
+  Q.init(a.queue, a.tiles_v * tiles_t, 0, 2);
   const int kept_v = kept_vocab_tiles(a.kept, a.tiles_v, tiles_t);
   // Tile order: W is shared by more tiles than H and comes first, unless tiles are parked: the block's stores are then spread
   // better with the vocabulary running fastest.  Forward-only calls, vocabulary first against tokens first: d = 4096, 768 rows
@@ -97,15 +97,17 @@ __device__ __forceinline__ void lmhead_fwd_body(FwdArgs a, bool steal, unsigned 
   int* stash = reinterpret_cast<int*>(g_smem + FWD_STASH_OFF);
   volatile int* claim = reinterpret_cast<volatile int*>(g_smem + FWD_CLAIM_OFF);
 
-  // the first two tiles (of at most one tile per workgroup a second claim would take another workgroup's only one)
-  if (tid == 0) {
-    const bool two = Q.total > (int)gridDim.x;
-    const unsigned k0 = Q.ticket(), k1 = two ? Q.ticket() : 0u;
-    claim[0] = Q.resolve(k0, steal);
-    claim[1] = two ? Q.resolve(k1, steal) : -1;
+  // the first two tiles (of at most one tile per workgroup there is no second)
+  const bool two = Q.total > (int)gridDim.x;
+  int b_cur = Q.entry(0), b_nxt = two ? Q.entry(1) : -1;
+  if (two && (b_cur < 0 || b_nxt < 0)) {      // (an XCD with a short share: others may have more)
+    if (tid == 0) {
+      claim[0] = b_cur < 0 ? Q.resolve(Q.ticket(), steal) : b_cur;
+      claim[1] = Q.resolve(Q.ticket(), steal);
+    }
+    __syncthreads();
+    b_cur = __builtin_amdgcn_readfirstlane(claim[0]); b_nxt = __builtin_amdgcn_readfirstlane(claim[1]);
   }
-  __syncthreads();
-  const int b_cur = __builtin_amdgcn_readfirstlane(claim[0]), b_nxt = __builtin_amdgcn_readfirstlane(claim[1]);
   if (b_cur < 0) return;
   int tm, tn, tm1 = 0, tn1 = 0;
   map_tile(b_cur, a.tiles_v, tiles_t, tm, tn, tokens_first);
@@ -269,12 +271,15 @@ constexpr int PERSISTENT_LDS_BYTES = CLAIM_OFF + 16;
 template <class TileFn>
 __device__ __forceinline__ void drain_queue(const TileQueue& Q, bool steal, volatile int* claim, TileFn&& tile) {
   const int tid = threadIdx.x;
-  int b = queue_broadcast(claim, tid == 0 ? Q.resolve(Q.ticket(), steal) : 0);
+  const bool all_dealt = Q.total <= (int)gridDim.x;
+  int b = Q.entry(0);
+  if (b < 0 && !all_dealt) b = queue_broadcast(claim, tid == 0 ? Q.resolve(Q.ticket(), steal) : 0);
   while (b >= 0) {
     // (ticket is left uninitialised on the other threads on purpose: a merged value would make the
     // compiler wait for the atomic where it is issued)
     unsigned ticket;
-    tile(b, [&]() { if (tid == 0) ticket = Q.ticket(); }, [&]() { if (tid == 0) claim[0] = Q.resolve(ticket, steal); });
+    tile(b, [&]() { if (tid == 0 && !all_dealt) ticket = Q.ticket(); }, [&]() { if (tid == 0 && !all_dealt) claim[0] = Q.resolve(ticket, steal); });
+    if (all_dealt) return;
     b = __builtin_amdgcn_readfirstlane(claim[0]);
     // every wavefront is done with the tile's LDS before the next tile's loads land in it
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
@@ -462,7 +467,7 @@ __global__ __launch_bounds__(NTHREADS) void lmhead_dlogits_kernel(DlogitsArgs a)
   if (LO) { a.dS_lo += skip * BM; a.dST_lo += (size_t)skip * BM * a.ld_t; }
   if (a.tiles_v == 0 || tiles_t == 0) return;
   TileQueue Q;
-  Q.init(a.queue, a.tiles_v * tiles_t, 0);
+  Q.init(a.queue, a.tiles_v * tiles_t, 0, 1);
   volatile int* claim = reinterpret_cast<volatile int*>(g_smem + CLAIM_OFF);
   // persistent: one workgroup per compute unit takes tiles from the XCD-aware queue until none is left
   drain_queue(Q, true, claim, [&](int b, auto&& after_loop, auto&& before_stores) {
@@ -722,7 +727,7 @@ __global__ __launch_bounds__(NTHREADS) void gemm_store_kernel(StoreArgs a) {
   if (a.dw_cap > 0 && sh.ks * sh.products > 1) { a.C = a.slabs; a.accumulate = 0; a.out_bf16 = 0; }
   if (a.m_from_ctl) a.C = static_cast<float*>(a.C) + (size_t)sh.t0 * BM * a.ldc;      // dH: this block's rows of the accumulator
   TileQueue Q;
-  Q.init(a.queue, sh.total, 1);
+  Q.init(a.queue, sh.total, 1, 1);
   volatile int* claim = reinterpret_cast<volatile int*>(g_smem + CLAIM_OFF);
   // persistent: one workgroup per compute unit takes tiles from the XCD-aware queue until none is left
   drain_queue(Q, true, claim, [&](int b, auto&& after_loop, auto&& before_stores) {

@@ -50,7 +50,7 @@ __global__ __launch_bounds__(NTHREADS) void store_timeline_kernel(StoreArgs a, u
   StoreShape sh;
   sh.init(a, ctl);
   TileQueue Q;
-  Q.init(a.queue, sh.total, 1);
+  Q.init(a.queue, sh.total, 1, 1);
   volatile int* claim = reinterpret_cast<volatile int*>(g_smem + CLAIM_OFF);
   int n = 0;
   unsigned long long tlast = t0;
@@ -66,7 +66,7 @@ __global__ __launch_bounds__(NTHREADS) void dlogits_timeline_kernel(DlogitsArgs 
   const Ctl ctl = *a.ctl;
   const int tiles_t = min(a.tiles_t, ctl.n_pad / BN);
   TileQueue Q;
-  Q.init(a.queue, a.tiles_v * tiles_t, 0);
+  Q.init(a.queue, a.tiles_v * tiles_t, 0, 1);
   volatile int* claim = reinterpret_cast<volatile int*>(g_smem + CLAIM_OFF);
   int n = 0;
   unsigned long long tlast = t0;

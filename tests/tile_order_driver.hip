@@ -37,6 +37,22 @@ int main() {
       const int nj = fwd_nj(rows, tiles_t);
       fails += (nj != 4 && nj != 6 && nj != 8) || nj * 32 < (rows + BK - 1) / BK * BK;
     }
+  // Entries dealt by workgroup index and tickets behind them: together every entry of every share once.
+  for (int grid : {8, 64, 256})
+    for (int total = 1; total <= 1200; total += 7)
+      for (int order = 0; order < 2; ++order)
+        for (int rounds = 1; rounds <= 2; ++rounds) {
+          if (grid < 256 && total > grid * 4) continue;
+          TileQueue Q{};
+          Q.total = total; Q.interleaved = order; Q.dealt = rounds * (grid >> 3);
+          long long handed = 0;
+          for (int b = 0; b < grid; ++b)
+            for (int r = 0; r < rounds; ++r) handed += (b >> 3) + r * (grid >> 3) < Q.share(b & 7);
+          for (int y = 0; y < 8; ++y) handed += imax(Q.share(y) - Q.dealt, 0);
+          fails += handed != total;
+          if (total <= grid && rounds == 1)
+            for (int y = 0; y < 8; ++y) fails += Q.share(y) > Q.dealt;      // nothing is left for the counters
+        }
   printf("tile order driver: (%d failures)\n", fails);
   return fails != 0;
 }
