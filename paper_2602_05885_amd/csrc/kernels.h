@@ -408,6 +408,7 @@ struct NormArgs {
   void* dX;             // [T, d] same dtype
   float* partial;       // [NORM_STRIPS, d]
   float* dgamma;        // [d]
+  int strips;           // partials in use
 };
 void launch_rmsnorm_fwd(const NormArgs& a, hipStream_t s);
 void launch_rmsnorm_bwd(const NormArgs& a, hipStream_t s);

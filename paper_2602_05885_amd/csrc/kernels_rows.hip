@@ -851,16 +851,25 @@ __device__ __forceinline__ void load8(const void* p, long long elem, float (&v)[
     for (int e = 0; e < 8; ++e) v[e] = (float)a[e];
   }
 }
-template <bool F32>
+template <bool F32, bool NT = false>
 __device__ __forceinline__ void store8(void* p, long long elem, const float (&v)[8]) {
   if (F32) {
-    *reinterpret_cast<float4*>(reinterpret_cast<float*>(p) + elem) = make_float4(v[0], v[1], v[2], v[3]);
-    *reinterpret_cast<float4*>(reinterpret_cast<float*>(p) + elem + 4) = make_float4(v[4], v[5], v[6], v[7]);
+    const f32x4 a = {v[0], v[1], v[2], v[3]}, b = {v[4], v[5], v[6], v[7]};
+    f32x4* q = reinterpret_cast<f32x4*>(reinterpret_cast<float*>(p) + elem);
+    if (NT) {
+      __builtin_nontemporal_store(a, q);
+      __builtin_nontemporal_store(b, q + 1);
+    } else {
+      q[0] = a;
+      q[1] = b;
+    }
   } else {
     bf16x8 a;
 #pragma unroll
     for (int e = 0; e < 8; ++e) a[e] = (__bf16)v[e];
-    *reinterpret_cast<bf16x8*>(reinterpret_cast<__bf16*>(p) + elem) = a;
+    bf16x8* q = reinterpret_cast<bf16x8*>(reinterpret_cast<__bf16*>(p) + elem);
+    if (NT) __builtin_nontemporal_store(a, q);
+    else *q = a;
   }
 }
 __device__ __forceinline__ float wave_sum(float v) {
@@ -874,14 +883,22 @@ __device__ __forceinline__ float wave_sum(float v) {
 constexpr int NORM_FC = NORM_MAX_D / 512;          // 8-column steps per lane
 
 template <bool F32> struct Raw8;
-template <> struct Raw8<true> { float4 a, b; };
+template <> struct Raw8<true> { f32x4 a, b; };
 template <> struct Raw8<false> { bf16x8 v; };
 __device__ __forceinline__ void raw_load(const void* p, long long elem, Raw8<true>& r) {
-  r.a = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(p) + elem);
-  r.b = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(p) + elem + 4);
+  r.a = *reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(p) + elem);
+  r.b = *reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(p) + elem + 4);
 }
 __device__ __forceinline__ void raw_load(const void* p, long long elem, Raw8<false>& r) {
   r.v = *reinterpret_cast<const bf16x8*>(reinterpret_cast<const __bf16*>(p) + elem);
+}
+// ... past the caches
+__device__ __forceinline__ void raw_stream(const void* p, long long elem, Raw8<true>& r) {
+  r.a = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(p) + elem));
+  r.b = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(p) + elem + 4));
+}
+__device__ __forceinline__ void raw_stream(const void* p, long long elem, Raw8<false>& r) {
+  r.v = __builtin_nontemporal_load(reinterpret_cast<const bf16x8*>(reinterpret_cast<const __bf16*>(p) + elem));
 }
 __device__ __forceinline__ void raw_unpack(const Raw8<true>& r, float (&v)[8]) {
   v[0] = r.a.x; v[1] = r.a.y; v[2] = r.a.z; v[3] = r.a.w; v[4] = r.b.x; v[5] = r.b.y; v[6] = r.b.z; v[7] = r.b.w;
@@ -891,7 +908,16 @@ __device__ __forceinline__ void raw_unpack(const Raw8<false>& r, float (&v)[8]) 
   for (int e = 0; e < 8; ++e) v[e] = (float)r.v[e];
 }
 
-template <bool F32>
+// The two stand-alone kernels write what nobody reads again before the caches have turned over, and X is read by both: the
+// stores go past the caches, so that X and dH stay in the memory-side one where they fit it; where they do not, bf16 rows are read past
+// them as well.  Forward and backward, plain accesses / stores past / both past: bf16 d = 4096, 1500 rows 29.0 / 28.3 / 33.2 us, 20000
+// rows 169.8 / 137.6 / 156.9; d = 5120, 22000 rows 228.7 / 216.5 / 213.9, 27000 275.6 / 267.0 / 256.8, 43697 433.0 / 423.2 / 406.5;
+// fp32 d = 5120, 8000 rows 174.7 / 158.6 / 184.4, 16000 rows 325.8 / 330.0 / 341.6.
+constexpr long long NORM_LARGE_BYTES = 256ll << 20;      // of one [T, d] matrix; the memory-side cache's size
+template <bool F32, bool LARGE> constexpr bool NT_LOADS = LARGE && !F32;
+template <bool F32, bool LARGE> constexpr bool NT_STORES = !(LARGE && F32);
+
+template <bool F32, bool LARGE>
 __global__ __launch_bounds__(256) void rmsnorm_fwd_kernel(NormArgs a) {
   const int lane = threadIdx.x & 63;
   const long long row = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -900,7 +926,7 @@ __global__ __launch_bounds__(256) void rmsnorm_fwd_kernel(NormArgs a) {
 #pragma unroll
   for (int q = 0; q < NORM_FC; ++q) {
     const int c = lane * 8 + q * 512;
-    if (c < a.d) raw_load(a.X, row * a.d + c, raw[q]);
+    if (c < a.d) NT_LOADS<F32, LARGE> ? raw_stream(a.X, row * a.d + c, raw[q]) : raw_load(a.X, row * a.d + c, raw[q]);
   }
   float ss = 0.f;
 #pragma unroll
@@ -925,15 +951,18 @@ __global__ __launch_bounds__(256) void rmsnorm_fwd_kernel(NormArgs a) {
       load8<F32>(a.gamma, c, g);
 #pragma unroll
       for (int e = 0; e < 8; ++e) h[e] = x[e] * rstd * g[e];
-      store8<F32>(a.H, row * a.d + c, h);
+      store8<F32, NT_STORES<F32, LARGE>>(a.H, row * a.d + c, h);
     }
   }
 }
+static bool norm_large(const NormArgs& a) { return a.T * a.d * (a.is_f32 ? 4 : 2) > NORM_LARGE_BYTES; }
 void launch_rmsnorm_fwd(const NormArgs& a, hipStream_t s) {
   if (a.T <= 0) return;
   const unsigned grid = (unsigned)((a.T + 3) / 4);
-  if (a.is_f32) hipLaunchKernelGGL(rmsnorm_fwd_kernel<true>, dim3(grid), dim3(256), 0, s, a);
-  else hipLaunchKernelGGL(rmsnorm_fwd_kernel<false>, dim3(grid), dim3(256), 0, s, a);
+  const bool large = norm_large(a);
+  auto kernel = a.is_f32 ? (large ? rmsnorm_fwd_kernel<true, true> : rmsnorm_fwd_kernel<true, false>)
+                         : (large ? rmsnorm_fwd_kernel<false, true> : rmsnorm_fwd_kernel<false, false>);
+  hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, s, a);
 }
 
 // Backward: dx = rstd (gamma g - xhat mean(gamma g xhat)), xhat = x rstd; dgamma = sum_rows g xhat.
@@ -955,7 +984,7 @@ __device__ __forceinline__ float block_sum4(float v, float* red, int lane, int w
 
 // Keeps the register values of a packed row opaque to the optimiser between the two passes over a row, so that
 // the unpacked fp32 copies of the first pass are not kept alive across the reduction (they are unpacked again).
-__device__ __forceinline__ void opaque(Raw8<true>& r) { asm volatile("" : "+v"(r.a.x), "+v"(r.a.y), "+v"(r.a.z), "+v"(r.a.w), "+v"(r.b.x), "+v"(r.b.y), "+v"(r.b.z), "+v"(r.b.w)); }
+__device__ __forceinline__ void opaque(Raw8<true>& r) { asm volatile("" : "+v"(r.a), "+v"(r.b)); }
 __device__ __forceinline__ void opaque(Raw8<false>& r) {
   i32x4 v = __builtin_bit_cast(i32x4, r.v);
   asm volatile("" : "+v"(v));
@@ -965,7 +994,7 @@ __device__ __forceinline__ void opaque(Raw8<false>& r) {
 // NC: 8-column steps per thread, ceil(d / 2048).  Rows stay in registers as loaded (bf16 rows packed) and are
 // unpacked on the fly in both passes: with three steps and bf16 rows the kernel fits 4 workgroups on a
 // compute unit, each with one row of X and dH in flight ahead of the one it works on.
-template <bool F32, int NC>
+template <bool F32, int NC, bool LARGE>
 __global__ __launch_bounds__(256) void rmsnorm_bwd_kernel(NormArgs a) {
   __shared__ float red[2][8];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -988,8 +1017,8 @@ __global__ __launch_bounds__(256) void rmsnorm_bwd_kernel(NormArgs a) {
     for (int q = 0; q < NC; ++q) {
       const int c = tid * 8 + q * 2048;
       if (c < a.d) {
-        raw_load(a.X, row * a.d + c, xa[q]);
-        raw_load(a.dH, row * a.d + c, ga[q]);
+        NT_LOADS<F32, LARGE> ? raw_stream(a.X, row * a.d + c, xa[q]) : raw_load(a.X, row * a.d + c, xa[q]);
+        NT_LOADS<F32, LARGE> ? raw_stream(a.dH, row * a.d + c, ga[q]) : raw_load(a.dH, row * a.d + c, ga[q]);
       }
     }
   };
@@ -1037,7 +1066,7 @@ __global__ __launch_bounds__(256) void rmsnorm_bwd_kernel(NormArgs a) {
           dx[e] = rstd * (g[e] * gr[e] - xh * dot);
           dg[q][e] = fmaf(gr[e], xh, dg[q][e]);
         }
-        store8<F32>(a.dX, row * a.d + c, dx);
+        store8<F32, NT_STORES<F32, LARGE>>(a.dX, row * a.d + c, dx);
       }
     }
 #pragma unroll
@@ -1054,41 +1083,52 @@ __global__ __launch_bounds__(256) void rmsnorm_bwd_kernel(NormArgs a) {
   }
 }
 
-// dgamma[c] = sum over the strips' partials, in a fixed order: workgroup = 32 columns x 8 strip
-// groups; group k adds strips k, k+8, ... in four interleaved chains, then the groups are folded.
+// dgamma[c] = sum over the strips' partials, in a fixed order: workgroup = 32 columns (four per lane) x 32 strip
+// groups; group k adds strips k, k + 32, ... in eight interleaved chains, then the groups are folded four, eight at a time.
+// Only as many strips as there are rows leave a partial: both calls at 257 rows, d = 5824, fp32 30.0 -> 21.3 us.  (1024 strips of
+// d = 5120 take 15 us: 21 MB that the rows' launch has just written.)
 __global__ __launch_bounds__(256) void rmsnorm_dgamma_kernel(NormArgs a) {
-  __shared__ float sh[8][32];
-  const int col = threadIdx.x & 31, grp = threadIdx.x >> 5;
-  const int c = blockIdx.x * 32 + col;
-  float acc[4] = {0.f, 0.f, 0.f, 0.f};
+  __shared__ f32x4 sh[32][8];
+  const int l4 = threadIdx.x & 7, grp = threadIdx.x >> 3;
+  const int c = blockIdx.x * 32 + l4 * 4;
+  f32x4 acc[8] = {};
   if (c < a.d) {
-    for (int b = grp; b < NORM_STRIPS; b += 32)
+    for (int b = grp; b < a.strips; b += 256)
 #pragma unroll
-      for (int k = 0; k < 4; ++k) acc[k] += a.partial[(size_t)(b + 8 * k) * a.d + c];
+      for (int k = 0; k < 8; ++k)
+        if (b + 32 * k < a.strips) acc[k] += *reinterpret_cast<const f32x4*>(a.partial + (size_t)(b + 32 * k) * a.d + c);
   }
-  sh[grp][col] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+  sh[grp][l4] = ((acc[0] + acc[1]) + (acc[2] + acc[3])) + ((acc[4] + acc[5]) + (acc[6] + acc[7]));
+  __syncthreads();
+  f32x4 v = {0.f, 0.f, 0.f, 0.f};
+  if (grp < 8) v = (sh[grp][l4] + sh[grp + 8][l4]) + (sh[grp + 16][l4] + sh[grp + 24][l4]);
+  __syncthreads();
+  if (grp < 8) sh[grp][l4] = v;
   __syncthreads();
   if (grp == 0 && c < a.d) {
-    float v = 0.f;
 #pragma unroll
-    for (int k = 0; k < 8; ++k) v += sh[k][col];
-    a.dgamma[c] = v;
+    for (int k = 1; k < 8; ++k) v += sh[k][l4];
+    *reinterpret_cast<f32x4*>(a.dgamma + c) = v;
   }
 }
-static_assert(NORM_STRIPS % 32 == 0, "strip groups");
 
-template <bool F32>
+template <bool F32, bool LARGE>
 static void launch_rmsnorm_bwd_rows(const NormArgs& a, hipStream_t s) {
   switch ((a.d + 2047) / 2048) {     // 8-column steps per thread; d <= NORM_MAX_D is checked by the caller
-    case 1: hipLaunchKernelGGL((rmsnorm_bwd_kernel<F32, 1>), dim3(NORM_STRIPS), dim3(256), 0, s, a); break;
-    case 2: hipLaunchKernelGGL((rmsnorm_bwd_kernel<F32, 2>), dim3(NORM_STRIPS), dim3(256), 0, s, a); break;
-    case 3: hipLaunchKernelGGL((rmsnorm_bwd_kernel<F32, 3>), dim3(NORM_STRIPS), dim3(256), 0, s, a); break;
-    default: hipLaunchKernelGGL((rmsnorm_bwd_kernel<F32, NORM_NC>), dim3(NORM_STRIPS), dim3(256), 0, s, a); break;
+    case 1: hipLaunchKernelGGL((rmsnorm_bwd_kernel<F32, 1, LARGE>), dim3(a.strips), dim3(256), 0, s, a); break;
+    case 2: hipLaunchKernelGGL((rmsnorm_bwd_kernel<F32, 2, LARGE>), dim3(a.strips), dim3(256), 0, s, a); break;
+    case 3: hipLaunchKernelGGL((rmsnorm_bwd_kernel<F32, 3, LARGE>), dim3(a.strips), dim3(256), 0, s, a); break;
+    default: hipLaunchKernelGGL((rmsnorm_bwd_kernel<F32, NORM_NC, LARGE>), dim3(a.strips), dim3(256), 0, s, a); break;
   }
 }
-void launch_rmsnorm_bwd(const NormArgs& a, hipStream_t s) {
-  if (a.is_f32) launch_rmsnorm_bwd_rows<true>(a, s);
-  else launch_rmsnorm_bwd_rows<false>(a, s);
+void launch_rmsnorm_bwd(const NormArgs& args, hipStream_t s) {
+  NormArgs a = args;
+  a.strips = (int)(a.T < NORM_STRIPS ? a.T : NORM_STRIPS);      // (a strip without a row leaves no partial)
+  if (a.strips > 0) {
+    const bool large = norm_large(a);
+    if (a.is_f32) large ? launch_rmsnorm_bwd_rows<true, true>(a, s) : launch_rmsnorm_bwd_rows<true, false>(a, s);
+    else large ? launch_rmsnorm_bwd_rows<false, true>(a, s) : launch_rmsnorm_bwd_rows<false, false>(a, s);
+  }
   hipLaunchKernelGGL(rmsnorm_dgamma_kernel, dim3((a.d + 31) / 32), dim3(256), 0, s, a);
 }
 
@@ -1278,8 +1318,8 @@ __global__ __launch_bounds__(256) void scatter_dx_norm_kernel(ScatterArgs a, Nor
 #pragma unroll
               for (int e = 0; e < 8; ++e) g[e] += w[e];
             }
-            gc[q].a = make_float4(g[0], g[1], g[2], g[3]);
-            gc[q].b = make_float4(g[4], g[5], g[6], g[7]);
+            gc[q].a = f32x4{g[0], g[1], g[2], g[3]};
+            gc[q].b = f32x4{g[4], g[5], g[6], g[7]};
           }
 #pragma unroll
           for (int e = 0; e < 8; ++e) dot = fmaf(gam[e] * g[e], x[e] * rstd, dot);
@@ -1339,7 +1379,7 @@ void launch_scatter_dx_norm(const ScatterArgs& a, const NormFuse& n, const Finis
   if (a.out_f32) launch_scatter_dx_norm_rows<true>(a, n, fin, fold, s);
   else launch_scatter_dx_norm_rows<false>(a, n, fin, fold, s);
   NormArgs f{};
-  f.d = a.d; f.partial = n.partial; f.dgamma = n.dgamma;
+  f.d = a.d; f.partial = n.partial; f.dgamma = n.dgamma; f.strips = NORM_STRIPS;
   hipLaunchKernelGGL(rmsnorm_dgamma_kernel, dim3((a.d + 31) / 32), dim3(256), 0, s, f);
 }
 
