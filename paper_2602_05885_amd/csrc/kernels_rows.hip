@@ -754,32 +754,42 @@ __device__ __forceinline__ double block_sum_256(double v, double* sh) {
   return r;
 }
 
-__device__ __forceinline__ double sumsq_slice(const void* p, int is_f32, long long n, int b, int tid) {
-  // slice b of MON_BLOCKS, in units of 8 elements so that loads stay 16-byte aligned
-  const long long units = (n + 7) / 8, per = (units + MON_BLOCKS - 1) / MON_BLOCKS;
-  const long long u0 = (long long)b * per, u1 = u0 + per < units ? u0 + per : units;
-  double acc = 0.0;
-  for (long long u = u0 + tid; u < u1; u += 256) {
-    const long long e0 = u * 8;
-    if (e0 + 8 <= n) {
-      if (is_f32) {
-        const float4 x = reinterpret_cast<const float4*>(p)[u * 2], y = reinterpret_cast<const float4*>(p)[u * 2 + 1];
-        acc += (double)x.x * x.x + (double)x.y * x.y + (double)x.z * x.z + (double)x.w * x.w +
-               (double)y.x * y.x + (double)y.y * y.y + (double)y.z * y.z + (double)y.w * y.w;
-      } else {
-        const bf16x8 x = reinterpret_cast<const bf16x8*>(p)[u];
+// Sum of squares of 8 consecutive elements.
+template <bool F32>
+__device__ __forceinline__ double sumsq8(const void* p, long long u) {
+  if constexpr (F32) {
+    const f32x4 x = reinterpret_cast<const f32x4*>(p)[u * 2], y = reinterpret_cast<const f32x4*>(p)[u * 2 + 1];
+    return ((double)x[0] * x[0] + (double)x[1] * x[1]) + ((double)x[2] * x[2] + (double)x[3] * x[3]) + (((double)y[0] * y[0] + (double)y[1] * y[1]) +
+           ((double)y[2] * y[2] + (double)y[3] * y[3]));
+  } else {
+    const bf16x8 x = reinterpret_cast<const bf16x8*>(p)[u];
+    double acc = 0.0;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) { const double v = (double)(float)x[e]; acc += v * v; }
-      }
-    } else {
-      for (long long e = e0; e < n; ++e) {
-        const double v = is_f32 ? (double)reinterpret_cast<const float*>(p)[e]
-                                : (double)(float)reinterpret_cast<const __bf16*>(p)[e];
-        acc += v * v;
-      }
-    }
+    for (int e = 0; e < 8; ++e) { const double v = (double)(float)x[e]; acc += v * v; }
+    return acc;
   }
-  return acc;
+}
+// Slice b of MON_BLOCKS of n elements, in units of 8 so that loads stay 16-byte aligned, four steps' loads in
+// flight: 3.56 GB 606 -> 594 us, 6.0 TB/s.  (Interleaving the workgroups' units over the whole array: 669 us.)
+template <bool F32>
+__device__ __forceinline__ double sumsq_share(const void* p, long long n, int b, int tid) {
+  const long long units = n / 8, per = (units + MON_BLOCKS - 1) / MON_BLOCKS;
+  long long u = (long long)b * per + tid;
+  const long long u1 = (long long)(b + 1) * per < units ? (long long)(b + 1) * per : units;
+  double acc[4] = {0.0, 0.0, 0.0, 0.0};
+  for (; u + 3 * 256 < u1; u += 4 * 256)
+#pragma unroll
+    for (int k = 0; k < 4; ++k) acc[k] += sumsq8<F32>(p, u + k * 256);
+  for (; u < u1; u += 256) acc[0] += sumsq8<F32>(p, u);
+  if (b == 0 && tid < (int)(n & 7)) {
+    const long long e = units * 8 + tid;
+    const double v = F32 ? reinterpret_cast<const float*>(p)[e] : (double)(float)reinterpret_cast<const __bf16*>(p)[e];
+    acc[1] += v * v;
+  }
+  return (acc[0] + acc[1]) + (acc[2] + acc[3]);
+}
+__device__ __forceinline__ double sumsq_share(const void* p, int is_f32, long long n, int b, int tid) {
+  return is_f32 ? sumsq_share<true>(p, n, b, tid) : sumsq_share<false>(p, n, b, tid);
 }
 
 __global__ __launch_bounds__(256) void monitors_partial_kernel(MonitorArgs a) {
@@ -798,8 +808,8 @@ __global__ __launch_bounds__(256) void monitors_partial_kernel(MonitorArgs a) {
   }
   const double r0 = block_sum_256(s_ent, sh), r1 = block_sum_256(s_tr, sh), r2 = block_sum_256(s_ro, sh),
                r5 = block_sum_256(s_n, sh);
-  const double r3 = a.dH ? block_sum_256(sumsq_slice(a.dH, a.dH_f32, a.dH_elems, b, tid), sh) : 0.0;
-  const double r4 = a.dW ? block_sum_256(sumsq_slice(a.dW, a.dW_f32, a.dW_elems, b, tid), sh) : 0.0;
+  const double r3 = a.dH ? block_sum_256(sumsq_share(a.dH, a.dH_f32, a.dH_elems, b, tid), sh) : 0.0;
+  const double r4 = a.dW ? block_sum_256(sumsq_share(a.dW, a.dW_f32, a.dW_elems, b, tid), sh) : 0.0;
   if (tid == 0) {
     a.partial[0 * MON_BLOCKS + b] = r0; a.partial[1 * MON_BLOCKS + b] = r1; a.partial[2 * MON_BLOCKS + b] = r2;
     a.partial[3 * MON_BLOCKS + b] = r3; a.partial[4 * MON_BLOCKS + b] = r4; a.partial[5 * MON_BLOCKS + b] = r5;

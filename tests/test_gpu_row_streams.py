@@ -31,3 +31,14 @@ def test_rmsnorm_variants(T, d, dtype):
         for got, ref in ((h[a:a + 4096], xh * ga), (dX[a:a + 4096], want)):
             assert ((got.double() - ref).norm(dim=1) <= tol * ref.norm(dim=1) + 1e-12).all()
     assert (dgamma.double() - want_g).norm() <= 1e-5 * want_g.norm()
+
+
+@pytest.mark.parametrize("n", [1, 7, 8, 9, 2047, 2048 * 1024 + 3, 4 * 2048 * 1024, 4 * 2048 * 1024 + 8 * 255 + 5, 5 * 2048 * 1024 + 2049])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_gradient_norms_of_every_remainder(n, dtype):
+    dev = torch.device("cuda:0")
+    g = torch.randn(n, generator=torch.Generator(device=dev).manual_seed(n), device=dev).to(dtype)
+    one = torch.full((3,), -1.0, device=dev)
+    out = B.pg_monitors(one, None, None, torch.ones(3, dtype=torch.uint8, device=dev), g, g)
+    want = g.double().norm().item()
+    assert abs(out[3].item() - want) <= 1e-12 * want and out[4].item() == out[3].item()      # fp64 sums
