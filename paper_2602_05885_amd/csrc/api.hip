@@ -350,12 +350,20 @@ bool in_place(const Plan& pl, const pg::PrepArgs& prep, bool need_HT) { return !
 // y_offset: first vocab row of W within the whole vocabulary (0 unless W is a vocab shard).  With
 // comb.partials_in set, the contraction is skipped and the rows' states come from there.
 void run_staging(const Plan& pl, void* ws, const void* H, const void* W, const int32_t* y, int64_t y_offset,
-                 const pg::PrepArgs& prep, bool need_HT, hipStream_t st, const pg::NormFuse* norm = nullptr) {
+                 pg::PrepArgs prep, bool need_HT, hipStream_t st, const pg::NormFuse* norm = nullptr) {
+  if (pl.is_f32) {
+    prep.W = static_cast<const float*>(W); prep.Wc = at<__bf16>(ws, pl.Wc);
+    prep.w_elems = (size_t)pl.V * pl.d; prep.d = (int)pl.d;
+  }
+  if (in_place(pl, prep, need_HT)) {
+    prep.y = y; prep.yc = at<int>(ws, pl.yc); prep.y_offset = (int)y_offset; prep.V = (int)pl.V;
+    pg::launch_prepass(prep, st);
+    return;
+  }
   pg::launch_prepass(prep, st);
-  if (pl.is_f32) pg::launch_split_w(static_cast<const float*>(W), at<__bf16>(ws, pl.Wc), pl.V, (int)pl.d, st);
   pg::GatherArgs g{};
   g.H = H; g.y = y; g.d = (int)pl.d; g.t_cap = pl.t_cap; g.is_f32 = pl.is_f32;
-  g.rows = at<int>(ws, pl.rows); g.Hc = in_place(pl, prep, need_HT) ? nullptr : at<__bf16>(ws, pl.Hc);
+  g.rows = at<int>(ws, pl.rows); g.Hc = at<__bf16>(ws, pl.Hc);
   g.HcT = need_HT ? at<__bf16>(ws, pl.HcT) : nullptr;
   g.HcT_lo = need_HT && pl.is_f32 ? at<__bf16>(ws, pl.HcT_lo) : nullptr;
   g.yc = at<int>(ws, pl.yc); g.ctl = at<pg::Ctl>(ws, pl.ctl); g.ld_t = pl.ld_h;

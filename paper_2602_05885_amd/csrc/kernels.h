@@ -258,6 +258,15 @@ struct PrepArgs {
   Ctl* ctl;
   // per-row outputs to clear
   float* out0; float* out1; float* out2;
+  // every row active and nothing gathered: the token ids (null: left to the gather), see GatherArgs
+  const int* y;
+  int* yc;
+  int y_offset, V;
+  // fp32 heads: W and its split operand (w_elems = 0: none)
+  const float* W;
+  __bf16* Wc;            // [V, 3d] bf16 = [hi | lo | hi]
+  size_t w_elems;
+  int d;
 };
 void launch_prepass(const PrepArgs& a, hipStream_t s);
 
@@ -267,7 +276,7 @@ struct GatherArgs {
   int d, t_cap;
   int is_f32;
   const int* rows;
-  __bf16* Hc;           // (null: only yc is written) [t_cap, ldh]   bf16: ldh = d;  fp32: ldh = 3d = [hi | hi | lo]
+  __bf16* Hc;           // [t_cap, ldh]   bf16: ldh = d;  fp32: ldh = 3d = [hi | hi | lo]
   __bf16* HcT;          // [d, ld_t] (nullable): transpose of the bf16 operand / of the hi parts
   __bf16* HcT_lo;       // [d, ld_t] (nullable, fp32 only): transpose of the lo parts
   int ld_t;             // leading dimension of HcT and HcT_lo
@@ -278,9 +287,6 @@ struct GatherArgs {
 void launch_gather(const GatherArgs& a, hipStream_t s);
 // HcT[j, i] = Hc[i, j] over d columns of row stride ldh, for the live rows
 void launch_transpose_hc(const __bf16* Hc, int ldh, __bf16* HcT, const GatherArgs& g, hipStream_t s);
-
-// fp32 head weight -> [V, 3d] bf16 = [hi | lo | hi]
-void launch_split_w(const float* W, __bf16* Wc, int64_t V, int d, hipStream_t s);
 
 struct CombineArgs {
   int tiles_v, t_cap;
