@@ -63,7 +63,7 @@ constexpr int FWD_STASH_OFF = FWD_RED_OFF + WM * 256 * 3 * 4; // [2][256] ints
 constexpr int FWD_CLAIM_OFF = FWD_STASH_OFF + 2 * 256 * 4;    // [4] ints
 constexpr int FWD_LDS_BYTES = FWD_CLAIM_OFF + 16;
 
-// Kept tiles, in units of f32x4: 16 (4 i + r-groups of lanes) x 16-column groups c of every 64-row group wm, 64 lanes each.
+// Where a kept tile holds 16-column group c of 64-row group wm, in units of f32x4: GM accumulators of 64 lanes.
 __device__ __forceinline__ int kept_column(int wm, int c) { return (wm * (BN / 16) + c) * (GM * 64); }
 
 // PROBE = true (the stand-alone measurement tool only) records wall-clock and shader-clock stamps of
@@ -88,10 +88,11 @@ __device__ __forceinline__ void lmhead_fwd_body(FwdArgs a, bool steal, unsigned 
   TileQueue Q;
   Q.init(a.queue, a.tiles_v * tiles_t, 0, 2);
   const int kept_v = kept_vocab_tiles(a.kept, a.tiles_v, tiles_t);
-  // Tile order: W is shared by more tiles than H and comes first, unless tiles are parked: the block's stores are then spread
-  // better with the vocabulary running fastest.  Forward-only calls, vocabulary first against tokens first: d = 4096, 768 rows
-  // 732 -> 722 us, 4100 rows 3796 -> 3764, 16384 rows 14.24 -> 13.93 ms; d = 5120, 131072 rows 143.2 -> 139.8 ms.  The forward of a
-  // loss call that keeps its logits: d = 5120, 32768 rows 36.4 against 37.4 ms, d = 4096, 2869 rows 2.81 against 2.86.
+  // Tile order: all token tiles of a vocab tile in a row, unless tiles are parked.  Forward-only calls, vocabulary fastest
+  // against tokens fastest: d = 4096, 768 rows 732 -> 722 us, 4100 rows 3796 -> 3764, 16384 rows 14.24 -> 13.93 ms; d = 5120, 131072
+  // rows 143.2 -> 139.8 ms (W is read from HBM once per panel of eight token tiles, and meets in the L2 more often).  The
+  // forward of a loss call that keeps its logits is the other way round: d = 5120, 32768 rows 36.4 against 37.4 ms, d = 4096, 2869
+  // rows 2.81 against 2.86 (every tile ends in 256 KiB of stores, which drives the tiles further apart in time).
   const bool tokens_first = a.kept.tiles == nullptr;
   float* red = reinterpret_cast<float*>(g_smem + FWD_RED_OFF);
   int* stash = reinterpret_cast<int*>(g_smem + FWD_STASH_OFF);
@@ -165,7 +166,8 @@ __device__ __forceinline__ void lmhead_fwd_body(FwdArgs a, bool steal, unsigned 
     }
     // Statistics of this wavefront's 64 vocab rows, per token: their maximum first, known to all four lanes of a token, so that
     // the sums over the lanes are plain additions.  Cross-lane steps are half-wavefront and row swaps (no LDS latency); a swap
-    // of two different values reduces both at once.
+    // of two different values reduces both at once.  Against merging lane-local states through the LDS unit: forward only,
+    // d = 5120, 32768 rows 35.62 -> 33.52 ms, d = 4096, 4100 rows 3745 -> 3633 us; loss call, d = 5120, 32768 rows 113.0 -> 112.2 ms.
     float mx[GN];
 #pragma unroll
     for (int j = 0; j < GN; ++j) {
@@ -564,8 +566,9 @@ __global__ __launch_bounds__(KEPT_THREADS, 2) void dlogits_kept_kernel(DlogitsAr
 // read-modify-write below was measured 6 % slower on the dH contraction.)
 // A lane pair (columns 2q, 2q + 1) swaps half of two MFMA tiles first, so that an instruction writes 128 bytes of each of 8
 // rows: pieces of 64 bytes go through a compute unit at half the rate (256 KiB of stores alone, at any number of active
-// compute units: 16 rows x 64 B 7.6 us, whole rows 3.7 us; all 256 at once 12 us, the HBM's rate).  STORE_FIGURES
-// The old values of an accumulated output are requested one column ahead of the stores.
+// compute units: 16 rows x 64 B 7.6 us, whole rows 3.7 us; all 256 at once 12 us, the HBM's rate).
+// dW of 675 rows, d = 5120: 1258 -> 1158 us.  The old values of an accumulated output are requested one column ahead of the
+// stores (2869 rows, d = 4096, accumulating: call 9160 -> 9025 us; without, no gain).
 __device__ __forceinline__ float of_lane_pair(float x) {      // x of lane ^ 1
   return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), 0xB1, 0xf, 0xf, true));
 }
