@@ -647,18 +647,28 @@ __device__ __forceinline__ void mainloop_stream(const OperandLanes& VA, const Op
 // The first entries of every share are dealt by workgroup index (entry), without the counter: a workgroup starts on its first
 // loads at once, and where that is all there is, no counter is touched (fp32 head of 64 x 1000, 1024 rows: call 85.0 -> 81.8
 // us; d = 4096, 677 rows forward only: 704 -> 697).
+// With few more tiles than workgroups, as few workgroups as that takes get two and the others none: one for everybody first is the same
+// two rounds with all of the chip's power and bandwidth spent in the first.  Forward only, one for everybody / two for few: d = 4096,
+// 24 rows, 257 tiles 185 / 150 us; 1024 rows, 284 tiles 171 / 148, 344 tiles 168 / 154; 512 rows, 348 tiles 181 / 172; 256 rows, 360
+// tiles 193 / 193, 391 tiles 205 / 211; 512 rows, 454 tiles 193 / 198.
 // cnt[0..7] must be zero at launch.
 struct TileQueue {
   unsigned* cnt;
   int total;          // tiles of the launch
   int interleaved;    // 0: map_tile order, 1: map_tile_interleaved order
   int home;           // XCD this workgroup runs on
-  int dealt = 0;      // entries of every share that are dealt by workgroup index
+  int stride = 0;     // workgroup b is dealt the entries (b >> 3) + k stride of XCD b & 7 for k < rounds, if (b >> 3) < stride,
+  int dealt = 0;      // which are the first rounds * stride of every share
 
   // rounds: how many entries a workgroup is dealt at most
+  __host__ __device__ inline void deal(int grid, int rounds) {      // (the grid is a multiple of 8)
+    stride = grid >> 3;
+    if (rounds == 2 && total <= grid + grid / 8 * 3) stride = imin(stride, (total + 15) / 16);
+    dealt = rounds * stride;
+  }
   __device__ __forceinline__ void init(unsigned* cnt_, int total_, int interleaved_, int rounds) {
     cnt = cnt_; total = total_; interleaved = interleaved_;
-    dealt = rounds * ((int)gridDim.x >> 3);      // (the grid is a multiple of 8)
+    deal((int)gridDim.x, rounds);
     unsigned x;
     asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(x));
     home = (int)(x & 7u);
@@ -675,10 +685,10 @@ struct TileQueue {
   // the workgroup index that map_tile / map_tile_interleaved would have seen for entry i of XCD y
   static __host__ __device__ inline int encode(int y, int i) { return (i << 3) | y; }
 
-  // The entry that this workgroup is dealt in a round, encoded, or -1 where the share has none.
-  __device__ __forceinline__ int entry(int round) const {
-    const int y = blockIdx.x & 7, i = (blockIdx.x >> 3) + round * ((int)gridDim.x >> 3);
-    return i < share(y) ? encode(y, i) : -1;
+  // The entry that a workgroup is dealt in a round, encoded, or -1 where there is none for it.
+  __host__ __device__ inline int entry(int block, int round) const {
+    const int y = block & 7, i = (block >> 3) + round * stride;
+    return (block >> 3) < stride && i < share(y) ? encode(y, i) : -1;
   }
 
   // Issues the claim on the home share; the ticket is resolved later, so that the atomic's latency

@@ -86,7 +86,8 @@ __device__ __forceinline__ void lmhead_fwd_body(FwdArgs a, bool steal, unsigned 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave / WN, wn = wave % WN;
   TileQueue Q;
-  Q.init(a.queue, a.tiles_v * tiles_t, 0, 2);
+  const bool two = a.tiles_v * tiles_t > (int)gridDim.x;      // (of at most one tile per workgroup there is no second)
+  Q.init(a.queue, a.tiles_v * tiles_t, 0, two ? 2 : 1);
   const int kept_v = kept_vocab_tiles(a.kept, a.tiles_v, tiles_t);
   // Tile order: all token tiles of a vocab tile in a row, unless tiles are parked.  Forward-only calls, vocabulary fastest
   // against tokens fastest: d = 4096, 768 rows 732 -> 722 us, 4100 rows 3796 -> 3764, 16384 rows 14.24 -> 13.93 ms; d = 5120, 131072
@@ -98,10 +99,10 @@ __device__ __forceinline__ void lmhead_fwd_body(FwdArgs a, bool steal, unsigned 
   int* stash = reinterpret_cast<int*>(g_smem + FWD_STASH_OFF);
   volatile int* claim = reinterpret_cast<volatile int*>(g_smem + FWD_CLAIM_OFF);
 
-  // the first two tiles (of at most one tile per workgroup there is no second)
-  const bool two = Q.total > (int)gridDim.x;
-  int b_cur = Q.entry(0), b_nxt = two ? Q.entry(1) : -1;
-  if (two && (b_cur < 0 || b_nxt < 0)) {      // (an XCD with a short share: others may have more)
+  // the first two tiles
+  const bool all_dealt = Q.total <= 2 * (int)gridDim.x;
+  int b_cur = Q.entry(blockIdx.x, 0), b_nxt = two ? Q.entry(blockIdx.x, 1) : -1;
+  if (!all_dealt && (b_cur < 0 || b_nxt < 0)) {      // (an XCD with a short share: others may have more)
     if (tid == 0) {
       claim[0] = b_cur < 0 ? Q.resolve(Q.ticket(), steal) : b_cur;
       claim[1] = Q.resolve(Q.ticket(), steal);
@@ -274,7 +275,7 @@ template <class TileFn>
 __device__ __forceinline__ void drain_queue(const TileQueue& Q, bool steal, volatile int* claim, TileFn&& tile) {
   const int tid = threadIdx.x;
   const bool all_dealt = Q.total <= (int)gridDim.x;
-  int b = Q.entry(0);
+  int b = Q.entry(blockIdx.x, 0);
   if (b < 0 && !all_dealt) b = queue_broadcast(claim, tid == 0 ? Q.resolve(Q.ticket(), steal) : 0);
   while (b >= 0) {
     // (ticket is left uninitialised on the other threads on purpose: a merged value would make the

@@ -53,6 +53,26 @@ int main() {
           if (total <= grid && rounds == 1)
             for (int y = 0; y < 8; ++y) fails += Q.share(y) > Q.dealt;      // nothing is left for the counters
         }
+  // The forward's two entries each: with few more tiles than workgroups, as few workgroups as that takes have any.
+  for (int grid : {8, 64, 256})
+    for (int total = grid + 1; total <= grid + grid / 8 * 3; ++total) {
+      TileQueue Q{};
+      Q.total = total;
+      Q.deal(grid, 2);
+      std::vector<int> seen((size_t)total + 64, 0);
+      int busy = 0;
+      for (int b = 0; b < grid; ++b) {
+        busy += Q.entry(b, 0) >= 0;
+        for (int r = 0; r < 2; ++r) {
+          const int e = Q.entry(b, r);
+          int tm, tn;
+          if (e >= 0 && map_tile(e, total, 1, tm, tn)) ++seen[tm];
+          else fails += e >= 0;
+        }
+      }
+      for (int t = 0; t < total; ++t) fails += seen[t] != 1;
+      fails += busy > (total + 1) / 2 + 8;
+    }
   printf("tile order driver: (%d failures)\n", fails);
   return fails != 0;
 }
