@@ -2,13 +2,15 @@
 host time only, go through _stage_calls.so first).
 
 Every computation happens in the HIP kernels behind the C entry points.  torch is used
-for device memory, data pointers and the current stream.  There is no fallback: if a
-library is missing or a call fails, an exception is raised.
+for device memory, data pointers and the current stream.  There is no fallback: if the
+library is missing or a call fails, an exception is raised.  (_stage_calls.so computes nothing: without
+it the small stages are marshalled by ctypes like every other call, after one warning.)
 """
 from __future__ import annotations
 
 import ctypes as C
 import os
+import warnings
 from dataclasses import dataclass
 from typing import Optional
 
@@ -74,12 +76,13 @@ class PgError(RuntimeError):
 
 
 _lib = None
-_stage = None        # csrc/stage_calls.cpp, bound to the entry points of _lib
+_stage = None        # csrc/stage_calls.cpp, bound to the entry points of _lib (None: it does not load)
+_stage_error = None  # why it does not, until that has been said
 
 
 def lib() -> C.CDLL:
     """Loads the shared library (once).  Raises if it has not been built."""
-    global _lib, _stage
+    global _lib, _stage, _stage_error
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise RuntimeError(f"{LIB_PATH} is missing: build it with `python -m paper_2602_05885_amd.build`")
@@ -161,18 +164,25 @@ def lib() -> C.CDLL:
         L.pg_profile_read.argtypes = [C.POINTER(C.c_double), C.POINTER(C.c_int64)]
         try:
             from . import _stage_calls
-        except ImportError as e:
-            raise RuntimeError(f"_stage_calls.so does not load ({e}): build it with `python -m paper_2602_05885_amd.build`") from e
-        _stage_calls.bind(*(C.cast(f, C.c_void_p).value for f in (L.turn_reward, L.prs_retain, L.trloo_advantage, L.grpo_advantage)))
-        _stage = _stage_calls
+            _stage_calls.bind(*(C.cast(f, C.c_void_p).value for f in (L.turn_reward, L.prs_retain, L.trloo_advantage, L.grpo_advantage)))
+            _stage = _stage_calls
+        except ImportError as e:        # (built for another Python or torch, or not at all)
+            _stage, _stage_error = None, e
         _lib = L
     return _lib
 
 
 def _staged(call: str, *args, stream):
     """The native step of a small stage: its outputs, or None where the general path below it has to look at the arguments."""
+    global _stage_error
     if _stage is None:
         lib()
+        if _stage is None:
+            if _stage_error is not None:
+                e, _stage_error = _stage_error, None
+                warnings.warn(f"_stage_calls.so does not load ({e}): small stages' calls take longer on the host; "
+                              "`python -m paper_2602_05885_amd.build` builds it")
+            return None
     r = getattr(_stage, call)(*args, None if stream is None else stream.cuda_stream)
     if type(r) is int:
         _check(r)
