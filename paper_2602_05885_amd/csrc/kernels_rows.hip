@@ -1122,7 +1122,9 @@ __global__ __launch_bounds__(256) void rmsnorm_dgamma_kernel(NormArgs a) {
   if (grp == 0 && c < a.d) {
 #pragma unroll
     for (int k = 1; k < 8; ++k) v += sh[k][l4];
-    *reinterpret_cast<f32x4*>(a.dgamma + c) = v;
+    // (the caller's: 4-byte aligned, a slice of a flat gradient buffer for instance)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) a.dgamma[c + e] = v[e];
   }
 }
 
