@@ -922,16 +922,20 @@ __device__ __forceinline__ void raw_unpack(const Raw8<false>& r, float (&v)[8]) 
   for (int e = 0; e < 8; ++e) v[e] = (float)r.v[e];
 }
 
-// The two stand-alone kernels write what nobody reads again before the caches have turned over, and X is read by both: the
-// stores go past the caches, so that X and dH stay in the memory-side one where they fit it; where they do not, bf16 rows are read past
-// them as well.  Forward and backward, plain accesses / stores past / both past: bf16 d = 4096, 1500 rows 29.0 / 28.3 / 33.2 us, 20000
-// rows 169.8 / 137.6 / 156.9; d = 5120, 22000 rows 228.7 / 216.5 / 213.9, 27000 275.6 / 267.0 / 256.8, 43697 433.0 / 423.2 / 406.5;
-// fp32 d = 5120, 8000 rows 174.7 / 158.6 / 184.4, 16000 rows 325.8 / 330.0 / 341.6.
-constexpr long long NORM_LARGE_BYTES = 256ll << 20;      // of one [T, d] matrix; the memory-side cache's size
-template <bool F32, bool LARGE> constexpr bool NT_LOADS = LARGE && !F32;
-template <bool F32, bool LARGE> constexpr bool NT_STORES = !(LARGE && F32);
+// Which of the two stand-alone kernels' accesses go past the caches, from calls in a trainer's order: what writes X, forward, head call,
+// backward (X has long left the caches), what reads dX.  Sums of the store's launch and the reader's, plain / past the caches, in us:
+//   H, read by the head's gather: bf16 d = 4096, 3000 rows 23.7 / 27.7, 6000 40.5 / 46.4, 14000 86.6 / 84.7, 20000 126.5 / 126.6, 24000 153.7 /
+//   149.5; d = 5120, 27000 rows 212 / 195, 43697 351 / 337.  Read in place by a forward-only call (V = 32768): d = 4096, 12000 rows 2345 / 2355,
+//   17000 3262 / 3291, 20000 3920 / 3915, 24000 4630 / 4597.  So from about 150 MB on, where X and H no longer share the memory-side cache.
+//   dX: 3000 rows 30.5 / 31.8, 12000 97.5 / 103.9, 24000 210.8 / 218.0, 30000 267 / 272; d = 5120, 27000 rows 294 / 278, 43697 485 / 462.  So where
+//   dX itself does not fit that cache; X, dH and the forward's X are then read past it too (27000 rows, all five launches: 643 -> 599).
+//   fp32: past is never shorter (H 4000 x 1024 18.6 / 21.4, 8000 x 4096 114 / 116, 12000 x 5120 221 / 232; dX 21.3 / 22.3, 145 / 149, 274 / 276).
+// (Forward and backward right after each other on one X like stores past the caches at any size, as X then stays for the backward: 20000 rows of
+// d = 4096 137 us with all stores past them, 153 with these lines, 170 with plain ones.)
+constexpr long long NORM_H_PAST_BYTES = 144ll << 20;      // of one bf16 [T, d] matrix
+constexpr long long NORM_ALL_PAST_BYTES = 256ll << 20;    // ... the memory-side cache's size
 
-template <bool F32, bool LARGE>
+template <bool F32, bool NT_LOAD, bool NT_STORE>
 __global__ __launch_bounds__(256) void rmsnorm_fwd_kernel(NormArgs a) {
   const int lane = threadIdx.x & 63;
   const long long row = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -940,7 +944,7 @@ __global__ __launch_bounds__(256) void rmsnorm_fwd_kernel(NormArgs a) {
 #pragma unroll
   for (int q = 0; q < NORM_FC; ++q) {
     const int c = lane * 8 + q * 512;
-    if (c < a.d) NT_LOADS<F32, LARGE> ? raw_stream(a.X, row * a.d + c, raw[q]) : raw_load(a.X, row * a.d + c, raw[q]);
+    if (c < a.d) NT_LOAD ? raw_stream(a.X, row * a.d + c, raw[q]) : raw_load(a.X, row * a.d + c, raw[q]);
   }
   float ss = 0.f;
 #pragma unroll
@@ -965,17 +969,17 @@ __global__ __launch_bounds__(256) void rmsnorm_fwd_kernel(NormArgs a) {
       load8<F32>(a.gamma, c, g);
 #pragma unroll
       for (int e = 0; e < 8; ++e) h[e] = x[e] * rstd * g[e];
-      store8<F32, NT_STORES<F32, LARGE>>(a.H, row * a.d + c, h);
+      store8<F32, NT_STORE>(a.H, row * a.d + c, h);
     }
   }
 }
-static bool norm_large(const NormArgs& a) { return a.T * a.d * (a.is_f32 ? 4 : 2) > NORM_LARGE_BYTES; }
+static bool norm_past(const NormArgs& a, long long bytes) { return !a.is_f32 && a.T * a.d * 2 > bytes; }
 void launch_rmsnorm_fwd(const NormArgs& a, hipStream_t s) {
   if (a.T <= 0) return;
   const unsigned grid = (unsigned)((a.T + 3) / 4);
-  const bool large = norm_large(a);
-  auto kernel = a.is_f32 ? (large ? rmsnorm_fwd_kernel<true, true> : rmsnorm_fwd_kernel<true, false>)
-                         : (large ? rmsnorm_fwd_kernel<false, true> : rmsnorm_fwd_kernel<false, false>);
+  auto kernel = a.is_f32 ? rmsnorm_fwd_kernel<true, false, false>
+                : norm_past(a, NORM_ALL_PAST_BYTES) ? rmsnorm_fwd_kernel<false, true, true>
+                : norm_past(a, NORM_H_PAST_BYTES) ? rmsnorm_fwd_kernel<false, false, true> : rmsnorm_fwd_kernel<false, false, false>;
   hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, s, a);
 }
 
@@ -1008,7 +1012,7 @@ __device__ __forceinline__ void opaque(Raw8<false>& r) {
 // NC: 8-column steps per thread, ceil(d / 2048).  Rows stay in registers as loaded (bf16 rows packed) and are
 // unpacked on the fly in both passes: with three steps and bf16 rows the kernel fits 4 workgroups on a
 // compute unit, each with one row of X and dH in flight ahead of the one it works on.
-template <bool F32, int NC, bool LARGE>
+template <bool F32, int NC, bool PAST>
 __global__ __launch_bounds__(256) void rmsnorm_bwd_kernel(NormArgs a) {
   __shared__ float red[2][8];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -1031,8 +1035,8 @@ __global__ __launch_bounds__(256) void rmsnorm_bwd_kernel(NormArgs a) {
     for (int q = 0; q < NC; ++q) {
       const int c = tid * 8 + q * 2048;
       if (c < a.d) {
-        NT_LOADS<F32, LARGE> ? raw_stream(a.X, row * a.d + c, xa[q]) : raw_load(a.X, row * a.d + c, xa[q]);
-        NT_LOADS<F32, LARGE> ? raw_stream(a.dH, row * a.d + c, ga[q]) : raw_load(a.dH, row * a.d + c, ga[q]);
+        PAST ? raw_stream(a.X, row * a.d + c, xa[q]) : raw_load(a.X, row * a.d + c, xa[q]);
+        PAST ? raw_stream(a.dH, row * a.d + c, ga[q]) : raw_load(a.dH, row * a.d + c, ga[q]);
       }
     }
   };
@@ -1080,7 +1084,7 @@ __global__ __launch_bounds__(256) void rmsnorm_bwd_kernel(NormArgs a) {
           dx[e] = rstd * (g[e] * gr[e] - xh * dot);
           dg[q][e] = fmaf(gr[e], xh, dg[q][e]);
         }
-        store8<F32, NT_STORES<F32, LARGE>>(a.dX, row * a.d + c, dx);
+        store8<F32, PAST>(a.dX, row * a.d + c, dx);
       }
     }
 #pragma unroll
@@ -1128,22 +1132,22 @@ __global__ __launch_bounds__(256) void rmsnorm_dgamma_kernel(NormArgs a) {
   }
 }
 
-template <bool F32, bool LARGE>
+template <bool F32, bool PAST>
 static void launch_rmsnorm_bwd_rows(const NormArgs& a, hipStream_t s) {
   switch ((a.d + 2047) / 2048) {     // 8-column steps per thread; d <= NORM_MAX_D is checked by the caller
-    case 1: hipLaunchKernelGGL((rmsnorm_bwd_kernel<F32, 1, LARGE>), dim3(a.strips), dim3(256), 0, s, a); break;
-    case 2: hipLaunchKernelGGL((rmsnorm_bwd_kernel<F32, 2, LARGE>), dim3(a.strips), dim3(256), 0, s, a); break;
-    case 3: hipLaunchKernelGGL((rmsnorm_bwd_kernel<F32, 3, LARGE>), dim3(a.strips), dim3(256), 0, s, a); break;
-    default: hipLaunchKernelGGL((rmsnorm_bwd_kernel<F32, NORM_NC, LARGE>), dim3(a.strips), dim3(256), 0, s, a); break;
+    case 1: hipLaunchKernelGGL((rmsnorm_bwd_kernel<F32, 1, PAST>), dim3(a.strips), dim3(256), 0, s, a); break;
+    case 2: hipLaunchKernelGGL((rmsnorm_bwd_kernel<F32, 2, PAST>), dim3(a.strips), dim3(256), 0, s, a); break;
+    case 3: hipLaunchKernelGGL((rmsnorm_bwd_kernel<F32, 3, PAST>), dim3(a.strips), dim3(256), 0, s, a); break;
+    default: hipLaunchKernelGGL((rmsnorm_bwd_kernel<F32, NORM_NC, PAST>), dim3(a.strips), dim3(256), 0, s, a); break;
   }
 }
 void launch_rmsnorm_bwd(const NormArgs& args, hipStream_t s) {
   NormArgs a = args;
   a.strips = (int)(a.T < NORM_STRIPS ? a.T : NORM_STRIPS);      // (a strip without a row leaves no partial)
   if (a.strips > 0) {
-    const bool large = norm_large(a);
-    if (a.is_f32) large ? launch_rmsnorm_bwd_rows<true, true>(a, s) : launch_rmsnorm_bwd_rows<true, false>(a, s);
-    else large ? launch_rmsnorm_bwd_rows<false, true>(a, s) : launch_rmsnorm_bwd_rows<false, false>(a, s);
+    if (a.is_f32) launch_rmsnorm_bwd_rows<true, false>(a, s);
+    else if (norm_past(a, NORM_ALL_PAST_BYTES)) launch_rmsnorm_bwd_rows<false, true>(a, s);
+    else launch_rmsnorm_bwd_rows<false, false>(a, s);
   }
   hipLaunchKernelGGL(rmsnorm_dgamma_kernel, dim3((a.d + 31) / 32), dim3(256), 0, s, a);
 }
