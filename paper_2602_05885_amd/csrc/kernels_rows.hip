@@ -1103,14 +1103,20 @@ __global__ __launch_bounds__(256) void rmsnorm_bwd_kernel(NormArgs a) {
 
 // dgamma[c] = sum over the strips' partials, in a fixed order: workgroup = 32 columns (four per lane) x 32 strip
 // groups; group k adds strips k, k + 32, ... in eight interleaved chains, then the groups are folded four, eight at a time.
-// Only as many strips as there are rows leave a partial: both calls at 257 rows, d = 5824, fp32 30.0 -> 21.3 us.  (1024 strips of
-// d = 5120 take 15 us: 21 MB that the rows' launch has just written.)
+// Only as many strips as there are rows leave a partial: both calls at 257 rows, d = 5824, fp32 30.0 -> 21.3 us.  Bound by latency: with
+// all strips the 32 loads of a lane have no condition and are in flight together, 1024 strips of d = 4096 5.5 us (3 TB/s), of 5120 6.0; eight
+// at a time, each with its condition, 11.7 and 13.1; by single floats 11.1 and 12.5.
 __global__ __launch_bounds__(256) void rmsnorm_dgamma_kernel(NormArgs a) {
   __shared__ f32x4 sh[32][8];
   const int l4 = threadIdx.x & 7, grp = threadIdx.x >> 3;
   const int c = blockIdx.x * 32 + l4 * 4;
   f32x4 acc[8] = {};
-  if (c < a.d) {
+  if (c < a.d && a.strips == NORM_STRIPS) {
+#pragma unroll
+    for (int b = 0; b < NORM_STRIPS; b += 256)
+#pragma unroll
+      for (int k = 0; k < 8; ++k) acc[k] += *reinterpret_cast<const f32x4*>(a.partial + (size_t)(b + grp + 32 * k) * a.d + c);
+  } else if (c < a.d) {
     for (int b = grp; b < a.strips; b += 256)
 #pragma unroll
       for (int k = 0; k < 8; ++k)
@@ -1131,6 +1137,7 @@ __global__ __launch_bounds__(256) void rmsnorm_dgamma_kernel(NormArgs a) {
     for (int e = 0; e < 4; ++e) a.dgamma[c + e] = v[e];
   }
 }
+static_assert(NORM_STRIPS % 256 == 0, "strip groups");
 
 template <bool F32, bool PAST>
 static void launch_rmsnorm_bwd_rows(const NormArgs& a, hipStream_t s) {
