@@ -649,8 +649,8 @@ __device__ __forceinline__ void mainloop_stream(const OperandLanes& VA, const Op
 // us; d = 4096, 677 rows forward only: 704 -> 697).
 // With few more tiles than workgroups, as few workgroups as that takes get two and the others none: one for everybody first is the same
 // two rounds with all of the chip's power and bandwidth spent in the first.  Forward only, one for everybody / two for few: d = 4096,
-// 24 rows, 257 tiles 185 / 150 us; 1024 rows, 284 tiles 171 / 148, 344 tiles 168 / 154; 512 rows, 348 tiles 181 / 172; 256 rows, 360
-// tiles 193 / 193, 391 tiles 205 / 211; 512 rows, 454 tiles 193 / 198.
+// 24 rows, 257 tiles 185 / 150 us; 1024 rows, 284 tiles 171 / 148; 1280 rows, 360 tiles 168 / 159, 400 tiles 168 / 168, 450 tiles 180 / 182; 192
+// rows, 380 tiles 189 / 184; d = 2048, 256 rows, 360 tiles 121 / 112, 400 tiles 127 / 123, 430 tiles 127 / 127, 490 tiles 144 / 145.
 // cnt[0..7] must be zero at launch.
 struct TileQueue {
   unsigned* cnt;
@@ -663,7 +663,7 @@ struct TileQueue {
   // rounds: how many entries a workgroup is dealt at most
   __host__ __device__ inline void deal(int grid, int rounds) {      // (the grid is a multiple of 8)
     stride = grid >> 3;
-    if (rounds == 2 && total <= grid + grid / 8 * 3) stride = imin(stride, (total + 15) / 16);
+    if (rounds == 2 && total <= grid + grid * 9 / 16) stride = imin(stride, (total + 15) / 16);
     dealt = rounds * stride;
   }
   __device__ __forceinline__ void init(unsigned* cnt_, int total_, int interleaved_, int rounds) {

@@ -55,7 +55,7 @@ int main() {
         }
   // The forward's two entries each: with few more tiles than workgroups, as few workgroups as that takes have any.
   for (int grid : {8, 64, 256})
-    for (int total = grid + 1; total <= grid + grid / 8 * 3; ++total) {
+    for (int total = grid + 1; total <= grid + grid * 9 / 16; ++total) {
       TileQueue Q{};
       Q.total = total;
       Q.deal(grid, 2);
