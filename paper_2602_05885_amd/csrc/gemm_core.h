@@ -337,6 +337,14 @@ template <> struct FragA<RowsLoader> {
   }
 };
 
+// Where a main loop begins, in the 32-byte pieces that instructions are fetched in.  It decides how closely the workgroups of an XCD stay
+// together in k, and with that how often their operands meet in its L2: forward-only, d = 5120, 16384 rows, 0, 4 or 8 bytes into a piece
+// 17.65 ms and 96 GB fetched, 12 bytes 16.9 and 52, 16 to 28 16.8 and 48 (d = 4096, 14.4 / 13.65 / 13.55 ms; loss calls' forward 1 %).  dW, dH
+// and the recompute: 0.3 to 1 % (dH of 2869 rows 2 %) longer at 0 and 4 than from 8 to 28.  (Left to itself the position changes with any
+// line in front of it.)  PAD: four-byte steps from a piece's start, to which the compiler adds what it puts in front of the loop.
+template <int PAD>
+__device__ __forceinline__ void place_loop() { asm volatile(".p2align 5\n\t.rept %0\n\ts_nop 0\n\t.endr" ::"n"(PAD)); }
+
 // Accumulates C(256x256) += A(256 x K) B(256 x K)^T for this workgroup's tile, K = 64 nk.
 // acc[i][j] is the 16x16 MFMA tile at rows wm*64+i*16, cols wn*128+j*16 of the workgroup tile;
 // within it, register r of lane l is row 4*(l>>4)+r, column l&15.
@@ -398,6 +406,7 @@ __device__ __forceinline__ void mainloop(const LoaderA& LA, const TileLoader& LB
   for (int i = 0; i < GM; ++i) a[0][i] = rdA(smem, 0, i);
   bq[1] = rdB(smem, 1);
 
+  place_loop<3>();
   for (int kt = 0; kt < nk; ++kt) {
     char* cur = smem + (kt & 1) * STAGE_BYTES;
     char* nxt = smem + ((kt + 1) & 1) * STAGE_BYTES;
@@ -589,6 +598,7 @@ __device__ __forceinline__ void mainloop_stream(const OperandLanes& VA, const Op
     bq[1] = rdB(s0, 1);
   }
 
+  place_loop<0>();      // (16 or 20 bytes into a piece)
   for (int kt = 0; kt < nk; ++kt) {
     char* cur = smem + ((par0 + kt) & 1) * STAGE_BYTES;
     char* nxt = smem + ((par0 + kt + 1) & 1) * STAGE_BYTES;
