@@ -511,7 +511,13 @@ __device__ __forceinline__ void pick_stage(const TileSrc cur, const TileSrc nxt,
 // (d = 4096, V = 151936, 677 rows: 3.7 GB read instead of 1.8), so NJ = 6 loses what it saves.  Forward-only call, whole
 // tiles against this: 128 rows 300 -> 272 us, 192 318 -> 290, 384 500 -> 488, 448 527 -> 520, 640 727 -> 720, 2176 2156 -> 2081; NJ = 6
 // at 704 rows 743 -> 755, at 1216 1208 -> 1233.  (The dH contraction and the recompute of the logits gained nothing: +-0.3 %.)
+// Where a vocab tile's token tiles are handed out before the next one (no logits kept), the early start costs more the more of them share W
+// in the last panel (of SB_N), and the longer the contraction: from five on at K >= 3072 the tile stays whole (short_tile_pays).  Forward-only,
+// last tile short / whole: d = 5120, V = 473637, 1150 rows 4480 / 4260 us, 1664 rows 6244 / 5926; V = 151936, 1400 rows 1693 / 1633, 3968 rows 4388 / 4252;
+// d = 3072, 1400 rows 1025 / 1005, 1150 rows 854 / 854; but d = 2560, 1150 rows 711 / 721; four tiles, 800 rows, d = 4096 869 / 873, d = 5120 1093 / 1099; one, 2176 rows 1967 / 2002, 2458 / 2498; short
+// contractions d = 2048, V = 100000, 1150 rows 387 / 388, 1400 rows 458 / 464.
 __host__ __device__ inline int fwd_nj(int cols, int tiles_t) { return cols > (tiles_t > 2 ? 128 : 192) ? 8 : cols > 128 ? 6 : 4; }
+__host__ __device__ inline bool short_tile_pays(int tiles_t, int K) { return K < 3072 || (tiles_t - 1) % SB_N < 4; }
 
 // The two wavefronts of a row take the 16-column groups of the tile in turn, so that the first NJ MFMA columns of both are its
 // first 32 NJ columns:

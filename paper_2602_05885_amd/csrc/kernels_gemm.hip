@@ -95,6 +95,7 @@ __device__ __forceinline__ void lmhead_fwd_body(FwdArgs a, bool steal, unsigned 
   // forward of a loss call that keeps its logits is the other way round: d = 5120, 32768 rows 36.4 against 37.4 ms, d = 4096, 2869
   // rows 2.81 against 2.86 (every tile ends in 256 KiB of stores, which drives the tiles further apart in time).
   const bool tokens_first = a.kept.tiles == nullptr;
+  const bool whole = tokens_first && !short_tile_pays(tiles_t, a.K);
   float* red = reinterpret_cast<float*>(g_smem + FWD_RED_OFF);
   int* stash = reinterpret_cast<int*>(g_smem + FWD_STASH_OFF);
   volatile int* claim = reinterpret_cast<volatile int*>(g_smem + FWD_CLAIM_OFF);
@@ -135,7 +136,7 @@ __device__ __forceinline__ void lmhead_fwd_body(FwdArgs a, bool steal, unsigned 
     const bool probe = PROBE && tl && tid == 0 && n >= PROBE_FIRST && n < PROBE_FIRST + PROBE_TILES;
     unsigned long long* stamp = probe ? tl + ((size_t)blockIdx.x * PROBE_TILES + (n - PROBE_FIRST)) * 4 : nullptr;
     if (probe) stamp[0] = wall_clock64();
-    const int nj = fwd_nj(live_rows - tn * BN, tiles_t);
+    const int nj = whole ? GN : fwd_nj(live_rows - tn * BN, tiles_t);
     mainloop_stream(VA, VB, A0, B0, A1, B1, nk, n == 0 || !ahead, par, nj, g_smem, acc);
     par = (par + nk) & 1;
     if (probe) stamp[1] = wall_clock64();
