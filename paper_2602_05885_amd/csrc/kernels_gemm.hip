@@ -516,12 +516,10 @@ __global__ __launch_bounds__(KEPT_THREADS, 2) void dlogits_kept_kernel(DlogitsAr
                       kept_column(wm, (h & 1) * GN) + lane;
 #pragma unroll
     for (int j = 0; j < GN; ++j)
-      if (j < groups) {
 #pragma unroll
-        for (int i = 0; i < GM; ++i) acc[i][j] = __builtin_nontemporal_load(kp + (kept_column(0, j) + i * 64));
-      } else {
-#pragma unroll
-        for (int i = 0; i < GM; ++i) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int i = 0; i < GM; ++i) {      // (no branch around the loads, a parked group instead: with one, 12000 rows, d = 5120 2.80 ms, without 2.71)
+        const f32x4 v = __builtin_nontemporal_load(kp + (kept_column(0, j < groups ? j : 0) + i * 64));
+        acc[i][j] = j < groups ? v : f32x4{0.f, 0.f, 0.f, 0.f};
       }
   };
   for (int item = blockIdx.x; item < total; item += gridDim.x) {
