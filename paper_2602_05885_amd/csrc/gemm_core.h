@@ -712,25 +712,36 @@ struct TileQueue {
   // atomicAdd the compiler does not turn it into a wave-wide reduction that needs the result at once.)
   __device__ __forceinline__ unsigned ticket() const { return atomicInc(cnt + home, 0xffffffffu); }
 
+  // What ticket tk of XCD y's counter stands for, encoded, or -1 beyond its share: tickets count from behind the dealt entries.
+  __host__ __device__ inline int claimed(int y, unsigned tk) const {
+    const int i = (int)(tk < 0x40000000u ? tk : 0x40000000u) + dealt;
+    return i < share(y) ? encode(y, i) : -1;
+  }
   // Workgroup index (see encode) of the claimed tile, or -1 when no tile is left anywhere.  Every failed
   // attempt means one more XCD's share is used up, so the loop ends after at most nine rounds.
+  // drawn(y): tickets drawn from counter y so far; draw(y): the next one.
   // steal = false confines every XCD to its own share (used by the measurement tool only).
-  __device__ __forceinline__ int resolve(unsigned tk, bool steal = true) const {
-    const int t0 = (int)min(tk, 0x40000000u) + dealt;
-    if (t0 < share(home)) return encode(home, t0);
-    if (!steal) return -1;
+  template <class Drawn, class Draw>
+  __host__ __device__ inline int resolve(unsigned tk, bool steal, Drawn&& drawn, Draw&& draw) const {
+    const int own = claimed(home, tk);
+    if (own >= 0 || !steal) return own;
     for (int attempt = 0; attempt < 9; ++attempt) {
       int best = -1, best_left = 0;
       for (int y = 0; y < 8; ++y) {
-        const unsigned c = __hip_atomic_load(cnt + y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const int left = share(y) - dealt - (int)min(c, 0x40000000u);
+        const unsigned c = drawn(y);
+        const int left = share(y) - dealt - (int)(c < 0x40000000u ? c : 0x40000000u);
         if (left > best_left) { best_left = left; best = y; }
       }
       if (best < 0) return -1;
-      const int t = (int)min(atomicInc(cnt + best, 0xffffffffu), 0x40000000u) + dealt;
-      if (t < share(best)) return encode(best, t);
+      const int b = claimed(best, draw(best));
+      if (b >= 0) return b;
     }
     return -1;
+  }
+  __device__ __forceinline__ int resolve(unsigned tk, bool steal = true) const {
+    return resolve(
+        tk, steal, [&](int y) { return __hip_atomic_load(cnt + y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); },
+        [&](int y) { return atomicInc(cnt + y, 0xffffffffu); });
   }
 };
 
