@@ -223,7 +223,7 @@ int32_t make_plan(int64_t T, int64_t d, int64_t V, int32_t S, const pg_params* p
     // there is room for the largest split, up to ACC_ROWS_SPLIT rows in all
     const int64_t split_rows = pg::SPLIT_MAX * t_cap < ACC_ROWS_SPLIT ? pg::SPLIT_MAX * t_cap : ACC_ROWS_SPLIT;
     pl.acc_rows = (int)(t_cap > split_rows ? t_cap : split_rows);
-    pl.dHacc = take((size_t)pl.acc_rows * d * 4);
+    pl.dHacc = take((size_t)pl.acc_rows * d * 4);      // (parts of n_pad rows; in each, those from n_active on are never written)
     pl.queue_words = pg::QUEUE_SET_WORDS * pg::queue_sets((int)nchunks) * pl.nblocks;
   }
   pl.queue = take((size_t)pl.queue_words * sizeof(unsigned));

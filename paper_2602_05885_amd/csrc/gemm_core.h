@@ -126,8 +126,8 @@ __host__ __device__ inline bool map_tile(int bid, int tiles_m, int tiles_n, int&
 // The last (< 256) tiles are split evenly.  Pays when the n-panel (B rows x K) is too large to
 // stay cached while an XCD walks the whole M extent on its own: measured +1..3 % on the dW and
 // dH contractions, -1.5 % on the logits contraction (whose token panels do stay cached).
-// d <= 8192 is one panel: panels of 8 took the loss calls of d = 4096, 4100 rows from 12.98 to 13.06 ms, of d = 5120, 32768
-// rows from 114.5 to 115.5.
+// d <= 8192 is one panel: with panels of 8, dW and dH of d = 4096, 2869 rows took 1.4 to 2.3 % longer, of d = 5120, 12000 rows 2.0 % (loss calls of
+// 2869 rows 8.85 -> 8.99 ms, 4100 rows 12.95 -> 13.03, 32768 rows of d = 5120 the same).
 // A contraction cut into `slabs` parts has the tiles of one part after those of the other (parts share no operand): dH of
 // 675 rows, d = 5120, 3.5 -> 2.8 GB read, 630 -> 570 us.
 constexpr int STORE_PANEL = 32;
@@ -201,7 +201,7 @@ __host__ __device__ inline int dh_slabs(int n_pad, int acc_rows, int tiles_n, in
   return ks * dh_products(n_pad, acc_rows, tiles_n, ks, split_f32);
 }
 
-// Split-K factor of the dW contraction (over the padded active rows) of a head so small that its tiles leave most
+// Split-K factor of the dW contraction (over the stages of dw_stages) of a head so small that its tiles leave most
 // compute units idle: parts of at least DW_MIN_STAGES stages, at most `cap` of them (what the slabs hold).
 constexpr int DW_MIN_STAGES = 4, DW_SPLIT_MAX = 16;
 // Stages of the dW contraction over `rows` active rows: it ends at the last stage that holds one, not at the padded count
@@ -509,13 +509,13 @@ __device__ __forceinline__ void pick_stage(const TileSrc cur, const TileSrc nxt,
 // of every wavefront.  A stage of NJ = 4 is as long as its loads, so nothing shorter; and where a vocab tile has more than two
 // token tiles, one that ends early starts the next before the others are there and their W no longer meets in the L2
 // (d = 4096, V = 151936, 677 rows: 3.7 GB read instead of 1.8), so NJ = 6 loses what it saves.  Forward-only call, whole
-// tiles against this: 128 rows 300 -> 272 us, 192 318 -> 290, 384 500 -> 488, 448 527 -> 520, 640 727 -> 720, 2176 2156 -> 2081; NJ = 6
+// tiles against this: 128 rows 295 -> 267 us, 192 331 -> 291, 384 473 -> 454, 448 487 -> 484, 640 681 -> 675, 2176 2002 -> 1967; NJ = 6
 // at 704 rows 743 -> 755, at 1216 1208 -> 1233.  (The dH contraction and the recompute of the logits gained nothing: +-0.3 %.)
 // Where a vocab tile's token tiles are handed out before the next one (no logits kept), the early start costs more the more of them share W
 // in the last panel (of SB_N), and the longer the contraction: from five on at K >= 3072 the tile stays whole (short_tile_pays).  Forward-only,
 // last tile short / whole: d = 5120, V = 473637, 1150 rows 4480 / 4260 us, 1664 rows 6244 / 5926; V = 151936, 1400 rows 1693 / 1633, 3968 rows 4388 / 4252;
-// d = 3072, 1400 rows 1025 / 1005, 1150 rows 854 / 854; but d = 2560, 1150 rows 711 / 721; four tiles, 800 rows, d = 4096 869 / 873, d = 5120 1093 / 1099; one, 2176 rows 1967 / 2002, 2458 / 2498; short
-// contractions d = 2048, V = 100000, 1150 rows 387 / 388, 1400 rows 458 / 464.
+// d = 3072, 1400 rows 1025 / 1005, 1150 rows 854 / 854; but d = 2560, 1150 rows 711 / 721; four tiles, 800 rows, d = 4096 869 / 873, d = 5120 1093 /
+// 1099; one, 2176 rows 1967 / 2002, 2458 / 2498; short contractions d = 2048, V = 100000, 1150 rows 387 / 388, 1400 rows 458 / 464.
 __host__ __device__ inline int fwd_nj(int cols, int tiles_t) { return cols > (tiles_t > 2 ? 128 : 192) ? 8 : cols > 128 ? 6 : 4; }
 __host__ __device__ inline bool short_tile_pays(int tiles_t, int K) { return K < 3072 || (tiles_t - 1) % SB_N < 4; }
 

@@ -182,8 +182,8 @@ struct StoreArgs {
   int ldc;
   int accumulate;
   int out_bf16;
-  int k_from_ctl;       // contraction length = padded active-token count
-  int m_from_ctl;       // row extent        = padded active-token count
+  int k_from_ctl;       // contraction length = active tokens, up to whole stages (dw_stages)
+  int m_from_ctl;       // row extent = active tokens: rows of C from there on, up to the padded count, are left as they are
   TokenBlocks blk;      // of the token extent
   int split_k;          // with m_from_ctl: cut K into dh_slabs(n_pad, acc_rows, tiles_n, split_stages, ..) parts, part p writes rows p n_pad + m
   int acc_rows;         // rows of C

@@ -90,10 +90,10 @@ __device__ __forceinline__ void lmhead_fwd_body(FwdArgs a, bool steal, unsigned 
   Q.init(a.queue, a.tiles_v * tiles_t, 0, two ? 2 : 1);
   const int kept_v = kept_vocab_tiles(a.kept, a.tiles_v, tiles_t);
   // Tile order: all token tiles of a vocab tile in a row, unless tiles are parked.  Forward-only calls, vocabulary fastest
-  // against tokens fastest: d = 4096, 768 rows 732 -> 722 us, 4100 rows 3796 -> 3764, 16384 rows 14.24 -> 13.93 ms; d = 5120, 131072
-  // rows 143.2 -> 139.8 ms (W is read from HBM once per panel of eight token tiles, and meets in the L2 more often).  The
-  // forward of a loss call that keeps its logits is the other way round: d = 5120, 32768 rows 36.4 against 37.4 ms, d = 4096, 2869
-  // rows 2.81 against 2.86 (every tile ends in 256 KiB of stores, which drives the tiles further apart in time).
+  // against tokens fastest: d = 4096, 768 rows 722 -> 706 us, 4100 rows 3725 -> 3705, 16384 rows 13.95 -> 13.65 ms; d = 5120, 131072
+  // rows 142.4 -> 138.7 ms (W is read from HBM once per panel of eight token tiles, and meets in the L2 more often).  The
+  // forward of a loss call that keeps its logits is the other way round: d = 5120, 12000 rows 13.73 against 14.09 ms, d = 4096, 2869
+  // rows 2.71 against 2.75 (every tile ends in 256 KiB of stores, which drives the tiles further apart in time).
   const bool tokens_first = a.kept.tiles == nullptr;
   const bool whole = tokens_first && !short_tile_pays(tiles_t, a.K);
   float* red = reinterpret_cast<float*>(g_smem + FWD_RED_OFF);
@@ -168,8 +168,9 @@ __device__ __forceinline__ void lmhead_fwd_body(FwdArgs a, bool steal, unsigned 
     }
     // Statistics of this wavefront's 64 vocab rows, per token: their maximum first, known to all four lanes of a token, so that
     // the sums over the lanes are plain additions.  Cross-lane steps are half-wavefront and row swaps (no LDS latency); a swap
-    // of two different values reduces both at once.  Against merging lane-local states through the LDS unit: forward only,
-    // d = 5120, 32768 rows 35.62 -> 33.52 ms, d = 4096, 4100 rows 3745 -> 3633 us; loss call, d = 5120, 32768 rows 113.0 -> 112.2 ms.
+    // of two different values reduces both at once.  Against merging lane-local states through the LDS unit, main loops at the same
+    // place (place_loop): forward only, d = 5120, 32768 rows 34.5 -> 34.1 ms, d = 4096, 16384 rows 13.93 -> 13.68, 4100 rows 3758 -> 3706 us.  (Without any
+    // statistics 33.3, 13.23 and 3563.)
     float mx[GN];
 #pragma unroll
     for (int j = 0; j < GN; ++j) {
@@ -558,17 +559,18 @@ __global__ __launch_bounds__(KEPT_THREADS, 2) void dlogits_kept_kernel(DlogitsAr
 // Plain contraction with a store epilogue: C[m,n] (+)= sum_k A[m,k] B[n,k].
 // Used for dW (A = dS^T chunk, B = H^T, k = compacted tokens) and for dH
 // (A = dS chunk, B = W^T chunk, k = vocab chunk).  The extent marked by k_from_ctl /
-// m_from_ctl is the device-side padded token count.
+// m_from_ctl follows from the active-token count, which only the device knows (StoreShape).
 // ------------------------------------------------------------------------------------
 // The engine's row side (4 consecutive rows per lane and MFMA tile) is given the B matrix, so that a
 // lane owns 4 consecutive n of one m and C[m, n..n+3] leaves as one 16-byte (fp32) or 8-byte (bf16)
 // access; N is a multiple of 4.  (Accumulating with fp32 adds performed at the L2 instead of the
 // read-modify-write below was measured 6 % slower on the dH contraction.)
 // A lane pair (columns 2q, 2q + 1) swaps half of two MFMA tiles first, so that an instruction writes 128 bytes of each of 8
-// rows: pieces of 64 bytes go through a compute unit at half the rate (256 KiB of stores alone, at any number of active
-// compute units: 16 rows x 64 B 7.6 us, whole rows 3.7 us; all 256 at once 12 us, the HBM's rate).
+// rows: pieces of 64 bytes go through a compute unit at half the rate (256 KiB of stores alone, with 8 or 128 compute units active:
+// 16 rows x 64 B 7.6 us, whole rows 3.7 us; with all 256 either takes 12 us, the HBM's rate).
 // dW of 675 rows, d = 5120: 1258 -> 1158 us.  The old values of an accumulated output are requested one column ahead of the
-// stores (2869 rows, d = 4096, accumulating: call 9160 -> 9025 us; without, no gain).
+// stores (2869 rows, d = 4096, accumulating: call 9160 -> 9025 us; without, no gain).  (The lane masks of the 16 row conditions
+// spill 64 scalar registers; they are read back per tile, two per column, and none of that lies in a main loop.)
 __device__ __forceinline__ float of_lane_pair(float x) {      // x of lane ^ 1
   return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), 0xB1, 0xf, 0xf, true));
 }
@@ -616,14 +618,14 @@ __device__ __forceinline__ void store_tile(const StoreArgs& a, int tm, int tn, i
   }
 }
 
-// The run-time extents of a store contraction (the padded active-token count is known only on the device).
+// The run-time extents of a store contraction (the active-token count is known only on the device).
 struct StoreShape {
   int m_lim, tiles_m, K, ks, products, slab_rows, total;
   int t0, nt;             // token tiles of this launch's block
   uint32_t b_off;         // dW: byte offset of the block's first column in a row of H^T
   __device__ __forceinline__ void init(const StoreArgs& a, const Ctl& ctl) {
     token_block(a.blk, ctl.n_pad / BM, t0, nt);
-    m_lim = a.m_from_ctl ? min(a.M, max(0, min(nt * BM, ctl.n_active - t0 * BM))) : a.M;      // (rows beyond the active ones: nobody reads them)
+    m_lim = a.m_from_ctl ? min(a.M, max(0, min(nt * BM, ctl.n_active - t0 * BM))) : a.M;      // (rows beyond the active ones are not written, and must not be read)
     tiles_m = min(a.tiles_m, (m_lim + BM - 1) / BM);
     K = a.k_from_ctl ? min(nt * BM, dw_stages(ctl.n_active - t0 * BM) * BK) : a.K;
     b_off = a.k_from_ctl ? (uint32_t)t0 * BM * 2u : 0u;
