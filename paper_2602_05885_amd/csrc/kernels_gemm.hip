@@ -494,7 +494,10 @@ constexpr int KEPT_THREADS = 256;
 constexpr int KEPT_LDS_BYTES = 256 * KEPT_STRIDE_T;
 static_assert(KEPT_LDS_BYTES >= 128 * EPI_STRIDE && 2 * KEPT_LDS_BYTES <= 160 * 1024, "LDS budget");
 
-template <bool SPLIT>
+// FEW: of at most two token tiles (or an fp32 head), where a group that was not parked is not loaded.  Elsewhere another one's is, as the
+// branch holds the other loads up: d = 5120, 12000 rows 2.80 -> 2.71 ms, 768 rows 187 -> 179 us; but 24 rows of d = 4096 50 -> 53 us, fp32 64 x 1000,
+// 1024 rows 15.3 -> 16.5 us.
+template <bool SPLIT, bool FEW>
 __global__ __launch_bounds__(KEPT_THREADS, 2) void dlogits_kept_kernel(DlogitsArgs a) {
   const Ctl ctl = *a.ctl;
   int ld_t_all;
@@ -518,9 +521,14 @@ __global__ __launch_bounds__(KEPT_THREADS, 2) void dlogits_kept_kernel(DlogitsAr
 #pragma unroll
     for (int j = 0; j < GN; ++j)
 #pragma unroll
-      for (int i = 0; i < GM; ++i) {      // (no branch around the loads, a parked group instead: with one, 12000 rows, d = 5120 2.80 ms, without 2.71)
-        const f32x4 v = __builtin_nontemporal_load(kp + (kept_column(0, j < groups ? j : 0) + i * 64));
-        acc[i][j] = j < groups ? v : f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int i = 0; i < GM; ++i) {
+        if (FEW) {
+          acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+          if (j < groups) acc[i][j] = __builtin_nontemporal_load(kp + (kept_column(0, j) + i * 64));
+        } else {
+          const f32x4 v = __builtin_nontemporal_load(kp + (kept_column(0, j < groups ? j : 0) + i * 64));
+          acc[i][j] = j < groups ? v : f32x4{0.f, 0.f, 0.f, 0.f};
+        }
       }
   };
   for (int item = blockIdx.x; item < total; item += gridDim.x) {
@@ -754,7 +762,8 @@ hipError_t init_gemm_kernels() {
                                hipFuncAttributeMaxDynamicSharedMemorySize, PERSISTENT_LDS_BYTES)) != hipSuccess) return e;
   for (const void* k : {reinterpret_cast<const void*>(gemm_store_kernel<false>), reinterpret_cast<const void*>(gemm_store_kernel<true>)})
     if ((e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, PERSISTENT_LDS_BYTES)) != hipSuccess) return e;
-  for (const void* k : {reinterpret_cast<const void*>(dlogits_kept_kernel<false>), reinterpret_cast<const void*>(dlogits_kept_kernel<true>)})
+  for (const void* k : {reinterpret_cast<const void*>(dlogits_kept_kernel<false, false>), reinterpret_cast<const void*>(dlogits_kept_kernel<false, true>),
+                        reinterpret_cast<const void*>(dlogits_kept_kernel<true, true>)})
     if ((e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, KEPT_LDS_BYTES)) != hipSuccess) return e;
   int dev = 0, cus = 0;
   if ((e = hipGetDevice(&dev)) != hipSuccess) return e;
@@ -774,8 +783,8 @@ void launch_lmhead_dlogits(const DlogitsArgs& a, hipStream_t s) {
   if (a.kept.cap > 0) {    // at most: every half tile of the launch's widest form
     const long long halves = (a.dS_lo ? 4ll : 2ll) * (a.rc.enabled ? a.rc.tiles_v_all : a.tiles_v) * a.tiles_t;
     const dim3 grid((unsigned)(halves < 2 * g_persistent_grid ? halves : 2 * g_persistent_grid));
-    if (a.dS_lo) hipLaunchKernelGGL(dlogits_kept_kernel<true>, grid, dim3(KEPT_THREADS), KEPT_LDS_BYTES, s, a);
-    else hipLaunchKernelGGL(dlogits_kept_kernel<false>, grid, dim3(KEPT_THREADS), KEPT_LDS_BYTES, s, a);
+    auto kernel = a.dS_lo ? dlogits_kept_kernel<true, true> : a.tiles_t <= 2 ? dlogits_kept_kernel<false, true> : dlogits_kept_kernel<false, false>;
+    hipLaunchKernelGGL(kernel, grid, dim3(KEPT_THREADS), KEPT_LDS_BYTES, s, a);
     if ((long long)a.kept.cap >= (long long)a.tiles_v_all * a.tiles_t) return;      // whatever is live, all of it is kept
   }
   hipLaunchKernelGGL(lmhead_dlogits_kernel<false>, dim3(persistent_grid(a.tiles_v, a.tiles_t)), dim3(NTHREADS), PERSISTENT_LDS_BYTES, s, a);
