@@ -46,8 +46,8 @@ def measured_mfma_only_tflops():
 # summarised in profiles/gemm_store_kernel_hbm_traffic.md (mean over a step's 30 launches, of which 20 have work, each
 # counter scaled by what it reads for a plain 1 GiB copy).  Valid only for the kernel sources the
 # counters were taken with: the digest below is of csrc/gemm_core.h + csrc/kernels_gemm.hip.
-TRAFFIC_GEMM_STORE = {"read_bytes": 2871350.6 * 1024 * 2.000, "write_bytes": 311846.1 * 1024 * 1.000,
-                      "sources_sha256": "f4165c128e2a1def2cb94e85659ae956f262514b978bf72787240822f546afda"}
+TRAFFIC_GEMM_STORE = {"read_bytes": 2890192.9 * 1024 * 2.000, "write_bytes": 311846.1 * 1024 * 1.000,
+                      "sources_sha256": "4639371e3610c5d6c5204dda45142fa67681d55e28902bd1d5e8f49560ab3c49"}
 
 
 def kernel_sources_digest() -> str:

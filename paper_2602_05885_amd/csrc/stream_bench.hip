@@ -32,13 +32,13 @@ constexpr int TL_FIRST = PROBE_FIRST, TL_TILES = PROBE_TILES;   // tiles of ever
 
 namespace pg {
 
-// The forward as the library had it before it became persistent: one workgroup per tile, placed by the
-// hardware dispatcher (workgroup b on XCD b mod 8), cold prologue and drain for every tile.
+// The forward as one workgroup per tile, placed by the hardware dispatcher (workgroup b on XCD b mod 8): the same statistics and
+// the same tile order as the persistent form, cold prologue and drain for every tile.
 __global__ __launch_bounds__(NTHREADS) void fwd_one_tile_kernel(FwdArgs a) {
   const Ctl ctl = *a.ctl;
   int tm, tn;
   // the live token tiles are known only on the device; the grid covers the host-side maximum
-  if (!map_tile(blockIdx.x, a.tiles_v, min(a.tiles_t, ctl.n_pad / BN), tm, tn)) return;
+  if (!map_tile(blockIdx.x, a.tiles_v, min(a.tiles_t, ctl.n_pad / BN), tm, tn, true)) return;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave / WN, wn = wave % WN;
@@ -52,13 +52,12 @@ __global__ __launch_bounds__(NTHREADS) void fwd_one_tile_kernel(FwdArgs a) {
 
   const int v_base = tm * BM + wm * WROWS;            // first vocab row of this wavefront's block
   const bool ragged = (tm * BM + BM > a.V);
-  float* red = reinterpret_cast<float*>(g_smem);      // [WM][256 tokens][3]
+  float* red = reinterpret_cast<float*>(g_smem);      // [m, s, u][WM][256 tokens]
 
+  // the library's statistics (lmhead_fwd_body): maxima first, then plain sums, two token columns at a time
+  float mx[GN];
 #pragma unroll
   for (int j = 0; j < GN; ++j) {
-    const int tok_l = wn * WCOLS + j * 16 + (lane & 15);
-    const int tok = tn * BN + tok_l;
-    // max over the raw accumulators (scale > 0 keeps the order); the scale goes on inside the fma
     float mr = NEG_BIG;
 #pragma unroll
     for (int i = 0; i < GM; ++i)
@@ -67,51 +66,54 @@ __global__ __launch_bounds__(NTHREADS) void fwd_one_tile_kernel(FwdArgs a) {
         if (ragged && (v_base + i * 16 + acc_row(r, lane) >= a.V)) acc[i][j][r] = NEG_BIG;
         mr = fmaxf(mr, acc[i][j][r]);
       }
-    float mx = mr * a.scale;
-    const float nmx = -mx;
-    float s = 0.f, u = 0.f;
+    const Two h = swap_halves(mr, mr);
+    mr = fmaxf(h.a, h.b);
+    const Two q = swap_rows(mr, mr);
+    mx[j] = fmaxf(q.a, q.b) * a.scale;
+  }
 #pragma unroll
-    for (int i = 0; i < GM; ++i)
+  for (int j0 = 0; j0 < GN; j0 += 2) {
+    float su[2];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const float dlt = fmaf(acc[i][j][r], a.scale, nmx);
-        const float e = __builtin_amdgcn_exp2f(dlt);
-        s += e;
-        u = fmaf(e, dlt, u);
-      }
-    // sampled token's logit: at most one lane of the whole grid owns (tok, y[tok])
-    const int ytok = a.yc[tok];
-    const int yrel = ytok - v_base;
-    const bool mine = (yrel >= 0) && (yrel < WROWS) && (ytok < a.V) && (((yrel >> 2) & 3) == (lane >> 4));
-    if (__any(mine)) {
-      float zy = 0.f;
+    for (int h = 0; h < 2; ++h) {
+      const int j = j0 + h, tok = tn * BN + wn * WCOLS + j * 16 + (lane & 15);
+      float s = 0.f, u = 0.f;
 #pragma unroll
       for (int i = 0; i < GM; ++i)
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-          if (yrel == i * 16 + acc_row(r, lane)) zy = acc[i][j][r] * a.scale;
-      if (mine) a.zy[tok] = zy;
-    }
-    // the other three 16-lane groups hold the other vocab rows of the same token
+        for (int r = 0; r < 4; ++r) {
+          const float dlt = fmaf(acc[i][j][r], a.scale, -mx[j]);
+          const float e = __builtin_amdgcn_exp2f(dlt);
+          s += e;
+          u = fmaf(e, dlt, u);
+        }
+      const Two x = swap_halves(s, u);
+      su[h] = x.a + x.b;
+      // sampled token's logit: at most one lane of the whole grid owns (tok, y[tok])
+      const int ytok = a.yc[tok];
+      const int yrel = ytok - v_base;
+      const bool mine = (yrel >= 0) && (yrel < WROWS) && (ytok < a.V) && (((yrel >> 2) & 3) == (lane >> 4));
+      if (__any(mine)) {
+        float zy = 0.f;
 #pragma unroll
-    for (int sh = 16; sh <= 32; sh <<= 1) {
-      const float m2 = __shfl_xor(mx, sh), s2 = __shfl_xor(s, sh), u2 = __shfl_xor(u, sh);
-      merge_state(mx, s, u, m2, s2, u2);
+        for (int i = 0; i < GM; ++i)
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            if (yrel == i * 16 + acc_row(r, lane)) zy = acc[i][j][r] * a.scale;
+        if (mine) a.zy[tok] = zy;
+      }
     }
-    if (lane < 16) {
-      float* p = red + (wm * 256 + tok_l) * 3;
-      p[0] = mx; p[1] = s; p[2] = u;
-    }
+    const Two y = swap_rows(su[0], su[1]);
+    const int tok_l = wn * WCOLS + (j0 + ((lane >> 4) & 1)) * 16 + (lane & 15);
+    red[(1 + (lane >> 5)) * (WM * BN) + wm * BN + tok_l] = y.a + y.b;
+    if (lane < 32) red[wm * BN + tok_l] = lane < 16 ? mx[j0] : mx[j0 + 1];
   }
   __syncthreads();
   if (tid < BN) {
-    const float* p0 = red + tid * 3;
-    float m = p0[0], s = p0[1], u = p0[2];
+    const float* p = red + tid;
+    float m = p[0], s = p[WM * BN], u = p[2 * WM * BN];
 #pragma unroll
-    for (int w = 1; w < WM; ++w) {
-      const float* p1 = red + (w * 256 + tid) * 3;
-      merge_state(m, s, u, p1[0], p1[1], p1[2]);
-    }
+    for (int w = 1; w < WM; ++w) merge_state(m, s, u, p[w * BN], p[(WM + w) * BN], p[(2 * WM + w) * BN]);
     const size_t o = (size_t)tm * a.t_cap + (size_t)tn * BN + tid;
     a.part_m[o] = m; a.part_s[o] = s; a.part_u[o] = u;
   }
