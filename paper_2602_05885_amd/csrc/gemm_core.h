@@ -512,12 +512,15 @@ __device__ __forceinline__ void pick_stage(const TileSrc cur, const TileSrc nxt,
 // tiles against this: 128 rows 295 -> 267 us, 192 331 -> 291, 384 473 -> 454, 448 487 -> 484, 640 681 -> 675, 2176 2002 -> 1967; NJ = 6
 // at 704 rows 743 -> 755, at 1216 1208 -> 1233.  (The dH contraction and the recompute of the logits gained nothing: +-0.3 %.)
 // Where a vocab tile's token tiles are handed out before the next one (no logits kept), the early start costs more the more of them share W
-// in the last panel (of SB_N), and the longer the contraction: from five on at K >= 3072 the tile stays whole (short_tile_pays).  Forward-only,
+// in the last panel (of SB_N), and the longer the contraction: from five on at K >= 3072 the tile stays whole (short_tile_pays), unless the launch is so
+// short that what does not fill its last round counts for more.  Forward-only,
 // last tile short / whole: d = 5120, V = 473637, 1150 rows 4480 / 4260 us, 1664 rows 6244 / 5926; V = 151936, 1400 rows 1693 / 1633, 3968 rows 4388 / 4252;
 // d = 3072, 1400 rows 1025 / 1005, 1150 rows 854 / 854; but d = 2560, 1150 rows 711 / 721; four tiles, 800 rows, d = 4096 869 / 873, d = 5120 1093 /
-// 1099; one, 2176 rows 1967 / 2002, 2458 / 2498; short contractions d = 2048, V = 100000, 1150 rows 387 / 388, 1400 rows 458 / 464.
+// 1099; one, 2176 rows 1967 / 2002, 2458 / 2498; short contractions d = 2048, V = 100000, 1150 rows 387 / 388, 1400 rows 458 / 464;
+// fewer than eight rounds of tiles, d = 5120, 1578 rows, V = 28498, 3.06 rounds 392 / 414, d = 4096, 1144 rows, 4.1 rounds 409 / 424, 1664 rows, 4.3 and 6.4 rounds 425 /
+// 431 and 625 / 626; but 10.7 rounds 1028 / 1006, d = 5120, 1400 rows, 7.3 and 9.2 rounds 887 / 879 and 1101 / 1093.
 __host__ __device__ inline int fwd_nj(int cols, int tiles_t) { return cols > (tiles_t > 2 ? 128 : 192) ? 8 : cols > 128 ? 6 : 4; }
-__host__ __device__ inline bool short_tile_pays(int tiles_t, int K) { return K < 3072 || (tiles_t - 1) % SB_N < 4; }
+__host__ __device__ inline bool short_tile_pays(int tiles_t, int K, int tiles, int grid) { return K < 3072 || (tiles_t - 1) % SB_N < 4 || tiles / 8 < grid; }
 
 // The two wavefronts of a row take the 16-column groups of the tile in turn, so that the first NJ MFMA columns of both are its
 // first 32 NJ columns:

@@ -95,7 +95,7 @@ __device__ __forceinline__ void lmhead_fwd_body(FwdArgs a, bool steal, unsigned 
   // forward of a loss call that keeps its logits is the other way round: d = 5120, 12000 rows 13.73 against 14.09 ms, d = 4096, 2869
   // rows 2.71 against 2.75 (every tile ends in 256 KiB of stores, which drives the tiles further apart in time).
   const bool tokens_first = a.kept.tiles == nullptr;
-  const bool whole = tokens_first && !short_tile_pays(tiles_t, a.K);
+  const bool whole = tokens_first && !short_tile_pays(tiles_t, a.K, a.tiles_v * tiles_t, (int)gridDim.x);
   float* red = reinterpret_cast<float*>(g_smem + FWD_RED_OFF);
   int* stash = reinterpret_cast<int*>(g_smem + FWD_STASH_OFF);
   volatile int* claim = reinterpret_cast<volatile int*>(g_smem + FWD_CLAIM_OFF);

@@ -1,5 +1,5 @@
 """Forward-only calls whose last token tile holds few rows, on both sides of the lines between a shortened and a whole one (four and five
-token tiles in the last panel, contractions of 3072): against plain fp64 arithmetic on the same bf16 operands."""
+token tiles in the last panel, contractions of 3072, eight rounds of tiles): against plain fp64 arithmetic on the same bf16 operands."""
 import pytest
 import torch
 
@@ -9,10 +9,11 @@ from paper_2602_05885_amd import synth
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("d", [3008, 3072])
+# (V: 2 vocab tiles, or as many as make eight rounds of tiles on 256 compute units)
+@pytest.mark.parametrize("d,V", [(3008, 300), (3072, 300), (3008, 256 * 410), (3072, 256 * 410)])
 @pytest.mark.parametrize("T", [769, 1025, 1152, 1153, 2048 - 128, 2049, 3073])
-def test_forward_with_a_short_last_tile(T, d):
-    dev, V = torch.device("cuda:0"), 300
+def test_forward_with_a_short_last_tile(T, d, V):
+    dev = torch.device("cuda:0")
     H, W, y = synth.make_head(T, d, V, "bf16", T, dev)
     p = B.Params()
     ws = B.alloc_workspace(T, d, V, 0, p, B.CALL_LOGPROB_FWD, dev)
