@@ -670,6 +670,7 @@ __device__ __forceinline__ void mainloop_stream(const OperandLanes& VA, const Op
 // two rounds with all of the chip's power and bandwidth spent in the first.  Forward only, one for everybody / two for few: d = 4096,
 // 24 rows, 257 tiles 185 / 150 us; 1024 rows, 284 tiles 171 / 148; 1280 rows, 360 tiles 168 / 159, 400 tiles 168 / 168, 450 tiles 180 / 182; 192
 // rows, 380 tiles 189 / 184; d = 2048, 256 rows, 360 tiles 121 / 112, 400 tiles 127 / 123, 430 tiles 127 / 127, 490 tiles 144 / 145.
+// (The caller says where it may, few: see lmhead_fwd_body.)
 // cnt[0..7] must be zero at launch.
 struct TileQueue {
   unsigned* cnt;
@@ -680,14 +681,14 @@ struct TileQueue {
   int dealt = 0;      // which are the first rounds * stride of every share
 
   // rounds: how many entries a workgroup is dealt at most
-  __host__ __device__ inline void deal(int grid, int rounds) {      // (the grid is a multiple of 8)
+  __host__ __device__ inline void deal(int grid, int rounds, bool few) {      // (the grid is a multiple of 8)
     stride = grid >> 3;
-    if (rounds == 2 && total <= grid + grid * 9 / 16) stride = imin(stride, (total + 15) / 16);
+    if (few && rounds == 2 && total <= grid + grid * 9 / 16) stride = imin(stride, (total + 15) / 16);
     dealt = rounds * stride;
   }
-  __device__ __forceinline__ void init(unsigned* cnt_, int total_, int interleaved_, int rounds) {
+  __device__ __forceinline__ void init(unsigned* cnt_, int total_, int interleaved_, int rounds, bool few = false) {
     cnt = cnt_; total = total_; interleaved = interleaved_;
-    deal((int)gridDim.x, rounds);
+    deal((int)gridDim.x, rounds, few);
     unsigned x;
     asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(x));
     home = (int)(x & 7u);

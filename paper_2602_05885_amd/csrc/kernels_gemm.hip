@@ -87,7 +87,12 @@ __device__ __forceinline__ void lmhead_fwd_body(FwdArgs a, bool steal, unsigned 
   const int wm = wave / WN, wn = wave % WN;
   TileQueue Q;
   const bool two = a.tiles_v * tiles_t > (int)gridDim.x;      // (of at most one tile per workgroup there is no second)
-  Q.init(a.queue, a.tiles_v * tiles_t, 0, two ? 2 : 1);
+  // Two tiles for few workgroups (TileQueue): not where logits are parked, K is long and the last token tile is a short one: a launch of
+  // which a part costs less than half is over sooner where no workgroup has two whole tiles.  One for everybody / two for few, d = 4096,
+  // 544 rows, 285 tiles 141 / 158 us, 375 tiles 173 / 179, d = 5120 179 / 196 and 213 / 223, 288 rows, 398 tiles 225 / 236; but d = 2048, 288 rows, 316
+  // tiles 90 / 77, 1312 rows, 318 tiles 97 / 91, and all token tiles whole, d = 4096, 1024 rows, 260 tiles 174 / 165, d = 5120, 256 rows, 316 tiles 268 / 247.
+  const bool few = a.kept.tiles == nullptr || a.K < 3072 || fwd_nj(live_rows - (tiles_t - 1) * BN, tiles_t) == GN;
+  Q.init(a.queue, a.tiles_v * tiles_t, 0, two ? 2 : 1, few);
   const int kept_v = kept_vocab_tiles(a.kept, a.tiles_v, tiles_t);
   // Tile order: all token tiles of a vocab tile in a row, unless tiles are parked.  Forward-only calls, vocabulary fastest
   // against tokens fastest: d = 4096, 768 rows 722 -> 706 us, 4100 rows 3725 -> 3705, 16384 rows 13.95 -> 13.65 ms; d = 5120, 131072
@@ -494,9 +499,9 @@ constexpr int KEPT_THREADS = 256;
 constexpr int KEPT_LDS_BYTES = 256 * KEPT_STRIDE_T;
 static_assert(KEPT_LDS_BYTES >= 128 * EPI_STRIDE && 2 * KEPT_LDS_BYTES <= 160 * 1024, "LDS budget");
 
-// FEW: of at most two token tiles (or an fp32 head), where a group that was not parked is not loaded.  Elsewhere another one's is, as the
-// branch holds the other loads up: d = 5120, 12000 rows 2.80 -> 2.71 ms, 768 rows 187 -> 179 us; but 24 rows of d = 4096 50 -> 53 us, fp32 64 x 1000,
-// 1024 rows 15.3 -> 16.5 us.
+// FEW: of at most two token tiles or two rounds of workgroups (or an fp32 head), where a group that was not parked is not loaded.  Elsewhere
+// another one's is, as the branch holds the other loads up: d = 5120, 12000 rows 2.80 -> 2.71 ms, 768 rows 187 -> 179 us, 1536 rows, 942 tiles 103.6 -> 99.5;
+// but 24 rows of d = 4096 50 -> 53 us, 1536 rows, 348 tiles 38.6 -> 40.0, 1312 rows, 318 tiles 36.0 -> 37.6, fp32 64 x 1000, 1024 rows 15.3 -> 16.5 us.
 template <bool SPLIT, bool FEW>
 __global__ __launch_bounds__(KEPT_THREADS, 2) void dlogits_kept_kernel(DlogitsArgs a) {
   const Ctl ctl = *a.ctl;
@@ -783,7 +788,8 @@ void launch_lmhead_dlogits(const DlogitsArgs& a, hipStream_t s) {
   if (a.kept.cap > 0) {    // at most: every half tile of the launch's widest form
     const long long halves = (a.dS_lo ? 4ll : 2ll) * (a.rc.enabled ? a.rc.tiles_v_all : a.tiles_v) * a.tiles_t;
     const dim3 grid((unsigned)(halves < 2 * g_persistent_grid ? halves : 2 * g_persistent_grid));
-    auto kernel = a.dS_lo ? dlogits_kept_kernel<true, true> : a.tiles_t <= 2 ? dlogits_kept_kernel<false, true> : dlogits_kept_kernel<false, false>;
+    const bool few = a.tiles_t <= 2 || halves <= 4 * g_persistent_grid;
+    auto kernel = a.dS_lo ? dlogits_kept_kernel<true, true> : few ? dlogits_kept_kernel<false, true> : dlogits_kept_kernel<false, false>;
     hipLaunchKernelGGL(kernel, grid, dim3(KEPT_THREADS), KEPT_LDS_BYTES, s, a);
     if ((long long)a.kept.cap >= (long long)a.tiles_v_all * a.tiles_t) return;      // whatever is live, all of it is kept
   }

@@ -30,7 +30,7 @@ static int run_launch(int grid, int total, int order, int forward, int homes, un
     TileQueue& q = w[b].q;
     q.total = total; q.interleaved = order;
     w[b].two = forward && total > grid;
-    q.deal(grid, w[b].two ? 2 : 1);
+    q.deal(grid, w[b].two ? 2 : 1, forward != 2);
     q.home = homes == 0 ? b & 7 : homes == 1 ? (b * 5 + 3) >> 2 & 7 : 2;
     w[b].dealt = total <= (forward ? 2 : 1) * grid;       // nothing beside the dealt entries
   }
@@ -104,7 +104,7 @@ int main() {
   unsigned seed = 1;
   for (int grid : {8, 64, 256})
     for (int order = 0; order < 2; ++order)
-      for (int forward = 0; forward < 2; ++forward)
+      for (int forward = 0; forward < 3; ++forward)      // (2: two tiles each for everybody)
         for (int homes = 0; homes < 3; ++homes)
           for (int total = 1; total <= 5 * grid; total += 1 + (grid > 8) * (int)((seed >> 8) % 23)) {
             seed = seed * 1664525u + 1013904223u;
@@ -112,12 +112,12 @@ int main() {
             if (wrong && fails < 20) printf("grid %d total %d order %d forward %d homes %d: %d wrong\n", grid, total, order, forward, homes, wrong);
             fails += wrong;
           }
-  // The forward's two entries each: with few more tiles than workgroups, as few workgroups as that takes have any.
+  // The forward's two entries each: with few more tiles than workgroups, as few workgroups as that takes have any, where it asks for that.
   for (int grid : {8, 64, 256})
     for (int total = grid + 1; total <= grid + grid * 9 / 16; ++total) {
       TileQueue Q{};
       Q.total = total;
-      Q.deal(grid, 2);
+      Q.deal(grid, 2, true);
       std::vector<int> seen((size_t)total + 64, 0);
       int busy = 0;
       for (int b = 0; b < grid; ++b) {
