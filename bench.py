@@ -46,8 +46,8 @@ def measured_mfma_only_tflops():
 # summarised in profiles/gemm_store_kernel_hbm_traffic.md (mean over a step's 30 launches, of which 20 have work, each
 # counter scaled by what it reads for a plain 1 GiB copy).  Valid only for the kernel sources the
 # counters were taken with: the digest below is of csrc/gemm_core.h + csrc/kernels_gemm.hip.
-TRAFFIC_GEMM_STORE = {"read_bytes": 2919040.9 * 1024 * 2.000, "write_bytes": 311846.1 * 1024 * 1.000,
-                      "sources_sha256": "6474245b17328c239c785742d825225e06d1ac8579225a88ac191d3be3584d6f"}
+TRAFFIC_GEMM_STORE = {"read_bytes": 2941369.6 * 1024 * 2.000, "write_bytes": 311846.1 * 1024 * 1.000,
+                      "sources_sha256": "bec550ee27f2ded6738128bd045a88ebcf3609fe3771815c524e12512fd3c3a2"}
 
 
 def kernel_sources_digest() -> str:
