@@ -931,7 +931,8 @@ __device__ __forceinline__ void raw_unpack(const Raw8<false>& r, float (&v)[8]) 
 //   dX itself does not fit that cache; X, dH and the forward's X are then read past it too (27000 rows, all five launches: 643 -> 599).
 //   fp32: past is never shorter (H 4000 x 1024 18.6 / 21.4, 8000 x 4096 114 / 116, 12000 x 5120 221 / 232; dX 21.3 / 22.3, 145 / 149, 274 / 276).
 // (Forward and backward right after each other on one X like stores past the caches at any size, as X then stays for the backward: 20000 rows of
-// d = 4096 137 us with all stores past them, 153 with these lines, 170 with plain ones.)
+// d = 4096 137 us with all stores past them, 147 to 153 with these lines, 170 with plain ones; 17000 rows 118, 141 and 147; fp32, d = 5120, 8000
+// rows 159 with all past them, 170 with none.  That is not the order of a step, so the lines follow the order above.)
 constexpr long long NORM_H_PAST_BYTES = 144ll << 20;      // of one bf16 [T, d] matrix
 constexpr long long NORM_ALL_PAST_BYTES = 256ll << 20;    // ... the memory-side cache's size
 
