@@ -345,6 +345,28 @@ template <> struct FragA<RowsLoader> {
 template <int PAD>
 __device__ __forceinline__ void place_loop() { asm volatile(".p2align 5\n\t.rept %0\n\ts_nop 0\n\t.endr" ::"n"(PAD)); }
 
+// The order of a stage's MFMAs: every one shares an operand with the one before it.  The matrix cores draw less where an operand stays, and the
+// chip is power-limited: operands in registers (256 workgroups of 8 wavefronts, the engine's 4 x 8 tiles, random values), column by column
+// from row 0 down 2088 TFLOP/s, mfma_snake 2135, mfma_pairs 2148, neither operand shared 2030.  In the contractions, against
+// column by column: forward only 13.35 -> 13.22 ms (16384 rows, d = 4096) and 33.56 -> 33.26 ms (32768 rows, d = 5120) with the snake, which the pairs make
+// longer (13.37 and 34.18: their LDS reads come in twos, and the workgroups of an XCD drift further apart); dW and dH of 12000 rows, d = 5120, together
+// 26.04 -> 25.81 ms with the snake and 25.66 with the pairs.
+// MFMA q (of four) of step s, NJ columns of GM rows in each k-half.  Snake: column s, every second column from the last row up.
+template <int NJ>
+__device__ __forceinline__ void mfma_snake(int s, int q, const bf16x8 (&a)[2][GM], const bf16x8 (&bq)[4], f32x4 (&acc)[GM][GN]) {
+  const int i = s % 2 ? GM - 1 - q : q, ks = s / NJ, j = s % NJ;
+  acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[ks][i], bq[s & 3], acc[i][j], 0, 0, 0);
+}
+// Pairs: steps 2p and 2p + 1 take the columns 2p and 2p + 1 together, row 0 in columns 0, 1, row 1 in columns 1, 0, and so on; every second pair from
+// the last row up.
+template <int NJ>
+__device__ __forceinline__ void mfma_pairs(int s, int q, const bf16x8 (&a)[2][GM], const bf16x8 (&bq)[4], f32x4 (&acc)[GM][GN]) {
+  const int p = s / 2, u = (s % 2) * 2 + q / 2;         // pair of columns, place of the row in its order
+  const int i = p % 2 ? GM - 1 - u : u, h = (u + q) % 2;
+  const int ks = s / NJ, j = (2 * p) % NJ + h;
+  acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[ks][i], bq[(2 * p + h) & 3], acc[i][j], 0, 0, 0);
+}
+
 // Accumulates C(256x256) += A(256 x K) B(256 x K)^T for this workgroup's tile, K = 64 nk.
 // acc[i][j] is the 16x16 MFMA tile at rows wm*64+i*16, cols wn*128+j*16 of the workgroup tile;
 // within it, register r of lane l is row 4*(l>>4)+r, column l&15.
@@ -417,29 +439,24 @@ __device__ __forceinline__ void mainloop(const LoaderA& LA, const TileLoader& LB
     const __amdgpu_buffer_rsrc_t ra2 = LA.rsrc(a2), rb2 = LB.rsrc(kt + 2 < nk);
 #pragma unroll
     for (int s = 0; s < NS - TAIL; ++s) {
-      const int ks = s / GN, j = s % GN;
-      bq[(s + 2) & 3] = rdB(cur, s + 2);
+      if (s % 2 == 0) { bq[(s + 2) & 3] = rdB(cur, s + 2); bq[(s + 3) & 3] = rdB(cur, s + 3); }
       if (s < GM) a[1][s] = rdA(cur, 1, s);
       if (s < BH) LB.issue1(rb1, BH + s, kb1, nxt + SLAB_BYTES, wave);
       if (s > XS && s <= XS + CHUNKS) LA.issue1(ra2, s - XS - 1, ka2, cur, wave);
 #pragma unroll
-      for (int i = 0; i < GM; ++i)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[ks][i], bq[s & 3], acc[i][j], 0, 0, 0);
-      // barrier X: all LDS reads but the newest one (a B fragment) are complete
-      if (s == XS) asm volatile("s_waitcnt lgkmcnt(1)\n\ts_barrier" ::: "memory");
+      for (int q = 0; q < 4; ++q) mfma_pairs<GN>(s, q, a, bq, acc);
+      // barrier X: all LDS reads but the newest two (B fragments) are complete
+      if (s == XS) asm volatile("s_waitcnt lgkmcnt(2)\n\ts_barrier" ::: "memory");
       __builtin_amdgcn_sched_barrier(0);   // keep this read/load/MFMA interleave as written
     }
     // barrier Y
     asm volatile("s_waitcnt vmcnt(4) lgkmcnt(0)\n\ts_barrier" ::: "memory");
 #pragma unroll
     for (int m = 0; m < TAIL * GM; ++m) {
-      const int s = NS - TAIL + m / GM, i = m % GM;
-      const int ks = s / GN, j = s % GN;
-      if (m == 0) bq[0] = rdB(nxt, 0);
-      else if (m <= GM) a[0][m - 1] = rdA(nxt, 0, m - 1);
-      else if (m == GM + 1) bq[1] = rdB(nxt, 1);
+      if (m < 2) bq[m] = rdB(nxt, m);
+      else if (m < 2 + GM) a[0][m - 2] = rdA(nxt, 0, m - 2);
       if (m % GM == 0) LB.issue1(rb2, m / GM, kb2, cur + SLAB_BYTES, wave);
-      acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[ks][i], bq[s & 3], acc[i][j], 0, 0, 0);
+      mfma_pairs<GN>(NS - TAIL + m / GM, m % GM, a, bq, acc);
       __builtin_amdgcn_sched_barrier(0);
     }
   }
@@ -618,7 +635,6 @@ __device__ __forceinline__ void mainloop_stream(const OperandLanes& VA, const Op
     pick_stage(B0, B1, kt + 2, nk, rb2, kb2b);
 #pragma unroll
     for (int s = 0; s < NS - TAIL; ++s) {
-      const int ks = s / NJ, j = s % NJ;
       bq[(s + 2) & 3] = rdB(cur, s + 2);
 #pragma unroll
       for (int q = s * St::A_READS; q < (s + 1) * St::A_READS && q < GM; ++q) a[1][q] = rdA(cur, 1, q);
@@ -626,21 +642,18 @@ __device__ __forceinline__ void mainloop_stream(const OperandLanes& VA, const Op
 #pragma unroll
       for (int q = St::a_first(s); q < St::a_last(s) && q < CHUNKS; ++q) issue_lds(ra2, VA, q, kb2, cur, wave);
 #pragma unroll
-      for (int i = 0; i < GM; ++i)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[ks][i], bq[s & 3], acc[i][j], 0, 0, 0);
+      for (int q = 0; q < 4; ++q) mfma_snake<NJ>(s, q, a, bq, acc);
       if (s == XS) asm volatile("s_waitcnt lgkmcnt(1)\n\ts_barrier" ::: "memory");   // barrier X
       __builtin_amdgcn_sched_barrier(0);
     }
     asm volatile("s_waitcnt vmcnt(4) lgkmcnt(0)\n\ts_barrier" ::: "memory");          // barrier Y
 #pragma unroll
     for (int m = 0; m < TAIL * GM; ++m) {
-      const int s = NS - TAIL + m / GM, i = m % GM;
-      const int ks = s / NJ, j = s % NJ;
       if (m == 0) bq[0] = rdB(nxt, 0);
       else if (m <= GM) a[0][m - 1] = rdA(nxt, 0, m - 1);
       else if (m == GM + 1) bq[1] = rdB(nxt, 1);
       if (m % GM == 0) issue_lds(rb2, VB, m / GM, kb2b, cur + SLAB_BYTES, wave);
-      acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[ks][i], bq[s & 3], acc[i][j], 0, 0, 0);
+      mfma_snake<NJ>(NS - TAIL + m / GM, m % GM, a, bq, acc);
       __builtin_amdgcn_sched_barrier(0);
     }
   }
