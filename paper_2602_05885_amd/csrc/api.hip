@@ -837,7 +837,7 @@ int32_t loss_fwd_bwd(int sft, const void* H, const void* W, const int32_t* y, co
   run_staging(pl, ws, H, W, y, shard.v_offset, prep, true, st, norm ? &nf : nullptr);
 
   const void* Wop = pl.is_f32 ? static_cast<const void*>(at<__bf16>(ws, pl.Wc)) : W;
-  const pg::Ctl* ctl = at<pg::Ctl>(ws, pl.ctl);
+  pg::Ctl* ctl = at<pg::Ctl>(ws, pl.ctl);
   const int d_i = (int)pl.d;
   const int kc0 = (int)(((pl.V < pl.vc ? pl.V : pl.vc) + 255) / 256 * 256);      // contraction length of the first chunk
   const bool direct = pl.direct_fits && !p.w_transposed, transposed = !direct || pl.t_cap > pg::DIRECT_MAX_ROWS;
@@ -943,8 +943,7 @@ int32_t loss_fwd_bwd(int sft, const void* H, const void* W, const int32_t* y, co
 
   pg::FinishArgs fin{at<float>(ws, pl.lossterm), at<unsigned long long>(ws, pl.counters), loss_out,
                      reinterpret_cast<long long*>(counters_out), at<pg::Ctl>(ws, pl.ctl)};
-  pg::ScatterArgs sc{at<float>(ws, pl.dHacc), at<int>(ws, pl.pos), dH, (int)pl.T, d_i, pl.is_f32 || shard.dH_f32,
-                     1, pl.acc_rows, (d_i + 255) / 256, kc0 / 64, pl.is_f32, pl.cap_t, few, ctl};
+  pg::ScatterArgs sc{at<float>(ws, pl.dHacc), at<int>(ws, pl.pos), dH, (int)pl.T, d_i, pl.is_f32 || shard.dH_f32, ctl};
   if (norm) pg::launch_scatter_dx_norm(sc, nf, fin, fold, st);
   else pg::launch_scatter_dh(sc, fin, fold, st);
   return guard.check(shard.what ? shard.what : sft ? "pg_sft_fwd_bwd" : norm ? "pg_loss_fwd_bwd_normed" : "pg_loss_fwd_bwd");

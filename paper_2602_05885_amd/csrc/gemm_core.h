@@ -60,15 +60,17 @@ constexpr int CHUNKS = 32 / NW;                  // direct loads per wavefront p
 constexpr int EPI_STRIDE = 528;                  // 132 dwords
 constexpr int EPI_STRIDE_T = 544;                // 136 dwords
 constexpr int GEMM_LDS_BYTES = 256 * EPI_STRIDE_T; // 136 KiB >= the 128 KiB double-buffered main loop
+constexpr int GW = 5;             // MFMA tiles along m per wavefront in wide tiles
+constexpr int WIDE_ROWS = 64 * GW, WIDE_LDS_BYTES = 2 * (WIDE_ROWS * BK * 2 + SLAB_BYTES);
 static_assert(GEMM_LDS_BYTES >= 2 * STAGE_BYTES, "LDS budget");
 static_assert(GM == 4 && GN == 8, "the main loop's schedule is written for 4 x 8 MFMA tiles per wavefront");
 
-// ---- control block written by the row-compaction kernel (device memory) ----
+// ---- control block written by the row-compaction kernel, dh_slabs by the dH launches (device memory) ----
 struct Ctl {
   int n_active;   // number of compacted rows
   int n_pad;      // n_active rounded up to a multiple of 256
   float norm;     // loss normaliser
-  int pad_;
+  int dh_slabs;   // parts of the dH accumulator (DhForm): the dH launches settle it, the scatter adds that many
 };
 
 // ---- workgroup -> tile mapping -------------------------------------------------
@@ -175,8 +177,8 @@ __host__ __device__ inline int dh_split(int n_pad, int acc_rows, int tiles_n, in
   const int tiles = (n_pad / 256) * tiles_n;
   int best = 1;
   long long best_cost = 0;
-  // (unrolled: every workgroup of the dH and scatter launches comes through here, and a division by a variable is a
-  // sequence of 20 instructions; scatter of 4951 rows 23 -> 11 us)
+  // (unrolled: every workgroup of a dH launch comes through here, and a division by a variable is a
+  // sequence of 20 instructions)
 #pragma unroll
   for (int ks = 1; ks <= SPLIT_MAX; ++ks) {
     if (ks > 1 && ((long long)ks * n_pad > acc_rows || ks * SPLIT_MIN_STAGES > k_stages)) break;
@@ -201,6 +203,39 @@ __host__ __device__ inline int dh_slabs(int n_pad, int acc_rows, int tiles_n, in
   return ks * dh_products(n_pad, acc_rows, tiles_n, ks, split_f32);
 }
 
+// dW and dH run in tiles of 256 or of 320 (wide) output columns.  A wide tile takes 1.25 times as long, less WIDE_GAIN thousandths for the operand bytes
+// that it saves, so it is chosen by the tiles that either needs, and by how these fill the rounds over 256 compute units.  A
+// last round that is partly filled costs about the mean of its share and of a whole round: with the rest of the chip idle, what runs runs faster.
+// Measured, launches in turn in one process, 256 / 320:
+//   d = 5120 (20 / 16 tiles)   dH, 12000 rows, 3.67 / 2.94 rounds 7.72 / 6.99 ms, 16384 rows, 5 / 4 rounds 3.69 / 3.57;
+//                              dW, 10 / 8 rounds of 128 vocab tiles 3.60 / 3.48 ms, 46.4 / 37.1 rounds, 11 stages 1323 / 1273 us
+//   d = 4096 (16 / 13 tiles)   dH, 10000 rows, 2.5 / 2.03 rounds 5.82 / 6.51 ms (stays 256), 4100 rows, split 4.00 / 3.95;
+//                              dW, 37.1 / 30.2 rounds, 16 stages 1308 / 1255 us, 65 stages, bf16 3.55 / 3.51 ms
+//   d = 1920 (8 / 6 tiles)     20000 rows, dW 2.98 / 2.65 ms, dH 3.10 / 2.66
+constexpr int WIDE_GAIN = 35;
+__host__ __device__ inline int store_tiles_n(int n, bool wide) { return wide ? (n + WIDE_ROWS - 1) / WIDE_ROWS : (n + BN - 1) / BN; }
+__host__ __device__ inline long long launch_cost(int tiles, int stages, bool wide) {
+  const long long rounds_x512 = ((long long)tiles + 255) / 256 * 256 + tiles;
+  return rounds_x512 * (stages + SPLIT_TILE_STAGES) * (wide ? GW * (1000 - WIDE_GAIN) : GM * 1000);
+}
+__host__ __device__ inline bool wide_pays(int tiles_m, int n, int stages, int ks_256 = 1, int ks_320 = 1) {
+  return launch_cost(tiles_m * ks_320 * store_tiles_n(n, true), (stages + ks_320 - 1) / ks_320, true) <
+         launch_cost(tiles_m * ks_256 * store_tiles_n(n, false), (stages + ks_256 - 1) / ks_256, false);
+}
+// The form of a dH contraction that may be split (the rows of a single token block): parts, products (slabs: ks products) and tiles.
+struct DhForm { int ks, products; bool wide; };
+__host__ __device__ inline DhForm dh_form(int n_pad, int acc_rows, int n, int k_stages, int split_f32) {
+  DhForm f;
+  f.wide = false;
+  f.ks = dh_split(n_pad, acc_rows, store_tiles_n(n, false), k_stages);
+  f.products = dh_products(n_pad, acc_rows, store_tiles_n(n, false), f.ks, split_f32);
+  if (split_f32) return f;
+  const int ks = dh_split(n_pad, acc_rows, store_tiles_n(n, true), k_stages);
+  f.wide = wide_pays(n_pad / BM, n, k_stages, f.ks, ks);
+  if (f.wide) f.ks = ks;
+  return f;
+}
+
 // Split-K factor of the dW contraction (over the stages of dw_stages) of a head so small that its tiles leave most
 // compute units idle: parts of at least DW_MIN_STAGES stages, at most `cap` of them (what the slabs hold).
 constexpr int DW_MIN_STAGES = 4, DW_SPLIT_MAX = 16;
@@ -217,13 +252,16 @@ __host__ __device__ inline int dw_split(int stages, int cap) { return imax(1, im
 // One wavefront load instruction fills 1024 contiguous LDS bytes (8 rows); lane l lands at row
 // l/8, position l%8, so it fetches the logical chunk (l%8) ^ ((row>>1)&7) of that row.
 // Loads beyond the buffer resource's size return 0, which pads ragged tiles.
+// G: MFMA rows of a wavefront, i.e. the slab has 64 G rows.
 static_assert(BM == BN, "one loader serves both operands");
-struct TileLoader {
+template <int G>
+struct SlabLoader {
+  static constexpr int GROUPS = G;
   static constexpr uint32_t k_step = BK * 2;   // bytes from one stage to the next
   __device__ __forceinline__ bool on(int kt, int nk) const { return kt < nk; }
   const void* base;
   uint32_t bytes;
-  uint32_t voff[CHUNKS];
+  uint32_t voff[G];
 
   // Buffer resource over the operand; with on == false its range is empty, so loads through it
   // fetch nothing and deliver zeros (used to switch the loads off beyond the last stage without
@@ -232,12 +270,12 @@ struct TileLoader {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, on ? bytes : 0u, 0x00020000);
   }
 
-  // The resource covers only the (up to) 256 rows of this tile, from byte k_byte0 of its first
+  // The resource covers only the (up to) 64 G rows of this tile, from byte k_byte0 of its first
   // row to the end of its last existing row, so operands of any size can be addressed (a
   // resource's range and the lane offsets are 32-bit) and rows beyond rows_total read as 0.
   __device__ __forceinline__ void init(const void* base_, int rows_total, int row0, int ld_elems, uint32_t k_byte0,
                                        int tid) {
-    const int rows = min(max(rows_total - row0, 0), BM);
+    const int rows = min(max(rows_total - row0, 0), 64 * G);
     const uint64_t b = reinterpret_cast<uint64_t>(base_) + (uint64_t)row0 * (uint64_t)ld_elems * 2u + k_byte0;
     // the tile index is the same for the whole workgroup: keep the resource in scalar registers
     // (left to itself the compiler treats it as per-lane and loops over every load)
@@ -247,7 +285,7 @@ struct TileLoader {
     bytes = __builtin_amdgcn_readfirstlane(rows > 0 ? (uint32_t)rows * (uint32_t)ld_elems * 2u - k_byte0 : 0u);
     const int lane = tid & 63, wave = tid >> 6;
 #pragma unroll
-    for (int i = 0; i < CHUNKS; ++i) {
+    for (int i = 0; i < G; ++i) {
       const int row = (i * NW + wave) * 8 + (lane >> 3);
       const int chunk = (lane & 7) ^ ((row >> 1) & 7);
       voff[i] = (uint32_t)row * (uint32_t)ld_elems * 2u + (uint32_t)chunk * 16u;
@@ -262,17 +300,23 @@ struct TileLoader {
     __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void*)dst, 16, voff[i], k_byte_off, 0, 0);
   }
 };
+typedef SlabLoader<GM> TileLoader;
 
-// An A operand whose k runs over the ROWS of its matrix (X[k][n], n contiguous): a slab is 64 rows x 256
-// columns, 512 B per row, and the fragments are read transposed (ds_read_b64_tr_b16: a 16-lane group reads 4 rows
+// An A operand whose k runs over the ROWS of its matrix (X[k][n], n contiguous): a slab is 64 rows x 64 G
+// columns, 128 G bytes per row, and the fragments are read transposed (ds_read_b64_tr_b16: a 16-lane group reads 4 rows
 // x 16 columns, lane i receives the 4 rows of column i).  The 32-byte column group p of row r is stored at position
-// p ^ s(r), s(r) = (r & 3) | (((r >> 3) & 1) << 2): the eight rows that a half-wavefront reads then lie in eight
-// different groups of 8 banks.  One wavefront load instruction fills two rows.
+// p ^ swizzle(r): the eight rows that a half-wavefront reads (four in a row, and the four that lie eight further) then lie in eight
+// different groups of 8 banks.  Rows of 512 bytes all begin in the same bank, so that takes three bits; rows of 640 begin in either half of
+// the banks in turn, which leaves two, and keeps the twenty column groups among themselves.
 typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
+template <int G>
 struct RowsLoader {
+  static_assert(G == 4 || G == 5, "rows of 512 or 640 bytes");
+  static constexpr int GROUPS = G, ROW_BYTES = 128 * G, ROW_CHUNKS = ROW_BYTES / 16;
+  static __host__ __device__ inline int swizzle(int row) { return G == 4 ? (row & 3) | (((row >> 3) & 1) << 2) : ((row >> 1) & 1) | (((row >> 3) & 1) << 1); }
   const void* base;
   uint32_t bytes;
-  uint32_t voff[CHUNKS];
+  uint32_t voff[G];
   uint32_t k_step;      // bytes from one stage to the next
   int rows;             // rows that exist
   // (a stage without a single row is switched off: its offset would lie beyond the resource's range)
@@ -280,6 +324,12 @@ struct RowsLoader {
 
   __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(bool on) const {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, on ? bytes : 0u, 0x00020000);
+  }
+  // Where 16-byte chunk c of the slab in LDS (counted through its rows) comes from: row and byte in the row
+  static __host__ __device__ inline void source(int c, int& row, int& byte) {
+    row = c / ROW_CHUNKS;
+    const int q = c - row * ROW_CHUNKS;
+    byte = ((((q >> 1) ^ swizzle(row)) << 1) | (q & 1)) * 16;
   }
   // rows [k_row0, k_rows) of a matrix of row length ld, from column col0 on.  Rows at and beyond k_rows read as
   // zero; columns beyond the matrix read whatever follows in memory within it (they only reach output columns
@@ -294,10 +344,10 @@ struct RowsLoader {
     k_step = (uint32_t)BK * (uint32_t)ld * 2u;
     const int lane = tid & 63, wave = tid >> 6;
 #pragma unroll
-    for (int i = 0; i < CHUNKS; ++i) {
-      const int row = (i * NW + wave) * 2 + (lane >> 5), c = lane & 31;
-      const int s = (row & 3) | (((row >> 3) & 1) << 2);
-      voff[i] = (uint32_t)row * (uint32_t)ld * 2u + (uint32_t)((((c >> 1) ^ s) << 1) | (c & 1)) * 16u;
+    for (int i = 0; i < G; ++i) {
+      int row, byte;
+      source((i * NW + wave) * 64 + lane, row, byte);
+      voff[i] = (uint32_t)row * (uint32_t)ld * 2u + (uint32_t)byte;
     }
   }
   __device__ __forceinline__ void issue1(__amdgpu_buffer_rsrc_t r, int i, uint32_t k_byte_off, char* slab, int wave) const {
@@ -310,29 +360,35 @@ struct RowsLoader {
 // it the compiler waits for every outstanding global -> LDS load in front of it.  The schedule's barriers order the two.)
 __device__ __forceinline__ bf16x4 ds_read_tr(lds_bf16x4* __restrict__ p) { return __builtin_amdgcn_ds_read_tr16_b64_v4bf16(p); }
 
+// Which 16 rows of the A slab MFMA tile i of wavefront row wm has: 64 in a row per wavefront, and the fifth tiles of the four behind them, so that what
+// a wavefront stores begins on a 128-byte line (80 rows in a row per wavefront: an accumulating dW of d = 4096 took 6 % longer).
+__host__ __device__ inline int mfma_rows(int wm, int i) { return i < GM ? wm * GM + i : WM * GM + wm; }
+
 // Fragments of the A slab: MFMA tile i of this wavefront, k-half ks of the stage.
 template <class Loader> struct FragA;
-template <> struct FragA<TileLoader> {
-  uint32_t off, koff[2];
+template <int G> struct FragA<SlabLoader<G>> {
+  uint32_t off, off5, koff[2];
   __device__ __forceinline__ FragA(int lane, int wm) {
-    off = (uint32_t)(wm * WROWS + (lane & 15)) * 128u;
+    off = (uint32_t)(mfma_rows(wm, 0) * 16 + (lane & 15)) * 128u;
+    off5 = (uint32_t)(mfma_rows(wm, GM) * 16 + (lane & 15)) * 128u;
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) koff[ks] = (uint32_t)(((ks * 4 + (lane >> 4)) ^ ((lane >> 1) & 7)) << 4);
   }
   __device__ __forceinline__ bf16x8 read(const char* st, int ks, int i) const {
-    return *reinterpret_cast<const bf16x8*>(st + off + i * (16 * 128) + koff[ks]);
+    return *reinterpret_cast<const bf16x8*>(st + (i < GM ? off + i * (16 * 128) : off5) + koff[ks]);
   }
 };
-template <> struct FragA<RowsLoader> {
-  uint32_t off[GM];
+template <int G> struct FragA<RowsLoader<G>> {
+  static constexpr int ROW_BYTES = RowsLoader<G>::ROW_BYTES;
+  uint32_t off[G];
   __device__ __forceinline__ FragA(int lane, int wm) {
-    const int r = (lane & 15) >> 2, g = lane >> 4, s = r | ((g & 1) << 2);
+    const int row = (lane >> 4) * 8 + ((lane & 15) >> 2), s = RowsLoader<G>::swizzle(row);       // (the same four rows further)
 #pragma unroll
-    for (int i = 0; i < GM; ++i) off[i] = (uint32_t)(g * 8 + r) * 512u + (uint32_t)((wm * GM + i) ^ s) * 32u + (uint32_t)(lane & 3) * 8u;
+    for (int i = 0; i < G; ++i) off[i] = (uint32_t)row * ROW_BYTES + (uint32_t)(mfma_rows(wm, i) ^ s) * 32u + (uint32_t)(lane & 3) * 8u;
   }
   __device__ __forceinline__ bf16x8 read(const char* st, int ks, int i) const {
-    const char* p = st + off[i] + ks * (32 * 512);
-    const bf16x4 lo = ds_read_tr((lds_bf16x4*)p), hi = ds_read_tr((lds_bf16x4*)(p + 4 * 512));
+    const char* p = st + off[i] + ks * (32 * ROW_BYTES);
+    const bf16x4 lo = ds_read_tr((lds_bf16x4*)p), hi = ds_read_tr((lds_bf16x4*)(p + 4 * ROW_BYTES));
     return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
   }
 };
@@ -351,7 +407,7 @@ __device__ __forceinline__ void place_loop() { asm volatile(".p2align 5\n\t.rept
 // column by column: forward only 13.35 -> 13.22 ms (16384 rows, d = 4096) and 33.56 -> 33.26 ms (32768 rows, d = 5120) with the snake, which the pairs make
 // longer (13.37 and 34.18: their LDS reads come in twos, and the workgroups of an XCD drift further apart); dW and dH of 12000 rows, d = 5120, together
 // 26.04 -> 25.81 ms with the snake and 25.66 with the pairs.
-// MFMA q (of four) of step s, NJ columns of GM rows in each k-half.  Snake: column s, every second column from the last row up.
+// MFMA q (of G) of step s, NJ columns of G rows in each k-half.  Snake: column s, every second column from the last row up.
 template <int NJ>
 __device__ __forceinline__ void mfma_snake(int s, int q, const bf16x8 (&a)[2][GM], const bf16x8 (&bq)[4], f32x4 (&acc)[GM][GN]) {
   const int i = s % 2 ? GM - 1 - q : q, ks = s / NJ, j = s % NJ;
@@ -359,51 +415,57 @@ __device__ __forceinline__ void mfma_snake(int s, int q, const bf16x8 (&a)[2][GM
 }
 // Pairs: steps 2p and 2p + 1 take the columns 2p and 2p + 1 together, row 0 in columns 0, 1, row 1 in columns 1, 0, and so on; every second pair from
 // the last row up.
-template <int NJ>
-__device__ __forceinline__ void mfma_pairs(int s, int q, const bf16x8 (&a)[2][GM], const bf16x8 (&bq)[4], f32x4 (&acc)[GM][GN]) {
-  const int p = s / 2, u = (s % 2) * 2 + q / 2;         // pair of columns, place of the row in its order
-  const int i = p % 2 ? GM - 1 - u : u, h = (u + q) % 2;
+template <int NJ, int G>
+__device__ __forceinline__ void mfma_pairs(int s, int q, const bf16x8 (&a)[2][G], const bf16x8 (&bq)[4], f32x4 (&acc)[G][GN]) {
+  const int p = s / 2, z = (s % 2) * G + q, u = z / 2;         // pair of columns, place in it, place of the row in its order
+  const int i = p % 2 ? G - 1 - u : u, h = (u + z) % 2;
   const int ks = s / NJ, j = (2 * p) % NJ + h;
   acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[ks][i], bq[(2 * p + h) & 3], acc[i][j], 0, 0, 0);
 }
 
-// Accumulates C(256x256) += A(256 x K) B(256 x K)^T for this workgroup's tile, K = 64 nk.
-// acc[i][j] is the 16x16 MFMA tile at rows wm*64+i*16, cols wn*128+j*16 of the workgroup tile;
+// Accumulates C(64G x 256) += A(64G x K) B(256 x K)^T for this workgroup's tile, K = 64 nk, G = 4 or 5.
+// acc[i][j] is the 16x16 MFMA tile at rows 16 mfma_rows(wm, i), cols wn*128+j*16 of the workgroup tile;
 // within it, register r of lane l is row 4*(l>>4)+r, column l&15.
 //
-// A stage (64 of k) is 16 steps s = (ks, j) of 4 MFMAs.  Per wavefront and stage:
+// Tiles of 320 rows: a tenth fewer operand bytes and an eighth fewer LDS reads per flop, which is what a power-limited contraction is made of.  This loop
+// alone, 256 / 320 rows: d x tokens of 5120 x 16384 over 32768 1484 / 1550 TFLOP/s, V x tokens of 151936 x 8192 over 5120 1539 / 1593, d x V of
+// 5120 x 151936 over 2816 1513 / 1542.  (More rows do not fit: two stages of LDS are 144 KiB here, and 160 of 256 registers accumulators.)
+//
+// A stage (64 of k) is 16 steps s = (ks, j) of G MFMAs.  Per wavefront and stage:
 //   steps 0..1   second half of the B loads of stage kt+1 (the first half went out in the
 //                previous tail), A fragments of the second k-half
-//   step  4      barrier X: every A read of this stage is complete -> its A slab is free
-//   steps 5..8   A loads of stage kt+2 into that slab, one per step
+//   step  G      barrier X: every A read of this stage is complete -> its A slab is free
+//   then         A loads of stage kt+2 into that slab, one in each of G steps
 //   step  13     barrier Y: every B read of this stage is complete and stage kt+1 has landed
-//                (the wavefront leaves only its 4 newest loads, the A loads of kt+2, in flight)
+//                (the wavefront leaves only its G newest loads, the A loads of kt+2, in flight)
 //   steps 14,15  "tail": first half of the B loads of stage kt+2, first LDS reads of stage kt+1,
-//                under the last 8 MFMAs of stage kt
+//                under the last 2 G MFMAs of stage kt
 // On return every load has landed and every wavefront has passed a barrier, so the caller may
 // reuse the LDS.  The barriers carry their own waits; the "memory" clobber keeps LDS accesses on
 // their side of them.
 template <class LoaderA>
 __device__ __forceinline__ void mainloop(const LoaderA& LA, const TileLoader& LB, int nk, char* smem,
-                                         f32x4 (&acc)[GM][GN]) {
+                                         f32x4 (&acc)[LoaderA::GROUPS][GN]) {
+  constexpr int G = LoaderA::GROUPS;
+  constexpr int A_BYTES = G * 64 * BK * 2, STAGE = A_BYTES + SLAB_BYTES;      // A slab, then B slab
   constexpr int NS = 2 * GN;          // steps per stage
   constexpr int TAIL = 2;             // steps behind barrier Y
-  constexpr int XS = 4;               // barrier X follows this step
+  constexpr int XS = G;               // barrier X follows this step
   constexpr int BH = CHUNKS / 2;      // B loads per half
-  static_assert(CHUNKS == 4 && BH <= XS && XS + CHUNKS < NS - TAIL, "load schedule");
+  static_assert(CHUNKS == 4 && BH <= XS && XS + G < NS - TAIL && G + 2 <= TAIL * G, "load schedule");
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WN, wn = wave % WN;
   const int lrow = lane & 15;
   const int xr = (lane >> 1) & 7;
   const FragA<LoaderA> fa(lane, wm);
-  const uint32_t b_off = (uint32_t)(wn * WCOLS + lrow) * 128u + SLAB_BYTES;
+  const uint32_t b_off = (uint32_t)(wn * WCOLS + lrow) * 128u + A_BYTES;
   uint32_t koff[2];
 #pragma unroll
   for (int ks = 0; ks < 2; ++ks) koff[ks] = (uint32_t)(((ks * 4 + (lane >> 4)) ^ xr) << 4);
   if (nk <= 0) return;
 
-  bf16x8 a[2][GM], bq[4];
+  bf16x8 a[2][G], bq[4];
   auto rdA = [&](const char* st, int ks, int i) -> bf16x8 { return fa.read(st, ks, i); };
   auto rdB = [&](const char* st, int s) -> bf16x8 {   // B fragment of step s
     return *reinterpret_cast<const bf16x8*>(st + b_off + (s % GN) * (16 * 128) + koff[s / GN]);
@@ -412,26 +474,26 @@ __device__ __forceinline__ void mainloop(const LoaderA& LA, const TileLoader& LB
   {  // prologue: stage 0 complete, A and the first half of B of stage 1
     const __amdgpu_buffer_rsrc_t ra = LA.rsrc(LA.on(0, nk)), rb = LB.rsrc(true);
 #pragma unroll
-    for (int i = 0; i < CHUNKS; ++i) LA.issue1(ra, i, 0, smem, wave);
+    for (int i = 0; i < G; ++i) LA.issue1(ra, i, 0, smem, wave);
 #pragma unroll
-    for (int i = 0; i < CHUNKS; ++i) LB.issue1(rb, i, 0, smem + SLAB_BYTES, wave);
+    for (int i = 0; i < CHUNKS; ++i) LB.issue1(rb, i, 0, smem + A_BYTES, wave);
     const bool a1 = LA.on(1, nk);
     const __amdgpu_buffer_rsrc_t ra1 = LA.rsrc(a1), rb1 = LB.rsrc(nk > 1);
 #pragma unroll
-    for (int i = 0; i < CHUNKS; ++i) LA.issue1(ra1, i, a1 ? LA.k_step : 0u, smem + STAGE_BYTES, wave);
+    for (int i = 0; i < G; ++i) LA.issue1(ra1, i, a1 ? LA.k_step : 0u, smem + STAGE, wave);
 #pragma unroll
-    for (int i = 0; i < BH; ++i) LB.issue1(rb1, i, BK * 2, smem + STAGE_BYTES + SLAB_BYTES, wave);
+    for (int i = 0; i < BH; ++i) LB.issue1(rb1, i, BK * 2, smem + STAGE + A_BYTES, wave);
   }
-  asm volatile("s_waitcnt vmcnt(6)\n\ts_barrier" ::: "memory");   // all but the CHUNKS + BH newest
+  asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(G + BH) : "memory");   // all but the G + BH newest
   bq[0] = rdB(smem, 0);
 #pragma unroll
-  for (int i = 0; i < GM; ++i) a[0][i] = rdA(smem, 0, i);
+  for (int i = 0; i < G; ++i) a[0][i] = rdA(smem, 0, i);
   bq[1] = rdB(smem, 1);
 
   place_loop<3>();
   for (int kt = 0; kt < nk; ++kt) {
-    char* cur = smem + (kt & 1) * STAGE_BYTES;
-    char* nxt = smem + ((kt + 1) & 1) * STAGE_BYTES;
+    char* cur = smem + (kt & 1) * STAGE;
+    char* nxt = smem + ((kt + 1) & 1) * STAGE;
     const uint32_t kb1 = (uint32_t)(kt + 1) * (BK * 2), kb2 = (uint32_t)(kt + 2) * (BK * 2);
     const bool a2 = LA.on(kt + 2, nk);
     const uint32_t ka2 = a2 ? (uint32_t)(kt + 2) * LA.k_step : 0u;
@@ -440,23 +502,23 @@ __device__ __forceinline__ void mainloop(const LoaderA& LA, const TileLoader& LB
 #pragma unroll
     for (int s = 0; s < NS - TAIL; ++s) {
       if (s % 2 == 0) { bq[(s + 2) & 3] = rdB(cur, s + 2); bq[(s + 3) & 3] = rdB(cur, s + 3); }
-      if (s < GM) a[1][s] = rdA(cur, 1, s);
-      if (s < BH) LB.issue1(rb1, BH + s, kb1, nxt + SLAB_BYTES, wave);
-      if (s > XS && s <= XS + CHUNKS) LA.issue1(ra2, s - XS - 1, ka2, cur, wave);
+      if (s < G) a[1][s] = rdA(cur, 1, s);
+      if (s < BH) LB.issue1(rb1, BH + s, kb1, nxt + A_BYTES, wave);
+      if (s > XS && s <= XS + G) LA.issue1(ra2, s - XS - 1, ka2, cur, wave);
 #pragma unroll
-      for (int q = 0; q < 4; ++q) mfma_pairs<GN>(s, q, a, bq, acc);
-      // barrier X: all LDS reads but the newest two (B fragments) are complete
-      if (s == XS) asm volatile("s_waitcnt lgkmcnt(2)\n\ts_barrier" ::: "memory");
+      for (int q = 0; q < G; ++q) mfma_pairs<GN>(s, q, a, bq, acc);
+      // barrier X: all LDS reads but those of an even step XS, two B fragments, are complete
+      if (s == XS) asm volatile("s_waitcnt lgkmcnt(%0)\n\ts_barrier" ::"n"(XS % 2 ? 0 : 2) : "memory");
       __builtin_amdgcn_sched_barrier(0);   // keep this read/load/MFMA interleave as written
     }
     // barrier Y
-    asm volatile("s_waitcnt vmcnt(4) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(G) : "memory");
 #pragma unroll
-    for (int m = 0; m < TAIL * GM; ++m) {
+    for (int m = 0; m < TAIL * G; ++m) {
       if (m < 2) bq[m] = rdB(nxt, m);
-      else if (m < 2 + GM) a[0][m - 2] = rdA(nxt, 0, m - 2);
-      if (m % GM == 0) LB.issue1(rb2, m / GM, kb2, cur + SLAB_BYTES, wave);
-      mfma_pairs<GN>(NS - TAIL + m / GM, m % GM, a, bq, acc);
+      else if (m < 2 + G) a[0][m - 2] = rdA(nxt, 0, m - 2);
+      if (m % G == 0) LB.issue1(rb2, m / G, kb2, cur + A_BYTES, wave);
+      mfma_pairs<GN>(NS - TAIL + m / G, m % G, a, bq, acc);
       __builtin_amdgcn_sched_barrier(0);
     }
   }
@@ -776,9 +838,10 @@ __device__ __forceinline__ int queue_broadcast(volatile int* slot, int value_of_
 // the column (n) is lane & 15.
 __device__ __forceinline__ int acc_row(int r, int lane) { return ((lane >> 4) << 2) + r; }
 
-__device__ __forceinline__ void zero_acc(f32x4 (&acc)[GM][GN]) {
+template <int G>
+__device__ __forceinline__ void zero_acc(f32x4 (&acc)[G][GN]) {
 #pragma unroll
-  for (int i = 0; i < GM; ++i)
+  for (int i = 0; i < G; ++i)
 #pragma unroll
     for (int j = 0; j < GN; ++j)
 #pragma unroll

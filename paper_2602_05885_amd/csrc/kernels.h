@@ -177,7 +177,7 @@ struct StoreArgs {
   int a_rows, b_rows;   // rows that exist in A / B (loads beyond them give 0)
   int lda, ldb;
   int M, N, K;
-  int tiles_m, tiles_n;
+  int tiles_m, tiles_n; // in tiles of 256 x 256 (StoreShape has those of the launch)
   void* C;              // [M, ldc] fp32 or bf16
   int ldc;
   int accumulate;
@@ -185,7 +185,7 @@ struct StoreArgs {
   int k_from_ctl;       // contraction length = active tokens, up to whole stages (dw_stages)
   int m_from_ctl;       // row extent = active tokens: rows of C from there on, up to the padded count, are left as they are
   TokenBlocks blk;      // of the token extent
-  int split_k;          // with m_from_ctl: cut K into dh_slabs(n_pad, acc_rows, tiles_n, split_stages, ..) parts, part p writes rows p n_pad + m
+  int split_k;          // with m_from_ctl: cut K into the parts of dh_form(n_pad, acc_rows, N, split_stages, ..), part p writes rows p n_pad + m
   int acc_rows;         // rows of C
   int dw_cap;           // > 0, with k_from_ctl: cut K into dw_split(K stages, dw_cap) parts (times three products for fp32
                         // heads); part p writes rows p slab_rows + m of `slabs`, fp32 scratch that dw_fold adds up.
@@ -194,7 +194,7 @@ struct StoreArgs {
   int slab_rows;
   float* slabs;
   int split_stages;     // stages of the first chunk's contraction
-  const Ctl* ctl;
+  Ctl* ctl;             // (a dH launch leaves its number of slabs there)
   unsigned* queue;      // [8] tile counters of this launch's queue, zero at launch
   Rechunk rc;           // see there; rc_role 0: not a chunked launch, 1: dW of a chunk, 2: dH of a chunk
   int rc_role;
@@ -331,12 +331,7 @@ struct ScatterArgs {
   void* dH;             // [T, d]
   int T, d;
   int out_f32;
-  // split-K slabs of the accumulator (see dh_split): 0 = one slab; else the arguments of dh_split
-  // as the first chunk's contraction saw them
-  int split_k, acc_rows, tiles_n, k_stages, split_f32;
-  int cap_t;            // see TokenBlocks: several blocks are never split
-  Rechunk rc;           // see dh_runs_whole: the contraction is then as long as the vocabulary
-  const Ctl* ctl;
+  const Ctl* ctl;       // n_pad, and the slabs of the accumulator (dh_slabs)
 };
 // (the loss and the counters, and the fold of a dW split over one vocab chunk, come from the same launch; fold.n = 0: none)
 void launch_scatter_dh(const ScatterArgs& a, const FinishArgs& fin, const DwFoldArgs& fold, hipStream_t s);

@@ -269,6 +269,7 @@ __global__ __launch_bounds__(NTHREADS) void lmhead_fwd_kernel(FwdArgs a) { lmhea
 // recompute epilogue's staging area (the largest LDS user).
 constexpr int CLAIM_OFF = GEMM_LDS_BYTES;
 constexpr int PERSISTENT_LDS_BYTES = CLAIM_OFF + 16;
+constexpr int STORE_CLAIM_OFF = WIDE_LDS_BYTES, STORE_LDS_BYTES = STORE_CLAIM_OFF + 16;
 
 // Takes tiles from the queue until it has none for this workgroup: with steal = false the XCD's own
 // share only, with steal = true the own share first and then whatever is left on other XCDs.
@@ -587,23 +588,34 @@ __global__ __launch_bounds__(KEPT_THREADS, 2) void dlogits_kept_kernel(DlogitsAr
 __device__ __forceinline__ float of_lane_pair(float x) {      // x of lane ^ 1
   return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), 0xB1, 0xf, 0xf, true));
 }
-template <typename OutT, bool ACCUMULATE>
-__device__ __forceinline__ void store_tile(const StoreArgs& a, int tm, int tn, int m_lim, f32x4 (&acc)[GM][GN]) {
+// G: MFMA tiles of the wavefront along n (mfma_rows).  N is a multiple of 64: either all of the first four lie within it or none.  The fifth has no
+// neighbour to be swapped with and leaves in pieces of 64 bytes.
+template <typename OutT, bool ACCUMULATE, int G>
+__device__ __forceinline__ void store_tile(const StoreArgs& a, int tm, int tn, int m_lim, f32x4 (&acc)[G][GN]) {
   typedef __attribute__((ext_vector_type(4))) OutT out4;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave / WN, wn = wave % WN;
   const bool odd = lane & 1;
-  const int n_w = tn * BN + wm * WROWS;
-  if (n_w >= a.N) return;                              // (N is a multiple of 64)
-  const int m0 = tm * BM + wn * WCOLS + (lane & 14);
+  const int n_w = tn * (64 * G) + wm * WROWS, n_5 = tn * (64 * G) + mfma_rows(wm, GM) * 16;
+  if (n_w >= a.N) return;                              // (the fifth lies beyond it then too)
+  const bool fifth = G > GM && n_5 < a.N;
+  const int m_w = tm * BM + wn * WCOLS, m0 = m_w + (lane & 14), m1 = m_w + (lane & 15);
   OutT* const C = reinterpret_cast<OutT*>(a.C) + (size_t)m0 * a.ldc + n_w + (odd ? 16 : 0) + ((lane >> 4) << 2);
-  out4 old[2][GM];
+  OutT* const C5 = reinterpret_cast<OutT*>(a.C) + (size_t)m1 * a.ldc + n_5 + ((lane >> 4) << 2);
+  out4 old[2][G];
   auto fetch = [&](int j) {
 #pragma unroll
     for (int h = 0; h < 2; ++h)
       if (m0 + j * 16 + h < m_lim)
 #pragma unroll
         for (int i = 0; i < GM; i += 2) old[j & 1][i + h] = *reinterpret_cast<const out4*>(C + (size_t)(j * 16 + h) * a.ldc + i * 16);
+    if (fifth && m1 + j * 16 < m_lim) old[j & 1][G - 1] = *reinterpret_cast<const out4*>(C5 + (size_t)(j * 16) * a.ldc);
+  };
+  auto put = [&](OutT* p, const f32x4& v, const out4& was) {
+    out4 o;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) o[r] = (OutT)(ACCUMULATE ? v[r] + (float)was[r] : v[r]);
+    *reinterpret_cast<out4*>(p) = o;
   };
   if (ACCUMULATE) fetch(0);
 #pragma unroll
@@ -620,20 +632,17 @@ __device__ __forceinline__ void store_tile(const StoreArgs& a, int tm, int tn, i
         v[1][r] = odd ? hi : lo_x;
       }
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        if (m0 + j * 16 + h >= m_lim) continue;
-        out4 o;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) o[r] = (OutT)(ACCUMULATE ? v[h][r] + (float)old[j & 1][i + h][r] : v[h][r]);
-        *reinterpret_cast<out4*>(C + (size_t)(j * 16 + h) * a.ldc + i * 16) = o;
-      }
+      for (int h = 0; h < 2; ++h)
+        if (m0 + j * 16 + h < m_lim) put(C + (size_t)(j * 16 + h) * a.ldc + i * 16, v[h], old[j & 1][i + h]);
     }
+    if (fifth && m1 + j * 16 < m_lim) put(C5 + (size_t)(j * 16) * a.ldc, acc[G - 1][j], old[j & 1][G - 1]);
   }
 }
 
 // The run-time extents of a store contraction (the active-token count is known only on the device).
 struct StoreShape {
-  int m_lim, tiles_m, K, ks, products, slab_rows, total;
+  int m_lim, tiles_m, tiles_n, K, ks, products, slab_rows, total;
+  bool wide;              // tiles of 320 n
   int t0, nt;             // token tiles of this launch's block
   uint32_t b_off;         // dW: byte offset of the block's first column in a row of H^T
   __device__ __forceinline__ void init(const StoreArgs& a, const Ctl& ctl) {
@@ -643,24 +652,28 @@ struct StoreShape {
     K = a.k_from_ctl ? min(nt * BM, dw_stages(ctl.n_active - t0 * BM) * BK) : a.K;
     b_off = a.k_from_ctl ? (uint32_t)t0 * BM * 2u : 0u;
     ks = 1; products = 1; slab_rows = ctl.n_pad;
+    wide = false;
     if (a.split_k && a.m_from_ctl && nt * BM == ctl.n_pad) {
-      ks = dh_split(ctl.n_pad, a.acc_rows, a.tiles_n, a.split_stages);
-      products = dh_products(ctl.n_pad, a.acc_rows, a.tiles_n, ks, a.A_lo != nullptr);
+      const DhForm f = dh_form(ctl.n_pad, a.acc_rows, a.N, a.split_stages, a.A_lo != nullptr);
+      ks = f.ks; products = f.products; wide = f.wide;
     } else if (a.dw_cap > 0) {
       ks = dw_split(K / BK, a.dw_cap);
       products = a.A_lo ? 3 : 1;
       slab_rows = a.slab_rows;
+    } else if (!a.A_lo) {
+      wide = wide_pays(tiles_m, a.N, K / BK);
     }
-    total = tiles_m * ks * products * a.tiles_n;
+    tiles_n = store_tiles_n(a.N, wide);
+    total = tiles_m * ks * products * tiles_n;
   }
 };
 
-template <bool DIRECT, class AfterLoop, class BeforeStores>
+template <bool DIRECT, int G, class AfterLoop, class BeforeStores>
 __device__ __forceinline__ void gemm_store_tile(StoreArgs a, const StoreShape& sh, int b, AfterLoop&& after_loop,
                                                 BeforeStores&& before_stores) {
   const int tid = threadIdx.x;
   int tm, tn, slab;
-  map_tile_interleaved(b, sh.tiles_m, a.tiles_n, sh.ks * sh.products, slab, tm, tn);
+  map_tile_interleaved(b, sh.tiles_m, sh.tiles_n, sh.ks * sh.products, slab, tm, tn);
   // (divisions only where the contraction is split, and in 32 bits: they run in front of every tile's first load)
   int part = 0, s0 = 0, s1 = sh.K / BK;
   if (sh.ks * sh.products > 1) {
@@ -676,18 +689,18 @@ __device__ __forceinline__ void gemm_store_tile(StoreArgs a, const StoreShape& s
 
   // (a tile here is hundreds of stages long: the claim for the next one simply travels under the main loop)
   after_loop();
-  typename std::conditional<DIRECT, RowsLoader, TileLoader>::type LA;      // engine rows <- n
+  typename std::conditional<DIRECT, RowsLoader<G>, SlabLoader<G>>::type LA;      // engine rows <- n
   TileLoader LB;
   auto init_n = [&](const void* B, int ldb) {
-    if constexpr (DIRECT) LA.init(B, a.b_rows, s0 * BK, ldb, tn * BN, tid);
-    else LA.init(B, a.b_rows, tn * BN, ldb, kb + sh.b_off, tid);
+    if constexpr (DIRECT) LA.init(B, a.b_rows, s0 * BK, ldb, tn * (64 * G), tid);
+    else LA.init(B, a.b_rows, tn * (64 * G), ldb, kb + sh.b_off, tid);
   };
   init_n(a.B, a.ldb);
   LB.init(a.A, a.a_rows, tm * BM, a.lda, kb, tid);     // engine columns <- m
-  f32x4 acc[GM][GN];
+  f32x4 acc[G][GN];
   zero_acc(acc);
   mainloop(LA, LB, s1 - s0, g_smem, acc);
-  if (a.A_lo && sh.products == 1) {   // split fp32 operands: add the two cross terms (the product of the remainders is dropped)
+  if (G == GM && a.A_lo && sh.products == 1) {   // split fp32 operands: add the two cross terms (the product of the remainders is dropped)
     __syncthreads();
     init_n(a.B_lo, a.ldb_lo);
     mainloop(LA, LB, s1 - s0, g_smem, acc);
@@ -700,11 +713,11 @@ __device__ __forceinline__ void gemm_store_tile(StoreArgs a, const StoreShape& s
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // the claim is visible behind this barrier
   a.C = static_cast<char*>(a.C) + (size_t)slab * sh.slab_rows * a.ldc * (a.out_bf16 ? 2 : 4);
   if (a.out_bf16) {
-    if (a.accumulate) store_tile<__bf16, true>(a, tm, tn, sh.m_lim, acc);
-    else store_tile<__bf16, false>(a, tm, tn, sh.m_lim, acc);
+    if (a.accumulate) store_tile<__bf16, true, G>(a, tm, tn, sh.m_lim, acc);
+    else store_tile<__bf16, false, G>(a, tm, tn, sh.m_lim, acc);
   } else {
-    if (a.accumulate) store_tile<float, true>(a, tm, tn, sh.m_lim, acc);
-    else store_tile<float, false>(a, tm, tn, sh.m_lim, acc);
+    if (a.accumulate) store_tile<float, true, G>(a, tm, tn, sh.m_lim, acc);
+    else store_tile<float, false, G>(a, tm, tn, sh.m_lim, acc);
   }
 }
 
@@ -738,6 +751,7 @@ __global__ __launch_bounds__(NTHREADS) void gemm_store_kernel(StoreArgs a) {
   // The grid has room for the largest split.  Workgroups beyond one per tile leave before they crowd the queue (2161 rows of
   // d = 832, 21 of them active: dW 26.3 -> 23.6 us, dH 23.7 -> 21.7).
   if ((int)blockIdx.x >= grid_for_tiles(sh.total, 1)) return;
+  if (a.m_from_ctl && blockIdx.x == 0 && threadIdx.x == 0) a.ctl->dh_slabs = sh.ks * sh.products;
   if (a.blk.b > 0) {
     if (sh.nt <= 0) return;
     if (a.k_from_ctl) a.accumulate = 1;                              // dW: on top of the blocks before
@@ -746,11 +760,10 @@ __global__ __launch_bounds__(NTHREADS) void gemm_store_kernel(StoreArgs a) {
   if (a.m_from_ctl) a.C = static_cast<float*>(a.C) + (size_t)sh.t0 * BM * a.ldc;      // dH: this block's rows of the accumulator
   TileQueue Q;
   Q.init(a.queue, sh.total, 1, 1);
-  volatile int* claim = reinterpret_cast<volatile int*>(g_smem + CLAIM_OFF);
+  volatile int* claim = reinterpret_cast<volatile int*>(g_smem + STORE_CLAIM_OFF);
   // persistent: one workgroup per compute unit takes tiles from the XCD-aware queue until none is left
-  drain_queue(Q, true, claim, [&](int b, auto&& after_loop, auto&& before_stores) {
-    gemm_store_tile<DIRECT>(a, sh, b, after_loop, before_stores);
-  });
+  if (sh.wide) drain_queue(Q, true, claim, [&](int b, auto&& after_loop, auto&& before_stores) { gemm_store_tile<DIRECT, GW>(a, sh, b, after_loop, before_stores); });
+  else drain_queue(Q, true, claim, [&](int b, auto&& after_loop, auto&& before_stores) { gemm_store_tile<DIRECT, GM>(a, sh, b, after_loop, before_stores); });
 }
 
 // ---- host-side launchers -------------------------------------------------------------
@@ -766,7 +779,7 @@ hipError_t init_gemm_kernels() {
   if ((e = hipFuncSetAttribute(reinterpret_cast<const void*>(lmhead_dlogits_kernel<true>),
                                hipFuncAttributeMaxDynamicSharedMemorySize, PERSISTENT_LDS_BYTES)) != hipSuccess) return e;
   for (const void* k : {reinterpret_cast<const void*>(gemm_store_kernel<false>), reinterpret_cast<const void*>(gemm_store_kernel<true>)})
-    if ((e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, PERSISTENT_LDS_BYTES)) != hipSuccess) return e;
+    if ((e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, STORE_LDS_BYTES)) != hipSuccess) return e;
   for (const void* k : {reinterpret_cast<const void*>(dlogits_kept_kernel<false, false>), reinterpret_cast<const void*>(dlogits_kept_kernel<false, true>),
                         reinterpret_cast<const void*>(dlogits_kept_kernel<true, true>)})
     if ((e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, KEPT_LDS_BYTES)) != hipSuccess) return e;
@@ -804,8 +817,8 @@ void launch_gemm_store(const StoreArgs& a, hipStream_t s) {
   // (a split dH has at most acc_rows / 256 row tiles over all parts, a split dW dw_cap parts of every product)
   const int tiles_m = a.rc_role == 1 && a.rc.enabled && a.rc.dw_whole ? a.rc.tiles_v_all : a.tiles_m;
   const dim3 grid(persistent_grid(a.split_k ? max(a.tiles_m, a.acc_rows / BM) : tiles_m * max(1, a.dw_cap) * (a.dw_cap && a.A_lo ? 3 : 1), a.tiles_n));
-  if (a.b_k_rows) hipLaunchKernelGGL(gemm_store_kernel<true>, grid, dim3(NTHREADS), PERSISTENT_LDS_BYTES, s, a);
-  else hipLaunchKernelGGL(gemm_store_kernel<false>, grid, dim3(NTHREADS), PERSISTENT_LDS_BYTES, s, a);
+  if (a.b_k_rows) hipLaunchKernelGGL(gemm_store_kernel<true>, grid, dim3(NTHREADS), STORE_LDS_BYTES, s, a);
+  else hipLaunchKernelGGL(gemm_store_kernel<false>, grid, dim3(NTHREADS), STORE_LDS_BYTES, s, a);
 }
 
 }  // namespace pg

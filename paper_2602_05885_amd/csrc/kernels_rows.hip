@@ -252,7 +252,7 @@ __global__ __launch_bounds__(1024) void prep_compact_kernel(PrepArgs a) {
     a.ctl->n_active = total;
     a.ctl->n_pad = (total + 255) / 256 * 256;
     a.ctl->norm = a.norm_override > 0.f ? a.norm_override : (float)max(total, 1);
-    a.ctl->pad_ = 0;
+    a.ctl->dh_slabs = 1;
     a.counters[0] = (unsigned long long)total;
     if (!a.cu) a.counters[6] = (unsigned long long)total;   // no segments: every flagged row is a loss row
   }
@@ -281,7 +281,7 @@ __global__ void prep_all_rows_kernel(PrepArgs a, int blocks) {
     a.ctl->n_active = a.T;
     a.ctl->n_pad = a.t_cap;
     a.ctl->norm = a.norm_override > 0.f ? a.norm_override : (float)a.T;
-    a.ctl->pad_ = 0;
+    a.ctl->dh_slabs = 1;
   }
 }
 
@@ -598,8 +598,7 @@ __global__ __launch_bounds__(256) void scatter_dh_kernel(ScatterArgs a, FinishAr
   const int p = a.pos[t];
   const float* src = a.acc + (size_t)(p < 0 ? 0 : p) * a.d;
   const int n_pad = a.ctl->n_pad;
-  int ks = 1;                                       // slabs
-  if (p >= 0 && a.split_k && (a.cap_t <= 0 || n_pad <= a.cap_t * BM)) ks = dh_slabs(n_pad, a.acc_rows, a.tiles_n, dh_runs_whole(a.rc, n_pad) ? a.rc.tiles_v_all * BM / BK : a.k_stages, a.split_f32, ks);
+  const int ks = a.ctl->dh_slabs;
   const size_t slab = (size_t)n_pad * a.d;
   for (int j = threadIdx.x * 4; j < a.d; j += 256 * 4) {
     float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -1282,8 +1281,7 @@ __global__ __launch_bounds__(256) void scatter_dx_norm_kernel(ScatterArgs a, Nor
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const long long T = a.T;
   const int n_pad = a.ctl->n_pad;
-  int ks = 1;                                       // slabs
-  if (a.split_k && (a.cap_t <= 0 || n_pad <= a.cap_t * BM)) ks = dh_slabs(n_pad, a.acc_rows, a.tiles_n, dh_runs_whole(a.rc, n_pad) ? a.rc.tiles_v_all * BM / BK : a.k_stages, a.split_f32, ks);
+  const int ks = a.ctl->dh_slabs;
   const size_t slab = (size_t)n_pad * a.d;
   float dg[NC][8];
   Raw8<F32> gam_raw[NC] = {};

@@ -56,7 +56,7 @@ __global__ __launch_bounds__(NTHREADS) void store_timeline_kernel(StoreArgs a, u
   unsigned long long tlast = t0;
   drain_queue(Q, true, claim, [&](int b, auto&& after_loop, auto&& before_stores) {
     ++n; tlast = wall();
-    gemm_store_tile<false>(a, sh, b, after_loop, before_stores);
+    gemm_store_tile<false, GM>(a, sh, b, after_loop, before_stores);
   });
   put_summary(pr, t0, tlast, Q.home, n);
 }
