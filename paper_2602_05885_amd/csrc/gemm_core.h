@@ -70,6 +70,7 @@ struct Ctl {
   int n_active;   // number of compacted rows
   int n_pad;      // n_active rounded up to a multiple of 256
   float norm;     // loss normaliser
+  unsigned step[8]; // of the workgroups of every XCD in a forward (InStep), zero at launch
   int dh_slabs;   // parts of the dH accumulator (DhForm): the dH launches settle it, the scatter adds that many
 };
 
@@ -821,6 +822,46 @@ struct TileQueue {
     return resolve(
         tk, steal, [&](int y) { return __hip_atomic_load(cnt + y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); },
         [&](int y) { return atomicInc(cnt + y, 0xffffffffu); });
+  }
+};
+
+// ---- workgroups of an XCD in step ------------------------------------------------------------------
+// The 32 workgroups of an XCD work on tiles that share operands, and what one has fetched is in the 4 MiB L2 for the others only while they are within some
+// ten stages of each other.  Nothing holds them there: over the hundreds of rounds of a long forward they drift apart, some XCDs by a few
+// stages, some by most of a tile (starts of one round in one launch: within 0.3 us on two XCDs, spread over 80 us of 118 on four).  So every 256 stages or so
+// a workgroup counts itself in on its XCD's counter when its main loop ends, and behind the statistics thread 0 looks whether all have, which by
+// then costs nothing if they are together.  It waits for the others at most POLLS looks (some 50 us, once: a workgroup whose wait runs out, or that has no next tile,
+// counts for good and looks no more; workgroups that have no compute unit, because another stream holds it, cost no more than that).  A matter of speed only.
+// Forward only, without / with: d = 5120, 131072 rows 136.6 / 133.8 and 141.0 / 138.6 ms, 32768 rows 33.4 / 33.2 and 33.8 / 33.3; d = 4096, 16384 rows 13.33 / 13.30 and
+// 13.43 / 13.35 ms (35 / 30 GB fetched, 30 being what 32 tiles at a time must).  At 131072 rows every tile instead of every fourth 134.4, every sixteenth 134.0; at
+// d = 1024, 20000 rows every fourth of 16 stages 1649 / 1667 us.  Launches of fewer than ROUNDS rounds do not drift that far (39 rounds: 3751 / 3756 us), and a
+// forward that parks its logits, whose look would wait for the stores, gains nothing: 12000 rows 13.43 / 13.55 ms, 16384 17.66 / 17.59.
+struct InStep {
+  static constexpr int STAGES = 256, POLLS = 48, ROUNDS = 64;
+  static constexpr unsigned FOR_GOOD = 1u << 24;      // more than a launch can count
+  unsigned* cnt;        // of this XCD
+  unsigned peers, want;
+  int period, left;     // tiles from one look to the next, until the next
+  bool on;
+  __device__ __forceinline__ void init(unsigned* counters, int home, int grid, int nk, bool on_) {
+    cnt = counters + home; peers = (unsigned)grid >> 3; want = 0u; on = on_;
+    period = left = imax(4, STAGES / nk);
+  }
+  // thread 0 only, both: when a tile's main loop has ended, and before the next tile
+  __device__ __forceinline__ void count(bool more) {
+    if (!on) return;
+    if (!more) atomicAdd(cnt, FOR_GOOD);
+    else if (--left == 0) { atomicAdd(cnt, 1u); want += peers; }
+  }
+  __device__ __forceinline__ void wait() {
+    if (!on || left > 0) return;
+    left = period;
+    for (int poll = 0; poll < POLLS; ++poll) {
+      if (__hip_atomic_load(cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= want) return;
+      __builtin_amdgcn_s_sleep(8);
+    }
+    on = false;
+    atomicAdd(cnt, FOR_GOOD);
   }
 };
 

@@ -133,7 +133,7 @@ struct FwdArgs {
   float* part_u;
   Kept kept;
   TokenBlocks blk;
-  const Ctl* ctl;
+  Ctl* ctl;             // (its step counters)
   unsigned* queue;      // [8] tile counters of this launch's queue, zero at launch
 };
 

@@ -116,7 +116,12 @@ __device__ __forceinline__ void lmhead_fwd_body(FwdArgs a, bool steal, unsigned 
     __syncthreads();
     b_cur = __builtin_amdgcn_readfirstlane(claim[0]); b_nxt = __builtin_amdgcn_readfirstlane(claim[1]);
   }
-  if (b_cur < 0) return;
+  InStep in_step;
+  in_step.init(a.ctl->step, Q.home, (int)gridDim.x, a.K / BK, a.kept.tiles == nullptr && Q.total >= InStep::ROUNDS * (int)gridDim.x);
+  if (b_cur < 0) {
+    if (tid == 0) in_step.count(false);
+    return;
+  }
   int tm, tn, tm1 = 0, tn1 = 0;
   map_tile(b_cur, a.tiles_v, tiles_t, tm, tn, tokens_first);
   bool more = b_nxt >= 0;
@@ -151,7 +156,10 @@ __device__ __forceinline__ void lmhead_fwd_body(FwdArgs a, bool steal, unsigned 
     // picked up at the end of the epilogue.  (Left uninitialised on the other threads on purpose: a
     // merged value would make the compiler wait for the atomic right here.)
     unsigned ticket;
-    if (tid == 0 && more) ticket = Q.ticket();
+    if (tid == 0) {
+      if (more) ticket = Q.ticket();
+      in_step.count(more);
+    }
     // the next tile's token ids: fetched now, parked in LDS before this tile's stores are issued, so
     // that neither this epilogue nor the next one waits on memory
     int y_next = 0;
@@ -231,7 +239,10 @@ __device__ __forceinline__ void lmhead_fwd_body(FwdArgs a, bool steal, unsigned 
       red[(1 + (lane >> 5)) * (WM * BN) + wm * BN + tok_l] = y.a + y.b;
       if (lane < 32) red[wm * BN + tok_l] = lane < 16 ? mx[j0] : mx[j0 + 1];
     }
-    if (tid == 0) claim[2] = more ? Q.resolve(ticket, steal) : -1;
+    if (tid == 0) {
+      claim[2] = more ? Q.resolve(ticket, steal) : -1;
+      in_step.wait();
+    }
     // LDS-only synchronisation: a full __syncthreads() would also wait for the next tile's loads
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
     const int b_nn = __builtin_amdgcn_readfirstlane(claim[2]);

@@ -248,6 +248,7 @@ __global__ __launch_bounds__(1024) void prep_compact_kernel(PrepArgs a) {
       }
     base += __shfl(incl, 63);
   }
+  if (tid < 8) a.ctl->step[tid] = 0u;
   if (tid == 0) {
     a.ctl->n_active = total;
     a.ctl->n_pad = (total + 255) / 256 * 256;
@@ -277,6 +278,7 @@ __global__ void prep_all_rows_kernel(PrepArgs a, int blocks) {
     if (a.yc) a.yc[i] = i < a.T ? local_id(a.y[i], a.y_offset, a.V) : -1;
   }
   if (i < a.T) { a.rows[i] = i; a.pos[i] = i; }
+  if (i < 8) a.ctl->step[i] = 0u;
   if (i == 0) {
     a.ctl->n_active = a.T;
     a.ctl->n_pad = a.t_cap;

@@ -141,7 +141,7 @@ int main(int argc, char** argv) {
   CK(hipMalloc(&yc, T * 4)); CK(hipMalloc(&lse2, T * 4)); CK(hipMalloc(&coefc, T * 4));
   CK(hipMalloc(&ctl, sizeof(Ctl))); CK(hipMalloc(&queue, 64));
   CK(hipMalloc(&pr, (size_t)grid * 4 * 8)); CK(hipMalloc(&tl, (size_t)grid * TL_TILES * 3 * 8));
-  Ctl h{T, T, 1.f, 0};
+  Ctl h{T, T, 1.f, {}, 1};
   CK(hipMemcpy(ctl, &h, sizeof h, hipMemcpyHostToDevice));
   fill_kernel<<<1024, 256>>>(dST, (size_t)vc * ld_t, 1u, 1e-3f);
   fill_kernel<<<1024, 256>>>(HcT, (size_t)d * ld_t, 2u, 3.4f);
