@@ -8,6 +8,7 @@
 // wavefront hold the other 48 rows of the same columns.  The two logits kernels put the
 // vocabulary on the rows (a token's statistics then reduce inside a lane first); the store
 // kernel puts the output's contiguous dimension there (4 consecutive elements per lane).
+#include <algorithm>
 #include <cstdlib>
 #include <type_traits>
 
@@ -373,10 +374,10 @@ __device__ __forceinline__ void ds_pack(const DlogitsArgs& a, const DsColumn& co
 }
 
 // ---- orientation 1: dS[tok][v], staged as rows of 256 v (wn: 128-token half of the staging area) ----
-template <int HALVES>
-__device__ __forceinline__ void ds_stage_rows(const uint32_t (&pk)[GM][GN][2], char* st, int wm, int wn, int lane) {
+template <int HALVES, int C>
+__device__ __forceinline__ void ds_stage_rows(const uint32_t (&pk)[GM][C][2], char* st, int wm, int wn, int lane) {
 #pragma unroll
-  for (int j = 0; j < GN; ++j) {
+  for (int j = 0; j < C; ++j) {
     const int tok_l = (HALVES > 1 ? wn * WCOLS : 0) + j * 16 + (lane & 15);
 #pragma unroll
     for (int i = 0; i < GM; ++i) {
@@ -390,14 +391,15 @@ __device__ __forceinline__ void ds_stage_rows(const uint32_t (&pk)[GM][GN][2], c
 // A quad of lanes holds a 4 (vocab rows) x 4 (tokens) block, one token per lane.  Two
 // butterfly exchanges inside the quad turn it so that lane q holds row q of all four tokens,
 // which then goes to LDS as one 8-byte store (instead of sixteen 2-byte ones per block).
-__device__ __forceinline__ void ds_stage_cols(const uint32_t (&pk)[GM][GN][2], char* st, int stride, int wm, int wn, int lane) {
+template <int C>
+__device__ __forceinline__ void ds_stage_cols(const uint32_t (&pk)[GM][C][2], char* st, int stride, int wm, int wn, int lane) {
   const int q = lane & 3;
   const uint32_t sel = (q & 1) ? 0x03020706u : 0x05040100u;   // v_perm byte selectors, see below
   const bool upper = q >= 2;
   const int row_l = wm * WROWS + ((lane >> 4) << 2) + q;
   const int tok0_l = wn * WCOLS + (((lane & 15) >> 2) << 2);
 #pragma unroll
-  for (int j = 0; j < GN; ++j) {
+  for (int j = 0; j < C; ++j) {
 #pragma unroll
     for (int i = 0; i < GM; ++i) {
       const uint32_t w0 = pk[i][j][0], w1 = pk[i][j][1];        // rows (0,1), (2,3) of my token
@@ -506,15 +508,21 @@ __global__ __launch_bounds__(NTHREADS) void lmhead_dlogits_kernel(DlogitsArgs a)
 // V = 151936: 768 rows 119 us (recompute 639 us; 7.8 TB/s, part of the kept tiles still sits in the
 // memory-side cache), 32768 rows in two token blocks 7.7 ms, 5.2 TB/s, above the rate of a plain copy (recompute
 // 36 ms).  Requesting a quarter or half of the next half tile before the stores: 126 us at 768 rows.
-constexpr int KEPT_STRIDE_T = 288;                          // 128 tokens + pad: 72 dwords, see EPI_STRIDE_T
 constexpr int KEPT_THREADS = 256;
-constexpr int KEPT_LDS_BYTES = 256 * KEPT_STRIDE_T;
-static_assert(KEPT_LDS_BYTES >= 128 * EPI_STRIDE && 2 * KEPT_LDS_BYTES <= 160 * 1024, "LDS budget");
+// C: 16-column groups of an item.  Rows of dS^T in LDS: 16 C tokens and a pad (72 dwords for 128 tokens, see EPI_STRIDE_T).
+constexpr int kept_stride_t(int C) { return C * 32 + (C == GN ? 32 : 16); }
+constexpr int kept_lds_bytes(int C) { return 256 * kept_stride_t(C) > C * 16 * EPI_STRIDE ? 256 * kept_stride_t(C) : C * 16 * EPI_STRIDE; }
+static_assert(2 * kept_lds_bytes(GN) <= 160 * 1024, "LDS budget");
 
 // FEW: of at most two token tiles or two rounds of workgroups (or an fp32 head), where a group that was not parked is not loaded.  Elsewhere
 // another one's is, as the branch holds the other loads up: d = 5120, 12000 rows 2.80 -> 2.71 ms, 768 rows 187 -> 179 us, 1536 rows, 942 tiles 103.6 -> 99.5;
 // but 24 rows of d = 4096 50 -> 53 us, 1536 rows, 348 tiles 38.6 -> 40.0, 1312 rows, 318 tiles 36.0 -> 37.6, fp32 64 x 1000, 1024 rows 15.3 -> 16.5 us.
-template <bool SPLIT, bool FEW>
+// Items of 32 tokens (C = KEPT_SMALL) where items of 128 leave most compute units idle: an item is a chain of latencies (loads, LDS, stores of one
+// compute unit), whose length goes with its tokens.  128 / 32 tokens: fp32 64 x 1000, 512 rows (32 half tiles) 15.5 / 9.3 us, 1024 rows (64) 15.5 / 8.6..11.3;
+// 200 rows, d = 1024, V = 8000 (64) 13.3 / 9.7; 700 x 512 x 3000 (72) 14.1 / 12.2; beyond, 32 tokens' stores lose (64-byte pieces of dS^T): 600 x 1024 x 12000
+// (282) 17.6 / 23.9, 1024 x 256 x 4000 fp32 (256) 16.1 / 20.3.  Items of 64 tokens lie between the two on either side (13.0 at 64, 14.9 at 256).
+constexpr int KEPT_SMALL = 2, KEPT_SMALL_HALVES = 96;
+template <bool SPLIT, bool FEW, int C>
 __global__ __launch_bounds__(KEPT_THREADS, 2) void dlogits_kept_kernel(DlogitsArgs a) {
   const Ctl ctl = *a.ctl;
   int ld_t_all;
@@ -527,16 +535,16 @@ __global__ __launch_bounds__(KEPT_THREADS, 2) void dlogits_kept_kernel(DlogitsAr
   const int tiles_t = min(a.tiles_t, nt);
   if (tiles_t <= 0) return;
   a.yc += t0 * BN; a.lse2 += t0 * BN; a.coefc += t0 * BN;
-  const int halves = 2 * kept_in_chunk(a, tiles_t) * tiles_t, total = SPLIT ? 2 * halves : halves;
+  constexpr int PER_TILE = BN / 16 / C;             // items of a kept tile
+  const int items = PER_TILE * kept_in_chunk(a, tiles_t) * tiles_t, total = SPLIT ? 2 * items : items;
   const int tid = threadIdx.x, lane = tid & 63, wm = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int tm0 = a.v0 / BM;
-  f32x4 acc[GM][GN];
-  // 16-column groups [8 half, 8 half + 8) of kept tile h / 2; those beyond the live ones were not parked and count as zero
-  auto fetch = [&](int h, int groups) {
-    const f32x4* kp = reinterpret_cast<const f32x4*>(a.kept.tiles + ((size_t)tm0 * tiles_t + (h >> 1)) * KEPT_TILE_FLOATS) +
-                      kept_column(wm, (h & 1) * GN) + lane;
+  f32x4 acc[GM][C];
+  // 16-column groups [C part, C part + C) of a kept tile; those beyond the live ones were not parked and count as zero
+  auto fetch = [&](int tile, int part, int groups) {
+    const f32x4* kp = reinterpret_cast<const f32x4*>(a.kept.tiles + ((size_t)tm0 * tiles_t + tile) * KEPT_TILE_FLOATS) + kept_column(wm, part * C) + lane;
 #pragma unroll
-    for (int j = 0; j < GN; ++j)
+    for (int j = 0; j < C; ++j)
 #pragma unroll
       for (int i = 0; i < GM; ++i) {
         if (FEW) {
@@ -549,21 +557,21 @@ __global__ __launch_bounds__(KEPT_THREADS, 2) void dlogits_kept_kernel(DlogitsAr
       }
   };
   for (int item = blockIdx.x; item < total; item += gridDim.x) {
-    const bool rest = SPLIT && item >= halves;        // fp32 heads: the remainders as items of their own
-    const int h = rest ? item - halves : item;
-    const int tm = (h >> 1) / tiles_t, tn = (h >> 1) - tm * tiles_t, half = h & 1;
-    const int groups = WN * fwd_nj(ctl.n_active - (t0 + tn) * BN, tiles_t) - half * GN;
-    if (groups <= 0) continue;                        // 128 columns without a row: nobody reads their dS
-    fetch(h, groups);
-    const size_t o_s = ((size_t)tn * BN + half * WCOLS) * a.ld_s + (size_t)tm * BM;
-    const size_t o_t = ((size_t)tm * BM) * a.ld_t + (size_t)tn * BN + half * WCOLS;
-    uint32_t pk[GM][GN][2];
+    const bool rest = SPLIT && item >= items;         // fp32 heads: the remainders as items of their own
+    const int h = rest ? item - items : item;
+    const int tile = h / PER_TILE, part = h % PER_TILE, tm = tile / tiles_t, tn = tile - tm * tiles_t;
+    const int groups = WN * fwd_nj(ctl.n_active - (t0 + tn) * BN, tiles_t) - part * C;
+    if (groups <= 0) continue;                        // columns without a row: nobody reads their dS
+    fetch(tile, part, groups);
+    const int col0 = tn * BN + part * (16 * C);
+    const size_t o_s = (size_t)col0 * a.ld_s + (size_t)tm * BM, o_t = ((size_t)tm * BM) * a.ld_t + col0;
+    uint32_t pk[GM][C][2];
 #pragma unroll
-    for (int j = 0; j < GN; ++j) {
+    for (int j = 0; j < C; ++j) {
       f32x4 z[GM];
 #pragma unroll
       for (int i = 0; i < GM; ++i) z[i] = acc[i][j];
-      const DsColumn col(a, tn * BN + half * WCOLS + j * 16 + (lane & 15));
+      const DsColumn col(a, col0 + j * 16 + (lane & 15));
       uint32_t p[GM][2];
       ds_pack<SPLIT ? DS_EITHER : DS_VALUE>(a, col, a.v0 + tm * BM + wm * WROWS, z, p, rest);
 #pragma unroll
@@ -571,11 +579,11 @@ __global__ __launch_bounds__(KEPT_THREADS, 2) void dlogits_kept_kernel(DlogitsAr
     }
     ds_stage_rows<1>(pk, g_smem, wm, 0, lane);
     lds_barrier();
-    ds_store<128, 512, EPI_STRIDE, KEPT_THREADS>(g_smem, (rest ? a.dS_lo : a.dS) + o_s, a.ld_s, tid);
+    ds_store<C * 16, 512, EPI_STRIDE, KEPT_THREADS>(g_smem, (rest ? a.dS_lo : a.dS) + o_s, a.ld_s, tid);
     lds_barrier();
-    ds_stage_cols(pk, g_smem, KEPT_STRIDE_T, wm, 0, lane);
+    ds_stage_cols(pk, g_smem, kept_stride_t(C), wm, 0, lane);
     lds_barrier();
-    ds_store<256, 256, KEPT_STRIDE_T, KEPT_THREADS>(g_smem, (rest ? a.dST_lo : a.dST) + o_t, a.ld_t, tid);
+    ds_store<256, C * 32, kept_stride_t(C), KEPT_THREADS>(g_smem, (rest ? a.dST_lo : a.dST) + o_t, a.ld_t, tid);
     lds_barrier();
   }
 }
@@ -791,9 +799,9 @@ hipError_t init_gemm_kernels() {
                                hipFuncAttributeMaxDynamicSharedMemorySize, PERSISTENT_LDS_BYTES)) != hipSuccess) return e;
   for (const void* k : {reinterpret_cast<const void*>(gemm_store_kernel<false>), reinterpret_cast<const void*>(gemm_store_kernel<true>)})
     if ((e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, STORE_LDS_BYTES)) != hipSuccess) return e;
-  for (const void* k : {reinterpret_cast<const void*>(dlogits_kept_kernel<false, false>), reinterpret_cast<const void*>(dlogits_kept_kernel<false, true>),
-                        reinterpret_cast<const void*>(dlogits_kept_kernel<true, true>)})
-    if ((e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, KEPT_LDS_BYTES)) != hipSuccess) return e;
+  for (const void* k : {reinterpret_cast<const void*>(dlogits_kept_kernel<false, false, GN>), reinterpret_cast<const void*>(dlogits_kept_kernel<false, true, GN>),
+                        reinterpret_cast<const void*>(dlogits_kept_kernel<true, true, GN>)})
+    if ((e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kept_lds_bytes(GN))) != hipSuccess) return e;
   int dev = 0, cus = 0;
   if ((e = hipGetDevice(&dev)) != hipSuccess) return e;
   if ((e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess) return e;
@@ -811,10 +819,11 @@ void launch_lmhead_fwd(const FwdArgs& a, hipStream_t s) {
 void launch_lmhead_dlogits(const DlogitsArgs& a, hipStream_t s) {
   if (a.kept.cap > 0) {    // at most: every half tile of the launch's widest form
     const long long halves = (a.dS_lo ? 4ll : 2ll) * (a.rc.enabled ? a.rc.tiles_v_all : a.tiles_v) * a.tiles_t;
-    const dim3 grid((unsigned)(halves < 2 * g_persistent_grid ? halves : 2 * g_persistent_grid));
-    const bool few = a.tiles_t <= 2 || halves <= 4 * g_persistent_grid;
-    auto kernel = a.dS_lo ? dlogits_kept_kernel<true, true> : few ? dlogits_kept_kernel<false, true> : dlogits_kept_kernel<false, false>;
-    hipLaunchKernelGGL(kernel, grid, dim3(KEPT_THREADS), KEPT_LDS_BYTES, s, a);
+    const bool few = a.tiles_t <= 2 || halves <= 4 * g_persistent_grid, small = halves <= KEPT_SMALL_HALVES;
+    const int items = (int)std::min<long long>(small ? halves * (GN / KEPT_SMALL) : halves, 2 * g_persistent_grid);
+    auto kernel = small ? (a.dS_lo ? dlogits_kept_kernel<true, true, KEPT_SMALL> : dlogits_kept_kernel<false, true, KEPT_SMALL>)
+                        : a.dS_lo ? dlogits_kept_kernel<true, true, GN> : few ? dlogits_kept_kernel<false, true, GN> : dlogits_kept_kernel<false, false, GN>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)items), dim3(KEPT_THREADS), small ? kept_lds_bytes(KEPT_SMALL) : kept_lds_bytes(GN), s, a);
     if ((long long)a.kept.cap >= (long long)a.tiles_v_all * a.tiles_t) return;      // whatever is live, all of it is kept
   }
   hipLaunchKernelGGL(lmhead_dlogits_kernel<false>, dim3(persistent_grid(a.tiles_v, a.tiles_t)), dim3(NTHREADS), PERSISTENT_LDS_BYTES, s, a);
