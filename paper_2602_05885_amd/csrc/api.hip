@@ -201,7 +201,6 @@ int32_t make_plan(int64_t T, int64_t d, int64_t V, int32_t S, const pg_params* p
     pl.ld_v = (int)ld_v; pl.ld_t = (int)ld_t; pl.ld_h = (int)ld_h;
     pl.HcT = take((size_t)d * ld_h * 2);
     pl.dS = take((size_t)rows_b * ld_v * 2);
-    pl.dST = take((size_t)vc * ld_t * 2);
     pl.direct_fits = (uint64_t)vc * kd * 2 < FOUR_GIB;      // RowsLoader's range
     pl.ld_wt = (int)(pl.cap_t ? wt_cache_ld(V) : ld_v);
     // (a whole W^T only where the caller has none; a chunk's stays, so that a size asked for with the cache does without it)
@@ -219,11 +218,17 @@ int32_t make_plan(int64_t T, int64_t d, int64_t V, int32_t S, const pg_params* p
       pl.dw_cap = (int)std::min<int64_t>(pg::DW_SPLIT_MAX, 256 / (dw_tiles * products));
       pl.dWslabs = take((size_t)pl.dw_cap * products * vc * d * 4);
     }
-    // fp32 dH accumulator: one slab of the active rows per part of the split contraction (dh_split); with few rows
-    // there is room for the largest split, up to ACC_ROWS_SPLIT rows in all
+    // fp32 dH accumulator: one slab of the active rows per part of the split contraction (dh_form); with few rows
+    // there is room for eight parts, up to ACC_ROWS_SPLIT rows in all
     const int64_t split_rows = pg::SPLIT_MAX * t_cap < ACC_ROWS_SPLIT ? pg::SPLIT_MAX * t_cap : ACC_ROWS_SPLIT;
     pl.acc_rows = (int)(t_cap > split_rows ? t_cap : split_rows);
+    pl.dST = take((size_t)vc * ld_t * 2);
     pl.dHacc = take((size_t)pl.acc_rows * d * 4);      // (parts of n_pad rows; in each, those from n_active on are never written)
+    // One block and one vocab chunk: dW, which is through before dH begins, was the last to read dS^T, so its room, just in front, serves more parts
+    if (nchunks == 1 && !pl.cap_t && pl.acc_rows < ACC_ROWS_SPLIT) {
+      pl.acc_rows = (int)std::min<int64_t>({(int64_t)((off - pl.dST) / ((size_t)d * 4)), pg::DH_PARTS_MAX * t_cap, ACC_ROWS_SPLIT});
+      pl.dHacc = pl.dST;
+    }
     pl.queue_words = pg::QUEUE_SET_WORDS * pg::queue_sets((int)nchunks) * pl.nblocks;
   }
   pl.queue = take((size_t)pl.queue_words * sizeof(unsigned));

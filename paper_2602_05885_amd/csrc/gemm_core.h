@@ -169,7 +169,7 @@ __host__ __device__ inline bool map_tile_interleaved(int bid, int tiles_m, int t
 // slab's extra pass in the scatter).  Measured at V = 151936 (one chunk, 2376 stages), dH launch alone:
 //   768 rows, d = 5120 (60 tiles)     one part 1466 us, 4 parts 579 us
 //   3072 rows, d = 4096 (192 tiles)   one part 3167 us, 4 parts 2479 us
-// (Longest split: 8 parts, beyond which the parts of a round no longer get shorter than their own overhead.)
+// (Longest split: 8 parts; dh_parts has more for few tiles.)
 // Every kernel derives ks from the same device-side values (k_stages: those of the first chunk, for all
 // chunks), so the decomposition, and with it the summation order, is fixed for given inputs.
 constexpr int SPLIT_MAX = 8, SPLIT_MIN_STAGES = 8, SPLIT_TILE_STAGES = 24;
@@ -223,15 +223,38 @@ __host__ __device__ inline bool wide_pays(int tiles_m, int n, int stages, int ks
   return launch_cost(tiles_m * ks_320 * store_tiles_n(n, true), (stages + ks_320 - 1) / ks_320, true) <
          launch_cost(tiles_m * ks_256 * store_tiles_n(n, false), (stages + ks_256 - 1) / ks_256, false);
 }
+// A dH of so few tiles that eight parts leave most compute units idle: as many parts as one round holds, up to DH_PARTS_MAX, or fewer where their
+// slabs would cost more than they save (written, and read again by the scatter: DH_ROUND_SLABS stages per round full of them).
+// Eight parts / more, dH launch and scatter together: 100 rows, d = 1024, V = 65536 (4 tiles, 48 parts) 164 / 60 us; 200 rows, d = 1024, V = 8000 (16 parts)
+// 33.9 / 30.2; 100 rows, d = 4096, V = 32000 (13 tiles) 134 / 115; 200 rows, d = 5120, V = 151936 (16) 452 / 371; 300 x 2560 x 50000 179 / 142; fp32
+// 512 rows, 64 x 1000 (8 / 12 slabs) 20.5 / 17.4, 1024 rows, 256 x 4000 50.7 / 39.0, 2000 rows, 512 x 10000 94 / 75.
+constexpr int DH_PARTS_MAX = 64, DH_MIN_STAGES = 4, DH_ROUND_SLABS = 16;
+__host__ __device__ inline int dh_parts(int n_pad, int acc_rows, int tiles_n, int k_stages) {
+  int best = dh_split(n_pad, acc_rows, tiles_n, k_stages);
+  if (n_pad <= 0) return best;
+  const int tiles = (n_pad / 256) * tiles_n;
+  auto cost = [&](int ks) { return ((tiles * ks + 255) / 256) * 256 * ((k_stages + ks - 1) / ks + SPLIT_TILE_STAGES) + tiles * ks * DH_ROUND_SLABS; };
+  int least = cost(best);
+  for (int ks = imin(imin(256 / tiles, k_stages / DH_MIN_STAGES), imin(acc_rows / n_pad, DH_PARTS_MAX)); ks > best; ks -= (ks + 3) / 4) {
+    const int c = cost(ks);
+    if (c < least) { best = ks; least = c; }
+  }
+  return best;
+}
 // The form of a dH contraction that may be split (the rows of a single token block): parts, products (slabs: ks products) and tiles.
 struct DhForm { int ks, products; bool wide; };
 __host__ __device__ inline DhForm dh_form(int n_pad, int acc_rows, int n, int k_stages, int split_f32) {
   DhForm f;
   f.wide = false;
-  f.ks = dh_split(n_pad, acc_rows, store_tiles_n(n, false), k_stages);
-  f.products = dh_products(n_pad, acc_rows, store_tiles_n(n, false), f.ks, split_f32);
+  if (split_f32) {        // the products side by side, where they and the parts fit one round
+    f.ks = dh_parts(n_pad, acc_rows / 3, 3 * store_tiles_n(n, false), k_stages);
+    f.products = dh_products(n_pad, acc_rows, store_tiles_n(n, false), f.ks, split_f32);
+    if (f.products == 3) return f;
+  }
+  f.ks = dh_parts(n_pad, acc_rows, store_tiles_n(n, false), k_stages);
+  f.products = 1;
   if (split_f32) return f;
-  const int ks = dh_split(n_pad, acc_rows, store_tiles_n(n, true), k_stages);
+  const int ks = dh_parts(n_pad, acc_rows, store_tiles_n(n, true), k_stages);
   f.wide = wide_pays(n_pad / BM, n, k_stages, f.ks, ks);
   if (f.wide) f.ks = ks;
   return f;

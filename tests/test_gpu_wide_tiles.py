@@ -14,6 +14,10 @@ def _cost(tiles, stages, wide):
     return (-(-tiles // 256) * 256 + tiles) * (stages + 24) * (5 * 965 if wide else 4 * 1000)
 
 
+def _pad_ld(n):
+    return n + 64 if n // 64 % 2 == 0 else n
+
+
 def _split(n_pad, acc_rows, tiles_n, stages):
     best = None
     for ks in range(1, 9):
@@ -22,7 +26,14 @@ def _split(n_pad, acc_rows, tiles_n, stages):
         c = -(-n_pad // 256 * tiles_n * ks // 256) * (-(-stages // ks) + 24)
         if best is None or c < best[0]:
             best = (c, ks)
-    return best[1]
+    ks, tiles = best[1], n_pad // 256 * tiles_n
+    cost = lambda p: -(-tiles * p // 256) * 256 * (-(-stages // p) + 24) + tiles * p * 16
+    least, p = cost(ks), min(256 // tiles, stages // 4, acc_rows // n_pad, 64)
+    while p > ks:                                          # more than eight parts of few tiles
+        if cost(p) < least:
+            ks, least = p, cost(p)
+        p -= (p + 3) // 4
+    return ks
 
 
 def _wide(tiles_m, d, stages, ks4=1, ks5=1):
@@ -42,6 +53,8 @@ def test_wide_tiles(T, d, V, wide, dw16, acc):
     dev = torch.device("cuda:0")
     tiles_v, t_pad = -(-V // 256), -(-T // 256) * 256
     acc_rows = max(t_pad, min(8 * t_pad, 32768))
+    if acc_rows < 32768:                                   # the accumulator takes dS^T's room as well
+        acc_rows = min(acc_rows + tiles_v * 256 * _pad_ld(t_pad) // (2 * d), 64 * t_pad, 32768)
     ks = [_split(t_pad, acc_rows, -(-d // n), 4 * tiles_v) for n in (256, 320)]
     whole_dW = 2 * tiles_v * -(-d // 256) > 256            # (a smaller head's dW is split into slabs)
     assert (whole_dW and _wide(tiles_v, d, -(-T // 64))) == ("dW" in wide)
