@@ -442,11 +442,13 @@ void launch_transpose_w(const void* W, int is_f32, int64_t V, int d, int ldw, in
 // Merges the per-vocab-tile softmax partials of every compacted row with the online merge rule
 // (m, s, u) + (m2, s2, u2), emits log-prob / entropy / logsumexp, and for the loss call evaluates
 // the clipped surrogate and the coefficient that scales (onehot - softmax) in the backward.
-// The vocab tiles of a row are dealt to COMBINE_WAVES wavefronts, each of which merges every 16th tile's state
-// (online, fixed order) with the loads of four tiles in flight; wavefront 0 then merges the 16 results in order and
-// finishes the row.  With few rows the serial chain of loads and merges is all there is (594 tiles: 76 us with
-// 4 wavefronts and one tile in flight at 768 rows, 15 us so); with many it is HBM-bound (32768 rows: 88 us, 46 us so).
+// A workgroup of COMBINE_WAVES wavefronts takes R rows and deals their vocab tiles to its 1024 / R parts, each of which merges every 1024 / R-th tile's state
+// (online, fixed order) with the loads of four tiles in flight; the parts' results are then merged in a fixed order, and R lanes finish
+// the rows.  With few rows the serial chain of loads and merges is all there is, with many it is HBM-bound, and rows of 64 bytes cost more than they save.
+// 594 tiles, R = 64 (the 16 results one after the other) / 16 (by exchange): 200 rows 14.0 / 9.0 us, 677 14.3 / 10.0, 3000 14.1 / 11.0, 6000 16.4 / 19.5,
+// 24 000 36 / 58; up to 79 tiles 4.0..4.7 either way.  (Five tiles at once in one merge: no faster.)
 constexpr int COMBINE_WAVES = 16;
+constexpr int COMBINE_FEW_ROWS = 3072;
 
 __device__ __forceinline__ void combine_merge(float& M, float& s, float& u, float m2, float s2, float u2) {
   const float mm = fmaxf(M, m2);
@@ -456,34 +458,59 @@ __device__ __forceinline__ void combine_merge(float& M, float& s, float& u, floa
   M = mm;
 }
 
+template <int R>
 __global__ __launch_bounds__(64 * COMBINE_WAVES) void combine_kernel(CombineArgs a) {
-  __shared__ float sh[COMBINE_WAVES - 1][3][64];
+  constexpr int PARTS = 64 * COMBINE_WAVES / R;
+  __shared__ float sh[PARTS - 1][3][R];
   const Ctl ctl = *a.ctl;
-  const int lane = threadIdx.x & 63, part = threadIdx.x >> 6;
+  const int lane = threadIdx.x % R, part = threadIdx.x / R;
   int t0, nt;
   token_block(a.blk, ctl.n_pad / BN, t0, nt);
-  if ((int)blockIdx.x * 64 >= nt * BN) return;   // whole workgroup beyond the padded rows
-  const int i = t0 * BN + blockIdx.x * 64 + lane;
+  if ((int)blockIdx.x * R >= nt * BN) return;   // whole workgroup beyond the padded rows
+  const int i = t0 * BN + blockIdx.x * R + lane;
   float M = -1.0e30f, s = 0.f, u = 0.f;
   int k = part;
-  for (; k + 3 * COMBINE_WAVES < a.tiles_v; k += 4 * COMBINE_WAVES) {
+  for (; k + 3 * PARTS < a.tiles_v; k += 4 * PARTS) {
     float m2[4], s2[4], u2[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const size_t o = (size_t)(k + q * COMBINE_WAVES) * a.t_cap + i;
+      const size_t o = (size_t)(k + q * PARTS) * a.t_cap + i;
       m2[q] = a.part_m[o]; s2[q] = a.part_s[o]; u2[q] = a.part_u[o];
     }
 #pragma unroll
     for (int q = 0; q < 4; ++q) combine_merge(M, s, u, m2[q], s2[q], u2[q]);
   }
-  for (; k < a.tiles_v; k += COMBINE_WAVES) {
+  for (; k < a.tiles_v; k += PARTS) {
     const size_t o = (size_t)k * a.t_cap + i;
     combine_merge(M, s, u, a.part_m[o], a.part_s[o], a.part_u[o]);
   }
-  if (part > 0) { sh[part - 1][0][lane] = M; sh[part - 1][1][lane] = s; sh[part - 1][2][lane] = u; }
-  __syncthreads();
-  if (part > 0) return;
-  for (int w = 0; w < COMBINE_WAVES - 1; ++w) combine_merge(M, s, u, sh[w][0][lane], sh[w][1][lane], sh[w][2][lane]);
+  if (R == 64) {
+    if (part > 0) { sh[part - 1][0][lane] = M; sh[part - 1][1][lane] = s; sh[part - 1][2][lane] = u; }
+    __syncthreads();
+    if (part > 0) return;
+    for (int w = 0; w < PARTS - 1; ++w) combine_merge(M, s, u, sh[w][0][lane], sh[w][1][lane], sh[w][2][lane]);
+  } else {                   // the parts of a wavefront by exchange, then those of the 16 wavefronts
+#pragma unroll
+    for (int w = R; w < 64; w *= 2) {
+      const float m2 = __shfl_xor(M, w), s2 = __shfl_xor(s, w), u2 = __shfl_xor(u, w);
+      combine_merge(M, s, u, m2, s2, u2);
+    }
+    const int wave = threadIdx.x >> 6;
+    if ((threadIdx.x & 63) < R) { sh[wave][0][lane] = M; sh[wave][1][lane] = s; sh[wave][2][lane] = u; }
+    __syncthreads();
+    if (wave > 0) return;
+    constexpr int EACH = COMBINE_WAVES * R / 64;           // wavefronts' states of a lane
+    const int first = (threadIdx.x / R) * EACH;
+    M = sh[first][0][lane]; s = sh[first][1][lane]; u = sh[first][2][lane];
+#pragma unroll
+    for (int w = 1; w < EACH; ++w) combine_merge(M, s, u, sh[first + w][0][lane], sh[first + w][1][lane], sh[first + w][2][lane]);
+#pragma unroll
+    for (int w = R; w < 64; w *= 2) {
+      const float m2 = __shfl_xor(M, w), s2 = __shfl_xor(s, w), u2 = __shfl_xor(u, w);
+      combine_merge(M, s, u, m2, s2, u2);
+    }
+    if ((int)threadIdx.x >= R) return;
+  }
   const float LN2 = 0.693147180559945309f, LOG2E = 1.44269504088896341f;
   if (a.partials_out) {      // this shard's state of the row, natural-log units
     if (i < ctl.n_active)
@@ -530,7 +557,9 @@ __global__ __launch_bounds__(64 * COMBINE_WAVES) void combine_kernel(CombineArgs
   a.lossterm[i] = c * l;
 }
 void launch_combine(const CombineArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(combine_kernel, dim3((a.blk.cap_t > 0 ? a.blk.cap_t * BN : a.t_cap) / 64), dim3(64 * COMBINE_WAVES), 0, s, a);
+  const int rows = a.blk.cap_t > 0 ? a.blk.cap_t * BN : a.t_cap;
+  if (a.t_cap <= COMBINE_FEW_ROWS) hipLaunchKernelGGL(combine_kernel<16>, dim3(rows / 16), dim3(64 * COMBINE_WAVES), 0, s, a);
+  else hipLaunchKernelGGL(combine_kernel<64>, dim3(rows / 64), dim3(64 * COMBINE_WAVES), 0, s, a);
 }
 
 // One workgroup of 256, fixed order, fp64: loss = (sum_t c_t l_t) / norm; publishes the counters.  It runs as a
