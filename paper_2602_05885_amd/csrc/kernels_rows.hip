@@ -95,10 +95,8 @@ __device__ __forceinline__ void split_w(const PrepArgs& a, int blocks) {
   }
 }
 
-__global__ void prep_init_kernel(PrepArgs a, int blocks) {
-  if ((int)blockIdx.x >= blocks) return split_w(a, blocks);
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < 8) a.counters[i] = 0ull;
+__device__ __forceinline__ void prep_init(const PrepArgs& a, int block, int blocks) {
+  const int i = block * blockDim.x + threadIdx.x;
   for (int w = i; w < a.queue_words; w += blocks * blockDim.x) a.queue[w] = 0u;
   if (i < a.t_cap) a.zy[i] = 0.f;
   if (i < a.T) {
@@ -106,7 +104,12 @@ __global__ void prep_init_kernel(PrepArgs a, int blocks) {
     if (a.out1) a.out1[i] = 0.f;
     if (a.out2) a.out2[i] = 0.f;
     if (a.cu) {
-      a.flag[i] = 0;
+      // A row of no segment.  (The offsets lead from the first to the last, so every row between these two is in one.)
+      if (a.S <= 0 || i < a.cu[0] || i >= a.cu[a.S]) {
+        bool in = false;
+        for (int s = 0; s < a.S; ++s) in |= i >= a.cu[s] && i < a.cu[s + 1];
+        if (!in) a.flag[i] = 0;
+      }
     } else {
       a.flag[i] = a.mask ? (a.mask[i] != 0) : 1;
       a.c_tok[i] = 1.f;
@@ -118,13 +121,16 @@ __global__ void prep_init_kernel(PrepArgs a, int blocks) {
 // One workgroup per segment (= one training sample): Sec. 5.1's geometric-mean ratio and
 // token veto over the sample's loss tokens, decided in fp64, then per-row weights.  A sample
 // whose keep flag is 0 (Sec. 5.2's rejection sampling), or whose index lies outside the
-// advantage table, is skipped before any of that.
-__global__ __launch_bounds__(256) void prep_segment_kernel(PrepArgs a) {
+// advantage table, is skipped before any of that.  What there is to count goes into the rows' flags, from which the compaction sums
+// it, so that nothing has to be cleared first and the segments are workgroups of the first launch.
+constexpr unsigned FLAG_ACTIVE = 1, FLAG_PASSED = 2, FLAG_TRUNCATED = 4;               // of the row (passed: carries loss, but its segment is out)
+constexpr unsigned FLAG_VETO = 8, FLAG_OUTSIDE = 16, FLAG_DROPPED = 32;                // of its segment, on the first row
+__device__ __forceinline__ void prep_segment(const PrepArgs& a, int s) {
   __shared__ double sh_sum[256];
   __shared__ double sh_min[256];
   __shared__ int sh_n[256];
-  __shared__ int sh_keep;
-  const int s = blockIdx.x, tid = threadIdx.x;
+  __shared__ unsigned sh_seg;
+  const int tid = threadIdx.x;
   int lo = a.cu[s], hi = a.cu[s + 1];
   lo = max(lo, 0);
   hi = min(hi, a.T);
@@ -155,45 +161,50 @@ __global__ __launch_bounds__(256) void prep_segment_kernel(PrepArgs a) {
     __syncthreads();
   }
   if (tid == 0) {
-    int keep = 1;
+    unsigned seg = 0;
     const int nn = sh_n[0];
     const bool dropped = !in_table || (a.sample_keep && !a.sample_keep[idx]);
     if (dropped) {            // filtered out before training (PRS): as if the sample had no loss rows
-      keep = 0;
-      if (nn > 0) atomicAdd(&a.counters[7], 1ull);
+      if (nn > 0) seg = FLAG_DROPPED;
     } else if (nn > 0) {
-      atomicAdd(&a.counters[6], (unsigned long long)nn);
       if (mm) {
         const bool vetoed = (a.veto_ratio > 0.f) && (exp(sh_min[0]) < (double)a.veto_ratio);
-        if (vetoed) { atomicAdd(&a.counters[4], 1ull); keep = 0; }
+        if (vetoed) seg |= FLAG_VETO;
         if (a.mismatch_mode == 1) {
           const double w = exp(sh_sum[0] / (double)nn);
           const bool inside = ((double)a.geo_lo <= w) && (w <= (double)a.geo_hi);
-          if (!inside) { atomicAdd(&a.counters[3], 1ull); keep = 0; }
+          if (!inside) seg |= FLAG_OUTSIDE;
         }
       }
     }
-    sh_keep = keep;
+    sh_seg = seg;
   }
   __syncthreads();
-  const int keep = sh_keep;
+  const unsigned seg = sh_seg;           // (a segment without a loss row has none of these, and no row to keep)
   const float A = in_table ? (float)a.adv[idx] : 0.f;
-  unsigned long long ntr = 0;
   for (int t = lo + tid; t < hi; t += 256) {
-    const bool act = a.mask[t] && keep;
+    const bool on = a.mask[t] != 0;
+    unsigned flag = (t == lo ? seg : 0u) | (on ? !seg ? FLAG_ACTIVE : seg & FLAG_DROPPED ? 0u : FLAG_PASSED : 0u);
     float c = 0.f;
-    if (act) {
+    if (on && !seg) {
       c = 1.f;
       if (a.mismatch_mode == 2) {
         const double ratio = exp((double)a.old_logp[t] - (double)a.rollout_logp[t]);
-        if (ratio > (double)a.trunc_c) { ++ntr; c = a.trunc_c; } else { c = (float)ratio; }
+        if (ratio > (double)a.trunc_c) { flag |= FLAG_TRUNCATED; c = a.trunc_c; } else { c = (float)ratio; }
       }
     }
-    a.flag[t] = act;
+    a.flag[t] = (uint8_t)flag;
     a.c_tok[t] = c;
     a.a_tok[t] = A;
   }
-  if (ntr) atomicAdd(&a.counters[5], ntr);
+}
+
+// The segments, what has to be cleared, and an fp32 head's split of W, in one launch.  Clearing, segments and compaction as three launches / two:
+// 512 rows, 64 x 1000 fp32 head 10.7 / 8.1 us, 16 082 rows 23.1 / 19.5, 43 697 rows 39.7 / 37.0.
+__global__ __launch_bounds__(256) void prep_first_kernel(PrepArgs a, int segments, int blocks) {
+  if ((int)blockIdx.x < segments) return prep_segment(a, (int)blockIdx.x);
+  if ((int)blockIdx.x < segments + blocks) return prep_init(a, (int)blockIdx.x - segments, blocks);
+  split_w(a, segments + blocks);
 }
 
 // Single workgroup: exclusive scan of the active flags -> compacted row list, inverse map, counts and the loss
@@ -201,35 +212,45 @@ __global__ __launch_bounds__(256) void prep_segment_kernel(PrepArgs a) {
 // them, and after the wavefronts' totals are known ranks them with a lane prefix.  Latency is all there is: one row at a time per
 // thread, as it was, took 64 us at 43697 rows and 19 us at 16082; so 24 and 9 us.
 __global__ __launch_bounds__(1024) void prep_compact_kernel(PrepArgs a) {
-  __shared__ int total_of[16];
+  constexpr int KINDS = 6;                                      // of flags, see FLAG_ACTIVE
+  __shared__ int total_of[KINDS][16];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int run = (a.T + 16 * 256 - 1) / (16 * 256) * 256;      // rows per wavefront (wave 15's may reach beyond T)
   const int lo = wave * run, hi = lo < a.T ? (a.T - lo < run ? a.T : lo + run) : lo;
   // four flags from row t on (the flag array is padded to whole groups; rows beyond T count as inactive)
   auto flags = [&](int t) -> unsigned {
     unsigned f = 0;
-    if (t < hi) f = *reinterpret_cast<const unsigned*>(a.flag + t) & 0x01010101u;
+    if (t < hi) f = *reinterpret_cast<const unsigned*>(a.flag + t);
     if (t + 4 > hi && t < hi) f &= (1u << ((hi - t) * 8)) - 1u;
     return f;
   };
-  int cnt = 0;
+  int cnt[KINDS] = {};
 #pragma unroll 4
-  for (int t = lo + lane * 4; t < hi; t += 256) cnt += __popc(flags(t));
+  for (int t = lo + lane * 4; t < hi; t += 256) {
+    const unsigned f = flags(t);
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) cnt += __shfl_xor(cnt, off);
-  if (lane == 0) total_of[wave] = cnt;
+    for (int q = 0; q < KINDS; ++q) cnt[q] += __popc(f & (0x01010101u << q));
+  }
+#pragma unroll
+  for (int q = 0; q < KINDS; ++q) {
+    if (q == 0 || __any(cnt[q])) {                     // (all but the first are rare: all six reduced, 4.9 us at 512 rows, so 3.7)
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) cnt[q] += __shfl_xor(cnt[q], off);
+    }
+    if (lane == 0) total_of[q][wave] = cnt[q];
+  }
   __syncthreads();
   int base = 0, total = 0;
 #pragma unroll
   for (int w = 0; w < 16; ++w) {
-    const int c = total_of[w];
+    const int c = total_of[0][w];
     if (w < wave) base += c;
     total += c;
   }
   unsigned ahead = flags(lo + lane * 4);
   for (int t0 = lo; t0 < hi; t0 += 256) {
     const int t = t0 + lane * 4;
-    const unsigned f = ahead;
+    const unsigned f = ahead & 0x01010101u;
     ahead = flags(t + 256);
     const int c = __popc(f);
     int incl = c;
@@ -254,8 +275,14 @@ __global__ __launch_bounds__(1024) void prep_compact_kernel(PrepArgs a) {
     a.ctl->n_pad = (total + 255) / 256 * 256;
     a.ctl->norm = a.norm_override > 0.f ? a.norm_override : (float)max(total, 1);
     a.ctl->dh_slabs = 1;
-    a.counters[0] = (unsigned long long)total;
-    if (!a.cu) a.counters[6] = (unsigned long long)total;   // no segments: every flagged row is a loss row
+  }
+  if (tid < 8) {      // counter: the flags that it counts (1 and 2 are the combine's; 6: active rows and those passed over)
+    const int kind = tid == 3 ? 4 : tid == 4 ? 3 : tid == 5 ? 2 : tid == 6 ? 1 : tid == 7 ? 5 : -1;
+    unsigned long long sum = tid == 0 || tid == 6 ? (unsigned long long)total : 0ull;
+    if (kind >= 0)
+#pragma unroll
+      for (int w = 0; w < 16; ++w) sum += (unsigned long long)total_of[kind][w];
+    a.counters[tid] = sum;
   }
 }
 
@@ -290,13 +317,13 @@ __global__ void prep_all_rows_kernel(PrepArgs a, int blocks) {
 void launch_prepass(const PrepArgs& a, hipStream_t s) {
   const int n = a.t_cap > 8 ? a.t_cap : 8, blocks = (n + 255) / 256;
   const size_t split = (a.w_elems + 255) / 256;
-  const dim3 grid(blocks + (unsigned)(split < 65536 ? split : 65536));
+  const unsigned split_blocks = (unsigned)(split < 65536 ? split : 65536);
   if (!a.cu && !a.mask) {
-    hipLaunchKernelGGL(prep_all_rows_kernel, grid, dim3(256), 0, s, a, blocks);
+    hipLaunchKernelGGL(prep_all_rows_kernel, dim3(blocks + split_blocks), dim3(256), 0, s, a, blocks);
     return;
   }
-  hipLaunchKernelGGL(prep_init_kernel, grid, dim3(256), 0, s, a, blocks);
-  if (a.cu && a.S > 0) hipLaunchKernelGGL(prep_segment_kernel, dim3(a.S), dim3(256), 0, s, a);
+  const int segments = a.cu && a.S > 0 ? a.S : 0;
+  hipLaunchKernelGGL(prep_first_kernel, dim3((unsigned)segments + blocks + split_blocks), dim3(256), 0, s, a, segments, blocks);
   hipLaunchKernelGGL(prep_compact_kernel, dim3(1), dim3(1024), 0, s, a);
 }
 
