@@ -208,7 +208,6 @@ int32_t make_plan(int64_t T, int64_t d, int64_t V, int32_t S, const pg_params* p
     if (pl.is_f32) {   // bf16 remainders of the four backward operands
       pl.HcT_lo = take((size_t)d * ld_h * 2);
       pl.dS_lo = take((size_t)rows_b * ld_v * 2);
-      pl.dST_lo = take((size_t)vc * ld_t * 2);
       pl.WT_lo = take((size_t)d * ld_v * 2);
     }
     // A head of so few dW tiles that half of the compute units would idle: parts of the contraction side by side
@@ -222,12 +221,15 @@ int32_t make_plan(int64_t T, int64_t d, int64_t V, int32_t S, const pg_params* p
     // there is room for eight parts, up to ACC_ROWS_SPLIT rows in all
     const int64_t split_rows = pg::SPLIT_MAX * t_cap < ACC_ROWS_SPLIT ? pg::SPLIT_MAX * t_cap : ACC_ROWS_SPLIT;
     pl.acc_rows = (int)(t_cap > split_rows ? t_cap : split_rows);
+    const size_t read_by_dW = off;
+    if (pl.is_f32) pl.dST_lo = take((size_t)vc * ld_t * 2);
     pl.dST = take((size_t)vc * ld_t * 2);
     pl.dHacc = take((size_t)pl.acc_rows * d * 4);      // (parts of n_pad rows; in each, those from n_active on are never written)
-    // One block and one vocab chunk: dW, which is through before dH begins, was the last to read dS^T, so its room, just in front, serves more parts
+    // One block and one vocab chunk: dW, which is through before dH begins, was the last to read dS^T (and its remainders), so that room, just in
+    // front, serves more parts
     if (nchunks == 1 && !pl.cap_t && pl.acc_rows < ACC_ROWS_SPLIT) {
-      pl.acc_rows = (int)std::min<int64_t>({(int64_t)((off - pl.dST) / ((size_t)d * 4)), pg::DH_PARTS_MAX * t_cap, ACC_ROWS_SPLIT});
-      pl.dHacc = pl.dST;
+      pl.acc_rows = (int)std::min<int64_t>({(int64_t)((off - read_by_dW) / ((size_t)d * 4)), pg::DH_PARTS_MAX * t_cap, ACC_ROWS_SPLIT});
+      pl.dHacc = read_by_dW;
     }
     pl.queue_words = pg::QUEUE_SET_WORDS * pg::queue_sets((int)nchunks) * pl.nblocks;
   }

@@ -227,7 +227,7 @@ __host__ __device__ inline bool wide_pays(int tiles_m, int n, int stages, int ks
 // slabs would cost more than they save (written, and read again by the scatter: DH_ROUND_SLABS stages per round full of them).
 // Eight parts / more, dH launch and scatter together: 100 rows, d = 1024, V = 65536 (4 tiles, 48 parts) 164 / 60 us; 200 rows, d = 1024, V = 8000 (16 parts)
 // 33.9 / 30.2; 100 rows, d = 4096, V = 32000 (13 tiles) 134 / 115; 200 rows, d = 5120, V = 151936 (16) 452 / 371; 300 x 2560 x 50000 179 / 142; fp32
-// 512 rows, 64 x 1000 (8 / 12 slabs) 20.5 / 17.4, 1024 rows, 256 x 4000 50.7 / 39.0, 2000 rows, 512 x 10000 94 / 75.
+// 512 rows, 64 x 1000 (8 / 12 slabs) 20.5 / 17.4, 1024 rows, 256 x 4000 50.7 / 36.0, 2000 rows, 512 x 10000 94 / 75.
 constexpr int DH_PARTS_MAX = 64, DH_MIN_STAGES = 4, DH_ROUND_SLABS = 16;
 __host__ __device__ inline int dh_parts(int n_pad, int acc_rows, int tiles_n, int k_stages) {
   int best = dh_split(n_pad, acc_rows, tiles_n, k_stages);
