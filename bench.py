@@ -46,8 +46,8 @@ def measured_mfma_only_tflops():
 # summarised in profiles/gemm_store_kernel_hbm_traffic.md (mean over a step's 30 launches, of which 20 have work, each
 # counter scaled by what it reads for a plain 1 GiB copy).  Valid only for the kernel sources the
 # counters were taken with: the digest below is of csrc/gemm_core.h + csrc/kernels_gemm.hip.
-TRAFFIC_GEMM_STORE = {"read_bytes": 2941369.6 * 1024 * 2.000, "write_bytes": 311846.1 * 1024 * 1.000,
-                      "sources_sha256": "bec550ee27f2ded6738128bd045a88ebcf3609fe3771815c524e12512fd3c3a2"}
+TRAFFIC_GEMM_STORE = {"read_bytes": 2401555.7 * 1024 * 2.000, "write_bytes": 312019.4 * 1024 * 1.000,
+                      "sources_sha256": "eec90b3728099ad63073e022689583e8a71a594e806d9cf317c8fbed3a8cb4c4"}
 
 
 def kernel_sources_digest() -> str:

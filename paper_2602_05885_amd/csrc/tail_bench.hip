@@ -51,12 +51,15 @@ __global__ __launch_bounds__(NTHREADS) void store_timeline_kernel(StoreArgs a, u
   sh.init(a, ctl);
   TileQueue Q;
   Q.init(a.queue, sh.total, 1, 1);
-  volatile int* claim = reinterpret_cast<volatile int*>(g_smem + CLAIM_OFF);
+  volatile int* claim = reinterpret_cast<volatile int*>(g_smem + STORE_CLAIM_OFF);
   int n = 0;
   unsigned long long tlast = t0;
   drain_queue(Q, true, claim, [&](int b, auto&& after_loop, auto&& before_stores) {
     ++n; tlast = wall();
-    gemm_store_tile<false, GM>(a, sh, b, after_loop, before_stores);
+#ifdef __HIP_DEVICE_COMPILE__      // (the host pass does not take the main loop's builtins on a wide slab)
+    if (sh.wide) gemm_store_tile<false, GW>(a, sh, b, after_loop, before_stores);
+    else gemm_store_tile<false, GM>(a, sh, b, after_loop, before_stores);
+#endif
   });
   put_summary(pr, t0, tlast, Q.home, n);
 }
@@ -122,7 +125,7 @@ int main(int argc, char** argv) {
   const int reps = argc > 1 ? atoi(argv[1]) : 2;
   const int T = 32768, d = 5120, vc = 22784, V = 151936;     // one full chunk of the one-block plan: 89 vocab tiles
   CK(init_gemm_kernels());
-  CK(hipFuncSetAttribute(reinterpret_cast<const void*>(store_timeline_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, PERSISTENT_LDS_BYTES));
+  CK(hipFuncSetAttribute(reinterpret_cast<const void*>(store_timeline_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, STORE_LDS_BYTES));
   CK(hipFuncSetAttribute(reinterpret_cast<const void*>(dlogits_timeline_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, PERSISTENT_LDS_BYTES));
   int cus = 0;
   CK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, 0));
@@ -163,7 +166,7 @@ int main(int argc, char** argv) {
   w.tiles_m = vc / 256; w.tiles_n = d / 256; w.C = dW; w.ldc = d; w.k_from_ctl = 1; w.ctl = ctl; w.queue = queue;
   StoreArgs g{};      // dH: [T, d] += dS [T, vc] x W^T [d, vc]
   g.A = dS; g.B = WT; g.a_rows = T; g.b_rows = d; g.lda = ld_v; g.ldb = ld_v; g.M = T; g.N = d; g.K = vc;
-  g.tiles_m = T / 256; g.tiles_n = d / 256; g.C = dH; g.ldc = d; g.accumulate = 1; g.m_from_ctl = 1; g.split_k = 1; g.ctl = ctl; g.queue = queue;
+  g.tiles_m = T / 256; g.tiles_n = d / 256; g.C = dH; g.ldc = d; g.accumulate = 1; g.m_from_ctl = 1; g.split_k = 1; g.split_stages = vc / 64; g.ctl = ctl; g.queue = queue;
   DlogitsArgs r{};    // recompute of the chunk's logits, dS and dS^T out
   r.W = W; r.Hc = Hc; r.w_rows = V; r.h_rows = T; r.ldw = d; r.ldh = d; r.K = d; r.V = V; r.v0 = vc; r.ld_s = ld_v; r.ld_t = ld_t;
   r.tiles_v = vc / 256; r.tiles_t = T / 256; r.t_cap = T; r.scale = 1.4427f; r.yc = yc; r.lse2 = lse2; r.coefc = coefc;
@@ -180,8 +183,8 @@ int main(int argc, char** argv) {
       for (int it = 0; it < 4; ++it) {         // three launches to settle the clock, the fourth is reported
         CK(hipMemsetAsync(queue, 0, 64, 0));
         if (it == 3) CK(hipEventRecord(e0));
-        if (which == 0) hipLaunchKernelGGL(store_timeline_kernel, dim3(grid), dim3(NTHREADS), PERSISTENT_LDS_BYTES, 0, w, pr);
-        else if (which == 1) hipLaunchKernelGGL(store_timeline_kernel, dim3(grid), dim3(NTHREADS), PERSISTENT_LDS_BYTES, 0, g, pr);
+        if (which == 0) hipLaunchKernelGGL(store_timeline_kernel, dim3(grid), dim3(NTHREADS), STORE_LDS_BYTES, 0, w, pr);
+        else if (which == 1) hipLaunchKernelGGL(store_timeline_kernel, dim3(grid), dim3(NTHREADS), STORE_LDS_BYTES, 0, g, pr);
         else hipLaunchKernelGGL(dlogits_timeline_kernel, dim3(grid), dim3(NTHREADS), PERSISTENT_LDS_BYTES, 0, r, pr, tl);
         if (it == 3) CK(hipEventRecord(e1));
       }
