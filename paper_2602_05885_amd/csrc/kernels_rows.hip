@@ -103,19 +103,24 @@ __device__ __forceinline__ void prep_init(const PrepArgs& a, int block, int bloc
     if (a.out0) a.out0[i] = 0.f;
     if (a.out1) a.out1[i] = 0.f;
     if (a.out2) a.out2[i] = 0.f;
-    if (a.cu) {
-      // A row of no segment.  (The offsets lead from the first to the last, so every row between these two is in one.)
-      if (a.S <= 0 || i < a.cu[0] || i >= a.cu[a.S]) {
-        bool in = false;
-        for (int s = 0; s < a.S; ++s) in |= i >= a.cu[s] && i < a.cu[s + 1];
-        if (!in) a.flag[i] = 0;
-      }
-    } else {
+    if (!a.cu) {
       a.flag[i] = a.mask ? (a.mask[i] != 0) : 1;
       a.c_tok[i] = 1.f;
       a.a_tok[i] = 0.f;
     }
   }
+  if (!a.cu) return;
+  // Rows of no segment.  The offsets lead from the first to the last, so every row between these two is in one; of the others, none is unless
+  // some offset goes back, which the wavefront looks for first.
+  const bool outside = i < a.T && (a.S <= 0 || i < a.cu[0] || i >= a.cu[a.S]);
+  if (!__any(outside)) return;
+  bool back = false;
+#pragma unroll 4
+  for (int s = threadIdx.x & 63; s < a.S; s += 64) back |= a.cu[s + 1] < a.cu[s];
+  bool in = false;
+  if (__any(back) && outside)
+    for (int s = 0; s < a.S; ++s) in |= i >= a.cu[s] && i < a.cu[s + 1];
+  if (outside && !in) a.flag[i] = 0;
 }
 
 // One workgroup per segment (= one training sample): Sec. 5.1's geometric-mean ratio and

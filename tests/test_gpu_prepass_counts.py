@@ -66,3 +66,20 @@ def test_counts(T, lo, hi, mode):
         assert (got[[0, 3, 4, 5, 6, 7]] == want[[0, 3, 4, 5, 6, 7]]).all(), (got, want)
         logp = out["logp"].cpu().numpy()
         assert ((logp != 0) == active).all() and not out["dH"].cpu().float().numpy()[~active].any()
+
+
+@pytest.mark.parametrize("cu", [[0, 100, 50], [90, 120, 40, 70], [0, 0, 0], [200, 300, 200]])
+def test_offsets_that_go_back(cu):
+    """A segment whose end lies before its start is empty; the rows of the others stay theirs, and rows of none are not active."""
+    dev, T, d, V = torch.device("cuda:0"), 600, 64, 300
+    H, W, y = synth.make_head(T, d, V, "bf16", 3, dev)
+    S, prm = len(cu) - 1, B.Params()
+    active = np.zeros(T, bool)
+    for a, b in zip(cu, cu[1:]):
+        active[a:b] = True
+    z = torch.zeros(T, device=dev)
+    ws = torch.full((B.pg_workspace_bytes(T, d, V, S, prm, B.CALL_LOSS_FWD_BWD),), 0xFF, dtype=torch.uint8, device=dev)
+    out = B.pg_loss_fwd_bwd(H, W, y, torch.ones(T, dtype=torch.uint8, device=dev), torch.tensor(cu, dtype=torch.int32, device=dev),
+                            torch.ones(S, dtype=torch.float64, device=dev), torch.arange(S, dtype=torch.int32, device=dev), z, z, prm, ws)
+    assert out["counters"][0].item() == out["counters"][6].item() == active.sum()
+    assert ((out["logp"].cpu().numpy() != 0) == active).all()
