@@ -655,10 +655,12 @@ void launch_dw_fold(const DwFoldArgs& a, hipStream_t s) {
 // ------------------------------------------------------------------ dH scatter
 // dH[t,:] = accumulated row of its compacted position, or zeros for rows that are not active.
 // A thread requests SCATTER_AHEAD slabs at once (one after the other, 16 slabs of 200 rows, d = 5120, took 24.5 us; with this and the split below 12.4).
-constexpr int SCATTER_AHEAD = 7;
+// (FEW: in calls of few rows only; in the others the wider kernel costs the launch more than the slabs, which are few there: 40 000 rows, d = 64, 12.5 / 18.2 us.)
+constexpr int SCATTER_AHEAD = 7, SCATTER_FEW_ROWS = 2048;
+template <bool FEW>
 __global__ __launch_bounds__(256) void scatter_dh_kernel(ScatterArgs a, FinishArgs fin, DwFoldArgs fold, int fold_groups) {
   const int t = (int)blockIdx.x - 1 - fold_groups;
-  if (t < 0 && blockIdx.y) return;
+  if (FEW && t < 0 && blockIdx.y) return;
   if (blockIdx.x == 0) return finish_loss(fin);
   if (t < 0) return dw_fold(fold, (int)blockIdx.x - 1, fold_groups);
   const int p = a.pos[t];
@@ -666,12 +668,12 @@ __global__ __launch_bounds__(256) void scatter_dh_kernel(ScatterArgs a, FinishAr
   const int n_pad = a.ctl->n_pad;
   const int ks = a.ctl->dh_slabs;
   const size_t slab = (size_t)n_pad * a.d;
-  for (int j = (blockIdx.y * 256 + threadIdx.x) * 4; j < a.d; j += gridDim.y * (256 * 4)) {
+  for (int j = ((FEW ? blockIdx.y * 256 : 0) + threadIdx.x) * 4; j < a.d; j += (FEW ? gridDim.y : 1) * (256 * 4)) {
     f32x4 v = {0.f, 0.f, 0.f, 0.f};
     if (p >= 0) {
       v = *reinterpret_cast<const f32x4*>(src + j);
       int q = 1;
-      for (; q + SCATTER_AHEAD <= ks; q += SCATTER_AHEAD) {               // split-K slabs, added in a fixed order
+      for (; FEW && q + SCATTER_AHEAD <= ks; q += SCATTER_AHEAD) {               // split-K slabs, added in a fixed order
         f32x4 w[SCATTER_AHEAD];
 #pragma unroll
         for (int r = 0; r < SCATTER_AHEAD; ++r) w[r] = *reinterpret_cast<const f32x4*>(src + (q + r) * slab + j);
@@ -746,7 +748,8 @@ void launch_scatter_dh(const ScatterArgs& a, const FinishArgs& fin, const DwFold
   if (a.T <= 0) return;
   const int f = dw_fold_groups(fold);
   const int parts = a.T <= SCATTER_PARTS_ROWS ? (a.d + 1023) / 1024 : 1;
-  hipLaunchKernelGGL(scatter_dh_kernel, dim3(a.T + 1 + f, parts), dim3(256), 0, s, a, fin, fold, f);
+  if (a.T <= SCATTER_FEW_ROWS) hipLaunchKernelGGL(scatter_dh_kernel<true>, dim3(a.T + 1 + f, parts), dim3(256), 0, s, a, fin, fold, f);
+  else hipLaunchKernelGGL(scatter_dh_kernel<false>, dim3(a.T + 1 + f), dim3(256), 0, s, a, fin, fold, f);
 }
 
 // ------------------------------------------------------------------ rewards (Eq. 1, Eq. 6-7)
