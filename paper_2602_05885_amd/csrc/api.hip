@@ -910,6 +910,7 @@ int32_t loss_fwd_bwd(int sft, const void* H, const void* W, const int32_t* y, co
       w.accumulate = p.accumulate_dW; w.out_bf16 = p.dW_dtype; w.k_from_ctl = 1; w.m_from_ctl = 0; w.ctl = ctl;
       w.queue = queues + pg::QUEUE_SET_WORDS;
       w.rc = few; w.rc_role = 1; w.v0 = v0; w.blk = blk;
+      w.wide_ok = pg::wide_fits(pl.ld_h);
       if (pl.dw_cap) {
         pg::DwFoldArgs& f = fold;
         f.slabs = at<float>(ws, pl.dWslabs); f.dW = w.C; f.n = (long long)rows_valid * d_i; f.slab = (long long)pl.vc * d_i;
@@ -935,6 +936,7 @@ int32_t loss_fwd_bwd(int sft, const void* H, const void* W, const int32_t* y, co
       h.queue = queues + 2 * pg::QUEUE_SET_WORDS;
       h.rc = few; h.rc_role = 2; h.v0 = v0;
       h.rule = rule; h.blk = blk;
+      h.wide_ok = pg::wide_fits(wt_cache_ld(pl.V));     // (with the cache and without: the same sums, see few.dh_whole)
       {
         ProfScope ps(PG_KERNEL_DH, st);
         if (transposed) pg::launch_gemm_store(h, st);

@@ -214,6 +214,8 @@ __host__ __device__ inline int dh_slabs(int n_pad, int acc_rows, int tiles_n, in
 //                              dW, 37.1 / 30.2 rounds, 16 stages 1308 / 1255 us, 65 stages, bf16 3.55 / 3.51 ms
 //   d = 1920 (8 / 6 tiles)     20000 rows, dW 2.98 / 2.65 ms, dH 3.10 / 2.66
 constexpr int WIDE_GAIN = 35;
+// The 320 rows of a W^T or H^T of this leading dimension lie within the 32-bit range of one tile's loads (SlabLoader); what the calls accept is bounded by 256.
+__host__ __device__ inline bool wide_fits(long long ld) { return (unsigned long long)ld * 2 * WIDE_ROWS < 1ull << 32; }
 __host__ __device__ inline int store_tiles_n(int n, bool wide) { return wide ? (n + WIDE_ROWS - 1) / WIDE_ROWS : (n + BN - 1) / BN; }
 __host__ __device__ inline long long launch_cost(int tiles, int stages, bool wide) {
   const long long rounds_x512 = ((long long)tiles + 255) / 256 * 256 + tiles;
@@ -243,7 +245,7 @@ __host__ __device__ inline int dh_parts(int n_pad, int acc_rows, int tiles_n, in
 }
 // The form of a dH contraction that may be split (the rows of a single token block): parts, products (slabs: ks products) and tiles.
 struct DhForm { int ks, products; bool wide; };
-__host__ __device__ inline DhForm dh_form(int n_pad, int acc_rows, int n, int k_stages, int split_f32) {
+__host__ __device__ inline DhForm dh_form(int n_pad, int acc_rows, int n, int k_stages, int split_f32, bool wide_ok) {
   DhForm f;
   f.wide = false;
   if (split_f32) {        // the products side by side, where they and the parts fit one round
@@ -253,7 +255,7 @@ __host__ __device__ inline DhForm dh_form(int n_pad, int acc_rows, int n, int k_
   }
   f.ks = dh_parts(n_pad, acc_rows, store_tiles_n(n, false), k_stages);
   f.products = 1;
-  if (split_f32) return f;
+  if (split_f32 || !wide_ok) return f;
   const int ks = dh_parts(n_pad, acc_rows, store_tiles_n(n, true), k_stages);
   f.wide = wide_pays(n_pad / BM, n, k_stages, f.ks, ks);
   if (f.wide) f.ks = ks;
@@ -295,8 +297,8 @@ struct SlabLoader {
   }
 
   // The resource covers only the (up to) 64 G rows of this tile, from byte k_byte0 of its first
-  // row to the end of its last existing row, so operands of any size can be addressed (a
-  // resource's range and the lane offsets are 32-bit) and rows beyond rows_total read as 0.
+  // row to the end of its last existing row, so operands of any number of rows can be addressed (a
+  // resource's range and the lane offsets are 32-bit: 64 G rows lie below 4 GiB, see wide_fits) and rows beyond rows_total read as 0.
   __device__ __forceinline__ void init(const void* base_, int rows_total, int row0, int ld_elems, uint32_t k_byte0,
                                        int tid) {
     const int rows = min(max(rows_total - row0, 0), 64 * G);

@@ -185,8 +185,9 @@ struct StoreArgs {
   int k_from_ctl;       // contraction length = active tokens, up to whole stages (dw_stages)
   int m_from_ctl;       // row extent = active tokens: rows of C from there on, up to the padded count, are left as they are
   TokenBlocks blk;      // of the token extent
-  int split_k;          // with m_from_ctl: cut K into the parts of dh_form(n_pad, acc_rows, N, split_stages, ..), part p writes rows p n_pad + m
+  int split_k;          // with m_from_ctl: cut K into the parts of dh_form, part p writes rows p n_pad + m
   int acc_rows;         // rows of C
+  int wide_ok;          // tiles of 320 n can address their operand (wide_fits)
   int dw_cap;           // > 0, with k_from_ctl: cut K into dw_split(K stages, dw_cap) parts (times three products for fp32
                         // heads); part p writes rows p slab_rows + m of `slabs`, fp32 scratch that dw_fold adds up.
                         // A single part is written to C like an unsplit one (19 of 2698 rows, d = 2304, V = 2322, bf16:

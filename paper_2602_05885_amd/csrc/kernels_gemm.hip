@@ -673,13 +673,13 @@ struct StoreShape {
     ks = 1; products = 1; slab_rows = ctl.n_pad;
     wide = false;
     if (a.split_k && a.m_from_ctl && nt * BM == ctl.n_pad) {
-      const DhForm f = dh_form(ctl.n_pad, a.acc_rows, a.N, a.split_stages, a.A_lo != nullptr);
+      const DhForm f = dh_form(ctl.n_pad, a.acc_rows, a.N, a.split_stages, a.A_lo != nullptr, a.wide_ok);
       ks = f.ks; products = f.products; wide = f.wide;
     } else if (a.dw_cap > 0) {
       ks = dw_split(K / BK, a.dw_cap);
       products = a.A_lo ? 3 : 1;
       slab_rows = a.slab_rows;
-    } else if (!a.A_lo) {
+    } else if (!a.A_lo && a.wide_ok) {
       wide = wide_pays(tiles_m, a.N, K / BK);
     }
     tiles_n = store_tiles_n(a.N, wide);

@@ -163,10 +163,10 @@ int main(int argc, char** argv) {
 
   StoreArgs w{};      // dW chunk: [vc, d] = dS^T [vc, T] x H^T [d, T]
   w.A = dST; w.B = HcT; w.a_rows = vc; w.b_rows = d; w.lda = ld_t; w.ldb = ld_t; w.M = vc; w.N = d; w.K = T;
-  w.tiles_m = vc / 256; w.tiles_n = d / 256; w.C = dW; w.ldc = d; w.k_from_ctl = 1; w.ctl = ctl; w.queue = queue;
+  w.tiles_m = vc / 256; w.tiles_n = d / 256; w.C = dW; w.ldc = d; w.k_from_ctl = 1; w.wide_ok = 1; w.ctl = ctl; w.queue = queue;
   StoreArgs g{};      // dH: [T, d] += dS [T, vc] x W^T [d, vc]
   g.A = dS; g.B = WT; g.a_rows = T; g.b_rows = d; g.lda = ld_v; g.ldb = ld_v; g.M = T; g.N = d; g.K = vc;
-  g.tiles_m = T / 256; g.tiles_n = d / 256; g.C = dH; g.ldc = d; g.accumulate = 1; g.m_from_ctl = 1; g.split_k = 1; g.split_stages = vc / 64; g.ctl = ctl; g.queue = queue;
+  g.tiles_m = T / 256; g.tiles_n = d / 256; g.C = dH; g.ldc = d; g.accumulate = 1; g.m_from_ctl = 1; g.split_k = 1; g.split_stages = vc / 64; g.wide_ok = 1; g.ctl = ctl; g.queue = queue;
   DlogitsArgs r{};    // recompute of the chunk's logits, dS and dS^T out
   r.W = W; r.Hc = Hc; r.w_rows = V; r.h_rows = T; r.ldw = d; r.ldh = d; r.K = d; r.V = V; r.v0 = vc; r.ld_s = ld_v; r.ld_t = ld_t;
   r.tiles_v = vc / 256; r.tiles_t = T / 256; r.t_cap = T; r.scale = 1.4427f; r.yc = yc; r.lse2 = lse2; r.coefc = coefc;

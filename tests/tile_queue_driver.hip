@@ -3,7 +3,7 @@
 // For every tile count swept and both orders: the entries i < share(y) of the 8 XCDs, decoded with the
 // order's map, hand out every tile (tm, tn) exactly once; entries at and beyond share(y) map to no tile;
 // 32 consecutive entries of one XCD form a block of at most 4 x 8 neighbouring tiles (what the L2 sharing
-// relies on); dh_split and dh_slabs keep their parts inside the accumulator; dw_split's parts are no shorter than
+// relies on); tiles of 320 rows stay within the range of their loads; dh_split and dh_slabs keep their parts inside the accumulator; dw_split's parts are no shorter than
 // its least; token blocks cut the live tiles without a gap or an overlap; and the kept tiles fit their region.
 #include <cstdio>
 #include <vector>
@@ -79,6 +79,21 @@ int main() {
             CHECK(products == 1 || (n_pad / 256) * tiles_n * slabs <= 256, "dh_slabs(%d, %d, %d, %d, 1): %d slabs are more than one round", n_pad, t_cap, tiles_n, stages, slabs);
           }
         }
+  // Wide tiles only where 320 rows of the operand lie below 4 GiB; what the calls accept has 256 of them there.
+  int wide_near = 0, wide_far = 0;
+  for (long long V : {25600ll, 2000000ll, 6710000ll, 6711000ll, 7000000ll, 8388000ll}) {
+    const long long ld = pad_ld((V + 255) / 256 * 256);
+    if (ld * 2 * 256 >= 1ll << 32) { CHECK(false, "V = %lld is not accepted", V); continue; }
+    for (int d : {320, 640, 1600, 5120})
+      for (int rows : {256, 2048, 8192, 20224, 65536})
+        for (int chunk : {4, 512, 16384}) {
+          const int acc_rows = imax(rows, imin(8 * rows, 32768)), stages = 4 * chunk;
+          const DhForm f = dh_form(rows, acc_rows, d, stages, 0, wide_fits(ld));
+          (ld * 2 * WIDE_ROWS < 1ll << 32 ? wide_near : wide_far) += f.wide;
+          CHECK(f.wide == (wide_fits(ld) && dh_form(rows, acc_rows, d, stages, 0, true).wide), "dh_form(%d, %d, %d, %d)", rows, acc_rows, d, stages);
+        }
+  }
+  CHECK(wide_near > 0 && wide_far == 0, "wide tiles: %d within their range, %d beyond", wide_near, wide_far);
   for (int stages = 0; stages <= 300; ++stages)
     for (int cap = 1; cap <= DW_SPLIT_MAX; ++cap) {
       const int ks = dw_split(stages, cap);
