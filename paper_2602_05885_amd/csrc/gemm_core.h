@@ -89,8 +89,8 @@ __host__ __device__ inline int grid_for_tiles(int tiles_m, int tiles_n) {
 
 // (host-callable too, like the queue's share() below: a host test sweeps them over tile counts and checks
 // that every tile is handed out exactly once)
-__host__ __device__ inline int imin(int a, int b) { return a < b ? a : b; }
-__host__ __device__ inline int imax(int a, int b) { return a > b ? a : b; }
+__host__ __device__ constexpr int imin(int a, int b) { return a < b ? a : b; }
+__host__ __device__ constexpr int imax(int a, int b) { return a > b ? a : b; }
 
 // Entry t of the flattened order: panels of `width` n-tiles, inside a panel groups of SB_M m-tiles with m running fastest, or
 // (n_first) one m-tile after the other.  A block of 32 is 4 x 8 tiles either way; what differs is which operand is asked for by
@@ -169,25 +169,66 @@ __host__ __device__ inline bool map_tile_interleaved(int bid, int tiles_m, int t
 // slab's extra pass in the scatter).  Measured at V = 151936 (one chunk, 2376 stages), dH launch alone:
 //   768 rows, d = 5120 (60 tiles)     one part 1466 us, 4 parts 579 us
 //   3072 rows, d = 4096 (192 tiles)   one part 3167 us, 4 parts 2479 us
-// (Longest split: 8 parts; dh_parts has more for few tiles.)
-// Every kernel derives ks from the same device-side values (k_stages: those of the first chunk, for all
-// chunks), so the decomposition, and with it the summation order, is fixed for given inputs.
-constexpr int SPLIT_MAX = 8, SPLIT_MIN_STAGES = 8, SPLIT_TILE_STAGES = 24;
-__host__ __device__ inline int dh_split(int n_pad, int acc_rows, int tiles_n, int k_stages) {
-  if (n_pad <= 0) return 1;
-  const int tiles = (n_pad / 256) * tiles_n;
-  int best = 1;
-  long long best_cost = 0;
-  // (unrolled: every workgroup of a dH launch comes through here, and a division by a variable is a
-  // sequence of 20 instructions)
+// (Up to 8 parts; dh_parts has more for few tiles.)
+// The values that it goes by (k_stages: those of the first chunk, for all chunks) are the same for every launch of a call, so the decomposition, and with it the
+// summation order, is fixed for given inputs.  The dH launches leave the number of slabs in Ctl, where the scatter finds it.
+constexpr int SPLIT_MAX = 8, SPLIT_MIN_STAGES = 8, SPLIT_TILE_STAGES = 24, DH_PARTS_MAX = 64;
+struct Parts { int ks, stages; };       // parts, and stages of the longest
+
+// The numbers of parts, 1 .. MAX, are tried side by side, one in each lane (whole wavefronts only; on the host one after the other): the least cost(parts,
+// stages), the fewest among equals.  Every workgroup of a dH launch comes through here before its first load, and a division by a variable is a sequence of
+// 25 instructions.  One number after the other / side by side, dH launch: 8 rows, d = 3712, V = 2817 19.1 / 15.8 us; 979 rows, 3072 x 3084 30.6 / 29.4;
+// 1126 rows, 1280 x 3596 26.0 / 24.6.
+constexpr unsigned long long NO_PARTS = ~0ull >> 6;
+#ifdef __HIP_DEVICE_COMPILE__
+template <int CTRL> __device__ __forceinline__ unsigned long long least_of_pair(unsigned long long x) {
+  const unsigned lo = (unsigned)__builtin_amdgcn_mov_dpp((int)(unsigned)x, CTRL, 0xf, 0xf, true);
+  const unsigned hi = (unsigned)__builtin_amdgcn_mov_dpp((int)(x >> 32), CTRL, 0xf, 0xf, true);
+  const unsigned long long y = (unsigned long long)hi << 32 | lo;
+  return y < x ? y : x;
+}
+__device__ __forceinline__ unsigned long long of_lane(unsigned long long x, int lane) {
+  return (unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(x >> 32), lane) << 32 | (unsigned)__builtin_amdgcn_readlane((int)(unsigned)x, lane);
+}
+#endif
+template <int MAX, class Cost>
+__host__ __device__ inline Parts least_parts(int k_stages, Cost&& cost) {
+  static_assert(MAX == 8 || MAX == 64, "lanes");
+#ifdef __HIP_DEVICE_COMPILE__
+  const int ks = (int)(threadIdx.x & 63) + 1, stages = (k_stages + ks - 1) / ks;
+  unsigned long long key = cost(ks, stages) << 6 | (unsigned)(ks - 1);
+  key = least_of_pair<0xB1>(key);          // lane ^ 1
+  key = least_of_pair<0x4E>(key);          // lane ^ 2
+  key = least_of_pair<0x141>(key);         // mirrored among 8
+  unsigned long long least = of_lane(key, 0);
+  if (MAX > 8) {
+    key = least_of_pair<0x140>(key);       // mirrored among 16
+    least = of_lane(key, 0);
 #pragma unroll
-  for (int ks = 1; ks <= SPLIT_MAX; ++ks) {
-    if (ks > 1 && ((long long)ks * n_pad > acc_rows || ks * SPLIT_MIN_STAGES > k_stages)) break;
-    const long long rounds = ((long long)tiles * ks + 255) / 256;
-    const long long cost = rounds * ((k_stages + ks - 1) / ks + SPLIT_TILE_STAGES);
-    if (ks == 1 || cost < best_cost) { best = ks; best_cost = cost; }
+    for (int lane = 16; lane < 64; lane += 16) {
+      const unsigned long long k = of_lane(key, lane);
+      least = k < least ? k : least;
+    }
   }
-  return best;
+  const int at = (int)(least & 63);
+  return Parts{at + 1, __builtin_amdgcn_readlane(stages, at)};
+#else
+  unsigned long long least = ~0ull;
+  for (int ks = 1; ks <= MAX; ++ks) {
+    const unsigned long long key = cost(ks, (k_stages + ks - 1) / ks) << 6 | (unsigned)(ks - 1);
+    least = key < least ? key : least;
+  }
+  const int ks = (int)(least & 63) + 1;
+  return Parts{ks, (k_stages + ks - 1) / ks};
+#endif
+}
+__host__ __device__ inline Parts dh_split(int n_pad, int acc_rows, int tiles_n, int k_stages) {
+  if (n_pad <= 0 || 2ll * n_pad > acc_rows || 2 * SPLIT_MIN_STAGES > k_stages) return Parts{1, k_stages};
+  const long long tiles = (long long)(n_pad / 256) * tiles_n;
+  return least_parts<SPLIT_MAX>(k_stages, [&](int ks, int stages) -> unsigned long long {
+    if (ks > 1 && ((long long)ks * n_pad > acc_rows || ks * SPLIT_MIN_STAGES > k_stages)) return NO_PARTS;
+    return (unsigned long long)((tiles * ks + 255) / 256) * (unsigned)(stages + SPLIT_TILE_STAGES);
+  });
 }
 
 // fp32 heads add three products per contraction (A B, A B_lo, A_lo B).  Where the parts of a launch leave room for it,
@@ -197,11 +238,6 @@ __host__ __device__ inline int split_products(int split_f32, int tiles, int ks, 
 }
 __host__ __device__ inline int dh_products(int n_pad, int acc_rows, int tiles_n, int ks, int split_f32) {
   return split_products(split_f32, (n_pad / 256) * tiles_n, ks, n_pad, acc_rows);
-}
-// Slabs of the dH accumulator.
-__host__ __device__ inline int dh_slabs(int n_pad, int acc_rows, int tiles_n, int k_stages, int split_f32, int& ks) {
-  ks = dh_split(n_pad, acc_rows, tiles_n, k_stages);
-  return ks * dh_products(n_pad, acc_rows, tiles_n, ks, split_f32);
 }
 
 // dW and dH run in tiles of 256 or of 320 (wide) output columns.  A wide tile takes 1.25 times as long, less WIDE_GAIN thousandths for the operand bytes
@@ -221,45 +257,41 @@ __host__ __device__ inline long long launch_cost(int tiles, int stages, bool wid
   const long long rounds_x512 = ((long long)tiles + 255) / 256 * 256 + tiles;
   return rounds_x512 * (stages + SPLIT_TILE_STAGES) * (wide ? GW * (1000 - WIDE_GAIN) : GM * 1000);
 }
-__host__ __device__ inline bool wide_pays(int tiles_m, int n, int stages, int ks_256 = 1, int ks_320 = 1) {
-  return launch_cost(tiles_m * ks_320 * store_tiles_n(n, true), (stages + ks_320 - 1) / ks_320, true) <
-         launch_cost(tiles_m * ks_256 * store_tiles_n(n, false), (stages + ks_256 - 1) / ks_256, false);
+__host__ __device__ inline bool wide_pays(int tiles_m, int n, Parts p256, Parts p320) {
+  return launch_cost(tiles_m * p320.ks * store_tiles_n(n, true), p320.stages, true) < launch_cost(tiles_m * p256.ks * store_tiles_n(n, false), p256.stages, false);
 }
 // A dH of so few tiles that eight parts leave most compute units idle: as many parts as one round holds, up to DH_PARTS_MAX, or fewer where their
 // slabs would cost more than they save (written, and read again by the scatter: DH_ROUND_SLABS stages per round full of them).
 // Eight parts / more, dH launch and scatter together: 100 rows, d = 1024, V = 65536 (4 tiles, 48 parts) 164 / 60 us; 200 rows, d = 1024, V = 8000 (16 parts)
 // 33.9 / 30.2; 100 rows, d = 4096, V = 32000 (13 tiles) 134 / 115; 200 rows, d = 5120, V = 151936 (16) 452 / 371; 300 x 2560 x 50000 179 / 142; fp32
 // 512 rows, 64 x 1000 (8 / 12 slabs) 20.5 / 17.4, 1024 rows, 256 x 4000 50.7 / 36.0, 2000 rows, 512 x 10000 94 / 75.
-constexpr int DH_PARTS_MAX = 64, DH_MIN_STAGES = 4, DH_ROUND_SLABS = 16;
-__host__ __device__ inline int dh_parts(int n_pad, int acc_rows, int tiles_n, int k_stages) {
-  int best = dh_split(n_pad, acc_rows, tiles_n, k_stages);
-  if (n_pad <= 0) return best;
-  const int tiles = (n_pad / 256) * tiles_n;
-  auto cost = [&](int ks) { return ((tiles * ks + 255) / 256) * 256 * ((k_stages + ks - 1) / ks + SPLIT_TILE_STAGES) + tiles * ks * DH_ROUND_SLABS; };
-  int least = cost(best);
-  for (int ks = imin(imin(256 / tiles, k_stages / DH_MIN_STAGES), imin(acc_rows / n_pad, DH_PARTS_MAX)); ks > best; ks -= (ks + 3) / 4) {
-    const int c = cost(ks);
-    if (c < least) { best = ks; least = c; }
-  }
-  return best;
+// The most parts whose cost is below that of eight / those of least cost, whole calls: 100 rows, 1024 x 65536 188.5 / 185.1 us, normed 203.6 / 199.9;
+// 215 of 12174 rows, 2752 x 13018, normed 265.8 / 252.6; 177 of 12352 rows, 2304 x 15669 173.4 / 167.7; 200 rows, 4096 x 151936 the same.
+constexpr int DH_MIN_STAGES = 4, DH_ROUND_SLABS = 16;
+__host__ __device__ inline Parts dh_parts(int n_pad, int acc_rows, int tiles_n, int k_stages) {
+  const Parts few = dh_split(n_pad, acc_rows, tiles_n, k_stages);
+  const long long tiles = (long long)(n_pad / 256) * tiles_n;
+  auto fits = [&](int ks) { return tiles * ks <= 256 && (long long)ks * n_pad <= acc_rows && ks * DH_MIN_STAGES <= k_stages; };
+  if (n_pad <= 0 || !fits(few.ks + 1)) return few;
+  return least_parts<DH_PARTS_MAX>(k_stages, [&](int ks, int stages) -> unsigned long long {
+    if (ks < few.ks || (ks > few.ks && !fits(ks))) return NO_PARTS;
+    const int t = (int)tiles * ks;
+    return (unsigned long long)((t + 255) / 256 * 256) * (unsigned)(stages + SPLIT_TILE_STAGES) + (unsigned)(t * DH_ROUND_SLABS);
+  });
 }
 // The form of a dH contraction that may be split (the rows of a single token block): parts, products (slabs: ks products) and tiles.
 struct DhForm { int ks, products; bool wide; };
 __host__ __device__ inline DhForm dh_form(int n_pad, int acc_rows, int n, int k_stages, int split_f32, bool wide_ok) {
-  DhForm f;
-  f.wide = false;
+  const int tiles_n = store_tiles_n(n, false);
   if (split_f32) {        // the products side by side, where they and the parts fit one round
-    f.ks = dh_parts(n_pad, acc_rows / 3, 3 * store_tiles_n(n, false), k_stages);
-    f.products = dh_products(n_pad, acc_rows, store_tiles_n(n, false), f.ks, split_f32);
-    if (f.products == 3) return f;
+    const int ks = dh_parts(n_pad, acc_rows / 3, 3 * tiles_n, k_stages).ks;
+    if (dh_products(n_pad, acc_rows, tiles_n, ks, split_f32) == 3) return DhForm{ks, 3, false};
   }
-  f.ks = dh_parts(n_pad, acc_rows, store_tiles_n(n, false), k_stages);
-  f.products = 1;
-  if (split_f32 || !wide_ok) return f;
-  const int ks = dh_parts(n_pad, acc_rows, store_tiles_n(n, true), k_stages);
-  f.wide = wide_pays(n_pad / BM, n, k_stages, f.ks, ks);
-  if (f.wide) f.ks = ks;
-  return f;
+  const Parts p256 = dh_parts(n_pad, acc_rows, tiles_n, k_stages);
+  if (split_f32 || !wide_ok) return DhForm{p256.ks, 1, false};
+  const Parts p320 = dh_parts(n_pad, acc_rows, store_tiles_n(n, true), k_stages);
+  const bool wide = wide_pays(n_pad / BM, n, p256, p320);
+  return DhForm{wide ? p320.ks : p256.ks, 1, wide};
 }
 
 // Split-K factor of the dW contraction (over the stages of dw_stages) of a head so small that its tiles leave most

@@ -680,7 +680,7 @@ struct StoreShape {
       products = a.A_lo ? 3 : 1;
       slab_rows = a.slab_rows;
     } else if (!a.A_lo && a.wide_ok) {
-      wide = wide_pays(tiles_m, a.N, K / BK);
+      wide = wide_pays(tiles_m, a.N, Parts{1, K / BK}, Parts{1, K / BK});
     }
     tiles_n = store_tiles_n(a.N, wide);
     total = tiles_m * ks * products * tiles_n;
@@ -700,7 +700,8 @@ __device__ __forceinline__ void gemm_store_tile(StoreArgs a, const StoreShape& s
     const int product = slab - part * sh.products;
     if (product == 1) { a.B = a.B_lo; a.ldb = a.ldb_lo; }
     if (product == 2) a.A = a.A_lo;
-    const unsigned stages = (unsigned)s1;              // below 2^23 (V or T in stages of 64), at most DW_SPLIT_MAX parts
+    static_assert((long long)imax(DH_PARTS_MAX, DW_SPLIT_MAX) * ((1 << 30) / BK) < 1ll << 32, "V and T are at most 2^30");
+    const unsigned stages = (unsigned)s1;
     s0 = (int)((unsigned)part * stages / (unsigned)sh.ks);
     s1 = (int)((unsigned)(part + 1) * stages / (unsigned)sh.ks);
   }

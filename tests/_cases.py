@@ -110,3 +110,49 @@ def recompute_covers_vocabulary(T: int, V: int, n_pad: int, chunk_rows: int, row
     if chunk_rows >= v_pad or n_pad <= 0:
         return False                                  # one chunk anyway / nothing to do
     return n_pad * pad_ld(v_pad) <= t_cap * pad_ld(chunk_rows) and v_pad * pad_ld(n_pad) <= chunk_rows * pad_ld(t_cap)
+
+
+def _dh_parts(n_pad, acc_rows, tiles, stages):
+    few = min((q for q in range(1, 9) if q == 1 or (q * n_pad <= acc_rows and q * 8 <= stages)),
+              key=lambda q: (-(-tiles * q // 256) * (-(-stages // q) + 24), q))
+    return min((q for q in range(few, 65) if q == few or (q * tiles <= 256 and q * n_pad <= acc_rows and q * 4 <= stages)),
+               key=lambda q: (-(-tiles * q // 256) * 256 * (-(-stages // q) + 24) + tiles * q * 16, q))
+
+
+def wide_pays(tiles_m: int, n: int, p256, p320) -> bool:
+    """Whether a dW or dH launch runs in tiles of 320 columns (the library's rule, restated); p256, p320: parts, stages of the longest."""
+    def cost(tiles, stages, width):
+        return (-(-tiles // 256) * 256 + tiles) * (stages + 24) * width
+    return cost(tiles_m * p320[0] * -(-n // 320), p320[1], 5 * 965) < cost(tiles_m * p256[0] * -(-n // 256), p256[1], 4 * 1000)
+
+
+def dh_form(n_pad: int, acc_rows: int, n: int, stages: int, f32=False, wide_ok=True):
+    """Parts, products and tile width of the dH contraction of a call's active rows, n_pad of them padded (the library's device-side rule, restated):
+    parts of least modelled rounds, more than eight where few tiles leave compute units idle, their slabs within the accumulator."""
+    tiles_m, t256, t320 = n_pad // 256, -(-n // 256), -(-n // 320)
+    if f32:
+        ks = _dh_parts(n_pad, acc_rows // 3, tiles_m * 3 * t256, stages)
+        if 3 * ks * tiles_m * t256 <= 256 and 3 * ks * n_pad <= acc_rows:
+            return ks, 3, False
+    k256 = _dh_parts(n_pad, acc_rows, tiles_m * t256, stages)
+    if f32 or not wide_ok:
+        return k256, 1, False
+    k320 = _dh_parts(n_pad, acc_rows, tiles_m * t320, stages)
+    wide = wide_pays(tiles_m, n, (k256, -(-stages // k256)), (k320, -(-stages // k320)))
+    return (k320 if wide else k256), 1, wide
+
+
+def dh_acc_rows(T: int, d: int, V: int, f32=False, chunks=1) -> int:
+    """Rows of the dH accumulator of a call in one token block (restated): eight slabs of all rows up to 32768 in all, and with a single vocab chunk the room
+    of dS^T (for an fp32 head with its remainders), up to 64 slabs."""
+    t_cap = (T + 255) // 256 * 256
+    rows = max(t_cap, min(8 * t_cap, 32768))
+    if chunks > 1 or rows >= 32768:
+        return rows
+    dst = -(-((V + 255) // 256 * 256 * pad_ld(t_cap) * 2) // 256) * 256
+    return min(((2 if f32 else 1) * dst + -(-(rows * d * 4) // 256) * 256) // (d * 4), 64 * t_cap, 32768)
+
+
+def dh_slabs(workspace: torch.Tensor) -> int:
+    """Slabs of the dH accumulator that the last call on this workspace wrote (twelfth word of the control block, at the workspace's start)."""
+    return int(workspace[:48].view(torch.int32)[11])

@@ -20,7 +20,7 @@ import torch
 from oracle import pg_oracle as O
 from paper_2602_05885_amd import binding as B
 from paper_2602_05885_amd import synth
-from tests._cases import block_rel_fro, np64, ratio_targets, rel_fro
+from tests._cases import block_rel_fro, dh_acc_rows, dh_form, dh_slabs, np64, ratio_targets, rel_fro
 
 pytestmark = pytest.mark.gpu
 
@@ -258,13 +258,6 @@ def test_full_all_rows_against_library_gradients(full_case):
     del lib_dW, lib_dH
 
 
-def dh_split_parts(n_pad, acc_rows, tiles_n, k_stages):
-    """The device's choice of how many parts the dH contraction is cut into, restated: the least rounds of 256 tiles times
-    (stages of a part + 24), at most 8 parts of at least 8 stages, whose slabs fit the accumulator."""
-    fits = [ks for ks in range(1, 9) if ks == 1 or (ks * n_pad <= acc_rows and ks * 8 <= k_stages)]
-    return min(fits, key=lambda ks: (-(-n_pad // 256 * tiles_n * ks // 256) * (-(-k_stages // ks) + 24), ks))
-
-
 def test_full_geometric_rejection_few_rows_split_contraction(full_case):
     """Sec. 5.1's rule at the benchmark's size with most samples rejected: two samples' log-ratios sit inside
     [0.999, 1.001] by construction, all others 5e-3 outside, so about 1.3 k of 32768 loss tokens stay active
@@ -291,7 +284,6 @@ def test_full_geometric_rejection_few_rows_split_contraction(full_case):
     out = B.pg_loss_fwd_bwd(tin["H"], tin["W"], tin["y"], tin["loss_mask"], tin["cu"], fc["adv"].reshape(-1),
                             tin["seg_sample"], tin["old"], rollout_t, prm, ws)
     torch.cuda.synchronize()
-    del ws
     oprm = O.Params(mismatch_mode=1, temperature=spec.temperature)
     c, active, keep, mm = O.mismatch_weights(fc["old"], rollout, batch.loss_mask, batch.cu_seqlens, oprm)
     cnt = out["counters"].cpu().numpy()
@@ -300,13 +292,14 @@ def test_full_geometric_rejection_few_rows_split_contraction(full_case):
     assert cnt[3] == mm["geo"] == S - 2 and cnt[4] == mm["veto"] == 0 and cnt[5] == 0
     # the launch really is the split one
     vc = B.pg_backward_chunk_rows(T, d, V, S, prm)
-    t_cap, n_pad = (T + 255) // 256 * 256, (n_act + 255) // 256 * 256
-    # (few rows: one launch over the whole vocabulary; the accumulator has t_cap rows from 32768 on)
-    parts = dh_split_parts(n_pad, t_cap, (d + 255) // 256, (V + 255) // 256 * 4)
-    print(f"[fullsize] geometric rejection keeps {n_act} rows (padded {n_pad}): dH contraction in {parts} parts", flush=True)
-    assert parts >= 2
+    n_pad = (n_act + 255) // 256 * 256
+    # (few rows: one launch over the whole vocabulary)
+    parts, _, wide = dh_form(n_pad, dh_acc_rows(T, d, V, chunks=2), d, (V + 255) // 256 * 4)
+    print(f"[fullsize] geometric rejection keeps {n_act} rows (padded {n_pad}): dH contraction in {parts} parts, tiles of {320 if wide else 256} columns", flush=True)
+    assert dh_slabs(ws) == parts >= 2
     # ... and the recompute of the whole vocabulary runs in the first chunk's launch
     from tests._cases import block_rows, recompute_covers_vocabulary
+    del ws
     assert vc < V and recompute_covers_vocabulary(T, V, n_pad, vc, block_rows(T, d, V))
     # per-row outputs against the oracle on sampled active rows; inactive rows are zero
     act = np.nonzero(active)[0]

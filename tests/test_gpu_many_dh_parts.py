@@ -6,20 +6,25 @@ import torch
 
 from paper_2602_05885_amd import binding as B
 from paper_2602_05885_amd import synth
-from tests._cases import block_rel_fro, np64
+from tests._cases import block_rel_fro, dh_acc_rows, dh_form, dh_slabs, np64
 
 pytestmark = pytest.mark.gpu
 
 
-# T, active rows, d, V, dtype, vocab tiles of a chunk.  Parts: 64 of 4 stages; 48 in wide tiles; 9, all that the room takes and all that the stages do; 10 of
-# two row tiles, and as many of the 513 rows' three; 11 and 16 of three products; the whole vocabulary in a first chunk
-@pytest.mark.parametrize("T,active,d,V,dtype,chunk", [
-    (100, 100, 64, 16384, "bf16", None), (1, 1, 1088, 65536, "bf16", None), (200, 199, 1024, 2100, "bf16", None), (512, 500, 1088, 2600, "bf16", None),
-    (513, 513, 1088, 2600, "bf16", None), (100, 90, 192, 2900, "f32", None), (300, 257, 320, 9000, "f32", None), (2000, 150, 320, 9000, "bf16", 18),
-    (2000, 0, 320, 9000, "bf16", None)])
+# T, active rows, d, V, dtype, vocab tiles of a chunk; parts, products and whether the tiles are wide.  64 parts of 4 stages; all that the room takes; all
+# that the stages do; of two row tiles and three; three products; few active rows of several vocab chunks, their columns in one launch; wide tiles: one
+# a row tile, a last one without its fifth MFMA rows, whole ones
+@pytest.mark.parametrize("T,active,d,V,dtype,chunk,form", [
+    (100, 100, 64, 16384, "bf16", None, (64, 1, False)), (1, 1, 1088, 65536, "bf16", None, (45, 1, False)), (200, 199, 1024, 2100, "bf16", None, (9, 1, False)),
+    (512, 500, 1088, 2600, "bf16", None, (9, 1, False)), (513, 513, 1088, 2600, "bf16", None, (9, 1, False)), (100, 90, 192, 2900, "f32", None, (8, 3, False)),
+    (300, 257, 320, 9000, "f32", None, (12, 3, False)), (2000, 150, 320, 9000, "bf16", 18, (36, 1, False)), (2000, 0, 320, 9000, "bf16", None, (1, 1, False)),
+    (500, 490, 320, 32000, "bf16", None, (63, 1, True)), (1250, 1250, 576, 24000, "bf16", None, (24, 1, True)), (1000, 999, 1600, 24000, "bf16", None, (12, 1, True))])
 @pytest.mark.parametrize("acc", [0, 1])
-def test_many_parts(T, active, d, V, dtype, chunk, acc, monkeypatch):
+def test_many_parts(T, active, d, V, dtype, chunk, form, acc, monkeypatch):
     dev = torch.device("cuda:0")
+    tiles_v, f32 = -(-V // 256), dtype == "f32"
+    if active:
+        assert dh_form(-(-active // 256) * 256, dh_acc_rows(T, d, V, f32, 2 if chunk else 1), d, 4 * tiles_v, f32) == form
     if chunk:
         monkeypatch.setenv("PG_HEAD_DS_BUDGET_BYTES", str((T + 255) // 256 * 256 * 2 * 256 * chunk))
     H, W, y = synth.make_head(T, d, V, dtype, T, dev)
@@ -31,6 +36,7 @@ def test_many_parts(T, active, d, V, dtype, chunk, acc, monkeypatch):
         prm = B.Params(dtype=int(dtype == "f32"), accumulate_dW=acc, w_transposed=cache)
         ws = torch.full((B.pg_workspace_bytes(T, d, V, 0, prm, B.CALL_LOSS_FWD_BWD),), 0xFF, dtype=torch.uint8, device=dev)
         outs.append(B.pg_sft_fwd_bwd(H, W, y, mask, prm, ws, dW=start.clone() if acc else torch.full_like(start, float("nan"))))
+        assert dh_slabs(ws) == form[0] * form[1]
     out = outs[0]
     for q in out:
         assert torch.equal(out[q], outs[1][q]), q

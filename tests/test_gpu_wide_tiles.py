@@ -5,40 +5,9 @@ import torch
 
 from paper_2602_05885_amd import binding as B
 from paper_2602_05885_amd import synth
-from tests._cases import block_rel_fro, np64
+from tests._cases import block_rel_fro, dh_acc_rows, dh_form, np64, wide_pays
 
 pytestmark = pytest.mark.gpu
-
-
-def _cost(tiles, stages, wide):
-    return (-(-tiles // 256) * 256 + tiles) * (stages + 24) * (5 * 965 if wide else 4 * 1000)
-
-
-def _pad_ld(n):
-    return n + 64 if n // 64 % 2 == 0 else n
-
-
-def _split(n_pad, acc_rows, tiles_n, stages):
-    best = None
-    for ks in range(1, 9):
-        if ks > 1 and (ks * n_pad > acc_rows or ks * 8 > stages):
-            break
-        c = -(-n_pad // 256 * tiles_n * ks // 256) * (-(-stages // ks) + 24)
-        if best is None or c < best[0]:
-            best = (c, ks)
-    ks, tiles = best[1], n_pad // 256 * tiles_n
-    cost = lambda p: -(-tiles * p // 256) * 256 * (-(-stages // p) + 24) + tiles * p * 16
-    least, p = cost(ks), min(256 // tiles, stages // 4, acc_rows // n_pad, 64)
-    while p > ks:                                          # more than eight parts of few tiles
-        if cost(p) < least:
-            ks, least = p, cost(p)
-        p -= (p + 3) // 4
-    return ks
-
-
-def _wide(tiles_m, d, stages, ks4=1, ks5=1):
-    """The library's rule, restated."""
-    return _cost(tiles_m * ks5 * -(-d // 320), -(-stages // ks5), True) < _cost(tiles_m * ks4 * -(-d // 256), -(-stages // ks4), False)
 
 
 # T, d, V, which of dW / dH are wide.  d = 320: one tile; 576: the second has its first four MFMA rows per wavefront and not the fifth;
@@ -52,13 +21,10 @@ CASES = [(70, 320, 17000, "dW"), (300, 576, 23552, "dW"), (130, 832, 37000, "dW"
 def test_wide_tiles(T, d, V, wide, dw16, acc):
     dev = torch.device("cuda:0")
     tiles_v, t_pad = -(-V // 256), -(-T // 256) * 256
-    acc_rows = max(t_pad, min(8 * t_pad, 32768))
-    if acc_rows < 32768:                                   # the accumulator takes dS^T's room as well
-        acc_rows = min(acc_rows + tiles_v * 256 * _pad_ld(t_pad) // (2 * d), 64 * t_pad, 32768)
-    ks = [_split(t_pad, acc_rows, -(-d // n), 4 * tiles_v) for n in (256, 320)]
     whole_dW = 2 * tiles_v * -(-d // 256) > 256            # (a smaller head's dW is split into slabs)
-    assert (whole_dW and _wide(tiles_v, d, -(-T // 64))) == ("dW" in wide)
-    assert _wide(t_pad // 256, d, 4 * tiles_v, *ks) == ("dH" in wide), ks
+    whole = (1, -(-T // 64))
+    assert (whole_dW and wide_pays(tiles_v, d, whole, whole)) == ("dW" in wide)
+    assert dh_form(t_pad, dh_acc_rows(T, d, V), d, 4 * tiles_v)[2] == ("dH" in wide)
     H, W, y = synth.make_head(T, d, V, "bf16", T, dev)
     mask = torch.ones(T, dtype=torch.uint8, device=dev)
     mask[T // 2] = 0                                       # the compacted rows are not the rows

@@ -3,8 +3,8 @@
 // For every tile count swept and both orders: the entries i < share(y) of the 8 XCDs, decoded with the
 // order's map, hand out every tile (tm, tn) exactly once; entries at and beyond share(y) map to no tile;
 // 32 consecutive entries of one XCD form a block of at most 4 x 8 neighbouring tiles (what the L2 sharing
-// relies on); tiles of 320 rows stay within the range of their loads; dh_split and dh_slabs keep their parts inside the accumulator; dw_split's parts are no shorter than
-// its least; token blocks cut the live tiles without a gap or an overlap; and the kept tiles fit their region.
+// relies on); tiles of 320 rows stay within the range of their loads; the parts of a dH
+// launch (dh_form) stay inside the accumulator and are the least of its model; dw_split's parts are no shorter than its least; token blocks cut the live tiles without a gap or an overlap; and the kept tiles fit their region.
 #include <cstdio>
 #include <vector>
 #include "../paper_2602_05885_amd/csrc/gemm_core.h"
@@ -50,35 +50,87 @@ static void sweep(int tiles_m, int tiles_n, int interleaved) {
     }
 }
 
-int main() {
+// The parts of dh_parts, tried one after the other.
+static int least_parts_of(long long tiles, int n_pad, int acc_rows, int stages) {
+  int few = 1;             // up to eight: the least modelled rounds, the fewest parts among equals
+  long long least = 0;
+  for (int q = 1; q <= 8 && (q == 1 || ((long long)q * n_pad <= acc_rows && q * 8 <= stages)); ++q) {
+    const long long cost = (tiles * q + 255) / 256 * ((stages + q - 1) / q + 24);
+    if (q == 1 || cost < least) { few = q; least = cost; }
+  }
+  int best = few;          // of few tiles: the least rounds and slabs
+  for (int q = few; q <= 64; ++q) {
+    if (q > few && (q * tiles > 256 || (long long)q * n_pad > acc_rows || q * 4 > stages)) break;
+    const long long cost = (tiles * q + 255) / 256 * 256 * ((stages + q - 1) / q + 24) + tiles * q * 16;
+    if (q == few || cost < least) { best = q; least = cost; }
+  }
+  return best;
+}
+
+// Every form of a dH launch: the slabs fit the accumulator, the parts are what the rule says and long enough, fp32 products side by side fit one round, the
+// parts' stages follow on each other, and every tile of every slab is handed out once.
+static void sweep_dh_forms() {
+  int most = 0, wide = 0, wide_many = 0, three = 0;
+  for (int n_pad : {256, 512, 768, 1024, 1536, 2048, 3072, 5120, 8192, 12288, 16640, 32768, 65536})
+    for (int acc_rows : {n_pad, 2 * n_pad, 3 * n_pad + 100, 9 * n_pad, 32768, 60 * 256 + 77})
+      for (int n : {64, 256, 320, 576, 1024, 1088, 1600, 2560, 4096, 5120, 8192})
+        for (int stages : {1, 4, 8, 31, 44, 63, 104, 356, 1023, 2376})
+          for (int f32 = 0; f32 < 2; ++f32)
+            for (int wide_ok = 0; wide_ok < 2; ++wide_ok) {
+              if (acc_rows < n_pad) continue;
+              const DhForm f = dh_form(n_pad, acc_rows, n, stages, f32, wide_ok);
+              const int slabs = f.ks * f.products, tiles_m = n_pad / 256, tiles_n = store_tiles_n(n, f.wide);
+              const long long tiles = (long long)tiles_m * tiles_n;
+#define AT "dh_form(%d, %d, %d, %d, %d, %d) = %d parts, %d products, wide %d: "
+#define FORM n_pad, acc_rows, n, stages, f32, wide_ok, f.ks, f.products, f.wide
+              CHECK((long long)slabs * n_pad <= acc_rows, AT "beyond the accumulator", FORM);
+              CHECK(f.ks >= 1 && f.ks <= DH_PARTS_MAX && f.ks <= imax(SPLIT_MAX, stages / DH_MIN_STAGES) && (f.ks == 1 || f.ks * DH_MIN_STAGES <= stages), AT "parts too short", FORM);
+              CHECK(f.ks <= SPLIT_MAX || tiles * slabs <= 256, AT "more than one round", FORM);
+              CHECK(f.products == 1 || (f.products == 3 && f32 && tiles * slabs <= 256), AT "products", FORM);
+              CHECK(!f.wide || (wide_ok && !f32), AT "wide", FORM);
+              CHECK(f.ks == (f.products == 3 ? least_parts_of(3 * tiles, n_pad, acc_rows / 3, stages) : least_parts_of(tiles, n_pad, acc_rows, stages)), AT "not the least", FORM);
+              int at = 0;        // the parts of gemm_store_tile
+              for (int p = 0; p < f.ks; ++p) {
+                const int s0 = (int)((unsigned)p * (unsigned)stages / (unsigned)f.ks), s1 = (int)((unsigned)(p + 1) * (unsigned)stages / (unsigned)f.ks);
+                CHECK(s0 == at && s1 >= s0, AT "part %d is stages %d .. %d", FORM, p, s0, s1);
+                at = s1;
+              }
+              CHECK(at == stages, AT "the parts end at stage %d", FORM, at);
+              most = imax(most, f.ks); wide += f.wide; wide_many += f.wide && f.ks > SPLIT_MAX; three += f.products == 3;
+              if (slabs == 1 || (n_pad + n + stages + f32) % 3) continue;       // (the orders of one slab: sweep())
+              TileQueue Q{};
+              Q.total = (int)tiles * slabs; Q.interleaved = 1;
+              std::vector<int> seen((size_t)Q.total, 0);
+              for (int y = 0; y < 8; ++y)
+                for (int i = 0; i < Q.share(y); ++i) {
+                  int slab = -1, tm = -1, tn = -1;
+                  if (map_tile_interleaved(TileQueue::encode(y, i), tiles_m, tiles_n, slabs, slab, tm, tn) && slab >= 0 && slab < slabs && tm >= 0 && tm < tiles_m && tn >= 0 && tn < tiles_n)
+                    ++seen[((size_t)slab * tiles_m + tm) * tiles_n + tn];
+                }
+              for (int t = 0; t < Q.total; ++t) CHECK(seen[t] == 1, AT "tile %d handed out %d times", FORM, t, seen[t]);
+            }
+  CHECK(most == DH_PARTS_MAX && wide > 0 && wide_many > 0 && three > 0, "the sweep reaches %d parts, %d wide forms (%d of many parts), %d of three products", most, wide, wide_many, three);
+}
+
+// The forms of a list (n_pad acc_rows n stages f32 wide_ok a line), for the tests' restatement of the rule.
+static int print_forms() {
+  int n_pad, acc_rows, n, stages, f32, wide_ok;
+  while (scanf("%d %d %d %d %d %d", &n_pad, &acc_rows, &n, &stages, &f32, &wide_ok) == 6) {
+    const DhForm f = dh_form(n_pad, acc_rows, n, stages, f32, wide_ok);
+    printf("%d %d %d\n", f.ks, f.products, f.wide);
+  }
+  return 0;
+}
+
+int main(int argc, char**) {
+  if (argc > 1) return print_forms();
   for (int tm = 1; tm <= 70; ++tm)
     for (int tn = 1; tn <= 45; ++tn)
       for (int order = 0; order < 2; ++order) sweep(tm, tn, order);
   for (int order = 0; order < 2; ++order) {     // the shapes the 14B head produces
     sweep(594, 128, order); sweep(89, 20, order); sweep(128, 20, order); sweep(60, 20, order); sweep(594, 512, order);
   }
-  for (int n_pad = 256; n_pad <= 65536; n_pad += 256)
-    for (int t_cap = n_pad; t_cap <= 65536; t_cap += 4096)
-      for (int tiles_n : {1, 2, 16, 20})
-        for (int stages : {4, 8, 63, 356, 2374}) {
-          const int ks = dh_split(n_pad, t_cap, tiles_n, stages);
-          CHECK(ks >= 1 && ks <= 8 && (long long)ks * n_pad <= (long long)imax(t_cap, n_pad) && (ks == 1 || stages / ks >= 8),
-                "dh_split(%d, %d, %d, %d) = %d", n_pad, t_cap, tiles_n, stages, ks);
-          int least = 1;           // the least modelled rounds, the fewest parts among equals
-          long long least_cost = 0;
-          for (int q = 1; q <= 8 && (q == 1 || ((long long)q * n_pad <= t_cap && q * 8 <= stages)); ++q) {
-            const long long cost = ((long long)(n_pad / 256) * tiles_n * q + 255) / 256 * ((stages + q - 1) / q + 24);
-            if (q == 1 || cost < least_cost) { least = q; least_cost = cost; }
-          }
-          CHECK(ks == least, "dh_split(%d, %d, %d, %d) = %d, not %d", n_pad, t_cap, tiles_n, stages, ks, least);
-          for (int f32 = 0; f32 < 2; ++f32) {
-            int parts = 0;
-            const int slabs = dh_slabs(n_pad, t_cap, tiles_n, stages, f32, parts), products = slabs / parts;
-            CHECK(parts == ks && slabs == parts * products && (products == 1 || (products == 3 && f32)) && (long long)slabs * n_pad <= t_cap,
-                  "dh_slabs(%d, %d, %d, %d, %d) = %d of %d parts", n_pad, t_cap, tiles_n, stages, f32, slabs, parts);
-            CHECK(products == 1 || (n_pad / 256) * tiles_n * slabs <= 256, "dh_slabs(%d, %d, %d, %d, 1): %d slabs are more than one round", n_pad, t_cap, tiles_n, stages, slabs);
-          }
-        }
+  sweep_dh_forms();
   // Wide tiles only where 320 rows of the operand lie below 4 GiB; what the calls accept has 256 of them there.
   int wide_near = 0, wide_far = 0;
   for (long long V : {25600ll, 2000000ll, 6710000ll, 6711000ll, 7000000ll, 8388000ll}) {
