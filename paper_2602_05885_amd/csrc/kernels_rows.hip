@@ -654,9 +654,11 @@ void launch_dw_fold(const DwFoldArgs& a, hipStream_t s) {
 
 // ------------------------------------------------------------------ dH scatter
 // dH[t,:] = accumulated row of its compacted position, or zeros for rows that are not active.
-// A thread requests SCATTER_AHEAD slabs at once (one after the other, 16 slabs of 200 rows, d = 5120, took 24.5 us; with this and the split below 12.4).
-// (FEW: in calls of few rows only; in the others the wider kernel costs the launch more than the slabs, which are few there: 40 000 rows, d = 64, 12.5 / 18.2 us.)
-constexpr int SCATTER_AHEAD = 7, SCATTER_FEW_ROWS = 2048;
+// A thread requests AHEAD slabs at once (one after the other, 16 slabs of 200 rows, d = 5120, took 24.5 us; with seven and the split below 12.4).  FEW: calls of few
+// rows.  The slabs go by the active rows, so a call of many rows has as many of them when few are active, but seven at once cost such a launch more for the rows
+// that have none.  One / four / seven: 177 of 12352 rows, 2304 x 15669, 27.6 / 18.4 / 23.2 us; 100 of 4000, 1024 x 100000, 22.7 / 11.6 / 12.2; 200 of
+// 16000, 1024 x 65536, 32.5 / 23.1 / 23.4; all of 40 000, d = 64, 14.8 / 14.7 / 17.4; all of 20 000, d = 512, 15.0 / 15.5 / 17.1.
+constexpr int SCATTER_FEW_ROWS = 2048;
 template <bool FEW>
 __global__ __launch_bounds__(256) void scatter_dh_kernel(ScatterArgs a, FinishArgs fin, DwFoldArgs fold, int fold_groups) {
   const int t = (int)blockIdx.x - 1 - fold_groups;
@@ -672,13 +674,14 @@ __global__ __launch_bounds__(256) void scatter_dh_kernel(ScatterArgs a, FinishAr
     f32x4 v = {0.f, 0.f, 0.f, 0.f};
     if (p >= 0) {
       v = *reinterpret_cast<const f32x4*>(src + j);
+      constexpr int AHEAD = FEW ? 7 : 4;
       int q = 1;
-      for (; FEW && q + SCATTER_AHEAD <= ks; q += SCATTER_AHEAD) {               // split-K slabs, added in a fixed order
-        f32x4 w[SCATTER_AHEAD];
+      for (; q + AHEAD <= ks; q += AHEAD) {               // split-K slabs, added in a fixed order
+        f32x4 w[AHEAD];
 #pragma unroll
-        for (int r = 0; r < SCATTER_AHEAD; ++r) w[r] = *reinterpret_cast<const f32x4*>(src + (q + r) * slab + j);
+        for (int r = 0; r < AHEAD; ++r) w[r] = *reinterpret_cast<const f32x4*>(src + (q + r) * slab + j);
 #pragma unroll
-        for (int r = 0; r < SCATTER_AHEAD; ++r) v += w[r];
+        for (int r = 0; r < AHEAD; ++r) v += w[r];
       }
       for (; q < ks; ++q) v += *reinterpret_cast<const f32x4*>(src + q * slab + j);
     }

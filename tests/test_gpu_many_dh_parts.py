@@ -13,12 +13,13 @@ pytestmark = pytest.mark.gpu
 
 # T, active rows, d, V, dtype, vocab tiles of a chunk; parts, products and whether the tiles are wide.  64 parts of 4 stages; all that the room takes; all
 # that the stages do; of two row tiles and three; three products; few active rows of several vocab chunks, their columns in one launch; wide tiles: one
-# a row tile, a last one without its fifth MFMA rows, whole ones
+# a row tile, a last one without its fifth MFMA rows, whole ones; few active of more rows than the scatter's form for few
 @pytest.mark.parametrize("T,active,d,V,dtype,chunk,form", [
     (100, 100, 64, 16384, "bf16", None, (64, 1, False)), (1, 1, 1088, 65536, "bf16", None, (45, 1, False)), (200, 199, 1024, 2100, "bf16", None, (9, 1, False)),
     (512, 500, 1088, 2600, "bf16", None, (9, 1, False)), (513, 513, 1088, 2600, "bf16", None, (9, 1, False)), (100, 90, 192, 2900, "f32", None, (8, 3, False)),
     (300, 257, 320, 9000, "f32", None, (12, 3, False)), (2000, 150, 320, 9000, "bf16", 18, (36, 1, False)), (2000, 0, 320, 9000, "bf16", None, (1, 1, False)),
-    (500, 490, 320, 32000, "bf16", None, (63, 1, True)), (1250, 1250, 576, 24000, "bf16", None, (24, 1, True)), (1000, 999, 1600, 24000, "bf16", None, (12, 1, True))])
+    (500, 490, 320, 32000, "bf16", None, (63, 1, True)), (1250, 1250, 576, 24000, "bf16", None, (24, 1, True)), (1000, 999, 1600, 24000, "bf16", None, (12, 1, True)),
+    (2500, 90, 320, 16000, "bf16", None, (42, 1, False)), (4000, 64, 1088, 20000, "bf16", None, (32, 1, False)), (2600, 100, 192, 9000, "f32", None, (29, 3, False))])
 @pytest.mark.parametrize("acc", [0, 1])
 def test_many_parts(T, active, d, V, dtype, chunk, form, acc, monkeypatch):
     dev = torch.device("cuda:0")
@@ -50,3 +51,27 @@ def test_many_parts(T, active, d, V, dtype, chunk, form, acc, monkeypatch):
     if active:
         assert block_rel_fro(np64(out["dH"][on]), np64(dS @ Wd)) <= bound
     assert block_rel_fro(np64(out["dW"]), np64(dS.T @ Hd + (start.double() if acc else 0))) <= bound
+
+
+@pytest.mark.parametrize("T,active", [(300, 290), (2200, 130)])
+def test_many_parts_of_a_shard(T, active):
+    """The backward from the rows' states, fp32 dH out, against the same call on the whole head."""
+    dev = torch.device("cuda:0")
+    d, V = 320, 16000
+    H, W, y = synth.make_head(T, d, V, "bf16", T, dev)
+    mask = torch.zeros(T, dtype=torch.uint8, device=dev)
+    mask[torch.randperm(T, generator=torch.Generator().manual_seed(3))[:active].to(dev)] = 1
+    cu, adv = torch.tensor([0, T], dtype=torch.int32, device=dev), torch.tensor([-0.7], dtype=torch.float64, device=dev)
+    prm = B.Params()
+    ws = torch.full((B.pg_workspace_bytes(T, d, V, 1, prm, B.CALL_LOSS_FWD_BWD),), 0xFF, dtype=torch.uint8, device=dev)
+    states = B.pg_head_shard_fwd(H, W, y, mask, 0, prm, ws)
+    out = B.pg_loss_shard_bwd(H, W, y, mask, cu, adv, None, None, None, states, 0, prm, ws)
+    assert dh_slabs(ws) == dh_form(-(-active // 256) * 256, dh_acc_rows(T, d, V), d, 4 * -(-V // 256))[0] > 8
+    on = mask.bool()
+    Hd, Wd = H[on].double(), W.double()
+    dS = torch.softmax(Hd @ Wd.T, 1)
+    dS[torch.arange(active, device=dev), y[on].long()] -= 1
+    dS *= -0.7 / active                            # loss = -A log p / n: dz = A (p - onehot) / n
+    assert not out["dH"][~on].any()
+    assert block_rel_fro(np64(out["dH"][on]), np64(dS @ Wd)) <= 1e-2           # bf16 dS: 2^-9 per element
+    assert block_rel_fro(np64(out["dW"]), np64(dS.T @ Hd)) <= 1e-2
