@@ -1374,6 +1374,11 @@ __global__ __launch_bounds__(256) void scatter_dx_norm_kernel(ScatterArgs a, Nor
     for (int e = 0; e < 8; ++e) dg[q][e] = 0.f;
     if (c < a.d) raw_load(n.gamma, c, gam_raw[q]);
   }
+  // Slabs requested at once, before the next row's inputs are.  More, or two in a bf16 head of two column groups, take registers that cost a compute unit
+  // wavefronts (4000 rows of d = 4096, one slab, two at once 35.2 -> 38.1 us).
+  // One / two at once: 189 of 3192 rows, 7360 x 39365, 48.3 / 38.7 us; 200 rows, 5120 x 151936, 21.1 / 17.3; 1738 of 8855, 320 x 11839, 41.5 / 30.6; 681 of
+  // 7834, 256 x 3145, 25.4 / 18.4; one slab, 20 000 rows of d = 1024 45.4 / 45.2.
+  constexpr int AHEAD = !F32 && NC == 2 ? 1 : 2;
   const float inv_d = 1.f / (float)a.d;
   // Row r of the workgroup is T-row blockIdx.x + r NORM_STRIPS; the inputs of the next one (its compacted
   // position, rstd, the row of X and the first slab of the accumulator) are requested before the current
@@ -1398,6 +1403,27 @@ __global__ __launch_bounds__(256) void scatter_dx_norm_kernel(ScatterArgs a, Nor
   long long row = blockIdx.x;
   if (row < T) fetch(row, xc, gc, pc, rc);
   for (; row < T; row += NORM_STRIPS) {
+    if (ks > 1 && pc >= 0) {                        // split-K slabs, added in a fixed order
+#pragma unroll
+      for (int q = 0; q < NC; ++q) {
+        const int c = tid * 8 + q * 2048;
+        if (c >= a.d) continue;
+        const float* src = a.acc + (size_t)pc * a.d + c;
+        int k = 1;
+        for (; k + AHEAD <= ks; k += AHEAD) {
+          Raw8<true> w[AHEAD];
+#pragma unroll
+          for (int r = 0; r < AHEAD; ++r) raw_load(src, (long long)((k + r) * slab), w[r]);
+#pragma unroll
+          for (int r = 0; r < AHEAD; ++r) { gc[q].a += w[r].a; gc[q].b += w[r].b; }
+        }
+        for (; k < ks; ++k) {
+          Raw8<true> w;
+          raw_load(src, (long long)(k * slab), w);
+          gc[q].a += w.a; gc[q].b += w.b;
+        }
+      }
+    }
     int pn = -1;
     float rn = 0.f;
     if (row + NORM_STRIPS < T) fetch(row + NORM_STRIPS, xn, gn, pn, rn);
@@ -1419,16 +1445,6 @@ __global__ __launch_bounds__(256) void scatter_dx_norm_kernel(ScatterArgs a, Nor
           raw_unpack(xc[q], x);
           raw_unpack(gc[q], g);
           raw_unpack(gam_raw[q], gam);
-          if (ks > 1) {
-            for (int s2 = 1; s2 < ks; ++s2) {       // split-K slabs, added in a fixed order
-              float w[8];
-              load8<true>(a.acc, (long long)(s2 * slab) + (long long)pc * a.d + c, w);
-#pragma unroll
-              for (int e = 0; e < 8; ++e) g[e] += w[e];
-            }
-            gc[q].a = f32x4{g[0], g[1], g[2], g[3]};
-            gc[q].b = f32x4{g[4], g[5], g[6], g[7]};
-          }
 #pragma unroll
           for (int e = 0; e < 8; ++e) dot = fmaf(gam[e] * g[e], x[e] * rstd, dot);
         }

@@ -75,3 +75,34 @@ def test_many_parts_of_a_shard(T, active):
     assert not out["dH"][~on].any()
     assert block_rel_fro(np64(out["dH"][on]), np64(dS @ Wd)) <= 1e-2           # bf16 dS: 2^-9 per element
     assert block_rel_fro(np64(out["dW"]), np64(dS.T @ Hd)) <= 1e-2
+
+
+# one to four column groups a thread; rows that fit the strips and rows that do not; an odd number of slabs and an even one
+@pytest.mark.parametrize("T,active,d,V,dtype,slabs", [
+    (90, 90, 256, 12000, "bf16", 32), (2300, 300, 256, 12000, "bf16", 38), (2300, 200, 2112, 10000, "bf16", 16), (1100, 200, 4160, 20000, "bf16", 14),
+    (1100, 40, 6208, 20000, "bf16", 10), (1100, 300, 192, 9000, "f32", 54), (1100, 100, 2112, 9000, "f32", 27), (1100, 100, 4160, 6000, "f32", 15), (1100, 100, 6208, 6000, "f32", 9)])
+def test_many_parts_behind_a_normalisation(T, active, d, V, dtype, slabs):
+    dev = torch.device("cuda:0")
+    X, W, y = synth.make_head(T, d, V, dtype, T, dev)
+    gamma = 1 + 0.2 * torch.randn(d, generator=torch.Generator(device=dev).manual_seed(7), device=dev)
+    gamma = gamma.to(X.dtype)
+    mask = torch.zeros(T, dtype=torch.uint8, device=dev)
+    mask[torch.randperm(T, generator=torch.Generator().manual_seed(3))[:active].to(dev)] = 1
+    cu, adv = torch.tensor([0, T], dtype=torch.int32, device=dev), torch.tensor([-0.7], dtype=torch.float64, device=dev)
+    prm = B.Params(dtype=int(dtype == "f32"))
+    ws = torch.full((B.pg_workspace_bytes(T, d, V, 1, prm, B.CALL_LOSS_FWD_BWD_NORMED),), 0xFF, dtype=torch.uint8, device=dev)
+    out = B.pg_loss_fwd_bwd_normed(X, gamma, 1e-5, W, y, mask, cu, adv, None, None, None, prm, ws)
+    assert dh_slabs(ws) == slabs
+    on = mask.bool()
+    Xd, gd, Wd = X[on].double(), gamma.double(), W.double()
+    rstd = (Xd.pow(2).mean(1, keepdim=True) + 1e-5).rsqrt()
+    xhat = Xd * rstd
+    H = (xhat * gd).to(X.dtype).double()           # the head sees it in the storage type
+    dS = torch.softmax(H @ Wd.T, 1)
+    dS[torch.arange(active, device=dev), y[on].long()] -= 1
+    dH = (dS * (-0.7 / active)) @ Wd
+    want = rstd * (gd * dH - xhat * (gd * dH * xhat).mean(1, keepdim=True))
+    bound = 5e-5 if dtype == "f32" else 1e-2           # bf16 dS and dX: 2^-9 per element each; fp32 heads carry about 16 mantissa bits
+    assert not out["dX"][~on].any()
+    assert block_rel_fro(np64(out["dX"][on]), np64(want)) <= bound
+    assert block_rel_fro(np64(out["dgamma"][:, None]), np64((dH * xhat).sum(0)[:, None])) <= bound
