@@ -267,7 +267,11 @@ __host__ __device__ inline bool wide_pays(int tiles_m, int n, Parts p256, Parts 
 // 512 rows, 64 x 1000 (8 / 12 slabs) 20.5 / 17.4, 1024 rows, 256 x 4000 50.7 / 36.0, 2000 rows, 512 x 10000 94 / 75.
 // The most parts whose cost is below that of eight / those of least cost, whole calls: 100 rows, 1024 x 65536 188.5 / 185.1 us, normed 203.6 / 199.9;
 // 215 of 12174 rows, 2752 x 13018, normed 265.8 / 252.6; 177 of 12352 rows, 2304 x 15669 173.4 / 167.7; 200 rows, 4096 x 151936 the same.
-constexpr int DH_MIN_STAGES = 4, DH_ROUND_SLABS = 16;
+// The three products of an fp32 head one after the other cost a tile two more starts, DH_PRODUCTS_STAGES; side by side they leave room for fewer parts.
+// Whole calls, side by side wherever they fit / in turn: 4178 of 6011 rows, 704 x 22504 (1 / 5 parts) 1645 / 1524 us; 5747 of 8279, 256 x 13783 (1 / 5) 992 / 918;
+// 2638 rows, 128 x 27007 (3 / 11) 671 / 655; but 1126 rows, 256 x 17739 (8 / 24) 276 / 280, 2134 of 3091, 512 x 8761 (4 / 10) 372 / 378.  Over 300 such
+// calls the choice costs 1.2 % at most where it is wrong.
+constexpr int DH_MIN_STAGES = 4, DH_ROUND_SLABS = 16, DH_PRODUCTS_STAGES = 12;
 __host__ __device__ inline Parts dh_parts(int n_pad, int acc_rows, int tiles_n, int k_stages) {
   const Parts few = dh_split(n_pad, acc_rows, tiles_n, k_stages);
   const long long tiles = (long long)(n_pad / 256) * tiles_n;
@@ -283,11 +287,14 @@ __host__ __device__ inline Parts dh_parts(int n_pad, int acc_rows, int tiles_n, 
 struct DhForm { int ks, products; bool wide; };
 __host__ __device__ inline DhForm dh_form(int n_pad, int acc_rows, int n, int k_stages, int split_f32, bool wide_ok) {
   const int tiles_n = store_tiles_n(n, false);
-  if (split_f32) {        // the products side by side, where they and the parts fit one round
-    const int ks = dh_parts(n_pad, acc_rows / 3, 3 * tiles_n, k_stages).ks;
-    if (dh_products(n_pad, acc_rows, tiles_n, ks, split_f32) == 3) return DhForm{ks, 3, false};
-  }
   const Parts p256 = dh_parts(n_pad, acc_rows, tiles_n, k_stages);
+  if (split_f32) {        // the products side by side, where they and the parts fit one round and that is the shorter
+    const Parts three = dh_parts(n_pad, acc_rows / 3, 3 * tiles_n, k_stages);
+    const long long tiles = (long long)(n_pad / 256) * tiles_n;
+    const long long beside = 256ll * (three.stages + SPLIT_TILE_STAGES) + 3 * tiles * three.ks * DH_ROUND_SLABS;
+    const long long in_turn = (tiles * p256.ks + 255) / 256 * 256 * (3ll * p256.stages + SPLIT_TILE_STAGES + DH_PRODUCTS_STAGES) + tiles * p256.ks * DH_ROUND_SLABS;
+    if (beside < in_turn && dh_products(n_pad, acc_rows, tiles_n, three.ks, split_f32) == 3) return DhForm{three.ks, 3, false};
+  }
   if (split_f32 || !wide_ok) return DhForm{p256.ks, 1, false};
   const Parts p320 = dh_parts(n_pad, acc_rows, store_tiles_n(n, true), k_stages);
   const bool wide = wide_pays(n_pad / BM, n, p256, p320);

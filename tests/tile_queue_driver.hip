@@ -70,7 +70,7 @@ static int least_parts_of(long long tiles, int n_pad, int acc_rows, int stages) 
 // Every form of a dH launch: the slabs fit the accumulator, the parts are what the rule says and long enough, fp32 products side by side fit one round, the
 // parts' stages follow on each other, and every tile of every slab is handed out once.
 static void sweep_dh_forms() {
-  int most = 0, wide = 0, wide_many = 0, three = 0;
+  int most = 0, wide = 0, wide_many = 0, three = 0, in_turn_fit = 0;
   for (int n_pad : {256, 512, 768, 1024, 1536, 2048, 3072, 5120, 8192, 12288, 16640, 32768, 65536})
     for (int acc_rows : {n_pad, 2 * n_pad, 3 * n_pad + 100, 9 * n_pad, 32768, 60 * 256 + 77})
       for (int n : {64, 256, 320, 576, 1024, 1088, 1600, 2560, 4096, 5120, 8192})
@@ -89,6 +89,14 @@ static void sweep_dh_forms() {
               CHECK(f.products == 1 || (f.products == 3 && f32 && tiles * slabs <= 256), AT "products", FORM);
               CHECK(!f.wide || (wide_ok && !f32), AT "wide", FORM);
               CHECK(f.ks == (f.products == 3 ? least_parts_of(3 * tiles, n_pad, acc_rows / 3, stages) : least_parts_of(tiles, n_pad, acc_rows, stages)), AT "not the least", FORM);
+              if (f32) {         // products in turn or side by side: the shorter one
+                const int k1 = least_parts_of(tiles, n_pad, acc_rows, stages), k3 = least_parts_of(3 * tiles, n_pad, acc_rows / 3, stages);
+                const bool fit = 3 * k3 * tiles <= 256 && 3ll * k3 * n_pad <= acc_rows;
+                const long long in_turn = (tiles * k1 + 255) / 256 * 256 * (3ll * ((stages + k1 - 1) / k1) + 36) + tiles * k1 * 16;
+                const long long beside = 256ll * ((stages + k3 - 1) / k3 + 24) + 3 * tiles * k3 * 16;
+                CHECK(f.products == (fit && beside < in_turn ? 3 : 1), AT "%lld in turn, %lld side by side", FORM, in_turn, beside);
+                in_turn_fit += fit && f.products == 1;
+              }
               int at = 0;        // the parts of gemm_store_tile
               for (int p = 0; p < f.ks; ++p) {
                 const int s0 = (int)((unsigned)p * (unsigned)stages / (unsigned)f.ks), s1 = (int)((unsigned)(p + 1) * (unsigned)stages / (unsigned)f.ks);
@@ -109,7 +117,8 @@ static void sweep_dh_forms() {
                 }
               for (int t = 0; t < Q.total; ++t) CHECK(seen[t] == 1, AT "tile %d handed out %d times", FORM, t, seen[t]);
             }
-  CHECK(most == DH_PARTS_MAX && wide > 0 && wide_many > 0 && three > 0, "the sweep reaches %d parts, %d wide forms (%d of many parts), %d of three products", most, wide, wide_many, three);
+  CHECK(most == DH_PARTS_MAX && wide > 0 && wide_many > 0 && three > 0 && in_turn_fit > 0,
+        "the sweep reaches %d parts, %d wide forms (%d of many parts), %d of three products, %d of one where three fit", most, wide, wide_many, three, in_turn_fit);
 }
 
 // The forms of a list (n_pad acc_rows n stages f32 wide_ok a line), for the tests' restatement of the rule.
