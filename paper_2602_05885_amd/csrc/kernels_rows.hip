@@ -661,6 +661,8 @@ void launch_dw_fold(const DwFoldArgs& a, hipStream_t s) {
 // rows.  The slabs go by the active rows, so a call of many rows has as many of them when few are active, but seven at once cost such a launch more for the rows
 // that have none.  One / four / seven: 177 of 12352 rows, 2304 x 15669, 27.6 / 18.4 / 23.2 us; 100 of 4000, 1024 x 100000, 22.7 / 11.6 / 12.2; 200 of
 // 16000, 1024 x 65536, 32.5 / 23.1 / 23.4; all of 40 000, d = 64, 14.8 / 14.7 / 17.4; all of 20 000, d = 512, 15.0 / 15.5 / 17.1.
+// Rows without a slab take a way of their own, to which the wider loop is no burden.  In one way / apart: 780 of 39 013 rows, d = 896, 35.4 / 24.3 us; 760 of
+// 37 930, d = 2240, 39.5 / 31.8; 177 of 12 352, d = 2304, 18.7 / 17.4; all of 40 000, d = 64, 14.7 / 15.4.
 constexpr int SCATTER_FEW_ROWS = 2048;
 template <bool FEW>
 __global__ __launch_bounds__(256) void scatter_dh_kernel(ScatterArgs a, FinishArgs fin, DwFoldArgs fold, int fold_groups) {
@@ -669,25 +671,29 @@ __global__ __launch_bounds__(256) void scatter_dh_kernel(ScatterArgs a, FinishAr
   if (blockIdx.x == 0) return finish_loss(fin);
   if (t < 0) return dw_fold(fold, (int)blockIdx.x - 1, fold_groups);
   const int p = a.pos[t];
-  const float* src = a.acc + (size_t)(p < 0 ? 0 : p) * a.d;
+  const float* src = a.acc + (size_t)p * a.d;         // (not followed where there is none)
   const int n_pad = a.ctl->n_pad;
   const int ks = a.ctl->dh_slabs;
   const size_t slab = (size_t)n_pad * a.d;
-  for (int j = ((FEW ? blockIdx.y * 256 : 0) + threadIdx.x) * 4; j < a.d; j += (FEW ? gridDim.y : 1) * (256 * 4)) {
-    f32x4 v = {0.f, 0.f, 0.f, 0.f};
-    if (p >= 0) {
-      v = *reinterpret_cast<const f32x4*>(src + j);
-      constexpr int AHEAD = FEW ? 7 : 4;
-      int q = 1;
-      for (; q + AHEAD <= ks; q += AHEAD) {               // split-K slabs, added in a fixed order
-        f32x4 w[AHEAD];
-#pragma unroll
-        for (int r = 0; r < AHEAD; ++r) w[r] = *reinterpret_cast<const f32x4*>(src + (q + r) * slab + j);
-#pragma unroll
-        for (int r = 0; r < AHEAD; ++r) v += w[r];
-      }
-      for (; q < ks; ++q) v += *reinterpret_cast<const f32x4*>(src + q * slab + j);
+  if (__builtin_expect(p < 0, 0)) {
+    for (int j = ((FEW ? blockIdx.y * 256 : 0) + threadIdx.x) * 4; j < a.d; j += (FEW ? gridDim.y : 1) * (256 * 4)) {
+      if (a.out_f32) *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(a.dH) + (size_t)t * a.d + j) = f32x4{};
+      else *reinterpret_cast<bf16x4*>(reinterpret_cast<__bf16*>(a.dH) + (size_t)t * a.d + j) = bf16x4{};
     }
+    return;
+  }
+  for (int j = ((FEW ? blockIdx.y * 256 : 0) + threadIdx.x) * 4; j < a.d; j += (FEW ? gridDim.y : 1) * (256 * 4)) {
+    f32x4 v = *reinterpret_cast<const f32x4*>(src + j);
+    constexpr int AHEAD = FEW ? 7 : 4;
+    int q = 1;
+    for (; q + AHEAD <= ks; q += AHEAD) {               // split-K slabs, added in a fixed order
+      f32x4 w[AHEAD];
+#pragma unroll
+      for (int r = 0; r < AHEAD; ++r) w[r] = *reinterpret_cast<const f32x4*>(src + (q + r) * slab + j);
+#pragma unroll
+      for (int r = 0; r < AHEAD; ++r) v += w[r];
+    }
+    for (; q < ks; ++q) v += *reinterpret_cast<const f32x4*>(src + q * slab + j);
     if (a.out_f32) {
       *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(a.dH) + (size_t)t * a.d + j) = v;
     } else {
