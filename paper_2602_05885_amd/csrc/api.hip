@@ -857,6 +857,8 @@ int32_t loss_fwd_bwd(int sft, const void* H, const void* W, const int32_t* y, co
   few.dh_whole = !pl.is_f32 && pl.direct_fits && (uint64_t)pl.V * pl.kd * 2 < FOUR_GIB;
   if (p.w_transposed && !p.w_transposed_valid)       // the caller's cache is filled whole, before anything reads it
     pg::launch_transpose_w(W, pl.is_f32, pl.V, d_i, d_i, 0, pl.tiles_v * 256, (int)wt_cache_ld(pl.V), static_cast<__bf16*>(p.w_transposed), pg::DirectRule{}, st);
+  // (wide tiles with the cache and without: the same sums, see few.dh_whole)
+  comb.dh = pg::DhRule{d_i, pl.acc_rows, kc0 / 64, pl.is_f32, pg::wide_fits(wt_cache_ld(pl.V)), few};
   const int tiles_b = pl.cap_t ? pl.cap_t : pl.tiles_t;
   pg::DwFoldArgs fold{};                            // of a dW that was split in a single chunk
   for (int b = 0; b < pl.nblocks; ++b) {      // token blocks; the backward of a block one vocab chunk at a time
@@ -932,11 +934,11 @@ int32_t loss_fwd_bwd(int sft, const void* H, const void* W, const int32_t* y, co
       h.tiles_m = tiles_b; h.tiles_n = (d_i + 255) / 256;
       h.C = at<float>(ws, pl.dHacc); h.ldc = d_i;
       h.accumulate = c > 0; h.out_bf16 = 0; h.k_from_ctl = 0; h.m_from_ctl = 1; h.split_k = 1; h.ctl = ctl;
-      h.acc_rows = pl.acc_rows; h.split_stages = kc0 / 64;
+      h.acc_rows = pl.acc_rows;
       h.queue = queues + 2 * pg::QUEUE_SET_WORDS;
       h.rc = few; h.rc_role = 2; h.v0 = v0;
       h.rule = rule; h.blk = blk;
-      h.wide_ok = pg::wide_fits(wt_cache_ld(pl.V));     // (with the cache and without: the same sums, see few.dh_whole)
+      h.wide_ok = comb.dh.wide_ok;
       {
         ProfScope ps(PG_KERNEL_DH, st);
         if (transposed) pg::launch_gemm_store(h, st);

@@ -65,13 +65,14 @@ constexpr int WIDE_ROWS = 64 * GW, WIDE_LDS_BYTES = 2 * (WIDE_ROWS * BK * 2 + SL
 static_assert(GEMM_LDS_BYTES >= 2 * STAGE_BYTES, "LDS budget");
 static_assert(GM == 4 && GN == 8, "the main loop's schedule is written for 4 x 8 MFMA tiles per wavefront");
 
-// ---- control block written by the row-compaction kernel, dh_slabs by the dH launches (device memory) ----
+// ---- control block written by the row-compaction kernel, the dH form by the combine (device memory) ----
 struct Ctl {
   int n_active;   // number of compacted rows
   int n_pad;      // n_active rounded up to a multiple of 256
   float norm;     // loss normaliser
   unsigned step[8]; // of the workgroups of every XCD in a forward (InStep), zero at launch
-  int dh_slabs;   // parts of the dH accumulator (DhForm): the dH launches settle it, the scatter adds that many
+  int dh_slabs;   // slabs of the dH accumulator: the scatter adds that many
+  int dh_ks, dh_products, dh_wide;      // of the dH launches (DhForm)
 };
 
 // ---- workgroup -> tile mapping -------------------------------------------------
@@ -171,14 +172,14 @@ __host__ __device__ inline bool map_tile_interleaved(int bid, int tiles_m, int t
 //   3072 rows, d = 4096 (192 tiles)   one part 3167 us, 4 parts 2479 us
 // (Up to 8 parts; dh_parts has more for few tiles.)
 // The values that it goes by (k_stages: those of the first chunk, for all chunks) are the same for every launch of a call, so the decomposition, and with it the
-// summation order, is fixed for given inputs.  The dH launches leave the number of slabs in Ctl, where the scatter finds it.
+// summation order, is fixed for given inputs.  A wavefront of the combine settles it, beside the rows' epilogue, and leaves it in Ctl for the dH launches and the
+// scatter.
 constexpr int SPLIT_MAX = 8, SPLIT_MIN_STAGES = 8, SPLIT_TILE_STAGES = 24, DH_PARTS_MAX = 64;
 struct Parts { int ks, stages; };       // parts, and stages of the longest
 
 // The numbers of parts, 1 .. MAX, are tried side by side, one in each lane (whole wavefronts only; on the host one after the other): the least cost(parts,
-// stages), the fewest among equals.  Every workgroup of a dH launch comes through here before its first load, and a division by a variable is a sequence of
-// 25 instructions.  One number after the other / side by side, dH launch: 8 rows, d = 3712, V = 2817 19.1 / 15.8 us; 979 rows, 3072 x 3084 30.6 / 29.4;
-// 1126 rows, 1280 x 3596 26.0 / 24.6.
+// stages), the fewest among equals.  (A division by a variable is a sequence of 25 instructions: one number after the other the search took longer than the
+// combine that it is to run beside.)
 constexpr unsigned long long NO_PARTS = ~0ull >> 6;
 #ifdef __HIP_DEVICE_COMPILE__
 template <int CTRL> __device__ __forceinline__ unsigned long long least_of_pair(unsigned long long x) {

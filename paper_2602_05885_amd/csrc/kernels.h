@@ -185,17 +185,16 @@ struct StoreArgs {
   int k_from_ctl;       // contraction length = active tokens, up to whole stages (dw_stages)
   int m_from_ctl;       // row extent = active tokens: rows of C from there on, up to the padded count, are left as they are
   TokenBlocks blk;      // of the token extent
-  int split_k;          // with m_from_ctl: cut K into the parts of dh_form, part p writes rows p n_pad + m
+  int split_k;          // with m_from_ctl: cut K into the parts that Ctl names (DhForm), part p writes rows p n_pad + m
   int acc_rows;         // rows of C
-  int wide_ok;          // tiles of 320 n can address their operand (wide_fits)
+  int wide_ok;          // tiles of 320 n can address their operand (wide_fits); of a dH see DhRule
   int dw_cap;           // > 0, with k_from_ctl: cut K into dw_split(K stages, dw_cap) parts (times three products for fp32
                         // heads); part p writes rows p slab_rows + m of `slabs`, fp32 scratch that dw_fold adds up.
                         // A single part is written to C like an unsplit one (19 of 2698 rows, d = 2304, V = 2322, bf16:
                         // through a slab and the fold 5.9 us more)
   int slab_rows;
   float* slabs;
-  int split_stages;     // stages of the first chunk's contraction
-  Ctl* ctl;             // (a dH launch leaves its number of slabs there)
+  const Ctl* ctl;
   unsigned* queue;      // [8] tile counters of this launch's queue, zero at launch
   Rechunk rc;           // see there; rc_role 0: not a chunked launch, 1: dW of a chunk, 2: dH of a chunk
   int rc_role;
@@ -289,6 +288,15 @@ void launch_gather(const GatherArgs& a, hipStream_t s);
 // HcT[j, i] = Hc[i, j] over d columns of row stride ldh, for the live rows
 void launch_transpose_hc(const __bf16* Hc, int ldh, __bf16* HcT, const GatherArgs& g, hipStream_t s);
 
+// What the form of the dH launches (dh_form) goes by, beside the active rows.
+struct DhRule {
+  int n;                // columns of dH; 0: the call has none
+  int acc_rows;         // rows of the accumulator
+  int stages;           // of the first chunk's contraction
+  int split_f32, wide_ok;
+  Rechunk rc;
+};
+
 struct CombineArgs {
   int tiles_v, t_cap;
   const float* part_m; const float* part_s; const float* part_u;
@@ -310,7 +318,8 @@ struct CombineArgs {
   float* partials_out;
   const float* partials_in;
   TokenBlocks blk;
-  const Ctl* ctl;
+  DhRule dh;                 // the first block's combine settles the form of the dH launches
+  Ctl* ctl;
 };
 void launch_combine(const CombineArgs& a, hipStream_t s);
 

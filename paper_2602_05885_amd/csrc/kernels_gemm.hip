@@ -673,8 +673,7 @@ struct StoreShape {
     ks = 1; products = 1; slab_rows = ctl.n_pad;
     wide = false;
     if (a.split_k && a.m_from_ctl && nt * BM == ctl.n_pad) {
-      const DhForm f = dh_form(ctl.n_pad, a.acc_rows, a.N, a.split_stages, a.A_lo != nullptr, a.wide_ok);
-      ks = f.ks; products = f.products; wide = f.wide;
+      ks = ctl.dh_ks; products = ctl.dh_products; wide = ctl.dh_wide;
     } else if (a.dw_cap > 0) {
       ks = dw_split(K / BK, a.dw_cap);
       products = a.A_lo ? 3 : 1;
@@ -753,7 +752,7 @@ __global__ __launch_bounds__(NTHREADS) void gemm_store_kernel(StoreArgs a) {
       a.lda = ld_t_all;
     } else if (a.rc_role == 2 && dh_runs_whole(a.rc, ctl.n_pad)) {      // dH: likewise
       if (a.rc.chunk > 0) return;
-      a.K = a.rc.tiles_v_all * BM; a.split_stages = a.K / BK;
+      a.K = a.rc.tiles_v_all * BM;
       if (DIRECT) a.b_rows = a.rc.V;
       a.lda = a.rc.ld_s_all;
     } else if (a.rc_role == 1) {   // dW: this chunk's rows of the dS^T that spans the whole vocabulary
@@ -771,7 +770,6 @@ __global__ __launch_bounds__(NTHREADS) void gemm_store_kernel(StoreArgs a) {
   // The grid has room for the largest split.  Workgroups beyond one per tile leave before they crowd the queue (2161 rows of
   // d = 832, 21 of them active: dW 26.3 -> 23.6 us, dH 23.7 -> 21.7).
   if ((int)blockIdx.x >= grid_for_tiles(sh.total, 1)) return;
-  if (a.m_from_ctl && blockIdx.x == 0 && threadIdx.x == 0) a.ctl->dh_slabs = sh.ks * sh.products;
   if (a.blk.b > 0) {
     if (sh.nt <= 0) return;
     if (a.k_from_ctl) a.accumulate = 1;                              // dW: on top of the blocks before

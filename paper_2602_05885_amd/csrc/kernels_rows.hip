@@ -281,7 +281,8 @@ __global__ __launch_bounds__(1024) void prep_compact_kernel(PrepArgs a) {
     a.ctl->n_active = total;
     a.ctl->n_pad = (total + 255) / 256 * 256;
     a.ctl->norm = a.norm_override > 0.f ? a.norm_override : (float)max(total, 1);
-    a.ctl->dh_slabs = 1;
+    a.ctl->dh_slabs = a.ctl->dh_ks = a.ctl->dh_products = 1;        // (what a call without rows is left with)
+    a.ctl->dh_wide = 0;
   }
   if (tid < 8) {      // counter: the flags that it counts (1 and 2 are the combine's; 6: active rows and those passed over)
     const int kind = tid == 3 ? 4 : tid == 4 ? 3 : tid == 5 ? 2 : tid == 6 ? 1 : tid == 7 ? 5 : -1;
@@ -317,7 +318,8 @@ __global__ void prep_all_rows_kernel(PrepArgs a, int blocks) {
     a.ctl->n_active = a.T;
     a.ctl->n_pad = a.t_cap;
     a.ctl->norm = a.norm_override > 0.f ? a.norm_override : (float)a.T;
-    a.ctl->dh_slabs = 1;
+    a.ctl->dh_slabs = a.ctl->dh_ks = a.ctl->dh_products = 1;        // (what a call without rows is left with)
+    a.ctl->dh_wide = 0;
   }
 }
 
@@ -493,7 +495,20 @@ __device__ __forceinline__ void combine_merge(float& M, float& s, float& u, floa
   M = mm;
 }
 
-template <int R>
+// The form of the call's dH launches, by one wavefront.  In front of every tile's first load, in each workgroup of a dH launch, the search took 1 to 3 us; here it
+// runs beside the rows' epilogue and costs nothing.
+__device__ __forceinline__ void settle_dh_form(const CombineArgs& a, int n_pad) {
+  DhForm f{1, 1, false};
+  if (a.blk.cap_t <= 0 || n_pad / BN <= a.blk.cap_t)       // (several token blocks are never split)
+    f = dh_form(n_pad, a.dh.acc_rows, a.dh.n, dh_runs_whole(a.dh.rc, n_pad) ? a.dh.rc.tiles_v_all * (BM / BK) : a.dh.stages, a.dh.split_f32, a.dh.wide_ok);
+  if ((threadIdx.x & 63) == 0) {
+    a.ctl->dh_slabs = f.ks * f.products;
+    a.ctl->dh_ks = f.ks; a.ctl->dh_products = f.products; a.ctl->dh_wide = f.wide;
+  }
+}
+
+// SETTLES: the call has dH launches.
+template <int R, bool SETTLES>
 __global__ __launch_bounds__(64 * COMBINE_WAVES) void combine_kernel(CombineArgs a) {
   constexpr int PARTS = 64 * COMBINE_WAVES / R;
   __shared__ float sh[PARTS - 1][3][R];
@@ -522,7 +537,10 @@ __global__ __launch_bounds__(64 * COMBINE_WAVES) void combine_kernel(CombineArgs
   if (R == 64) {
     if (part > 0) { sh[part - 1][0][lane] = M; sh[part - 1][1][lane] = s; sh[part - 1][2][lane] = u; }
     __syncthreads();
-    if (part > 0) return;
+    if (part > 0) {
+      if (SETTLES && blockIdx.x == 0 && part == COMBINE_WAVES - 1) settle_dh_form(a, ctl.n_pad);
+      return;
+    }
     for (int w = 0; w < PARTS - 1; ++w) combine_merge(M, s, u, sh[w][0][lane], sh[w][1][lane], sh[w][2][lane]);
   } else {                   // the parts of a wavefront by exchange, then those of the 16 wavefronts
 #pragma unroll
@@ -533,7 +551,10 @@ __global__ __launch_bounds__(64 * COMBINE_WAVES) void combine_kernel(CombineArgs
     const int wave = threadIdx.x >> 6;
     if ((threadIdx.x & 63) < R) { sh[wave][0][lane] = M; sh[wave][1][lane] = s; sh[wave][2][lane] = u; }
     __syncthreads();
-    if (wave > 0) return;
+    if (wave > 0) {
+      if (SETTLES && blockIdx.x == 0 && wave == COMBINE_WAVES - 1) settle_dh_form(a, ctl.n_pad);
+      return;
+    }
     constexpr int EACH = COMBINE_WAVES * R / 64;           // wavefronts' states of a lane
     const int first = (threadIdx.x / R) * EACH;
     M = sh[first][0][lane]; s = sh[first][1][lane]; u = sh[first][2][lane];
@@ -593,8 +614,9 @@ __global__ __launch_bounds__(64 * COMBINE_WAVES) void combine_kernel(CombineArgs
 }
 void launch_combine(const CombineArgs& a, hipStream_t s) {
   const int rows = a.blk.cap_t > 0 ? a.blk.cap_t * BN : a.t_cap;
-  if (a.t_cap <= COMBINE_FEW_ROWS) hipLaunchKernelGGL(combine_kernel<16>, dim3(rows / 16), dim3(64 * COMBINE_WAVES), 0, s, a);
-  else hipLaunchKernelGGL(combine_kernel<64>, dim3(rows / 64), dim3(64 * COMBINE_WAVES), 0, s, a);
+  const bool few = a.t_cap <= COMBINE_FEW_ROWS, settles = a.dh.n > 0 && a.blk.b == 0;
+  auto kernel = few ? (settles ? combine_kernel<16, true> : combine_kernel<16, false>) : settles ? combine_kernel<64, true> : combine_kernel<64, false>;
+  hipLaunchKernelGGL(kernel, dim3(rows / (few ? 16 : 64)), dim3(64 * COMBINE_WAVES), 0, s, a);
 }
 
 // One workgroup of 256, fixed order, fp64: loss = (sum_t c_t l_t) / norm; publishes the counters.  It runs as a

@@ -144,7 +144,8 @@ int main(int argc, char** argv) {
   CK(hipMalloc(&yc, T * 4)); CK(hipMalloc(&lse2, T * 4)); CK(hipMalloc(&coefc, T * 4));
   CK(hipMalloc(&ctl, sizeof(Ctl))); CK(hipMalloc(&queue, 64));
   CK(hipMalloc(&pr, (size_t)grid * 4 * 8)); CK(hipMalloc(&tl, (size_t)grid * TL_TILES * 3 * 8));
-  Ctl h{T, T, 1.f, {}, 1};
+  const DhForm form = dh_form(T, T, d, vc / 64, 0, true);
+  Ctl h{T, T, 1.f, {}, form.ks * form.products, form.ks, form.products, form.wide};
   CK(hipMemcpy(ctl, &h, sizeof h, hipMemcpyHostToDevice));
   fill_kernel<<<1024, 256>>>(dST, (size_t)vc * ld_t, 1u, 1e-3f);
   fill_kernel<<<1024, 256>>>(HcT, (size_t)d * ld_t, 2u, 3.4f);
@@ -166,7 +167,7 @@ int main(int argc, char** argv) {
   w.tiles_m = vc / 256; w.tiles_n = d / 256; w.C = dW; w.ldc = d; w.k_from_ctl = 1; w.wide_ok = 1; w.ctl = ctl; w.queue = queue;
   StoreArgs g{};      // dH: [T, d] += dS [T, vc] x W^T [d, vc]
   g.A = dS; g.B = WT; g.a_rows = T; g.b_rows = d; g.lda = ld_v; g.ldb = ld_v; g.M = T; g.N = d; g.K = vc;
-  g.tiles_m = T / 256; g.tiles_n = d / 256; g.C = dH; g.ldc = d; g.accumulate = 1; g.m_from_ctl = 1; g.split_k = 1; g.split_stages = vc / 64; g.wide_ok = 1; g.ctl = ctl; g.queue = queue;
+  g.tiles_m = T / 256; g.tiles_n = d / 256; g.C = dH; g.ldc = d; g.accumulate = 1; g.m_from_ctl = 1; g.split_k = 1; g.acc_rows = T; g.wide_ok = 1; g.ctl = ctl; g.queue = queue;
   DlogitsArgs r{};    // recompute of the chunk's logits, dS and dS^T out
   r.W = W; r.Hc = Hc; r.w_rows = V; r.h_rows = T; r.ldw = d; r.ldh = d; r.K = d; r.V = V; r.v0 = vc; r.ld_s = ld_v; r.ld_t = ld_t;
   r.tiles_v = vc / 256; r.tiles_t = T / 256; r.t_cap = T; r.scale = 1.4427f; r.yc = yc; r.lse2 = lse2; r.coefc = coefc;
