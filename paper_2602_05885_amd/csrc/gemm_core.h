@@ -1,5 +1,5 @@
 // 256x256x64 bf16 MFMA tile engine for gfx950 (CDNA4), shared by the three contractions
-// of the policy-gradient head:
+// of the policy-gradient head (dW and dH also in tiles of 320x256x64, see mainloop):
 //   logits^T = W H^T        (forward statistics, and the backward's recompute)
 //   dW       = dS^T H
 //   dH       = dS W
@@ -8,19 +8,20 @@
 //
 // Shape of the engine (each choice measured on MI355X):
 //   * 8 wavefronts per workgroup as 4 (m) x 2 (n), two per SIMD, each owning a 64 x 128 block
-//     = 4 x 8 MFMA 16x16x32 tiles (128 fp32 accumulators per lane).  Two wavefronts per SIMD
+//     = 4 x 8 MFMA 16x16x32 tiles (128 fp32 accumulators per lane; 80 x 128 = 5 x 8 tiles, 160
+//     accumulators, in the wide form).  Two wavefronts per SIMD
 //     hide each other's LDS and barrier latency; one wavefront per SIMD with a 128 x 128 block
 //     was 30 % slower with compiler-scheduled code.
 //   * v_mfma_f32_16x16x32_bf16 rather than 32x32x16: same LDS traffic per flop, half the
 //     accumulator traffic; the chip is power-limited under MFMA load and sustains a higher
 //     clock with it (+6 % end to end, +13 % on a pure MFMA stream).
 //   * operand slabs go global -> LDS directly (buffer_load ... lds, 16 B per lane), two
-//     64-deep stages of 64 KiB.
+//     64-deep stages of 64 KiB (72 wide).
 //   * a wavefront that issues a burst of such loads is held at the issue stage while the
 //     texture-address unit works through them (16 cycles per 1 KiB load, 64 loads per stage), and
 //     its MFMAs wait behind them.  The loads are therefore trickled out one per 64-cycle step over
 //     the whole stage, which a two-barrier stage schedule makes legal: the A slab of a stage is
-//     dead once the register-resident A fragments have been read (barrier X after step 4), the
+//     dead once the register-resident A fragments have been read (barrier X after step 4, 5 wide), the
 //     B slab once the last streamed B fragment has been read (barrier Y, two steps before the end
 //     of the stage).  Measured +10..13 % over issuing a stage's loads in one burst.
 //   * inside a stage the LDS->register traffic is software-pipelined by hand (A fragments
@@ -897,7 +898,7 @@ struct TileQueue {
 // a workgroup counts itself in on its XCD's counter when its main loop ends, and behind the statistics thread 0 looks whether all have, which by
 // then costs nothing if they are together.  It waits for the others at most POLLS looks (some 50 us, once: a workgroup whose wait runs out, or that has no next tile,
 // counts for good and looks no more; workgroups that have no compute unit, because another stream holds it, cost no more than that).  A matter of speed only.
-// Forward only, without / with: d = 5120, 131072 rows 136.6 / 133.8 and 141.0 / 138.6 ms, 32768 rows 33.4 / 33.2 and 33.8 / 33.3; d = 4096, 16384 rows 13.33 / 13.30 and
+// Forward only, without / with: d = 5120, 131072 rows 136.6 / 133.8, 141.0 / 138.6 and, on a box whose XCDs drift less, 136.1 / 135.6 ms, 32768 rows 33.4 / 33.2 and 33.8 / 33.3; d = 4096, 16384 rows 13.33 / 13.30 and
 // 13.43 / 13.35 ms (35 / 30 GB fetched, 30 being what 32 tiles at a time must).  At 131072 rows every tile instead of every fourth 134.4, every sixteenth 134.0; at
 // d = 1024, 20000 rows every fourth of 16 stages 1649 / 1667 us.  Launches of fewer than ROUNDS rounds do not drift that far (39 rounds: 3751 / 3756 us), and a
 // forward that parks its logits, whose look would wait for the stores, gains nothing: 12000 rows 13.43 / 13.55 ms, 16384 17.66 / 17.59.

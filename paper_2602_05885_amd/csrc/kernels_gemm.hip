@@ -2,10 +2,10 @@
 // from kept logits.
 //
 // Accumulator layout they all rely on: acc[i][j][r] of lane l is
-//   engine row     wm*64  + i*16 + 4*(l>>4) + r      (i < 4, r < 4)
+//   engine row     wm*64  + i*16 + 4*(l>>4) + r      (i < 4, r < 4; the fifth of a wide tile of the store kernel, i = 4: 256 + wm*16 + 4*(l>>4) + r)
 //   engine column  wn*128 + j*16 + (l & 15)          (j < 8; in the forward j*32 + wn*16 + (l & 15))
-// so one lane holds 16 rows of each of its 8 columns, and the four 16-lane groups of a
-// wavefront hold the other 48 rows of the same columns.  The two logits kernels put the
+// so one lane holds 16 rows (20 wide) of each of its 8 columns, and the four 16-lane groups of a
+// wavefront hold the other 48 (60) rows of the same columns.  The two logits kernels put the
 // vocabulary on the rows (a token's statistics then reduce inside a lane first); the store
 // kernel puts the output's contiguous dimension there (4 consecutive elements per lane).
 #include <algorithm>
@@ -602,8 +602,8 @@ __global__ __launch_bounds__(KEPT_THREADS, 2) void dlogits_kept_kernel(DlogitsAr
 // rows: pieces of 64 bytes go through a compute unit at half the rate (256 KiB of stores alone, with 8 or 128 compute units active:
 // 16 rows x 64 B 7.6 us, whole rows 3.7 us; with all 256 either takes 12 us, the HBM's rate).
 // dW of 675 rows, d = 5120: 1258 -> 1158 us.  The old values of an accumulated output are requested one column ahead of the
-// stores (2869 rows, d = 4096, accumulating: call 9160 -> 9025 us; without, no gain).  (The lane masks of the 16 row conditions
-// spill 64 scalar registers; they are read back per tile, two per column, and none of that lies in a main loop.)
+// stores (2869 rows, d = 4096, accumulating: call 9160 -> 9025 us; without, no gain).  (The lane masks of the row conditions
+// and the two widths spill 130 scalar registers, the form that reads W as it lies 16 vector registers too, 68 bytes a lane; none of that lies in a main loop.)
 __device__ __forceinline__ float of_lane_pair(float x) {      // x of lane ^ 1
   return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), 0xB1, 0xf, 0xf, true));
 }
