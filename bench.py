@@ -46,8 +46,8 @@ def measured_mfma_only_tflops():
 # summarised in profiles/gemm_store_kernel_hbm_traffic.md (mean over a step's 30 launches, of which 20 have work, each
 # counter scaled by what it reads for a plain 1 GiB copy).  Valid only for the kernel sources the
 # counters were taken with: the digest below is of csrc/gemm_core.h + csrc/kernels_gemm.hip.
-TRAFFIC_GEMM_STORE = {"read_bytes": 2401555.7 * 1024 * 2.000, "write_bytes": 312019.4 * 1024 * 1.000,
-                      "sources_sha256": "eec90b3728099ad63073e022689583e8a71a594e806d9cf317c8fbed3a8cb4c4"}
+TRAFFIC_GEMM_STORE = {"read_bytes": 2401117.6 * 1024 * 2.000, "write_bytes": 312026.7 * 1024 * 1.000,
+                      "sources_sha256": "31c7d45afe7ccee4199805979c84b3d271fe86105c93acd6675e5571426f66d5"}
 
 
 def kernel_sources_digest() -> str:
