@@ -46,8 +46,8 @@ def measured_mfma_only_tflops():
 # summarised in profiles/gemm_store_kernel_hbm_traffic.md (mean over a step's 30 launches, of which 20 have work, each
 # counter scaled by what it reads for a plain 1 GiB copy).  Valid only for the kernel sources the
 # counters were taken with: the digest below is of csrc/gemm_core.h + csrc/kernels_gemm.hip.
-TRAFFIC_GEMM_STORE = {"read_bytes": 2401117.6 * 1024 * 2.000, "write_bytes": 312026.7 * 1024 * 1.000,
-                      "sources_sha256": "31c7d45afe7ccee4199805979c84b3d271fe86105c93acd6675e5571426f66d5"}
+TRAFFIC_GEMM_STORE = {"read_bytes": 2401517.1 * 1024 * 2.000, "write_bytes": 312017.3 * 1024 * 1.000,
+                      "sources_sha256": "1d5a65a864ce80e0601cb480152966da32cd3bff81016d7d8d89a632b7ebab93"}
 
 
 def kernel_sources_digest() -> str:

@@ -898,7 +898,7 @@ struct TileQueue {
 // a workgroup counts itself in on its XCD's counter when its main loop ends, and behind the statistics thread 0 looks whether all have, which by
 // then costs nothing if they are together.  It waits for the others at most POLLS looks (some 50 us, once: a workgroup whose wait runs out, or that has no next tile,
 // counts for good and looks no more; workgroups that have no compute unit, because another stream holds it, cost no more than that).  A matter of speed only.
-// Forward only, without / with: d = 5120, 131072 rows 136.6 / 133.8, 141.0 / 138.6 and, on a box whose XCDs drift less, 136.1 / 135.6 ms, 32768 rows 33.4 / 33.2 and 33.8 / 33.3; d = 4096, 16384 rows 13.33 / 13.30 and
+// Forward only, without / with: d = 5120, 131072 rows 136.6 / 133.8, 141.0 / 138.6 and, on a card whose XCDs drift less, 136.1 / 135.6 ms, 32768 rows 33.4 / 33.2 and 33.8 / 33.3; d = 4096, 16384 rows 13.33 / 13.30 and
 // 13.43 / 13.35 ms (35 / 30 GB fetched, 30 being what 32 tiles at a time must).  At 131072 rows every tile instead of every fourth 134.4, every sixteenth 134.0; at
 // d = 1024, 20000 rows every fourth of 16 stages 1649 / 1667 us.  Launches of fewer than ROUNDS rounds do not drift that far (39 rounds: 3751 / 3756 us), and a
 // forward that parks its logits, whose look would wait for the stores, gains nothing: 12000 rows 13.43 / 13.55 ms, 16384 17.66 / 17.59.
