@@ -212,7 +212,7 @@ def test_binding_rejects_wrong_dtypes_shapes_and_devices():
         B.pg_sft_fwd_bwd(H, W, y, torch.ones(T, dtype=torch.uint8), P, ws)
 
     # the remaining checks are exercised through the helpers with the device check satisfied by a fake
-    # device argument (the tensors live on the CPU here; on the GPU machine the same code sees cuda tensors)
+    # device argument (the tensors live on the CPU here; with a GPU the same code sees cuda tensors)
     with pytest.raises(ValueError, match="dtype"):                    # torch's default int64 token ids
         B._want("y", y.long(), torch.int32, (T,), cpu)
     with pytest.raises(ValueError, match="dtype"):                    # bf16 H with params.dtype = fp32
